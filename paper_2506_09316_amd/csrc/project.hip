@@ -5,9 +5,9 @@
 // [M][width] - q, k, v and the two gate pre-activations - each laid out [B][T][H][d] as the prefill reads them, so
 // nothing is permuted or converted in between; with gate_mode = DSLA_GATE_PREACT the prefill applies the gate map.
 //     out_j[m][c] = sum_k x[m][k] W[j * width + c][k] (+ bias[j * width + c])
-// bf16 operands, fp32 accumulation, bf16 results.  Two kernels:
+// bf16 operands, fp32 accumulation, bf16 results.  Kernels (launch_project has the rule):
 //
-// project_kernel_256 (K a multiple of 128): workgroup = 256 threads = 4 wavefronts on a 256 x 256 output tile, one
+// project_tile_kernel<4> (K a multiple of 128): workgroup = 256 threads = 4 wavefronts on a 256 x 256 output tile, one
 // wavefront per SIMD with a 128 x 128 quadrant = sixteen 32 x 32 MFMA tiles whose 256 accumulator registers live in
 // the accumulation half of the register file.  Per 16 values of K a wavefront reads 4 + 4 fragments from LDS for 16
 // MFMAs - half a 16-byte LDS read per MFMA, a quarter of what a 64 x 64 quadrant needs, which is what keeps the LDS
@@ -16,9 +16,14 @@
 // stages to arrive.  A row of a stage is 64 bytes, its four 16-byte pieces stored at piece position c ^ ((row / 4) % 4),
 // so that the fragment reads of 16 lanes at a time touch every bank once.
 //
-// project_kernel (any K that is a multiple of 32): 128 x 128 tile, 64 x 64 quadrants, K in steps of 32.
+// project_tile_kernel<2>: the same on 128 x 128 tiles, two workgroups per compute unit, for outputs that do not fill the
+// chip with large tiles.
 //
-// Tile order, both kernels: see tile_of().
+// project_rows_kernel: up to 128 rows of x (the tokens of a decoding batch), where reading the weights is the work.
+//
+// project_kernel (more rows, K not a multiple of 128): 128 x 128 tile, 64 x 64 quadrants, K in steps of 32.
+//
+// Tile order of the tile kernels: see tile_of().
 #include "dsla_internal.h"
 
 #include <type_traits>
@@ -46,6 +51,17 @@ __device__ __forceinline__ uint32_t pack2(float a, float b)
     f32x2 x = {a, b};
     bf16x2 y = __builtin_convertvector(x, bf16x2);
     return __builtin_bit_cast(uint32_t, y);
+}
+
+// 16 bytes per lane from a buffer (lane offset `voff`, uniform offset `soff`) into LDS at `lds` (uniform) + 16 * lane
+__device__ __forceinline__ void buffer_load_lds16(__amdgpu_buffer_rsrc_t res, char *lds, uint32_t voff, int soff)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (__attribute__((address_space(3))) void *)(lds), 16, voff, soff, 0, 0);
+}
+template <int N>
+__device__ __forceinline__ void wait_loads()   // at most N of this wavefront's loads are still in flight
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
 // Tile order: the 8 XCDs each take a contiguous run of the linear tile order (workgroup ids go round-robin over the
@@ -90,18 +106,20 @@ __device__ __forceinline__ void store_tile(const f32x16 &acc, const ProjectOuts 
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// 256 x 256 tiles
+// 256 x 256 and 128 x 128 tiles, loads straight into LDS
 // ---------------------------------------------------------------------------------------------------------------
-constexpr int BM = 256, BN = 256;
 constexpr int BK = 32;                            // values of K per stage
 constexpr int ROWB = BK * 2;                     // bytes per LDS row: 64
-constexpr int OPB = BM * ROWB;                  // bytes per operand tile and stage: 16 KB
-constexpr int STAGEB = 2 * OPB;                 // A tile, then B tile: 32 KB
 
-__global__ __launch_bounds__(256) void project_kernel_256(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w,
+// Q: 32 x 32 tiles along each side of a wavefront's quadrant (4: 256 x 256 per workgroup, 2: 128 x 128)
+template <int Q>
+__global__ __launch_bounds__(256, Q == 4 ? 1 : 2) void project_tile_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w,
                                                                  const float *__restrict__ bias, ProjectOuts outs, long long M,
                                                                  int K, int N, int width, int tiles_m, int tiles_n)
 {
+    constexpr int BM = 64 * Q, BN = BM, QS = 32 * Q;   // workgroup tile, quadrant
+    constexpr int OPB = BM * ROWB;                      // bytes per operand tile and stage
+    constexpr int STAGEB = 2 * OPB;                     // A tile, then B tile
     // four stages as four objects: the compiler's wait-count insertion then knows that a load into one stage does not
     // touch what is read from another
     __shared__ __attribute__((aligned(1024))) char st0[STAGEB];
@@ -115,11 +133,11 @@ __global__ __launch_bounds__(256) void project_kernel_256(const bf16_t *__restri
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ln = lane & 31, g = lane >> 5;
-    const int wm = wave >> 1, wn = wave & 1;   // this wavefront's 128 x 128 quadrant
+    const int wm = wave >> 1, wn = wave & 1;   // this wavefront's quadrant
     const uint32_t uwave = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(wave));
 
     // Buffer loads with LDS as destination: one instruction of a wavefront fills 1 KB = 16 rows of 64 bytes of a
-    // tile; instruction n = wave + 4 i (i < 4) fills rows 16 n .. 16 n + 15.  A lane fills LDS slot (row lane / 4, piece
+    // tile; instruction n = wave + 4 i (i < Q) fills rows 16 n .. 16 n + 15.  A lane fills LDS slot (row lane / 4, piece
     // position lane % 4) and fetches the piece that belongs there: piece c of row r sits at position c ^ ((r / 4) % 4),
     // so the 16 rows that 16 lanes read at the same logical piece fall into 16 different groups of four banks.  The
     // descriptor of an operand starts at the tile's first row and ends with the last row that exists: rows past the
@@ -129,57 +147,56 @@ __global__ __launch_bounds__(256) void project_kernel_256(const bf16_t *__restri
         const_cast<bf16_t *>(x + static_cast<size_t>(m0) * K), 0, static_cast<int>(rows_a * K * 2), 0x00020000);
     const __amdgpu_buffer_rsrc_t res_b = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<bf16_t *>(w + static_cast<size_t>(n0) * K), 0, static_cast<int>(rows_b * K * 2), 0x00020000);
-    uint32_t voff[4];   // byte offset of this lane's piece from the first row of the tile (the range check is on it)
+    uint32_t voff[Q];   // byte offset of this lane's piece from the first row of the tile (the range check is on it)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < Q; ++i)
         voff[i] = (16 * (uwave + 4 * i) + (static_cast<uint32_t>(lane) >> 2)) * static_cast<uint32_t>(K) * 2u +
                   16 * ((lane & 3u) ^ ((static_cast<uint32_t>(lane) >> 4) & 3u));
     const int nk = K / BK;
-    typedef __attribute__((address_space(3))) void *lds_void;
     auto fetch = [&](char *st, int ks) {   // K-step ks (past the end: the last one again, never used) into a stage
         const int kbyte = (ks < nk ? ks : nk - 1) * BK * 2;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < Q; ++i) {
             const uint32_t n = uwave + 4 * i;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(res_a, (lds_void)(st + n * 1024), 16, voff[i], kbyte, 0, 0);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(res_b, (lds_void)(st + OPB + n * 1024), 16, voff[i], kbyte, 0, 0);
+            buffer_load_lds16(res_a, st + n * 1024, voff[i], kbyte);
+            buffer_load_lds16(res_b, st + OPB + n * 1024, voff[i], kbyte);
         }
     };
 
     // fragment reads: row (quadrant + 32 i + ln) of a tile, block kb of 16 values of K: piece 2 kb + g
     const uint32_t swz = (ln >> 2) & 3;
     const uint32_t fo0 = ((0 + g) ^ swz) << 4, fo1 = ((2 + g) ^ swz) << 4;
-    const uint32_t fa_row = static_cast<uint32_t>((128 * wm + ln) * ROWB);
-    const uint32_t fb_row = static_cast<uint32_t>(OPB + (128 * wn + ln) * ROWB);
-    bf16x8 fa[2][4], fb[2][4];   // fragments of two blocks: one in use, one arriving
+    const uint32_t fa_row = static_cast<uint32_t>((QS * wm + ln) * ROWB);
+    const uint32_t fb_row = static_cast<uint32_t>(OPB + (QS * wn + ln) * ROWB);
+    bf16x8 fa[2][Q], fb[2][Q];   // fragments of two blocks: one in use, one arriving
     auto read_frags = [&](int buf, const char *st, int kb) {
         const uint32_t fo = kb ? fo1 : fo0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < Q; ++i) {
             fa[buf][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(st + fa_row + i * 32 * ROWB + fo));
             fb[buf][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(st + fb_row + i * 32 * ROWB + fo));
         }
     };
 
-    f32x16 acc[4][4];
+    f32x16 acc[Q][Q];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < Q; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < Q; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
     auto block = [&](int kb) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < Q; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < Q; ++j)
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kb][j], fa[kb][i], acc[i][j], 0, 0, 0);
 #pragma unroll
-        for (int t = 0; t < 16; ++t) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                              // 1 MFMA
-            if (t % 2 == 0) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);              // 1 LDS read
-            if (kb == 0 && t % 2 == 1) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);   // 1 load into LDS
+        for (int t = 0; t < Q * Q; ++t) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                       // 1 MFMA
+            if (Q == 2 || t % 2 == 0) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);             // 1 LDS read
+            if (kb == 0 && (Q == 2 || t % 2 == 1)) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);   // 1 load into LDS
         }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -190,7 +207,8 @@ __global__ __launch_bounds__(256) void project_kernel_256(const bf16_t *__restri
     // ks + 3.  So a load has two steps to arrive, and no MFMA waits behind a barrier for LDS latency: the first
     // fragments of `nxt` are read during the second block.
     auto step = [&](const char *cur, const char *nxt, char *old, int ks) {
-        asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        wait_loads<2 * Q>();
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         fetch(old, ks + 3);
         read_frags(1, cur, 1);
@@ -202,7 +220,8 @@ __global__ __launch_bounds__(256) void project_kernel_256(const bf16_t *__restri
     fetch(st0, 0);
     fetch(st1, 1);
     fetch(st2, 2);
-    asm volatile("s_waitcnt vmcnt(16)\n\ts_barrier" ::: "memory");   // stage 0 is complete
+    wait_loads<4 * Q>();
+    asm volatile("s_barrier" ::: "memory");   // stage 0 is complete
     read_frags(0, st0, 0);
     __builtin_amdgcn_sched_barrier(0);
     for (int ks = 0; ks < nk; ks += 4) {
@@ -217,12 +236,13 @@ __global__ __launch_bounds__(256) void project_kernel_256(const bf16_t *__restri
     // piece c of row r at position c ^ (r % 16) - so that it leaves as whole rows: a lane holds 4 adjacent columns of a
     // row per register group and writes them as 8 bytes; then 16 lanes read one row as 16 bytes each and store 256
     // contiguous bytes.
+    constexpr int PPR = QS / 8;   // 16-byte pieces per quadrant row
     char *epi = wave == 0 ? st0 : (wave == 1 ? st1 : (wave == 2 ? st2 : st3));
-    const int nq = n0 + 128 * wn;   // first column of the quadrant: inside one output tensor (width is a multiple of 128)
+    const int nq = n0 + QS * wn;   // first column of the quadrant: inside one output tensor (width is a multiple of 128)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < Q; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < Q; ++j)
 #pragma unroll
             for (int rb4 = 0; rb4 < 4; ++rb4) {
                 const int cq = 32 * j + 8 * rb4 + 4 * g;   // column inside the quadrant
@@ -235,16 +255,16 @@ __global__ __launch_bounds__(256) void project_kernel_256(const bf16_t *__restri
                     c3 += bv[3];
                 }
                 const int row = 32 * i + ln, piece = cq >> 3;
-                *reinterpret_cast<u32x2 *>(epi + row * 256 + ((piece ^ (row & 15)) << 4) + (cq & 4) * 2) = u32x2{pack2(c0, c1), pack2(c2, c3)};
+                *reinterpret_cast<u32x2 *>(epi + row * (2 * QS) + ((piece ^ (row & (PPR - 1))) << 4) + (cq & 4) * 2) = u32x2{pack2(c0, c1), pack2(c2, c3)};
             }
     if (nq < N) {
         bf16_t *out = static_cast<bf16_t *>(outs.p[nq / width]) + nq % width;
-        const int rsub = lane >> 4, piece = lane & 15;   // 4 rows per instruction, 16 lanes per row
+        const int rsub = lane / PPR, piece = lane % PPR;   // PPR lanes per row
 #pragma unroll 4
-        for (int it = 0; it < 32; ++it) {
-            const int row = 4 * it + rsub;
-            const long long m = m0 + 128 * wm + row;
-            const u32x4 vrow = *reinterpret_cast<const u32x4 *>(epi + row * 256 + ((piece ^ (row & 15)) << 4));
+        for (int it = 0; it < QS * PPR / 64; ++it) {
+            const int row = 64 / PPR * it + rsub;
+            const long long m = m0 + QS * wm + row;
+            const u32x4 vrow = *reinterpret_cast<const u32x4 *>(epi + row * (2 * QS) + ((piece ^ (row & (PPR - 1))) << 4));
             if (m < M)   // streaming store: a tile of results is not read again by this kernel
                 __builtin_nontemporal_store(vrow, reinterpret_cast<u32x4 *>(out + static_cast<size_t>(m) * width + piece * 8));
         }
@@ -334,6 +354,217 @@ __global__ __launch_bounds__(256) void project_kernel(const bf16_t *__restrict__
     }
 }
 
+// ---------------------------------------------------------------------------------------------------------------
+// Few rows: the weights are the traffic
+// ---------------------------------------------------------------------------------------------------------------
+// Bound by HBM: 2 N K bytes of weights.  Workgroup = 4 wavefronts on 16 MT rows of x (all of them up to 128) and 16 NT
+// columns, NT chosen so that there is a workgroup per compute unit.  Stages of 64 KS values of K - KS lines of 128 bytes
+// of each of the 16 (NT + MT) rows; whole lines, because a request costs the L2 the same whatever its size - go through
+// a ring of LDS slots filled by loads that write LDS directly, so three stages are in flight whatever the registers
+// hold.  The fragments of the next stage are read while the MFMAs of the current one run (without that a stage costs
+// its LDS latency on top: M = 64 41.5 us instead of 36.7), and short stages are merged (KS) because the barrier of a
+// stage costs about 0.2 us (M = 20, N = 3072, K = 4096: KS = 1 18.2, 2 12.9, 4 11.0 us).
+// K = 4096, N = 20480 (170 MB): M = 1 29.8 us = 5.7 TB/s, M = 64 36.7 us = 4.7 TB/s, M = 128 51 us; the 256 x 256 tiles
+// take 75, 82 and 98 us.
+template <int MT, int NT>
+struct Rows {
+    static constexpr int KS = MT + NT <= 3 ? 4 : (MT + NT > 12 || (MT == 1 && NT == 5) ? 1 : 2);   // lines of 64 values per row and stage
+    static constexpr int LB = 2 * (NT + MT), L = LB * KS;                  // load instructions per stage: 8 rows of 128 bytes each
+    static constexpr uint32_t BLOCK = LB * 1024, STAGE = L * 1024;
+    static constexpr int DEPTH_MAX = 150 * 1024 / static_cast<int>(STAGE);
+    static constexpr int DEPTH = DEPTH_MAX > 4 ? 4 : DEPTH_MAX;             // (six and eight slots: no difference)
+    static constexpr int WM = MT < 4 ? MT : 4, WN = 4 / WM;      // wavefronts along the rows of x / along the columns
+    static constexpr int TM_ = MT / WM, TN_ = (NT + WN - 1) / WN;   // tiles of a wavefront
+};
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+// 16 bytes per lane from `base` (uniform) + `voff` (per lane) into LDS at `lds` (uniform) + 16 * lane; the compiler does
+// not know these loads: whoever reads the bytes waits with wait_loads() first.
+__device__ __forceinline__ void load_to_lds16(uint32_t lds, uint32_t voff, const char *base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "m0", "memory");
+}
+#pragma clang diagnostic pop
+
+template <int MT, int NT>
+__global__ __launch_bounds__(256) void project_rows_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w,
+                                                           const float *__restrict__ bias, ProjectOuts outs, int M, int K,
+                                                           int N, int width, int tiles_m, int tiles_n)
+{
+    using R = Rows<MT, NT>;
+    constexpr int DEPTH = R::DEPTH;
+    __shared__ __attribute__((aligned(1024))) char ring[DEPTH * R::STAGE];
+    // workgroup ids go round-robin over the 8 XCDs: the row tiles of one column tile follow each other on one XCD, so
+    // that its L2 serves the weights again
+    const int slot = blockIdx.x / 8, tn = slot / tiles_m * 8 + blockIdx.x % 8, tm = slot % tiles_m;
+    if (tn >= tiles_n) return;
+    const int m0 = tm * 16 * MT, n0 = tn * 16 * NT;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const uint32_t ring_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const char *)ring));
+
+    // ---- loading: instruction i of a stage fills rows 8 i .. 8 i + 7 (the 16 NT weight rows, then the rows of x), lane
+    // l position l % 8 of row l / 8; piece c of a row sits at position c ^ ((row / 2) % 8), which spreads the 16 rows
+    // that 16 lanes read at one piece over all banks.  Rows past the end re-read the last one (their results are not
+    // stored).  Wavefront w issues instructions w, w + 4, ... ----
+    constexpr int CMAX = (R::L + 3) / 4;
+    const int ns = (K + 64 * R::KS - 1) / (64 * R::KS);
+    const int last_units = K / 32 - (ns - 1) * 2 * R::KS;   // blocks of 32 values in the last stage; the others re-read its first
+    const char *src[CMAX];
+    uint32_t voff[CMAX], unit[CMAX];   // unit: which block of 32 values of the stage the lane's piece belongs to
+#pragma unroll
+    for (int c = 0; c < CMAX; ++c) {
+        const int n = wave + 4 * c, i = n % R::LB;
+        const uint32_t srow = 8 * i + (static_cast<uint32_t>(lane) >> 3), piece = (lane & 7u) ^ ((srow >> 1) & 7u);
+        int row;
+        if (i < 2 * NT) {
+            row = static_cast<int>(srow);
+            row = n0 + row < N ? row : N - 1 - n0;
+        } else {
+            row = static_cast<int>(srow) - 16 * NT;
+            row = m0 + row < M ? row : M - 1 - m0;
+        }
+        voff[c] = static_cast<uint32_t>(row) * static_cast<uint32_t>(K) * 2u + 128 * (n / R::LB) + 16 * piece;
+        unit[c] = 2 * (n / R::LB) + (piece >> 2);
+        src[c] = reinterpret_cast<const char *>(i < 2 * NT ? w + static_cast<size_t>(n0) * K : x + static_cast<size_t>(m0) * K);
+    }
+    // Workgroups start their walk at different stages, so that the lines they ask for at one time spread over the memory
+    // channels (rows are a large power of two apart; M = 16: 35.0 us when all start at stage 0, 29.8 us).
+    const int rot = (3 * slot) % ns;
+    auto issue = [&](int i, int at) {   // stage i of the walk into ring slot `at`
+        int s = i + rot;
+        s = s < ns ? s : s - ns;
+        const uint32_t units = s == ns - 1 ? last_units : 2 * R::KS;
+#pragma unroll
+        for (int c = 0; c < CMAX; ++c) {
+            const int n = wave + 4 * c;
+            if (n < R::L)
+                load_to_lds16(ring_lds + at * R::STAGE + n * 1024, unit[c] < units ? voff[c] : voff[c] - 64 * unit[c],
+                              src[c] + static_cast<size_t>(s) * (128 * R::KS));
+        }
+    };
+
+    // ---- fragments: lane (r, g) holds row r, values 8 g .. of a block of 32 ----
+    const int r = lane & 15, g = lane >> 4, wm = wave % R::WM, wn = wave / R::WM;
+    const uint32_t fpos[2] = {((0u + g) ^ ((r >> 1) & 7u)) << 4, ((4u + g) ^ ((r >> 1) & 7u)) << 4};
+    f32x4 acc[R::TM_][R::TN_];
+#pragma unroll
+    for (int i = 0; i < R::TM_; ++i)
+#pragma unroll
+        for (int j = 0; j < R::TN_; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    struct Frags {
+        bf16x8 x[2 * R::KS][R::TM_], w[2 * R::KS][R::TN_];
+    };
+    auto read = [&](Frags &f, int at) {
+#pragma unroll
+        for (int kk = 0; kk < 2 * R::KS; ++kk) {
+            const char *st = ring + at * R::STAGE + (kk >> 1) * R::BLOCK + r * 128;
+#pragma unroll
+            for (int a = 0; a < R::TM_; ++a)
+                f.x[kk][a] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(st + (NT + wm + R::WM * a) * 2048 + fpos[kk & 1]));
+#pragma unroll
+            for (int b = 0; b < R::TN_; ++b) {
+                const int t = wn + R::WN * b;   // (a wavefront with one tile less repeats the last one and drops it)
+                f.w[kk][b] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(st + (t < NT ? t : NT - 1) * 2048 + fpos[kk & 1]));
+            }
+        }
+    };
+    auto mma = [&](const Frags &f, int kk) {   // result transposed: lane (r, g) holds row r of x, columns 4 g .. 4 g + 3
+#pragma unroll
+        for (int b = 0; b < R::TN_; ++b)
+#pragma unroll
+            for (int a = 0; a < R::TM_; ++a)
+                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[kk][b], f.x[kk][a], acc[a][b], 0, 0, 0);
+    };
+
+    constexpr int REM = R::L % 4, CLO = R::L / 4, CHI = REM ? CLO + 1 : CLO;
+    auto arrive = [&](bool full) {   // all but the DEPTH - 2 youngest stages of every wavefront's loads are in LDS
+        if (!full) wait_loads<0>();
+        else if (REM && wave < REM) wait_loads<CHI * (DEPTH - 2)>();
+        else wait_loads<CLO * (DEPTH - 2)>();
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    };
+#pragma unroll
+    for (int i = 0; i < DEPTH - 1; ++i)
+        if (i < ns) issue(i, i);
+    arrive(DEPTH - 2 < ns);   // stage 0 has landed
+    Frags f0, f1;
+    read(f0, 0);
+    if (DEPTH - 1 < ns) issue(DEPTH - 1, DEPTH - 1);
+    int at = 0;   // slot of stage i
+    auto step = [&](const Frags &cur, Frags &nxt, int i) {
+        const int at_n = at + 1 == DEPTH ? 0 : at + 1;
+        if (i + 1 < ns) {
+            // stage i + 1 has landed; everybody holds the fragments of stage i, whose slot takes stage i + DEPTH
+            arrive(i + DEPTH - 1 < ns);
+            if (i + DEPTH < ns) issue(i + DEPTH, at);
+            read(nxt, at_n);
+        }
+        int s = i + rot;
+        s = s < ns ? s : s - ns;
+        const int units = s == ns - 1 ? last_units : 2 * R::KS;
+#pragma unroll
+        for (int kk = 0; kk < 2 * R::KS; ++kk)
+            if (kk == 0 || kk < units) mma(cur, kk);
+        at = at_n;
+    };
+    for (int i = 0; i < ns; i += 2) {
+        step(f0, f1, i);
+        if (i + 1 < ns) step(f1, f0, i + 1);
+    }
+#pragma unroll
+    for (int a = 0; a < R::TM_; ++a) {
+        const int m = m0 + 16 * (wm + R::WM * a) + r;
+        if (m >= M) continue;
+#pragma unroll
+        for (int b = 0; b < R::TN_; ++b) {
+            const int t = wn + R::WN * b, col = n0 + 16 * t + 4 * g;
+            if (t >= NT || col >= N) continue;
+            f32x4 s = acc[a][b];
+            if (bias) {
+                const f32x4 bv = *reinterpret_cast<const f32x4 *>(bias + col);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s[e] += bv[e];
+            }
+            bf16_t *dst = static_cast<bf16_t *>(outs.p[col / width]) + static_cast<size_t>(m) * width + col % width;
+            *reinterpret_cast<u32x2 *>(dst) = u32x2{pack2(s[0], s[1]), pack2(s[2], s[3])};
+        }
+    }
+}
+
+}  // namespace
+
+namespace {
+template <int MT, int NT>
+void launch_rows(ProfileScope &ps, int M, int K, int N, int width, const void *x, const void *w, const float *bias,
+                 const ProjectOuts &po, hipStream_t stream)
+{
+        const int tiles_m = (M + 16 * MT - 1) / (16 * MT), tiles_n = (N + 16 * NT - 1) / (16 * NT);
+    const unsigned grid = static_cast<unsigned>((tiles_n + 7) / 8 * 8) * tiles_m;
+    DSLA_LAUNCH(ps, (project_rows_kernel<MT, NT>), dim3(grid), dim3(256), 0, stream, static_cast<const bf16_t *>(x),
+                static_cast<const bf16_t *>(w), bias, po, M, K, N, width, tiles_m, tiles_n);
+}
+template <int MT>
+void launch_rows_n(ProfileScope &ps, int M, int K, int N, int width, const void *x, const void *w, const float *bias,
+                   const ProjectOuts &po, hipStream_t stream)
+{
+    // as many column tiles per workgroup as leave a workgroup for every compute unit
+    const int nt = N / (16 * 256);
+    if (nt >= 5) launch_rows<MT, 5>(ps, M, K, N, width, x, w, bias, po, stream);
+    else if (nt >= 3) launch_rows<MT, 3>(ps, M, K, N, width, x, w, bias, po, stream);
+    else if (nt == 2) launch_rows<MT, 2>(ps, M, K, N, width, x, w, bias, po, stream);
+    else launch_rows<MT, 1>(ps, M, K, N, width, x, w, bias, po, stream);
+}
+template <int Q>
+void launch_tiles(ProfileScope &ps, int64_t M, int K, int N, int width, const void *x, const void *w, const float *bias,
+                  const ProjectOuts &po, hipStream_t stream)
+{
+    constexpr int B = 64 * Q;
+    const int tiles_m = static_cast<int>((M + B - 1) / B), tiles_n = (N + B - 1) / B;
+    const long long ntiles = static_cast<long long>(tiles_m) * tiles_n;
+    const unsigned grid = static_cast<unsigned>((ntiles + 7) / 8 * 8);
+    DSLA_LAUNCH(ps, project_tile_kernel<Q>, dim3(grid), dim3(256), 0, stream, static_cast<const bf16_t *>(x),
+                static_cast<const bf16_t *>(w), bias, po, static_cast<long long>(M), K, N, width, tiles_m, tiles_n);
+}
 }  // namespace
 
 hipError_t launch_project(int64_t M, int K, int n_out, int width, const void *x, const void *w, const float *bias,
@@ -343,12 +574,22 @@ hipError_t launch_project(int64_t M, int K, int n_out, int width, const void *x,
     for (int j = 0; j < DSLA_MAX_PROJECTIONS; ++j) po.p[j] = j < n_out ? outs[j] : nullptr;
     const int N = n_out * width;
     ProfileScope ps(DSLA_KERNEL_PROJECT, stream);
-    if (K % (4 * BK) == 0) {   // the loop of project_kernel_256 goes four stages at a time
-        const int tiles_m = static_cast<int>((M + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
-        const long long ntiles = static_cast<long long>(tiles_m) * tiles_n;
-        const unsigned grid = static_cast<unsigned>((ntiles + 7) / 8 * 8);
-        DSLA_LAUNCH(ps, project_kernel_256, dim3(grid), dim3(256), 0, stream, static_cast<const bf16_t *>(x),
-                           static_cast<const bf16_t *>(w), bias, po, static_cast<long long>(M), K, N, width, tiles_m, tiles_n);
+    // Few rows: the weights are the traffic (65 .. 128 rows: 22 against 34 us at K = 4096, N = 3072, but 17 against 13 us at
+    // K = 1024, N = 20480, where the tile kernel's stages are few).
+    if (M <= 64 || (M <= 128 && (K >= 2048 || K % (4 * BK) != 0))) {
+        const int m = static_cast<int>(M);
+        if (M <= 16) launch_rows_n<1>(ps, m, K, N, width, x, w, bias, po, stream);
+        else if (M <= 32) launch_rows_n<2>(ps, m, K, N, width, x, w, bias, po, stream);
+        else if (M <= 64) launch_rows_n<4>(ps, m, K, N, width, x, w, bias, po, stream);
+        else launch_rows_n<8>(ps, m, K, N, width, x, w, bias, po, stream);
+    } else if (K % (4 * BK) == 0) {   // the loop of project_tile_kernel goes four stages at a time
+        // Small tiles while the chip has compute units for them: a large tile does four times the work of a small one in
+        // about 2.5 times its time, so the rounds over the 256 compute units decide (K = 4096: M = 384, N = 20480 95 against
+        // 102 us; M = 1300, N = 3072 59 against 77 us; M = 640, N = 20480 154 against 114 us).
+        const int64_t rounds128 = ((M + 127) / 128 * (N / 128) + 255) / 256;
+        const int64_t rounds256 = ((M + 255) / 256 * ((N + 255) / 256) + 255) / 256;
+        if (2 * rounds128 <= 5 * rounds256) launch_tiles<2>(ps, M, K, N, width, x, w, bias, po, stream);
+        else launch_tiles<4>(ps, M, K, N, width, x, w, bias, po, stream);
     } else {
         const int tiles_m = static_cast<int>((M + TM - 1) / TM), tiles_n = N / TN;
         const long long ntiles = static_cast<long long>(tiles_m) * tiles_n;

@@ -241,6 +241,34 @@ def test_project_against_library_matmul(M, K, n_out, width, bias):
         assert np.max(np.abs(got - r) / (np.abs(r) + 1e-2 * np.max(np.abs(r)))) <= 2 ** -8 * 1.1, f"output {j}"
 
 
+# (rows of x, K, tensors, width): row counts on and off the 16 .. 128 rows a workgroup takes, every number of column tiles
+# (N / 4096 = 0, 2, 3, 5 and a ragged last tile), K of one block of 32, of a partial last stage and of many stages; then
+# outputs that take the 128 x 128 and the 256 x 256 tiles, with ragged edges in both directions.
+@pytest.mark.parametrize("M,K,n_out,width", [(1, 32, 1, 128), (16, 96, 3, 256), (17, 160, 2, 4096), (32, 288, 5, 2560), (33, 352, 7, 2944),
+                                             (64, 1024, 5, 512), (5, 224, 7, 2944), (16, 4096, 4, 128), (65, 96, 2, 384), (100, 2048, 1, 256),
+                                             (128, 2080, 7, 2944), (129, 256, 3, 384), (1000, 128, 5, 640), (1991, 256, 7, 896)])
+def test_project_kernels(M, K, n_out, width):
+    """Every kernel behind dsla_project against a library matmul in fp64: each element within half a bf16 unit of itself
+    plus fp32 accumulation (as test_project_against_library_matmul), rows past the end of the outputs untouched."""
+    import torch
+    print(f"  project M={M} K={K} n_out={n_out} width={width}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1000 * M + K)
+    x = torch.randn(M, K, device="cuda", generator=gen).to(torch.bfloat16)
+    W = (torch.randn(n_out * width, K, device="cuda", generator=gen) * K ** -0.5).to(torch.bfloat16)
+    b = torch.randn(n_out * width, device="cuda", generator=gen)
+    bufs = [torch.full((M + 1, width), float("nan"), device="cuda", dtype=torch.bfloat16) for _ in range(n_out)]
+    dsla.dsla_project(x, W, [t[:M] for t in bufs], b)
+    torch.cuda.synchronize()
+    ref = x.double() @ W.double().T + b.double()
+    for j in range(n_out):
+        r = ref[:, j * width:(j + 1) * width]
+        got = bufs[j][:M].double()
+        assert bool(torch.isfinite(got).all()), f"output {j}"
+        assert float(((got - r).abs() / (r.abs() + 1e-2 * r.abs().max())).max()) <= 2 ** -8 * 1.1, f"output {j}"
+        assert bool(torch.isnan(bufs[j][M].float()).all()), f"output {j}: wrote past its last row"
+
+
 def test_projections_feed_the_prefill():
     """The layer from its input: x -> one GEMM -> q, k, v and the two gate pre-activations in the prefill's own
     layout -> dsla_prefill with gate_mode = DSLA_GATE_PREACT.  The oracle takes the same bf16 weights and input
