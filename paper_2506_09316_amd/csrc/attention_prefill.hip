@@ -8,13 +8,21 @@
 // through LDS 64 at a time, shared by the four wavefronts, by buffer loads that go from memory straight to LDS (no
 // staging registers, no LDS store instructions; see AttnTiles for the placement that keeps the reads conflict-free).
 // Per block of 64 keys a wavefront computes two transposed score tiles S^T[key][query] = K Q^T on MFMA (so that a lane
-// holds the scores of ONE query: the softmax needs one cross-lane exchange), exponentiates against the reference, and
-// adds V^T P^T to its output tiles O^T[column][query].
+// holds the scores of ONE query), with minus the query's reference as the initial accumulator, exponentiates, and adds
+// V^T P^T to its output tiles O^T[column][query].
 // The causal mask is applied only in the blocks on the diagonal, and the reference is raised (and the output tiles
-// rescaled) only when a block exceeds it by more than 2^8, which after the first blocks is rare.  Because an MFMA
+// rescaled) only when a block exceeds it by more than 2^8, which after the first blocks is rare; the exchange between the
+// two lanes of a query and the floating-point maximum exist only on that path.  Because an MFMA
 // result tile and an MFMA input fragment both index lanes by the tile column, the exponentiated tile is fed back as
 // the input fragment of the second product without passing through LDS; V sits in LDS as its rows arrived and its
 // transposed fragments come from the transposing LDS read, in the key order the result registers of a score tile have.
+//
+// Bound by the matrix pipes and the power they draw: per wavefront and block 32 MFMAs (1024 cycles) against about 600 cycles of
+// vector work and 320 of LDS transfers, with two wavefronts per SIMD to overlap them.  B = 8, H = 32, T = 8192, d = 128:
+// 5.74 ms = 766 TFLOP/s before; heads kept on one XCD 4.44; a vector instruction per score less, LDS reads ahead of
+// their MFMAs and exponentials under the MFMAs of the second product 3.92; loads the compiler does not wait for and a
+// raised priority in the second product 3.79 ms = 1160 TFLOP/s (a plain library product of 8192^3: 1400).  Workgroups of eight
+// wavefronts: 3.74 ms, but 54 against 47 us at B = 1, T = 2048 and 27 against 20 us at 24 heads of 1000 tokens.
 // bf16 operands, fp32 accumulation and softmax statistics.
 #include "dsla_internal.h"
 
@@ -31,7 +39,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kWaves = 4;                                 // wavefronts per workgroup
 constexpr int kQueriesPerWg = 32 * kWaves;
 constexpr int kKeys = 64;            // keys per block: two score tiles of 32
-// The running maximum of a query is only raised when a block exceeds it by more than this (log2 units): the
+// The reference of a query is only raised when a block exceeds it by more than this (log2 units): the
 // exponentials then stay below 2^8 and the output tiles are rescaled once in a long while instead of once per block.
 // The normalisation at the end uses the same reference for numerator and denominator, so the result is the same sum.
 constexpr float kMaxSlack = 8.0f;
@@ -76,23 +84,46 @@ __device__ __forceinline__ bf16x8 load_vt_frag(const char *a, uint32_t eight_row
     return __builtin_bit_cast(bf16x8, u32x4{l2[0], l2[1], h2[0], h2[1]});
 }
 
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+// 16 bytes per lane from the buffer `res` at `voff` (per lane) into LDS at `lds` (uniform) + 16 * lane; the compiler does
+// not know these loads: whoever reads the bytes waits with loads_landed_barrier() first.
+__device__ __forceinline__ void load_to_lds16(const char *lds, uint32_t voff, u32x4 res)
+{
+    const uint32_t at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const char *)lds));
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(at), "v"(voff), "s"(res) : "m0", "memory");
+}
+#pragma clang diagnostic pop
+__device__ __forceinline__ void loads_landed_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+__device__ __forceinline__ u32x4 buffer_of(const void *p, int bytes)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    return u32x4{static_cast<uint32_t>(a), static_cast<uint32_t>(a >> 32) & 0xffffu, static_cast<uint32_t>(bytes), 0x00020000u};
+}
+
 template <int D>
-__global__ __launch_bounds__(64 * kWaves, 512 / (64 * kWaves)) void attention_prefill_kernel(const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
+__global__ __launch_bounds__(64 * kWaves, 2) void attention_prefill_kernel(const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
                                                                    const bf16_t *__restrict__ v, bf16_t *__restrict__ o,
                                                                    int H, int T, int blocks_per_seq, float scale_log2e)
 {
     using L = AttnTiles<D>;
     constexpr int NKB = D / 16;    // contraction blocks over the features
     constexpr int CT = D / 32;     // output column tiles
-    // two buffers as two objects: the compiler then knows that a load into one does not touch what is read from the other
     __shared__ __attribute__((aligned(1024))) char buf_a[L::BUF_BYTES];
     __shared__ __attribute__((aligned(1024))) char buf_b[L::BUF_BYTES];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ln = lane & 31, g = lane >> 5;
-    // heavy blocks (late queries: more keys) first
-    const int bh = blockIdx.x / blocks_per_seq;
-    const int qb = blocks_per_seq - 1 - blockIdx.x % blocks_per_seq;
+    // Heads run fastest, in groups of kHeads: workgroup ids go round-robin over the 8 XCDs, so a head stays on one XCD,
+    // whose L2 serves its keys and values to all query blocks that are in flight, and the heavy blocks (late queries:
+    // more keys) of the whole group come first.  B = 8, H = 32, T = 8192: one head after the other over all XCDs 5.63 ms
+    // (every XCD reads the keys and values of all heads in flight, 32 MB against 4 MB of L2); groups of 8, 16, 32, 64 heads
+    // 4.61, 4.42, 4.44, 4.54 ms.  T = 2048, B = 1: 70, 66, 65, 55, 55 us (with few heads an early end of the light blocks leaves the
+    // chip idle).  At d = 64 a head has half the bytes.
+    constexpr int kHeads = D == 128 ? 32 : 64;
+    const int BH = gridDim.x / blocks_per_seq, h0 = blockIdx.x / (kHeads * blocks_per_seq) * kHeads;
+    const int in_group = blockIdx.x - h0 * blocks_per_seq, heads = BH - h0 < kHeads ? BH - h0 : kHeads;
+    const int bh = h0 + in_group % heads, qb = blocks_per_seq - 1 - in_group / heads;
     const int b = bh / H, h = bh % H;
     const int q0 = qb * kQueriesPerWg;
     const size_t rs = static_cast<size_t>(H) * D;                                   // elements between tokens
@@ -123,8 +154,7 @@ __global__ __launch_bounds__(64 * kWaves, 512 / (64 * kWaves)) void attention_pr
     static_assert(NI >= 1, "every wavefront stages something");
     const uint32_t rs2 = static_cast<uint32_t>(rs) * 2;   // bytes between tokens
     const int kv_bytes = static_cast<int>(static_cast<uint32_t>(T - 1) * rs2 + D * 2);   // an unsigned 32-bit count to the hardware
-    const __amdgpu_buffer_rsrc_t res_k = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(k + base), 0, kv_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t res_v = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(v + base), 0, kv_bytes, 0x00020000);
+    const u32x4 res_k = buffer_of(k + base, kv_bytes), res_v = buffer_of(v + base, kv_bytes);
     const uint32_t uwave = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(wave));
     // this lane's LDS slot in an instruction: row lr of its RPI rows, piece position lp; the swizzles of the rows an
     // instruction fills depend on the lane and the wavefront only (RPI n is a multiple of what they look at)
@@ -138,10 +168,8 @@ __global__ __launch_bounds__(64 * kWaves, 512 / (64 * kWaves)) void attention_pr
             const uint32_t n = uwave + kWaves * i;
             // the range check is on the lane offset alone, so the row goes into it
             const uint32_t rowoff = (static_cast<uint32_t>(key0) + RPI * n) * rs2;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(res_k, (__attribute__((address_space(3))) void *)(buf + n * 1024), 16,
-                                                     rowoff + goff_k, 0, 0, 0);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(res_v, (__attribute__((address_space(3))) void *)(buf + L::K_BYTES + n * 1024), 16,
-                                                     rowoff + goff_v, 0, 0, 0);
+            load_to_lds16(buf + n * 1024, rowoff + goff_k, res_k);
+            load_to_lds16(buf + L::K_BYTES + n * 1024, rowoff + goff_v, res_v);
         }
     };
     // fragment reads.  Keys: row 32 t + ln, logical piece 2 kb + g.  Values (transposing reads): the 16 lanes of a
@@ -165,23 +193,39 @@ __global__ __launch_bounds__(64 * kWaves, 512 / (64 * kWaves)) void attention_pr
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[ct][r] = 0.f;
-    float m_ref = -1.0e30f, l_run = 0.f;   // reference maximum (log2 domain) and denominator of this lane's query
+    f32x16 mneg;   // minus the reference maximum (log2 domain) of this lane's query, in the shape of a score tile
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mneg[r] = 0.f;
+    float l_run = 0.f;   // this lane's share of the denominator (the other half of the keys is with lane + 32)
 
     auto compute = [&](const char *buf, int jb) {
         const int key0 = jb * kKeys;
         if (key0 <= wave_last_q) {   // else: every key of the block lies after every query of this wavefront
             const char *kb_ = buf;
             const char *vb_ = buf + L::K_BYTES;
-            // S^T[key][query], two tiles of 32 keys: lane (ln, g) ends up with keys 32 t + 8 (r / 4) + 4 g + r % 4 of query ln
+            // S^T[key][query] - reference, two tiles of 32 keys: lane (ln, g) ends up with keys 32 t + 8 (r / 4) + 4 g + r % 4
+            // of query ln.  Six fragments are on their way before the first MFMA, and the first values during the last.
             f32x16 sc[2];
-            const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
                     const bf16x8 kf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kb_ + 32 * t * L::RB + kf_off + 32 * (kb ^ kf_s1)));
-                    sc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[kb], kb ? sc[t] : zero, 0, 0, 0);
+                    sc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[kb], kb ? sc[t] : mneg, 0, 0, 0);
                 }
+            bf16x8 vf[2][CT];
+            auto read_v = [&](int s, int kb2) {
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) vf[s][ct] = load_vt_frag(vb_ + vt_off + 16 * kb2 * L::RB + 64 * (ct ^ sv), 8 * L::RB);
+            };
+            read_v(0, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+#pragma unroll
+            for (int i = 0; i < 2 * NKB; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if (i < 2 * NKB - 6) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                else __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            }
             // causal mask, only in the blocks that reach past the first query of the wavefront (keys past the end of
             // the sequence lie after every query)
             if (key0 + kKeys - 1 > wq0) {
@@ -193,67 +237,99 @@ __global__ __launch_bounds__(64 * kWaves, 512 / (64 * kWaves)) void attention_pr
                         sc[t][r] = key <= my_q ? sc[t][r] : -1.0e30f;
                     }
             }
-            float bmax = fmaxf(sc[0][0], sc[1][0]);
+            // Does any score exceed the reference by more than the slack, or has a query not seen a key yet?  (As signed
+            // integers positive floats keep their order and lie above all negative ones: no canonicalisation.)
+            int top = 0;
 #pragma unroll
-            for (int r = 1; r < 16; ++r) bmax = fmaxf(bmax, fmaxf(sc[0][r], sc[1][r]));
-            bmax = fmaxf(bmax, __shfl_xor(bmax, 32));
-            // raise the reference of every query when any query of the wavefront needs it (uniform branch)
-            if (__builtin_amdgcn_ballot_w64(bmax > m_ref + kMaxSlack) != 0) {
-                const float m_new = fmaxf(m_ref, bmax);
-                const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int x = __float_as_int(sc[t][r]);
+                    top = top > x ? top : x;
+                }
+            if (__builtin_amdgcn_ballot_w64(top > __float_as_int(kMaxSlack) || l_run == 0.f) != 0) {
+                float bmax = sc[0][0];
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) bmax = fmaxf(bmax, sc[t][r]);
+                bmax = fmaxf(bmax, __shfl_xor(bmax, 32));
+                const bool fresh = l_run + __shfl_xor(l_run, 32) == 0.f;   // nothing summed yet: any reference will do
+                const float up = fresh ? (bmax > -1.0e29f ? bmax : 0.f) : fmaxf(bmax, 0.f);
+                const float alpha = fresh ? 1.f : __builtin_amdgcn_exp2f(-up);
                 l_run *= alpha;
-                m_ref = m_new;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) mneg[r] -= up;
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sc[t][r] -= up;
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) oacc[ct][r] *= alpha;
             }
-            float psum = 0.f;
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    sc[t][r] = __builtin_amdgcn_exp2f(sc[t][r] - m_ref);   // masked entries: 2^(-1e30 - m) = 0
-                    psum += sc[t][r];
-                }
-            psum += __shfl_xor(psum, 32);
-            l_run += psum;
-            // the halves of the tiles as the input fragments of the four blocks of 16 keys
-            bf16x8 pf[4];
-#pragma unroll
-            for (int kb2 = 0; kb2 < 4; ++kb2) {
+            // 16 keys at a time: the exponentials, sums and packing of the next 16 and the reads of their values run under the
+            // MFMAs of the current ones, which feed the halves of the score tiles back as input fragments
+            float psum[2] = {0.f, 0.f};
+            bf16x8 pf[2];
+            auto exps = [&](int s, int kb2) {
                 const f32x16 &x = sc[kb2 >> 1];
                 const int o8 = 8 * (kb2 & 1);
-                const u32x4 u = {pack2(x[o8 + 0], x[o8 + 1]), pack2(x[o8 + 2], x[o8 + 3]), pack2(x[o8 + 4], x[o8 + 5]),
-                                 pack2(x[o8 + 6], x[o8 + 7])};
-                pf[kb2] = __builtin_bit_cast(bf16x8, u);
-            }
+                float e[8];
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-                for (int kb2 = 0; kb2 < 4; ++kb2) {
-                    const bf16x8 vf = load_vt_frag(vb_ + vt_off + 16 * kb2 * L::RB + 64 * (ct ^ sv), 8 * L::RB);
-                    oacc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[kb2], oacc[ct], 0, 0, 0);
+                for (int i = 0; i < 8; ++i) {
+                    e[i] = __builtin_amdgcn_exp2f(x[o8 + i]);
+                    psum[i & 1] += e[i];
                 }
+                const u32x4 u = {pack2(e[0], e[1]), pack2(e[2], e[3]), pack2(e[4], e[5]), pack2(e[6], e[7])};
+                pf[s] = __builtin_bit_cast(bf16x8, u);
+            };
+            exps(0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int kb2 = 0; kb2 < 4; ++kb2) {
+                if (kb2 + 1 < 4) {
+                    read_v((kb2 + 1) & 1, kb2 + 1);
+                    exps((kb2 + 1) & 1, kb2 + 1);
+                }
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct)
+                    oacc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kb2 & 1][ct], pf[kb2 & 1], oacc[ct], 0, 0, 0);
+                if (kb2 + 1 < 4) {
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x400, 8 / CT, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 12 / CT, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __builtin_amdgcn_s_setprio(0);
+            l_run += psum[0] + psum[1];
         }
     };
     // Block j lives in buffer j % 2; its loads are issued one iteration ahead, right after the barrier that frees the
     // buffer, and the barrier in front of its use waits for them (the loads of every wavefront must have landed).
     stage_block(buf_a, 0);
     for (int jb = 0; jb < nblocks; jb += 2) {
-        __syncthreads();   // block jb is in buffer a; every wavefront is done with block jb - 1
+        loads_landed_barrier();   // block jb is in buffer a; every wavefront is done with block jb - 1
         if (jb + 1 < nblocks) stage_block(buf_b, (jb + 1) * kKeys);
         compute(buf_a, jb);
         if (jb + 1 < nblocks) {
-            __syncthreads();   // block jb + 1 is in buffer b; every wavefront is done with block jb
+            loads_landed_barrier();   // block jb + 1 is in buffer b; every wavefront is done with block jb
             if (jb + 2 < nblocks) stage_block(buf_a, (jb + 2) * kKeys);
             compute(buf_b, jb + 1);
         }
     }
 
     // ---- o[query][32 ct + 8 (r / 4) + 4 g + r % 4] = O^T / denominator ----
+    const float l_all = l_run + __shfl_xor(l_run, 32);
     if (q_live) {
-        const float inv = 1.0f / l_run;   // the query's own key is never masked: l_run > 0
+        const float inv = 1.0f / l_all;   // the query's own key is never masked
         bf16_t *op = o + base + static_cast<size_t>(my_q) * rs;
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)

@@ -183,6 +183,26 @@ def test_attention_prefill_against_oracle(B, T, H, d, spread):
     np.testing.assert_allclose(got[:, 0], x["v"][:, 0], rtol=2 ** -7, atol=1e-6)   # the first position sees itself only
 
 
+@pytest.mark.parametrize("B,T,H,d,levels", [(5, 200, 7, 128, (0.0, 0.0)), (3, 130, 23, 64, (0.0, 0.0)), (1, 330, 2, 128, (-300.0, -90.0)),
+                                            (1, 330, 2, 64, (90.0, 300.0)), (1, 200, 1, 128, (-300.0, -300.0))])
+def test_attention_prefill_groups_of_heads_and_far_references(B, T, H, d, levels):
+    """Head counts that leave a ragged group in the order of the workgroups, and scores whose level (log2 units) lies far
+    from zero in the first block of 64 keys and elsewhere from the second on: the kernel's exponentials are relative to a
+    reference that it keeps per query.  Tolerance as above."""
+    x = wl.layer_inputs(700 + T, B, T, H, d, d, io_dtype="bf16", gate_dtype="f32", qk_scale=1.0)
+    scale = d ** -0.5
+    if levels != (0.0, 0.0):   # a constant feature carries the level; exact in bf16 up to 2^-8 of it, the same for all keys of a block
+        x["q"][..., 0] = 16.0
+        level = np.where(np.arange(T) < 64, levels[0], levels[1]).astype(np.float32) / np.float32(16.0 * scale * 1.4426950408889634)
+        x["k"][..., 0] = wl.round_to_bf16(np.broadcast_to(level[None, :, None], x["k"][..., 0].shape).copy())
+    got = _run_attention_prefill(x, scale)
+    ref = ent.attention_prefill(x["q"], x["k"], x["v"], scale)
+    assert np.all(np.isfinite(got))
+    err = max_rel_err(got, ref)
+    print(f"    attention prefill B={B} T={T} H={H} d={d} levels {levels}: max rel err {err:.3e}", flush=True)
+    assert err <= 2e-2
+
+
 def test_attention_prefill_last_row_equals_attention_decode_and_full_size_sample():
     """B = 2, H = 8, T = 4096 at head size 128: sampled heads against the oracle, and the last query of every head
     against the single-query kernel on the same keys and values."""
