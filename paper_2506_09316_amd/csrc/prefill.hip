@@ -413,6 +413,7 @@ struct PrefillArgs {
     float wa, wb;
     const float *wa_per_head, *wb_per_head;   // optional [H]
     float gate_inv_tau;      // 0: g1, g2 are log-gates; else they are pre-activations and this is 1 / tau
+    int longest_first;       // chunk loop on whole packed sequences: workgroups take them in the order of their lengths
     int slot_mul;            // chunk loop: segment p starts from workspace slot p * slot_mul (the pre-pass and the scan may
                              // work on pieces of a segment: see PrefillPlan::pre_split)
 };
@@ -1210,6 +1211,35 @@ struct Kern {
         }
     }
 
+    // The r-th longest of the B <= NT packed sequences (the earlier one where lengths are equal).  With several rounds of
+    // workgroups per compute unit the last to start decide when the call ends: 37 sequences of up to 2782 tokens (32
+    // heads, d = 128) take 343 us in a random order and 242 us longest first; 37 of up to 413 tokens 115 and 104 us.
+    // Finding the rank costs a workgroup the two loads of a length and B / 4 LDS reads.
+    static __device__ int sequence_of_rank(const PrefillArgs &a, uint32_t sm, int r, int B)
+    {
+        typedef int i32x4 __attribute__((ext_vector_type(4)));
+        const int t = threadIdx.x;
+        int len = -1;
+        if (t < B) {
+            const int sq = a.seq ? a.seq[t] : t;
+            len = a.cu[sq + 1] - a.cu[sq];
+        }
+        lds_st<int>(sm + 4 * t, len);
+        __syncthreads();
+        int rank = 0;
+        for (int u = 0; u < B; u += 4) {   // entries past the last sequence hold -1
+            const i32x4 l = lds_ld<i32x4>(sm + 4 * u);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) rank += (l[e] > len || (l[e] == len && u + e < t)) ? 1 : 0;
+        }
+        __syncthreads();
+        if (t < B && rank == r) lds_st<int>(sm, t);
+        __syncthreads();
+        const int b = __builtin_amdgcn_readfirstlane(lds_ld<int>(sm));
+        __syncthreads();
+        return b;
+    }
+
     static __device__ void run(const PrefillArgs &a, uint32_t sm)
     {
         const int tid = threadIdx.x;
@@ -1236,6 +1266,7 @@ struct Kern {
             h = bh % a.H;
             slot0 = bh;
             slot_step = gridDim.x / nseg;   // B H
+            if (kFull && !kExt && a.longest_first) bidx = sequence_of_rank(a, sm, bidx, static_cast<int>(slot_step) / a.H);
         }
 
         // this sequence: first token in the token-major tensors, length, where its states live
@@ -1984,6 +2015,9 @@ bool combo_built(int D, int C, int io)
 }  // namespace
 
 namespace {
+// Workgroups of the chunk loop that the chip holds at one time: two per compute unit at d = 64 with 16-bit io, else one (LDS).
+int chip_slots(const dsla_desc &d) { return d.d_k == 64 && d.io_dtype == DSLA_BF16 ? 512 : 256; }
+
 // Fills the plan from the chunk length, the number of segments P the longest sequence is cut into, and its length.
 void finish_plan(const dsla_desc &d, int C, int64_t P, int64_t nchunks, bool may_split, PrefillPlan *plan)
 {
@@ -2035,20 +2069,39 @@ bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan)
     if (d.segments > 0) {
         P = d.segments;
     } else {
-        // enough workgroups to cover the 256 compute units (two per unit for the small head size),
-        // but at least 4 chunks per segment so that the extra segment_state pass stays cheap
+        // Enough workgroups to cover the chip, but at least 4 chunks per segment ...
         const int64_t target = (d.d_k == 64) ? 512 : 256;
         P = target / BH;
         if (P > nchunks / 4) P = nchunks / 4;
+        // ... or fewer where that leaves the chip idle (plans of one or two segments stay as they are in 16 bits: there
+        // the pre-pass and the scan cost what the shorter segments gain).  A step of 32 tokens takes 2 us in 16-bit
+        // arithmetic however few workgroups run, in fp32 7 us (d = 64) and 16 us (d = 128), a segment's share of the
+        // pre-pass half of that, pre-pass and scan about 15 us more.  Measured in us at 1000 tokens with 4, 3, 2 chunks per
+        // segment: bf16, 32 heads, d = 128 47, 43, 47; 8 heads 43, 38, 36; 4 heads, d = 64 35, 30, 27; fp32, 32 heads, d = 128
+        // 199, 166, 141; fp32, 4 heads, d = 64, 256 tokens whole and with 4, 2, 1 chunks: 60, 60, 49, 33.
+        const bool f32 = d.io_dtype == DSLA_F32;
+        // 256 heads of 1000, 2000, 8000 tokens, d = 64, whole / in two: 54 / 71, 104 / 156, 382 / 602; 160 heads whole / in three: 52 / 62, 127 / 135, 365 / 394
+        if (!f32 && d.d_k == 64 && BH > 128) P = 1;
+        if (P >= 3 || (f32 && (P < 2 || BH * P > chip_slots(d)))) {
+            const int64_t most = chip_slots(d) / BH;
+            const int64_t least = f32 ? 1 : (BH * ((nchunks + 1) / 2) <= 128 ? 2 : 3);   // chunks per segment
+            int64_t cps = most > 0 ? (nchunks + most - 1) / most : nchunks;
+            if (cps < least) cps = least;
+            P = (nchunks + cps - 1) / cps;
+        }
     }
     finish_plan(d, C, P, nchunks, d.segments <= 0, plan);
     return true;
 }
 
 // Packed sequences of different lengths share one segment length; a sequence of length T_b has
-// ceil(T_b / segment_tokens) segments.  The segment length is chosen so that all sequences together make about
-// one workgroup per compute unit, the same rule as above on the total instead of a common length (measured on
-// mixed batches: twice as many segments gain on some mixes and lose on others, within 10 %).
+// ceil(T_b / segment_tokens) segments.  If they are cut, the segment length is chosen so that all sequences together make
+// about one workgroup per compute unit, the same rule as above on the total instead of a common length (measured on
+// mixed batches: twice as many segments gain on some mixes and lose on others, within 10 %).  Whether they are cut is a
+// matter of estimates (us): whole sequences take as long as the longest one or as all of them spread over the chip; cut
+// ones pay the lists, the pre-pass and the scan for shorter chains.  Measured whole / cut: 40 sequences of up to 651
+// tokens (32 heads, d = 128) 127 / 180; 20 of up to 8192 659 / 742; 11 of up to 956 (d = 64) 63 / 78; 8 sequences, one of
+// 1900 tokens and 7 short ones 129 / 84; 22 of up to 4015 tokens with 8 heads 257 / 94.
 // The kernels find their work in lists built on the device (the lengths are not known here); list and workspace
 // sizes are worst cases: sum_b ceil(T_b / L) <= total_T / L + B segments, of which at most total_T / L have a
 // successor.
@@ -2065,6 +2118,25 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
         int64_t cps = (total_T * d.H / target + C - 1) / C;   // chunks per segment
         if (cps < 4) cps = 4;
         P = (nchunks + cps - 1) / cps;
+        if (P > 1) {
+            const bool f32 = d.io_dtype == DSLA_F32, small = d.d_k == 64, preact = d.gate_mode == DSLA_GATE_PREACT;
+            // a step of 32 tokens where the chain of one workgroup counts / where every compute unit is busy, a step of the
+            // pre-pass, what a workgroup costs besides its steps, a state slot written, scanned and read again
+            const double step = f32 ? (small ? 7.0 : 16.0) : (small ? (preact ? 1.8 : 1.4) : (preact ? 2.35 : 2.0));
+            const double step_full = f32 ? step : (small ? 2.5 : (preact ? 3.4 : 2.9));
+            const double pre = f32 ? step / 3 : (small ? 1.2 : (preact ? 2.1 : 1.5));
+            const double wg = small ? 5.0 : 8.0, slot = small ? 0.0125 : 0.05;
+            const double chip = chip_slots(d), steps = static_cast<double>(total_T) / 32, L = static_cast<double>(cps * C);
+            const double n = L / 32, longest = static_cast<double>(max_T) / 32;
+            const double cuts = static_cast<double>(total_T) / L * d.H, items = cuts + static_cast<double>(d.B) * d.H;
+            auto loop = [&](double chain, double workgroups) {
+                const double spread = workgroups / chip * wg + steps * d.H / chip * step_full;
+                return spread > wg + chain * step ? spread : wg + chain * step;
+            };
+            const double whole = loop(longest, static_cast<double>(d.B) * d.H);
+            const double cut = 7 + wg + (cuts > chip ? cuts / chip : 1.0) * n * pre + 4 + slot * items + loop(n, items);
+            if (whole <= cut) P = 1;
+        }
     }
     finish_plan(d, C, P, nchunks, false, plan);
     if (plan->segments > 1) {
@@ -2120,6 +2192,8 @@ hipError_t launch_prefill(const dsla_desc &d, const PrefillPlan &plan, int64_t T
         w += up(plan.max_items * 8);
         a.list_pre = reinterpret_cast<int2 *>(w);
     }
+    a.longest_first = cu_seqlens && plan.segments == 1 && d.B > 1 && d.B <= 4 * d.d_k &&
+                      T > 256 && static_cast<int64_t>(d.B) * d.H > chip_slots(d);   // (up to 256 tokens the rank costs what it gains)
     a.T = T;
     a.seg_tokens = plan.segment_tokens;
     a.H = d.H;

@@ -118,6 +118,20 @@ def test_varlen_many_sequences():
     _run_varlen(lengths, 1, 64, "bf16", "bf16", 2e-2, segments=6, chunk=32, seed=93)
 
 
+@pytest.mark.parametrize("lengths,H,d,io,gate", [
+    ([40, 0, 300, 7, 300, 64, 31, 200, 1, 90, 0, 290, 33, 120, 300, 5, 16, 280, 2], 14, 128, "bf16", "bf16"),   # equal and empty ones, B % 4 = 3
+    ([3, 270, 65, 1], 65, 64, "f32", "f32"),                        # 260 workgroups, one round holds 256
+    ([5] * 100 + [300] + [9, 0] * 77 + [17], 3, 64, "bf16", "bf16"),   # as many sequences as a workgroup has threads
+    ([5] * 100 + [300] + [9, 0] * 78, 3, 64, "bf16", "bf16")])         # one more: taken in their own order
+def test_varlen_longest_first(lengths, H, d, io, gate):
+    """Whole sequences whose workgroups do not fit the chip at one time: the workgroups take them by length."""
+    B = len(lengths)
+    assert B * H > (512 if d == 64 and io == "bf16" else 256) and max(lengths) > 256
+    desc = dsla.make_desc(B, H, d, d, io_dtype=code(io), gate_dtype=code(gate), chunk=64)
+    assert dsla.dsla_prefill_varlen_workspace_bytes(desc, sum(lengths), max(lengths)) == 0
+    _run_varlen(lengths, H, d, io, gate, 1e-4 if io == "f32" else 2e-2, slots=list(range(B))[::-1], n_slots=B + 1)
+
+
 def test_varlen_gate_preactivations():
     import torch
     lengths, H, d, tau = [300, 77, 1, 640], 2, 128, 16.0

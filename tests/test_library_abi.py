@@ -209,3 +209,22 @@ def test_conversion_logic_against_its_oracle(lib):
     cnt = ctypes.c_int32()
     assert lib.dsla_conversion_plan(3, bad, 10, 5, 2, 1, 1.0, conv, ctypes.byref(cnt), None, None) == 2
     assert lib.dsla_rank_layers(2, (ctypes.c_float * 2)(1.0, float("nan")), (ctypes.c_int32 * 2)()) == 2
+
+
+def test_plans_follow_the_work(lib):
+    slots = lambda n, H, d: n * H * 2 * d * d * 4
+    up = lambda n: (n + 255) // 256 * 256
+    dense = lambda B, H, d, io, T: lib.dsla_prefill_workspace_bytes(
+        ctypes.byref(dsla.make_desc(B, H, d, d, io_dtype=io, gate_dtype=io, chunk=64)), T)
+    want = lambda P, BH, d: slots(P, BH, d) + up((P - 1) * BH * 2 * d * 4)
+    assert dense(1, 32, 128, 1, 1000) == want(6, 32, 128)     # 3 chunks per segment
+    assert dense(1, 4, 128, 1, 1000) == want(8, 4, 128)       # 2 where that leaves most of the chip idle
+    assert dense(1, 4, 64, 0, 256) == want(4, 4, 64)          # fp32: short prompts are cut too, down to a chunk
+    assert dense(1, 32, 128, 0, 1000) == want(8, 32, 128)     # and never into more than the chip holds
+    assert dense(8, 32, 64, 1, 4000) == 0                     # 256 heads at d = 64: whole
+    assert dense(1, 32, 128, 1, 256) == 0
+    packed = lambda B, H, d, total, longest: lib.dsla_prefill_varlen_workspace_bytes(
+        ctypes.byref(dsla.make_desc(B, H, d, d, io_dtype=1, gate_dtype=1, chunk=64)), total, longest)
+    assert packed(40, 32, 128, 3460, 651) == 0                # many short sequences fill the chip whole
+    assert packed(8, 32, 128, 1959, 1900) > 0                 # one long chain is cut
+    assert packed(22, 8, 128, 9484, 4015) > 0
