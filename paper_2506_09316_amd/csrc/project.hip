@@ -8,13 +8,21 @@
 // bf16 operands, fp32 accumulation, bf16 results.  Kernels (launch_project has the rule):
 //
 // project_tile_kernel<4> (K a multiple of 128): workgroup = 256 threads = 4 wavefronts on a 256 x 256 output tile, one
-// wavefront per SIMD with a 128 x 128 quadrant = sixteen 32 x 32 MFMA tiles whose 256 accumulator registers live in
-// the accumulation half of the register file.  Per 16 values of K a wavefront reads 4 + 4 fragments from LDS for 16
-// MFMAs - half a 16-byte LDS read per MFMA, a quarter of what a 64 x 64 quadrant needs, which is what keeps the LDS
-// (128 bytes per clock and CU) out of the way.  K in stages of 32 through a ring of four LDS stages (4 x 32 KB),
+// wavefront per SIMD with a 128 x 128 quadrant = 8 x 8 MFMA tiles of 16 x 16 whose 256 accumulator registers live in
+// the accumulation half of the register file.  Per 32 values of K a wavefront reads 8 + 8 fragments from LDS for 64
+// MFMAs, which keeps the LDS out of the way.  K in stages of 32 through a ring of four LDS stages (4 x 32 KB),
 // filled by buffer loads that write LDS directly (no staging registers, no LDS store instructions): a load has two
-// stages to arrive.  A row of a stage is 64 bytes, its four 16-byte pieces stored at piece position c ^ ((row / 4) % 4),
-// so that the fragment reads of 16 lanes at a time touch every bank once.
+// stages to arrive.  Bound by power: the chip runs it at 1.8 GHz with the matrix pipes 73 % busy, and what an MFMA draws
+// decides - registers only, 16 x 16 x 32 sustains 2.04 PFLOP/s and 32 x 32 x 16 1.77 (fewer accumulators are read and written
+// per product).  M = 16384, K = 4096, N = 20480: 2.29 ms on 32 x 32 x 16, 2.09 on 16 x 16 x 32, 1.98 with the tile order
+// below (1390 TFLOP/s; a plain library product of this shape 1.87 ms); with other inputs each time 2.34 ms before and 2.15 now;
+// M = 4096 0.54, 0.49, 0.48 ms.
+// A row of a stage is 64 bytes; its piece c sits at piece position c ^ 2 (row / 8 % 2).  A 16-byte LDS read takes lanes 0-3,
+// 12-15, 20-27 at one time, then 4-11, 16-19, 28-31, and so on (32-63 alike): with this placement each of those
+// sixteen finds its own four banks (no conflicts; with c ^ (row / 4 % 4), made for sixteen lanes in a row, every read took
+// half as long again).  Tried and left out: a barrier every two stages (loads then have one and a half stages to arrive:
+// 2.31 against 2.13 ms), tiles one after the other on a persistent grid with the next tile's stages loaded under
+// the results' stores (2.17 against 2.08 ms: 512 registers do not hold it without spills).
 //
 // project_tile_kernel<2>: the same on 128 x 128 tiles, two workgroups per compute unit, for outputs that do not fill the
 // chip with large tiles.
@@ -67,10 +75,11 @@ __device__ __forceinline__ void wait_loads()   // at most N of this wavefront's 
 // Tile order: the 8 XCDs each take a contiguous run of the linear tile order (workgroup ids go round-robin over the
 // XCDs, each XCD has its own L2), and the linear order runs in groups of GM row tiles: inside a group the row tile
 // runs fastest, then the column tile, so the tiles in flight at one time (a few dozen per XCD) share GM panels of x
-// and a handful of panels of W instead of one panel of W and dozens of x.  False: no tile for this workgroup.
+// and a handful of panels of W instead of one panel of W and dozens of x.  M = 16384, K = 4096, N = 20480 with GM = 4, 6, 8,
+// 16: 1.98, 1.99, 2.09, 2.24 ms.  False: no tile for this workgroup.
 __device__ __forceinline__ bool tile_of(int tiles_m, int tiles_n, int &tm, int &tn)
 {
-    constexpr int GM = 8;
+    constexpr int GM = 4;
     const long long ntiles = static_cast<long long>(tiles_m) * tiles_n;
     const long long per_xcd = (ntiles + 7) / 8;
     const long long lin = static_cast<long long>(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
@@ -132,14 +141,13 @@ __global__ __launch_bounds__(256, Q == 4 ? 1 : 2) void project_tile_kernel(const
     const int n0 = tn * BN;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int ln = lane & 31, g = lane >> 5;
+    const int r = lane & 15, g = lane >> 4;
     const int wm = wave >> 1, wn = wave & 1;   // this wavefront's quadrant
     const uint32_t uwave = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(wave));
 
     // Buffer loads with LDS as destination: one instruction of a wavefront fills 1 KB = 16 rows of 64 bytes of a
     // tile; instruction n = wave + 4 i (i < Q) fills rows 16 n .. 16 n + 15.  A lane fills LDS slot (row lane / 4, piece
-    // position lane % 4) and fetches the piece that belongs there: piece c of row r sits at position c ^ ((r / 4) % 4),
-    // so the 16 rows that 16 lanes read at the same logical piece fall into 16 different groups of four banks.  The
+    // position lane % 4) and fetches the piece that belongs there (piece c of row R sits at c ^ 2 (R / 8 % 2)).  The
     // descriptor of an operand starts at the tile's first row and ends with the last row that exists: rows past the
     // end of x or W arrive as zeros.
     const long long rows_a = M - m0 < BM ? M - m0 : BM, rows_b = N - n0 < BN ? N - n0 : BN;
@@ -151,7 +159,7 @@ __global__ __launch_bounds__(256, Q == 4 ? 1 : 2) void project_tile_kernel(const
 #pragma unroll
     for (int i = 0; i < Q; ++i)
         voff[i] = (16 * (uwave + 4 * i) + (static_cast<uint32_t>(lane) >> 2)) * static_cast<uint32_t>(K) * 2u +
-                  16 * ((lane & 3u) ^ ((static_cast<uint32_t>(lane) >> 4) & 3u));
+                  16 * ((lane & 3u) ^ (((static_cast<uint32_t>(lane) >> 5) & 1u) << 1));
     const int nk = K / BK;
     auto fetch = [&](char *st, int ks) {   // K-step ks (past the end: the last one again, never used) into a stage
         const int kbyte = (ks < nk ? ks : nk - 1) * BK * 2;
@@ -163,58 +171,53 @@ __global__ __launch_bounds__(256, Q == 4 ? 1 : 2) void project_tile_kernel(const
         }
     };
 
-    // fragment reads: row (quadrant + 32 i + ln) of a tile, block kb of 16 values of K: piece 2 kb + g
-    const uint32_t swz = (ln >> 2) & 3;
-    const uint32_t fo0 = ((0 + g) ^ swz) << 4, fo1 = ((2 + g) ^ swz) << 4;
-    const uint32_t fa_row = static_cast<uint32_t>((QS * wm + ln) * ROWB);
-    const uint32_t fb_row = static_cast<uint32_t>(OPB + (QS * wn + ln) * ROWB);
-    bf16x8 fa[2][Q], fb[2][Q];   // fragments of two blocks: one in use, one arriving
-    auto read_frags = [&](int buf, const char *st, int kb) {
-        const uint32_t fo = kb ? fo1 : fo0;
+    // fragment reads: row (quadrant + 16 i + r) of a tile, values 8 g .. 8 g + 7 of the stage: piece g
+    constexpr int NF = 2 * Q;   // 16 x 16 tiles along each side of the quadrant
+    const uint32_t fo = (g ^ ((r >> 3) << 1)) << 4;
+    const uint32_t fa_row = static_cast<uint32_t>((QS * wm + r) * ROWB) + fo;
+    const uint32_t fb_row = static_cast<uint32_t>(OPB + (QS * wn + r) * ROWB) + fo;
+    struct Frags {
+        bf16x8 a[NF], b[NF];
+    };
+    auto read_frags = [&](Frags &f, const char *st) {
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            fa[buf][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(st + fa_row + i * 32 * ROWB + fo));
-            fb[buf][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(st + fb_row + i * 32 * ROWB + fo));
+        for (int i = 0; i < NF; ++i) {
+            f.a[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(st + fa_row + i * 16 * ROWB));
+            f.b[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(st + fb_row + i * 16 * ROWB));
         }
     };
 
-    f32x16 acc[Q][Q];
+    f32x4 acc[NF][NF];
 #pragma unroll
-    for (int i = 0; i < Q; ++i)
+    for (int i = 0; i < NF; ++i)
 #pragma unroll
-        for (int j = 0; j < Q; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int j = 0; j < NF; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    auto block = [&](int kb) {
-#pragma unroll
-        for (int i = 0; i < Q; ++i)
-#pragma unroll
-            for (int j = 0; j < Q; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kb][j], fa[kb][i], acc[i][j], 0, 0, 0);
-#pragma unroll
-        for (int t = 0; t < Q * Q; ++t) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                       // 1 MFMA
-            if (Q == 2 || t % 2 == 0) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);             // 1 LDS read
-            if (kb == 0 && (Q == 2 || t % 2 == 1)) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);   // 1 load into LDS
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    // One K-step from stage `cur`.  On entry the fragments of its first block are in registers and stage `nxt` holds
+    // One K-step.  On entry its fragments are in registers (or on their way) and stage `nxt` holds
     // what this wavefront loaded of the next step but one barrier short of being complete for everybody: the barrier
-    // at the start certifies `nxt` (every wavefront has waited for its own loads of it: all but the 8 youngest, which
-    // belong to the stage after) and frees `old` (everybody is done with the step before), which then takes K-step
-    // ks + 3.  So a load has two steps to arrive, and no MFMA waits behind a barrier for LDS latency: the first
-    // fragments of `nxt` are read during the second block.
-    auto step = [&](const char *cur, const char *nxt, char *old, int ks) {
+    // at the start certifies `nxt` (every wavefront has waited for its own loads of it: all but the 2 Q youngest, which
+    // belong to the stage after) and frees `old` (everybody has multiplied the step before, so nobody reads it any more),
+    // which then takes K-step ks + 3.  So a load has two steps to arrive, and the fragments of `nxt` are read under the
+    // MFMAs of the current step.
+    auto step = [&](const Frags &cur, Frags &nf, const char *nxt, char *old, int ks) {
         wait_loads<2 * Q>();
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        asm volatile("s_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         fetch(old, ks + 3);
-        read_frags(1, cur, 1);
-        block(0);
-        read_frags(0, nxt, 0);
-        block(1);
+        read_frags(nf, nxt);
+#pragma unroll
+        for (int i = 0; i < NF; ++i)
+#pragma unroll
+            for (int j = 0; j < NF; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.b[j], cur.a[i], acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int t = 0; t < 2 * NF; ++t) {
+            __builtin_amdgcn_sched_group_barrier(0x008, NF / 4, 0);                 // MFMAs
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                      // 1 LDS read
+            __builtin_amdgcn_sched_group_barrier(0x008, NF / 4, 0);
+            if (t % 2 == 0) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);      // 1 load into LDS
+        }
+        __builtin_amdgcn_sched_barrier(0);
     };
     // nk is a multiple of 4 (K is a multiple of 128): the loop body has no branch, so the accumulators stay where they are
     fetch(st0, 0);
@@ -222,13 +225,14 @@ __global__ __launch_bounds__(256, Q == 4 ? 1 : 2) void project_tile_kernel(const
     fetch(st2, 2);
     wait_loads<4 * Q>();
     asm volatile("s_barrier" ::: "memory");   // stage 0 is complete
-    read_frags(0, st0, 0);
+    Frags f0, f1;
+    read_frags(f0, st0);
     __builtin_amdgcn_sched_barrier(0);
     for (int ks = 0; ks < nk; ks += 4) {
-        step(st0, st1, st3, ks);
-        step(st1, st2, st0, ks + 1);
-        step(st2, st3, st1, ks + 2);
-        step(st3, st0, st2, ks + 3);
+        step(f0, f1, st1, st3, ks);
+        step(f1, f0, st2, st0, ks + 1);
+        step(f0, f1, st3, st1, ks + 2);
+        step(f1, f0, st0, st2, ks + 3);
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // nothing in flight; everybody is done reading
 
@@ -240,23 +244,19 @@ __global__ __launch_bounds__(256, Q == 4 ? 1 : 2) void project_tile_kernel(const
     char *epi = wave == 0 ? st0 : (wave == 1 ? st1 : (wave == 2 ? st2 : st3));
     const int nq = n0 + QS * wn;   // first column of the quadrant: inside one output tensor (width is a multiple of 128)
 #pragma unroll
-    for (int i = 0; i < Q; ++i)
+    for (int i = 0; i < NF; ++i)
 #pragma unroll
-        for (int j = 0; j < Q; ++j)
+        for (int j = 0; j < NF; ++j) {
+            const int cq = 16 * j + 4 * g;   // column inside the quadrant
+            f32x4 c = acc[i][j];
+            if (bias && nq + cq < N) {
+                const f32x4 bv = *reinterpret_cast<const f32x4 *>(bias + nq + cq);
 #pragma unroll
-            for (int rb4 = 0; rb4 < 4; ++rb4) {
-                const int cq = 32 * j + 8 * rb4 + 4 * g;   // column inside the quadrant
-                float c0 = acc[i][j][4 * rb4], c1 = acc[i][j][4 * rb4 + 1], c2 = acc[i][j][4 * rb4 + 2], c3 = acc[i][j][4 * rb4 + 3];
-                if (bias && nq + cq < N) {
-                    const f32x4 bv = *reinterpret_cast<const f32x4 *>(bias + nq + cq);
-                    c0 += bv[0];
-                    c1 += bv[1];
-                    c2 += bv[2];
-                    c3 += bv[3];
-                }
-                const int row = 32 * i + ln, piece = cq >> 3;
-                *reinterpret_cast<u32x2 *>(epi + row * (2 * QS) + ((piece ^ (row & (PPR - 1))) << 4) + (cq & 4) * 2) = u32x2{pack2(c0, c1), pack2(c2, c3)};
+                for (int e = 0; e < 4; ++e) c[e] += bv[e];
             }
+            const int row = 16 * i + r, piece = cq >> 3;
+            *reinterpret_cast<u32x2 *>(epi + row * (2 * QS) + ((piece ^ (row & (PPR - 1))) << 4) + (cq & 4) * 2) = u32x2{pack2(c[0], c[1]), pack2(c[2], c[3])};
+        }
     if (nq < N) {
         bf16_t *out = static_cast<bf16_t *>(outs.p[nq / width]) + nq % width;
         const int rsub = lane / PPR, piece = lane % PPR;   // PPR lanes per row
