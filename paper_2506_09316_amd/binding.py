@@ -11,6 +11,7 @@ import os
 HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(HERE, "libdsla.so")
 _lib = None
+_torch = None   # torch._C once the library is loaded
 
 DSLA_F32, DSLA_BF16 = 0, 1
 KERNEL_NAMES = ("state_init", "prefill_segment_state", "prefill_segment_scan", "prefill_chunk_loop", "decode",
@@ -52,7 +53,7 @@ def library_path() -> str:
 
 def load_library():
     """Loads libdsla.so (built by paper_2506_09316_amd/build.py).  Raises if it is absent."""
-    global _lib
+    global _lib, _torch
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -61,7 +62,7 @@ def load_library():
     # PyTorch ships its own copy of the HIP runtime.  Whichever copy is loaded first serves the whole process, and
     # tensors and kernels must live in the same one: load PyTorch's before the library pulls in the system's.
     try:
-        import torch  # noqa: F401
+        from torch import _C as _torch
     except ImportError:
         pass
     lib = ctypes.CDLL(_LIB_PATH)
@@ -147,12 +148,13 @@ def _ptr(t):
     if t is None:
         return None
     assert t.is_cuda and t.is_contiguous(), "tensors must be contiguous GPU tensors"
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Handle of torch's current stream on its current device.  torch.cuda.current_stream() builds a Stream object: 3.0 us
+    against 0.2, in a decode call of one sequence that took 8.8 us on the host for 4 us on the GPU (now 5.4)."""
+    return _torch._cuda_getCurrentRawStream(_torch._cuda_getDevice())
 
 
 def make_desc(B, H, d_k, d_v, *, io_dtype, gate_dtype, gamma=0.5, scale=1.0, chunk=0, segments=0,
