@@ -289,14 +289,34 @@ __global__ __launch_bounds__(D) void attn_decode_merge_kernel(const float *__res
 {
     const int bh = blockIdx.x, f = threadIdx.x;
     const float *rec = parts + static_cast<size_t>(bh) * P * (2 + D);
-    float M = rec[0];
-    for (int i = 1; i < P; ++i) M = fmaxf(M, rec[static_cast<size_t>(i) * (2 + D)]);
-    float Z = 0.f, A = 0.f;
-    for (int i = 0; i < P; ++i) {
-        const float *r = rec + static_cast<size_t>(i) * (2 + D);
-        const float c0 = expf(r[0] - M);
-        Z = fmaf(c0, r[1], Z);
-        A = fmaf(c0, r[2 + f], A);
+    // Bound by latency: eight records at a time, all requested before the first is used, in one walk for the maximum and the
+    // sums.  The whole step with 16 parts of 4993 positions (32 heads, d = 128) 27.4 -> 20.3 us, with 32 parts of 8000
+    // positions (8 heads) 25.0 -> 13.5 us; this kernel was half of it.  (Two batches of rows in flight in the kernel above:
+    // 8 x 32 heads of 8192 positions 147 instead of 141 us, 7 x 32 of 564 18.3 instead of 15.3; twice as many parts: 149.)
+    constexpr int U = 8;
+    float M = -1.0e30f, Z = 0.f, A = 0.f;
+    for (int i0 = 0; i0 < P; i0 += U) {
+        float m[U], z[U], a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float *r = rec + static_cast<size_t>(i0 + u < P ? i0 + u : P - 1) * (2 + D);
+            m[u] = r[0];
+            z[u] = r[1];
+            a[u] = r[2 + f];
+        }
+        float top = M;
+#pragma unroll
+        for (int u = 0; u < U; ++u) top = fmaxf(top, m[u]);
+        const float c0 = expf(M - top);
+        Z *= c0;
+        A *= c0;
+        M = top;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float w = i0 + u < P ? expf(m[u] - M) : 0.f;
+            Z = fmaf(w, z[u], Z);
+            A = fmaf(w, a[u], A);
+        }
     }
     o[static_cast<size_t>(bh) * D + f] = from_f32<TIO>(A / Z);
 }
