@@ -436,6 +436,7 @@ struct PrefillArgs {
 //     T <-  T + K~^T V
 //   between two steps the state moves from one middle frame to the next, at the end of a segment to its own frame:
 //     T <-  diag(2^{-(R + R_next)/2}) T          (R_next = 0 after the last step)
+//   (the 16-bit step loop leaves the frame where it is for several steps while the exponents stay small: line_scan_b)
 // Centring halves the largest exponent a step can produce: the factors stay finite while R < 2 * 115, and nothing
 // links the exponents of different steps.
 //
@@ -495,7 +496,8 @@ struct Kern {
     static __device__ __forceinline__ uint32_t vswz(uint32_t row) { return D == 128 ? (row & 3u) : ((row >> 1) & 1u); }
     static constexpr uint32_t O_VT = O_KT + (kTrK ? 0 : 2 * D * TP * ESZ);
     static constexpr uint32_t O_DEC = O_VT + D * TP * ESZ;                     // float [2D]  frame change after the step
-    static constexpr uint32_t SET_BYTES = O_DEC + 2 * D * 4;
+    static constexpr uint32_t O_FLAG = O_DEC + 2 * D * 4;                      // uint8 [CT] (kLineProd): does the frame change of these features do anything
+    static constexpr uint32_t SET_BYTES = O_FLAG + 16;
     static constexpr uint32_t LDS_MAX = 160 * 1024;                            // LDS of a gfx950 compute unit
     // Two operand sets where they fit (the producers then run a whole step ahead of the consumers); one set
     // otherwise (fp32 at d = 128): the producers then only load ahead and prepare between two barriers.
@@ -884,6 +886,7 @@ struct Kern {
         uint32_t tot;         // scan scratch [8 quads][64 features] floats: this lane's 8 features of quad sq
         uint32_t col;         // scan scratch: this lane's column (feature lane of the 64), quad 0
         uint32_t dec;         // decay factor of this lane's column
+        uint32_t flag;        // does it change anything: of this wavefront's columns
         uint32_t qrow[TPT];   // Q~ row of token 4 sq + j, element st D + 64 fh + 8 dg
         uint32_t krow[TPT];   // K~: its row slot
         uint32_t vrow[2];     // V rows of token 16 st + 2 sq + j, columns 64 fh + 8 dg ..
@@ -900,6 +903,7 @@ struct Kern {
             tot = csw + (sq * 64 + 8 * dg) * 4;
             col = csw + lane * 4;
             dec = sm + O_DEC + (st * D + 64 * fh + lane) * 4;
+            flag = sm + O_FLAG + pw;
 #pragma unroll
             for (uint32_t j = 0; j < TPT; ++j) {
                 const uint32_t t = 4 * sq + j;
@@ -944,15 +948,31 @@ struct Kern {
 #pragma unroll
         for (int s2 = 0; s2 < 8; ++s2) t[s2] = lds_ld<float>(pa.col + s2 * 64 * 4);
     }
-    static __device__ __forceinline__ void line_scan_b(const LineAddr &pa, const float (&t)[8], float &total)
+    // The frame of a column.  The state is kept as T with S = 2^{unit pos} T, pos the running gate sum since the frame was
+    // last changed, and the exponents of a step are gate sums counted from there.  As long as pos stays above
+    // -kLazyFrame (log2) in all 64 columns of the wavefront after the next step, the frame stays and the consumers multiply
+    // nothing; otherwise it moves to the middle of the next step (after the last step: to the state itself).  With
+    // gates of a temperature sigmoid that is once in some dozens of steps instead of 128 of the 340 vector
+    // instructions of a consumer in every step; gates so strong that every step would move it behave as they always did.
+    // With the 40 instructions that one exponent for both operands and the sign of the blend coefficient in q's unpacking save
+    // a producer: 8 x 8192 tokens (32 heads, d = 128) 737 -> 695 us = 4.6 TB/s, 16384 tokens 279 -> 269 us, a packed batch of up
+    // to 8192 tokens 665 -> 624 us.  Exponents of up to 32 cost no accuracy: they cancel between the operands, whose
+    // rounding is relative (6 seeds, against 64 bits: outputs 2.73e-3 before and after; gates of very different strength
+    // 2.90e-3 and 2.90e-3, states 1.65e-3 and 1.66e-3).
+    static constexpr float kLazyFrame = 32.f;
+    static __device__ __forceinline__ void line_scan_b(const LineAddr &pa, const float (&t)[8], bool first_or_past, float &pos, float &change,
+                                                       bool &move, float &total)
     {
         const float tot = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
-        float run = -0.5f * tot;   // centred on the step, as scan_b
+        move = first_or_past || __builtin_amdgcn_ballot_w64(!((pos + tot) * pa.unit >= -kLazyFrame)) != 0;
+        float run = move ? -0.5f * tot : pos;   // moved: centred on the step, as scan_b
+        change = (pos - run) * pa.unit;         // log2 of what the state is multiplied by
 #pragma unroll
         for (int s2 = 0; s2 < 8; ++s2) {
             lds_st<float>(pa.col + s2 * 64 * 4, run);
             run += t[s2];
         }
+        pos = run;
         total = tot;
     }
     static __device__ __forceinline__ void line_scan_c(const LineAddr &pa, LineScan &o)
@@ -961,8 +981,8 @@ struct Kern {
         const f32x4 p0 = lds_ld<f32x4>(pa.tot), p1 = lds_ld<f32x4>(pa.tot + 16);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            o.pre[e] = p0[e];
-            o.pre[4 + e] = p1[e];
+            o.pre[e] = p0[e] * pa.unit;
+            o.pre[4 + e] = p1[e] * pa.unit;
         }
     }
     static __device__ __forceinline__ void line_note_step(const LineAddr &pa, float total, int32_t *status)
@@ -973,7 +993,7 @@ struct Kern {
     // step m + 1 and the loads of later steps; as produce().  lg, sgn: of this wavefront's state.
     static __device__ __forceinline__ void line_produce(const LineAddr &pa, uint32_t set, LineIO &r, const LineScan &sc, int valid,
                                                         LineGates &gn, LineScan &sn, int valid_n, float lg, uint32_t sgn,
-                                                        float &tot, int32_t *status, const LineNext &next)
+                                                        float &pos, int32_t *status, const LineNext &next)
     {
         const uint32_t so = set * SET_BYTES;
         if (valid < S) {   // ragged tail: tokens past the end act as "no key, no value"
@@ -991,27 +1011,34 @@ struct Kern {
         next.at(3);
         auto block = [&](int j) {
             next.at(4 + j);
-            float kf[8], kh[8];
+            float kf[8], kh[8], y[8];
             r.k[j].unpack(kf);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) kh[e] = kf[e] * __builtin_amdgcn_exp2f(-pa.unit * (sc.pre[e] + sc.c[j][e]));
+            for (int e = 0; e < 8; ++e) {
+                y[e] = fmaf(sc.c[j][e], pa.unit, sc.pre[e]);
+                kh[e] = kf[e] * __builtin_amdgcn_exp2f(-y[e]);
+            }
             A::store_row(pa.krow[j] + so, A::pack_row(kh));
             next.at(8 + j);
-            float qf[8], qt[8];
-            r.q[j].unpack(qf);
+            float qt[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) qt[e] = qf[e] * __builtin_amdgcn_exp2f(fmaf(sc.pre[e] + sc.c[j][e], pa.unit, lg));
-            A::store_row(pa.qrow[j] + so, A::flip_sign(A::pack_row(qt), sgn));
+            for (int w = 0; w < 4; ++w) {   // the sign of the blend coefficient enters where q is unpacked
+                const uint32_t u = r.q[j].u[w];
+                qt[2 * w] = __uint_as_float((u << 16) + sgn) * __builtin_amdgcn_exp2f(y[2 * w] + lg);
+                qt[2 * w + 1] = __uint_as_float((u & 0xffff0000u) ^ sgn) * __builtin_amdgcn_exp2f(y[2 * w + 1] + lg);
+            }
+            A::store_row(pa.qrow[j] + so, A::pack_row(qt));
         };
         float t[8];
         line_scan_b_read(pa, t);   // the answers arrive while the first block is computed
         block(0);
         {
-            float tot_n;
-            line_scan_b(pa, t, tot_n);
-            lds_st<float>(pa.dec + so, __builtin_amdgcn_exp2f(0.5f * pa.unit * (tot + tot_n)));
+            float tot_n, change;
+            bool move;
+            line_scan_b(pa, t, valid_n == 0, pos, change, move, tot_n);
+            lds_st<float>(pa.dec + so, __builtin_amdgcn_exp2f(change));
+            if (threadIdx.x % 64 == 0) lds_st<uint8_t>(pa.flag + so, move);
             line_note_step(pa, tot_n, status);
-            tot = tot_n;
         }
         block(1);
         line_scan_c(pa, sn);
@@ -1073,6 +1100,7 @@ struct Kern {
         const uint32_t l16k = lo & 15, sgm = ((l16k & 1) << 1) | ((l16k >> 1) & 1);
         const uint32_t ktr_r = setb + O_KS + ((4 * (l16k >> 2) + g) * QP + 16 * ((lo >> 4) & 1) + 4 * sgm) * ESZ;
         const uint32_t dec_r = setb + O_DEC + (8 * g) * 4;
+        const uint32_t moves = kLineProd ? lds_ld<uint32_t>(setb + O_FLAG) : 0u;
 
         // transposing reads of the V rows: the 16 lanes of a group address 4 tokens x 4 pieces of 4 columns and each
         // receives 4 tokens of ONE column; lane l ends up with column 32 ct + l % 32 and tokens 16 kb + 4 g + 0..3 (first
@@ -1180,12 +1208,33 @@ struct Kern {
 
         // ---- the states move to the middle frame of the next step (after the last step: to their own frame) ----
         // (a block of its own for the register allocator: merged into the code above it costs four spilled registers)
-        if (opaque(1u)) rescale(acc, dec_r, g, 32 * ct + ln);
+        if constexpr (kLineProd) {
+            const uint32_t m = __builtin_amdgcn_readfirstlane(moves);   // byte i FHN + f: features 64 f .. + 63 of state i
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int f = 0; f < FHN; ++f)
+                    if (m >> (8 * (i * FHN + f)) & 0xff) {
+                        scale_tile(acc[i][2 * f], dec_r + (i * D + 64 * f) * 4);
+                        scale_tile(acc[i][2 * f + 1], dec_r + (i * D + 64 * f + 32) * 4);
+                    }
+        } else if (opaque(1u)) rescale(acc, dec_r, g, 32 * ct + ln);
     }
 
     // acc[i][dt][j] *= f[i D + feature of register j], f = 2 D floats at LDS address `fac` (+ 8 g floats for this lane);
     // beta mode: state 0 only, and every register of the lane also by the factor of the lane's column, f[D + column]
     // (`col` = the lane's column, 32 ct + ln).
+    // one 32-row tile of a state times the factors of its rows (fac: of this lane group's first row)
+    static __device__ __forceinline__ void scale_tile(f32x16 &t, uint32_t fac)
+    {
+        f32x4 dd[4];
+#pragma unroll
+        for (int jb = 0; jb < 4; ++jb) dd[jb] = lds_ld<f32x4>(fac + (16 * (jb >> 1) + 4 * (jb & 1)) * 4);
+#pragma unroll
+        for (int jb = 0; jb < 4; ++jb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t[4 * jb + e] *= dd[jb][e];
+    }
     static __device__ __forceinline__ void rescale(f32x16 (&acc)[2][DT], uint32_t fac, uint32_t g, uint32_t col)
     {
         if constexpr (kBeta) {
@@ -1198,16 +1247,7 @@ struct Kern {
 #pragma unroll
         for (int i = 0; i < NST; ++i) {
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                f32x4 dd[4];
-#pragma unroll
-                for (int jb = 0; jb < 4; ++jb)
-                    dd[jb] = lds_ld<f32x4>(fac + (i * D + 32 * dt + 16 * (jb >> 1) + 4 * (jb & 1)) * 4);
-#pragma unroll
-                for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[i][dt][4 * jb + e] *= dd[jb][e];
-            }
+            for (int dt = 0; dt < DT; ++dt) scale_tile(acc[i][dt], fac + (i * D + 32 * dt) * 4);
         }
     }
 
@@ -1376,8 +1416,8 @@ struct Kern {
                 pa.preact = a.gate_inv_tau != 0.f;
                 pa.unit = pa.preact ? a.gate_inv_tau : kLog2e;
                 const float lgs = pa.st ? lg[1] : lg[0];
-                const uint32_t sgns = pa.st ? sgn[1] : sgn[0];
-                float tot = 0.f;   // lane l: gate sum of column (state st, feature 64 fh + l) over the step whose operands come next
+                const uint32_t sgns = (pa.st ? gsv[1] : gsv[0]) < 0.f ? 0x80000000u : 0u;
+                float pos = 0.f;   // lane l: gate sum of column (state st, feature 64 fh + l) from its frame to the end of the step scanned last
                 const TIO *q0 = static_cast<const TIO *>(a.q) + seg0, *k0 = static_cast<const TIO *>(a.k) + seg0,
                           *v0 = static_cast<const TIO *>(a.v) + seg0;
                 const TG *g0p = static_cast<const TG *>(pa.st ? a.g2 : a.g1) + seg0;
@@ -1433,31 +1473,32 @@ struct Kern {
                 }
                 line_scan_a(pa, g0, valid_of(0), s0);
                 {
-                    float t[8];
+                    float t[8], change, tot;
+                    bool move;
                     line_scan_b_read(pa, t);
-                    line_scan_b(pa, t, tot);
+                    line_scan_b(pa, t, true, pos, change, move, tot);
                     line_note_step(pa, tot, a.status);
                     // the caller's states enter the middle frame of step 0
-                    lds_st<float>(sm + O_ENT + (pa.dec - (sm + O_DEC)), __builtin_amdgcn_exp2f(0.5f * pa.unit * tot));
+                    lds_st<float>(sm + O_ENT + (pa.dec - (sm + O_DEC)), __builtin_amdgcn_exp2f(change));
                 }
                 line_scan_c(pa, s0);
                 load_gates_l(g0, src_of(2));
                 {
                     const LineSrc io = src_of(1), gs = src_of(3);
-                    line_produce(pa, 0, r0, s0, valid_of(0), g1, s1, valid_of(1), lgs, sgns, tot, a.status, LineNext{r1, io, g1, gs});
+                    line_produce(pa, 0, r0, s0, valid_of(0), g1, s1, valid_of(1), lgs, sgns, pos, a.status, LineNext{r1, io, g1, gs});
                 }
                 lds_barrier();   // operands of step 0 are ready
                 int n = 0;
                 for (; n + 2 < nsteps; n += 2) {
                     {
                         const LineSrc io = src_of(n + 2), gs = src_of(n + 4);
-                        line_produce(pa, 1, r1, s1, valid_of(n + 1), g0, s0, valid_of(n + 2), lgs, sgns, tot, a.status,
+                        line_produce(pa, 1, r1, s1, valid_of(n + 1), g0, s0, valid_of(n + 2), lgs, sgns, pos, a.status,
                                      LineNext{r0, io, g0, gs});
                     }
                     lds_barrier();
                     {
                         const LineSrc io = src_of(n + 3), gs = src_of(n + 5);
-                        line_produce(pa, 0, r0, s0, valid_of(n + 2), g1, s1, valid_of(n + 3), lgs, sgns, tot, a.status,
+                        line_produce(pa, 0, r0, s0, valid_of(n + 2), g1, s1, valid_of(n + 3), lgs, sgns, pos, a.status,
                                      LineNext{r1, io, g1, gs});
                     }
                     lds_barrier();
@@ -1467,7 +1508,7 @@ struct Kern {
                 // 32 heads, d = 128: 17.4 -> 14.9 us; 85 tokens, 16 heads, d = 64: 14.3 -> 10.9; fp32, 32 tokens, 32 heads, d = 128: 27.4 -> 20.4.
                 if (n + 1 < nsteps) {
                     const LineSrc io = src_of(n + 2), gs = src_of(n + 4);
-                    line_produce(pa, 1, r1, s1, valid_of(n + 1), g0, s0, valid_of(n + 2), lgs, sgns, tot, a.status,
+                    line_produce(pa, 1, r1, s1, valid_of(n + 1), g0, s0, valid_of(n + 2), lgs, sgns, pos, a.status,
                                  LineNext{r0, io, g0, gs});
                 }
                 lds_barrier();

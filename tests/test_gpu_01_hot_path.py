@@ -66,6 +66,31 @@ def test_prefill_pre_pass_on_half_segments(io, d, B, H, T, chunk, init):
     run_prefill_case(B, T, H, d, io, gd, chunk=chunk, segments=0, gamma=0.35, seed=91, init=init, qk_scale=d ** -0.5)
 
 
+@pytest.mark.parametrize("d,T,segments,gamma,f1,f2", [
+    (128, 1000, 1, 0.4, (1, 1), (128, 128)),        # one state's frames never move, the other's in every step
+    (128, 777, 1, -0.3, (16, 64), (0, 32)),         # the halves of the features at their own times; gates of exactly one
+    (128, 1500, 3, 0.6, (64, 16), (16, 16)), (64, 640, 2, 0.4, (16, 16), (64, 64)), (64, 33, 1, 1.3, (128, 128), (0, 0)),
+    (128, 32, 1, 0.5, (0, 0), (1, 1)), (128, 96, 1, 0.5, (32, 0), (0, 32))])
+def test_prefill_frames_move_at_their_own_times(d, T, segments, gamma, f1, f2):
+    """The step loop leaves the frame of a state and 64 of its features where it is while the gate sum since its last change
+    stays small: gates whose strength (a power of two on the log-gates: exact in bf16) differs between the states and
+    between the first and the last 64 features move them never, now and then, and in every step."""
+    B, H = 2, 3
+    x = wl.layer_inputs(131, B, T, H, d, d, io_dtype="bf16", gate_dtype="bf16", qk_scale=d ** -0.5)
+    half = np.arange(d) < max(64, d // 2)
+    for name, (lo, hi) in (("g1", f1), ("g2", f2)):
+        x[name] = x[name] * np.where(half, lo, hi).astype(np.float32)
+    S10, S20 = wl.initial_states(131, B, H, d, d, amplitude=1.0)
+    layer = GpuLayer(B, H, d, "bf16", "bf16", gamma=gamma, chunk=64, segments=segments)
+    layer.set_states(S10, S20)
+    o = layer.prefill(x)
+    S1, S2 = layer.states()
+    ro, rS1, rS2 = orc.recurrent(x["q"], x["k"], x["v"], x["g1"], x["g2"], gamma, 1.0, S1=S10, S2=S20)
+    check("o", o, ro, TOL["bf16"])
+    check("S1", S1, rS1, TOL["bf16"])
+    check("S2", S2, rS2, TOL["bf16"])
+
+
 @pytest.mark.parametrize("io,d,segments,T", [("bf16", 128, 1, 300), ("bf16", 128, 4, 1000), ("f32", 64, 1, 77),
                                              ("f32", 64, 3, 450)])
 def test_prefill_zero_init_does_not_read_the_states(io, d, segments, T):
