@@ -1263,6 +1263,7 @@ struct Kern {
         if (t < B) {
             const int sq = a.seq ? a.seq[t] : t;
             len = a.cu[sq + 1] - a.cu[sq];
+            len = len > 0 ? len : 0;   // above the entries past the last sequence: the ranks are those of 0 .. B - 1 whatever the offsets
         }
         lds_st<int>(sm + 4 * t, len);
         __syncthreads();
