@@ -496,7 +496,7 @@ struct Kern {
     static __device__ __forceinline__ uint32_t vswz(uint32_t row) { return D == 128 ? (row & 3u) : ((row >> 1) & 1u); }
     static constexpr uint32_t O_VT = O_KT + (kTrK ? 0 : 2 * D * TP * ESZ);
     static constexpr uint32_t O_DEC = O_VT + D * TP * ESZ;                     // float [2D]  frame change after the step
-    static constexpr uint32_t O_FLAG = O_DEC + 2 * D * 4;                      // uint8 [CT] (kLineProd): does the frame change of these features do anything
+    static constexpr uint32_t O_FLAG = O_DEC + 2 * D * 4;                      // uint8 [CT] (kLineProd): how often the state is multiplied by the factors of these features (0 .. 2)
     static constexpr uint32_t SET_BYTES = O_FLAG + 16;
     static constexpr uint32_t LDS_MAX = 160 * 1024;                            // LDS of a gfx950 compute unit
     // Two operand sets where they fit (the producers then run a whole step ahead of the consumers); one set
@@ -886,7 +886,7 @@ struct Kern {
         uint32_t tot;         // scan scratch [8 quads][64 features] floats: this lane's 8 features of quad sq
         uint32_t col;         // scan scratch: this lane's column (feature lane of the 64), quad 0
         uint32_t dec;         // decay factor of this lane's column
-        uint32_t flag;        // does it change anything: of this wavefront's columns
+        uint32_t flag;        // how often the consumers multiply by it: of this wavefront's columns
         uint32_t qrow[TPT];   // Q~ row of token 4 sq + j, element st D + 64 fh + 8 dg
         uint32_t krow[TPT];   // K~: its row slot
         uint32_t vrow[2];     // V rows of token 16 st + 2 sq + j, columns 64 fh + 8 dg ..
@@ -949,9 +949,12 @@ struct Kern {
         for (int s2 = 0; s2 < 8; ++s2) t[s2] = lds_ld<float>(pa.col + s2 * 64 * 4);
     }
     // The frame of a column.  The state is kept as T with S = 2^{unit pos} T, pos the running gate sum since the frame was
-    // last changed, and the exponents of a step are gate sums counted from there.  As long as pos stays above
-    // -kLazyFrame (log2) in all 64 columns of the wavefront after the next step, the frame stays and the consumers multiply
-    // nothing; otherwise it moves to the middle of the next step (after the last step: to the state itself).  With
+    // last changed, and the exponents of a step are gate sums counted from there.  As long as pos stays within
+    // kLazyFrame (log2) of zero in all 64 columns of the wavefront after the next step, the frame stays and the consumers
+    // multiply nothing; otherwise it moves to the middle of the next step (after the last step: to the state itself).  A
+    // move can take a column through more than fp32 holds as one factor - it is up to 115 below its frame after a step that
+    // moved it, up to kLazyFrame otherwise, and the middle of the next step is up to 115 further on - so past kOneFactor
+    // the consumers multiply twice by half of it (in the exponent), and no part of the history is flushed to zero.  With
     // gates of a temperature sigmoid that is once in some dozens of steps instead of 128 of the 340 vector
     // instructions of a consumer in every step; gates so strong that every step would move it behave as they always did.
     // With the 40 instructions that one exponent for both operands and the sign of the blend coefficient in q's unpacking save
@@ -959,14 +962,18 @@ struct Kern {
     // to 8192 tokens 665 -> 624 us.  Exponents of up to 32 cost no accuracy: they cancel between the operands, whose
     // rounding is relative (6 seeds, against 64 bits: outputs 2.73e-3 before and after; gates of very different strength
     // 2.90e-3 and 2.90e-3, states 1.65e-3 and 1.66e-3).
-    static constexpr float kLazyFrame = 32.f;
-    static __device__ __forceinline__ void line_scan_b(const LineAddr &pa, const float (&t)[8], bool first_or_past, float &pos, float &change,
-                                                       bool &move, float &total)
+    static constexpr float kLazyFrame = 32.f, kOneFactor = 120.f;   // (the smallest normal number is 2^-126)
+    // factor, times: the state is multiplied by `factor` (per column) `times` times (uniform)
+    static __device__ __forceinline__ void line_scan_b(const LineAddr &pa, const float (&t)[8], bool first_or_past, float &pos, float &factor,
+                                                       uint32_t &times, float &total)
     {
         const float tot = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
-        move = first_or_past || __builtin_amdgcn_ballot_w64(!((pos + tot) * pa.unit >= -kLazyFrame)) != 0;
+        const bool move = first_or_past || __builtin_amdgcn_ballot_w64(!(fabsf((pos + tot) * pa.unit) <= kLazyFrame)) != 0;
         float run = move ? -0.5f * tot : pos;   // moved: centred on the step, as scan_b
-        change = (pos - run) * pa.unit;         // log2 of what the state is multiplied by
+        const float change = (pos - run) * pa.unit;
+        const bool twice = __builtin_amdgcn_ballot_w64(change < -kOneFactor) != 0;
+        factor = __builtin_amdgcn_exp2f(twice ? 0.5f * change : change);
+        times = move ? (twice ? 2 : 1) : 0;
 #pragma unroll
         for (int s2 = 0; s2 < 8; ++s2) {
             lds_st<float>(pa.col + s2 * 64 * 4, run);
@@ -1033,11 +1040,11 @@ struct Kern {
         line_scan_b_read(pa, t);   // the answers arrive while the first block is computed
         block(0);
         {
-            float tot_n, change;
-            bool move;
-            line_scan_b(pa, t, valid_n == 0, pos, change, move, tot_n);
-            lds_st<float>(pa.dec + so, __builtin_amdgcn_exp2f(change));
-            if (threadIdx.x % 64 == 0) lds_st<uint8_t>(pa.flag + so, move);
+            float tot_n, factor;
+            uint32_t times;
+            line_scan_b(pa, t, valid_n == 0, pos, factor, times, tot_n);
+            lds_st<float>(pa.dec + so, factor);
+            if (threadIdx.x % 64 == 0) lds_st<uint8_t>(pa.flag + so, static_cast<uint8_t>(times));
             line_note_step(pa, tot_n, status);
         }
         block(1);
@@ -1206,7 +1213,8 @@ struct Kern {
             }
         }
 
-        // ---- the states move to the middle frame of the next step (after the last step: to their own frame) ----
+        // ---- the states move to the middle frame of the next step (after the last step: to their own frame), with line
+        // producers those whose frame does move ----
         // (a block of its own for the register allocator: merged into the code above it costs four spilled registers)
         if constexpr (kLineProd) {
             const uint32_t m = __builtin_amdgcn_readfirstlane(moves);   // byte i FHN + f: features 64 f .. + 63 of state i
@@ -1214,17 +1222,14 @@ struct Kern {
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int f = 0; f < FHN; ++f)
-                    if (m >> (8 * (i * FHN + f)) & 0xff) {
+                    for (uint32_t times = m >> (8 * (i * FHN + f)) & 0xff; times > 0; --times) {
                         scale_tile(acc[i][2 * f], dec_r + (i * D + 64 * f) * 4);
                         scale_tile(acc[i][2 * f + 1], dec_r + (i * D + 64 * f + 32) * 4);
                     }
         } else if (opaque(1u)) rescale(acc, dec_r, g, 32 * ct + ln);
     }
 
-    // acc[i][dt][j] *= f[i D + feature of register j], f = 2 D floats at LDS address `fac` (+ 8 g floats for this lane);
-    // beta mode: state 0 only, and every register of the lane also by the factor of the lane's column, f[D + column]
-    // (`col` = the lane's column, 32 ct + ln).
-    // one 32-row tile of a state times the factors of its rows (fac: of this lane group's first row)
+    // One 32-row tile of a state times the factors of its rows (fac: of this lane group's first row)
     static __device__ __forceinline__ void scale_tile(f32x16 &t, uint32_t fac)
     {
         f32x4 dd[4];
@@ -1235,6 +1240,9 @@ struct Kern {
 #pragma unroll
             for (int e = 0; e < 4; ++e) t[4 * jb + e] *= dd[jb][e];
     }
+    // acc[i][dt][j] *= f[i D + feature of register j], f = 2 D floats at LDS address `fac` (+ 8 g floats for this lane);
+    // beta mode: state 0 only, and every register of the lane also by the factor of the lane's column, f[D + column]
+    // (`col` = the lane's column, 32 ct + ln).
     static __device__ __forceinline__ void rescale(f32x16 (&acc)[2][DT], uint32_t fac, uint32_t g, uint32_t col)
     {
         if constexpr (kBeta) {
@@ -1474,13 +1482,13 @@ struct Kern {
                 }
                 line_scan_a(pa, g0, valid_of(0), s0);
                 {
-                    float t[8], change, tot;
-                    bool move;
+                    float t[8], factor, tot;
+                    uint32_t times;
                     line_scan_b_read(pa, t);
-                    line_scan_b(pa, t, true, pos, change, move, tot);
+                    line_scan_b(pa, t, true, pos, factor, times, tot);
                     line_note_step(pa, tot, a.status);
-                    // the caller's states enter the middle frame of step 0
-                    lds_st<float>(sm + O_ENT + (pa.dec - (sm + O_DEC)), __builtin_amdgcn_exp2f(change));
+                    // the caller's states enter the middle frame of step 0 (half of a step: one factor)
+                    lds_st<float>(sm + O_ENT + (pa.dec - (sm + O_DEC)), factor);
                 }
                 line_scan_c(pa, s0);
                 load_gates_l(g0, src_of(2));

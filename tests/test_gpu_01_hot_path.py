@@ -7,7 +7,7 @@ import pytest
 from oracle import dsla_oracle as orc
 import workloads as wl
 import paper_2506_09316_amd as dsla
-from tests.gpu_common import TOL, check, run_prefill_case
+from tests.gpu_common import GATE_DOMAIN, TOL, check, run_prefill_case, step_gate_sums
 from tests.util import GpuLayer, code, max_rel_err, slice_t, to_gpu
 
 pytestmark = pytest.mark.gpu
@@ -89,6 +89,47 @@ def test_prefill_frames_move_at_their_own_times(d, T, segments, gamma, f1, f2):
     check("o", o, ro, TOL["bf16"])
     check("S1", S1, rS1, TOL["bf16"])
     check("S2", S2, rS2, TOL["bf16"])
+
+
+def _run_hard_resets(T, resets, d, io, gate, gates, segments, *, seed, init=True):
+    """Weak gates everywhere (2.3 log2 per group of 32 tokens) but for single tokens of every other feature that all but
+    close one: `resets` maps a token to its log alpha.  Against the oracle, the status word clear."""
+    import torch
+    B, H = 1, 2
+    x = wl.layer_inputs(seed, B, T, H, d, d, io_dtype=io, gate_dtype=gate, gates=gates, qk_scale=d ** -0.5)
+    for n in ("g1", "g2"):
+        x[n][:] = -0.05 if gates == "log" else 2.97          # -softplus(-2.97) = -0.05
+        for t, s in resets.items():
+            x[n][:, t, :, ::2] = s                           # -softplus(-s) = s at this distance
+        x[n] = wl.round_to_bf16(x[n]) if gate == "bf16" else x[n]
+    lg = {n: x[n] if gates == "log" else orc.log_gates_from_preactivations(x[n], 1.0) for n in ("g1", "g2")}
+    assert step_gate_sums(lg) < GATE_DOMAIN
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    layer = GpuLayer(B, H, d, io, gate, gamma=0.4, chunk=64, segments=segments, gate_mode=int(gates == "preact"), tau=1.0,
+                     status=status)
+    S10 = S20 = None
+    if init:
+        S10, S20 = wl.initial_states(seed, B, H, d, d, amplitude=1.0)
+        layer.set_states(S10, S20)
+    o = layer.prefill(x)
+    S1, S2 = layer.states()
+    ro, rS1, rS2 = orc.recurrent(x["q"], x["k"], x["v"], lg["g1"], lg["g2"], 0.4, 1.0, S1=S10, S2=S20)
+    check("o", o, ro, TOL[io])
+    check("S1", S1, rS1, TOL[io])
+    check("S2", S2, rS2, TOL[io])
+    assert int(status.item()) == 0
+
+
+@pytest.mark.parametrize("d,gate,gates,segments,init", [
+    (128, "bf16", "log", 1, True), (128, "bf16", "preact", 2, True), (64, "bf16", "log", 2, False), (64, "f32", "preact", 1, True),
+    (128, "f32", "log", 3, True), (64, "bf16", "log", 1, True)])
+def test_prefill_hard_resets_after_weak_gates(d, gate, gates, segments, init):
+    """13 groups of weak gates bring a state 25 to 31 log2 below the frame it was last moved to; a gate of log alpha = -135,
+    -145, -155 at the last token of the next group (R up to 226 of the allowed 230) then moves it by up to 2^-145, more
+    than one fp32 factor holds, and the outputs of that group before the reset still see the whole history."""
+    g = 14 * 32
+    _run_hard_resets(3 * g + 37, {g - 1: -135.0, 2 * g - 1: -145.0, 3 * g - 1: -155.0}, d, "bf16", gate, gates, segments,
+                     seed=201, init=init)
 
 
 @pytest.mark.parametrize("io,d,segments,T", [("bf16", 128, 1, 300), ("bf16", 128, 4, 1000), ("f32", 64, 1, 77),
