@@ -435,7 +435,7 @@ struct PrefillArgs {
 //     o  =  Q~ T  +  mask_{key <= query}(Q~ K~^T) V                        (both states in one contraction of width 2 d_k)
 //     T <-  T + K~^T V
 //   between two steps the state moves from one middle frame to the next, at the end of a segment to its own frame:
-//     T <-  diag(2^{-(R + R_next)/2}) T          (R_next = 0 after the last step)
+//     T <-  diag(2^{-(R + R_next)/2}) T          (R_next = 0 after the last step; past 2^-120 as two factors)
 //   (the 16-bit step loop leaves the frame where it is for several steps while the exponents stay small: line_scan_b)
 // Centring halves the largest exponent a step can produce: the factors stay finite while R < 2 * 115, and nothing
 // links the exponents of different steps.
@@ -496,8 +496,9 @@ struct Kern {
     static __device__ __forceinline__ uint32_t vswz(uint32_t row) { return D == 128 ? (row & 3u) : ((row >> 1) & 1u); }
     static constexpr uint32_t O_VT = O_KT + (kTrK ? 0 : 2 * D * TP * ESZ);
     static constexpr uint32_t O_DEC = O_VT + D * TP * ESZ;                     // float [2D]  frame change after the step
-    static constexpr uint32_t O_FLAG = O_DEC + 2 * D * 4;                      // uint8 [CT] (kLineProd): how often the state is multiplied by the factors of these features (0 .. 2)
-    static constexpr uint32_t SET_BYTES = O_FLAG + 16;
+    static constexpr uint32_t O_FLAG = O_DEC + 2 * D * 4;                      // uint8 [CT]: per producer wavefront, how often its factors are multiplied in (kLineProd: 0 .. 2) / whether O_DEC2 holds any
+    static constexpr uint32_t O_DEC2 = O_FLAG + 16;                            // float [2D] (not kLineProd)  the rest of a frame change beyond one factor
+    static constexpr uint32_t SET_BYTES = O_DEC2 + (ESZ == 2 && kFull && !kExt ? 0 : 2 * D * 4);
     static constexpr uint32_t LDS_MAX = 160 * 1024;                            // LDS of a gfx950 compute unit
     // Two operand sets where they fit (the producers then run a whole step ahead of the consumers); one set
     // otherwise (fp32 at d = 128): the producers then only load ahead and prepare between two barriers.
@@ -593,6 +594,7 @@ struct Kern {
         uint32_t tot;   // scan scratch [state][sg][feature]: this lane's 8 features of state 0 (state 1: + 2048)
         uint32_t col;   // scan scratch: this lane's column, token pair 0
         uint32_t dec;   // decay factor of this lane's column
+        uint32_t flag;  // does the change of any of this wavefront's columns take a second factor
         uint32_t row;   // row-layout operands: token 2sg, element f0 (token + 1: + QP, state 1: + D elements)
         uint32_t kt[2];   // Kt: row of feature e = 0 of state 0, position of tokens 2sg, 2sg+1; [x]: for features e with (e/2)%2 = x
         uint32_t vt[4];   // Vt: row of column f0, position of tokens 2sg, 2sg+1; [x]: for columns e with (e/2)%4 = x
@@ -611,6 +613,7 @@ struct Kern {
             tot = csw + (sg * 32 + 8 * dgl) * 4;
             col = csw + ((lane >> 5) * SGN * 32 + (lane & 31)) * 4;
             dec = sm + O_DEC + ((lane >> 5) * D + 32 * pw + (lane & 31)) * 4;
+            flag = sm + O_FLAG + pw;
             row = sm + (sg * RPT * QP + f0) * ESZ;
             // feature 8 dgl + e of the wavefront's 32 goes to row rho(8 dgl + e) = 16 (dgl/2) + 8 (e/4) + 4 (dgl%2) + e%4
             // the row of feature e is R = (multiple of 8) + 4 (dgl%2) + e%4 (+ 8 (e/4)): (R/2)%4 = 2 (dgl%2) + (e/2)%2
@@ -717,6 +720,9 @@ struct Kern {
         seg_log2_decay += r;
         if (status && !(r >= -kMaxStepLog2Decay)) *status = DSLA_STATUS_GATE_DOMAIN;
     }
+    // Past this (log2) a frame change goes into the operand set as its square root and the consumers multiply by it twice:
+    // the smallest normal fp32 number is 2^-126, and two neighbouring steps may move a state by up to 2^-230.
+    static constexpr float kOneFactor = 120.f;
     // stage C: the exclusive prefixes of this thread's token pair
     static __device__ __forceinline__ void scan_c(const ProdAddr &pa, ScanOut &o)
     {
@@ -813,7 +819,12 @@ struct Kern {
         {
             float tot_n;
             scan_b(pa, t, tot_n);
-            lds_st<float>(pa.dec + so, __builtin_amdgcn_exp2f(0.5f * pa.unit * (tot + tot_n)));
+            const float change = 0.5f * pa.unit * (tot + tot_n);
+            const bool twice = __builtin_amdgcn_ballot_w64(change < -kOneFactor) != 0;
+            const float factor = __builtin_amdgcn_exp2f(twice ? 0.5f * change : change);
+            lds_st<float>(pa.dec + so, factor);
+            lds_st<float>(pa.dec + so + (O_DEC2 - O_DEC), twice ? factor : 1.f);
+            if (__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0)) == 0) lds_st<uint8_t>(pa.flag + so, twice);
             note_step(pa, tot_n, seg_log2_decay, status);
             tot = tot_n;
         }
@@ -962,7 +973,7 @@ struct Kern {
     // to 8192 tokens 665 -> 624 us.  Exponents of up to 32 cost no accuracy: they cancel between the operands, whose
     // rounding is relative (6 seeds, against 64 bits: outputs 2.73e-3 before and after; gates of very different strength
     // 2.90e-3 and 2.90e-3, states 1.65e-3 and 1.66e-3).
-    static constexpr float kLazyFrame = 32.f, kOneFactor = 120.f;   // (the smallest normal number is 2^-126)
+    static constexpr float kLazyFrame = 32.f;
     // factor, times: the state is multiplied by `factor` (per column) `times` times (uniform)
     static __device__ __forceinline__ void line_scan_b(const LineAddr &pa, const float (&t)[8], bool first_or_past, float &pos, float &factor,
                                                        uint32_t &times, float &total)
@@ -1107,7 +1118,7 @@ struct Kern {
         const uint32_t l16k = lo & 15, sgm = ((l16k & 1) << 1) | ((l16k >> 1) & 1);
         const uint32_t ktr_r = setb + O_KS + ((4 * (l16k >> 2) + g) * QP + 16 * ((lo >> 4) & 1) + 4 * sgm) * ESZ;
         const uint32_t dec_r = setb + O_DEC + (8 * g) * 4;
-        const uint32_t moves = kLineProd ? lds_ld<uint32_t>(setb + O_FLAG) : 0u;
+        const uint32_t moves = lds_ld<uint32_t>(setb + O_FLAG);
 
         // transposing reads of the V rows: the 16 lanes of a group address 4 tokens x 4 pieces of 4 columns and each
         // receives 4 tokens of ONE column; lane l ends up with column 32 ct + l % 32 and tokens 16 kb + 4 g + 0..3 (first
@@ -1216,8 +1227,8 @@ struct Kern {
         // ---- the states move to the middle frame of the next step (after the last step: to their own frame), with line
         // producers those whose frame does move ----
         // (a block of its own for the register allocator: merged into the code above it costs four spilled registers)
-        if constexpr (kLineProd) {
-            const uint32_t m = __builtin_amdgcn_readfirstlane(moves);   // byte i FHN + f: features 64 f .. + 63 of state i
+        const uint32_t m = __builtin_amdgcn_readfirstlane(moves) & (CT == 4 ? 0xffffffffu : 0xffffu);
+        if constexpr (kLineProd) {   // byte i FHN + f of m: features 64 f .. + 63 of state i
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -1226,7 +1237,12 @@ struct Kern {
                         scale_tile(acc[i][2 * f], dec_r + (i * D + 64 * f) * 4);
                         scale_tile(acc[i][2 * f + 1], dec_r + (i * D + 64 * f + 32) * 4);
                     }
-        } else if (opaque(1u)) rescale(acc, dec_r, g, 32 * ct + ln);
+        } else if (opaque(1u)) {
+            rescale(acc, dec_r, g, 32 * ct + ln);
+            // (all tiles once more, those that need it or not: branches or loops around the tiles of one wavefront cost the
+            // extended kernel at d = 128 15 to 38 spilled registers, 4 to 9 % of a call with several states)
+            if (__builtin_expect(m != 0, 0)) rescale(acc, dec_r + (O_DEC2 - O_DEC), g, 32 * ct + ln);
+        }
     }
 
     // One 32-row tile of a state times the factors of its rows (fac: of this lane group's first row)

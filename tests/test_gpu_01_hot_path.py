@@ -132,6 +132,17 @@ def test_prefill_hard_resets_after_weak_gates(d, gate, gates, segments, init):
                      seed=201, init=init)
 
 
+@pytest.mark.parametrize("io,d,gate,gates,segments", [
+    ("bf16", 128, "bf16", "log", 1), ("bf16", 64, "bf16", "preact", 2), ("f32", 64, "f32", "log", 1), ("f32", 128, "f32", "preact", 2),
+    ("bf16", 64, "f32", "log", 2), ("bf16", 128, "f32", "log", 2), ("f32", 64, "bf16", "log", 3)])
+def test_prefill_hard_resets_in_neighbouring_groups(io, d, gate, gates, segments):
+    """A reset of log alpha = -155 at the first token of a group of 32 and another at the last token of the next: the state
+    moves through 2^-225 between their middles, and everything between the resets is carried by it.  Every producer of
+    the step loop and of the segment pre-pass."""
+    resets = {t: -155.0 for t in (32, 95, 160, 223, 288, 351)}
+    _run_hard_resets(384 + 9, resets, d, io, gate, gates, segments, seed=203)
+
+
 @pytest.mark.parametrize("io,d,segments,T", [("bf16", 128, 1, 300), ("bf16", 128, 4, 1000), ("f32", 64, 1, 77),
                                              ("f32", 64, 3, 450)])
 def test_prefill_zero_init_does_not_read_the_states(io, d, segments, T):

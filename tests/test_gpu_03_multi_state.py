@@ -7,7 +7,7 @@ from oracle import dsla_oracle as orc
 import workloads as wl
 import paper_2506_09316_amd as dsla
 from tests.gpu_common import TOL, check
-from tests.util import code, to_gpu
+from tests.util import code, max_rel_err, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -130,6 +130,36 @@ def test_prefill_multi_beta_gate_with_strong_column_decay():
     ro, rS = orc.nstate(q, k, v, ga, gb, w, 1.0, S=S0)
     check("o", o.cpu().numpy(), ro, 1e-4)
     check("S", S[0].cpu().numpy(), rS[0], 1e-4)
+    assert int(status.item()) == 0
+
+
+@pytest.mark.parametrize("io,d,segments", [("f32", 64, 2), ("bf16", 128, 1)])
+def test_prefill_multi_hard_resets_in_neighbouring_groups(io, d, segments):
+    """Resets of log -155 at the first token of a group of 32 and at the last of the next, in the row gates of three states
+    (one pair, one state on its own) and in the column gate of a fourth: the state moves through 2^-225 between them."""
+    import torch
+    B, T, H = 1, 200, 2
+    q, k, v, ga, gb, w, S0 = _inputs(390, 4, B, T, H, H, d, io, io, True)
+    for n in range(4):
+        for g in ([ga[n]] if n < 3 else [gb[n]]):
+            g[:, (32, 95, 128, 191), :, n::2] = -155.0
+        if n < 3:
+            gb[n] = 0.0
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    desc = dsla.make_desc(B, H, d, d, io_dtype=code(io), gate_dtype=code(io), chunk=64, segments=segments, status=status)
+    S = [torch.from_numpy(S0[n].copy()).cuda() for n in range(4)]
+    multi = dsla.make_multi([to_gpu(ga[n], io) for n in range(4)], S, w, g_beta=[None, None, None, to_gpu(gb[3], io)])
+    o = torch.full((B, T, H, d), float("nan"), device="cuda", dtype=to_gpu(q[:, :1], io).dtype)
+    ws = torch.empty(max(dsla.dsla_prefill_multi_workspace_bytes(desc, multi, T), 1), dtype=torch.uint8, device="cuda")
+    dsla.dsla_prefill_multi(desc, multi, T, to_gpu(q, io), to_gpu(k, io), to_gpu(v, io), o, ws)
+    torch.cuda.synchronize()
+    ro, rS = orc.nstate(q, k, v, ga, gb, w, 1.0, S=S0)
+    # (Norm of the whole tensor only: an fp32 exponent of 112 is rounded to 2^-18, every term of a sum therefore to 2.6e-6 of
+    # itself, and an element that cancellation keeps at 1e-3 of the largest may show 1e3 times that or a little more.)
+    for name, got, ref in [("o", o.float(), ro)] + [(f"S[{n}]", S[n], rS[n]) for n in range(4)]:
+        err = max_rel_err(got.cpu().numpy(), ref)
+        print(f"    {name}: max rel err {err:.3e}", flush=True)
+        assert err <= TOL[io], name
     assert int(status.item()) == 0
 
 
