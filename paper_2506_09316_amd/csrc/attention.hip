@@ -313,9 +313,9 @@ __global__ __launch_bounds__(D) void attn_decode_merge_kernel(const float *__res
         M = top;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const float w = i0 + u < P ? expf(m[u] - M) : 0.f;
-            Z = fmaf(w, z[u], Z);
-            A = fmaf(w, a[u], A);
+            const float w = expf(m[u] - M);
+            Z = i0 + u < P ? fmaf(w, z[u], Z) : Z;   // (past the end nothing is added: 0 times the last record is NaN where
+            A = i0 + u < P ? fmaf(w, a[u], A) : A;   // one of its sums is infinite)
         }
     }
     o[static_cast<size_t>(bh) * D + f] = from_f32<TIO>(A / Z);

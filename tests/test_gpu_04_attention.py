@@ -126,6 +126,24 @@ def test_attention_decode_full_size_sampled_heads():
         assert np.all(np.abs(got[b, h] - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-5 * np.max(np.abs(ref))), (b, h)
 
 
+@pytest.mark.parametrize("io,B,T,H,d", [("bf16", 1, 1000, 2, 128), ("f32", 2, 700, 3, 64), ("bf16", 8, 3000, 32, 128)])
+def test_attention_decode_infinite_values(io, B, T, H, d):
+    """An infinite value under a nonzero weight makes its feature infinite and leaves the others alone, in the first range of
+    keys and in the last, for numbers of ranges on and off the eight that are merged at a time."""
+    import torch
+    q, k = inputs(41, B, T, H, d, io)
+    v = wl.layer_inputs(43, B, T, H, d, d, io_dtype=io, gate_dtype="f32")["v"]
+    v[:, 5, :, 7] = -np.inf
+    v[:, T - 100, :, 3] = np.inf
+    got, nws = run_decode(q, k, v, d ** -0.5, io)
+    assert nws > 0
+    assert np.all(got[..., 3] == np.inf) and np.all(got[..., 7] == -np.inf)
+    rest = [f for f in range(d) if f not in (3, 7)]
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        ref = ent.attention_decode(q[b:b + 1, h:h + 1], k[b:b + 1, :, h:h + 1], v[b:b + 1, :, h:h + 1][..., rest], d ** -0.5)[0, 0]
+        assert max_rel_err(got[b, h][rest], ref) < (1e-4 if io == "f32" else 2e-2), (b, h)
+
+
 def test_attention_decode_mixed_context_lengths():
     """Requests of one batch at different context lengths in a cache of T positions each: only the filled positions
     count (the rest of the cache holds NaN here), also where a whole key range of the split lies past the end."""
