@@ -255,7 +255,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attention_prefill_kernel(const
                     for (int r = 0; r < 16; ++r) bmax = fmaxf(bmax, sc[t][r]);
                 bmax = fmaxf(bmax, __shfl_xor(bmax, 32));
                 const bool fresh = l_run + __shfl_xor(l_run, 32) == 0.f;   // nothing summed yet: any reference will do
-                const float up = fresh ? (bmax > -1.0e29f ? bmax : 0.f) : fmaxf(bmax, 0.f);
+                const float up = fresh ? (bmax > -1.0e30f ? bmax : 0.f) : fmaxf(bmax, 0.f);   // (-1e30: masked; -inf: no weight yet)
                 const float alpha = fresh ? 1.f : __builtin_amdgcn_exp2f(-up);
                 l_run *= alpha;
 #pragma unroll

@@ -221,6 +221,20 @@ def test_attention_prefill_groups_of_heads_and_far_references(B, T, H, d, levels
     assert err <= 2e-2
 
 
+@pytest.mark.parametrize("T,d", [(1, 128), (200, 64), (130, 128)])
+def test_attention_prefill_scores_near_the_mask(T, d):
+    """Equal scores of -3e29 and below (log2 units), next to the value that masked keys get: every position is the mean of
+    the values up to it."""
+    x = wl.layer_inputs(800 + T, 1, T, 2, d, d, io_dtype="bf16", gate_dtype="f32", qk_scale=1.0)
+    x["q"][:] = 0.0
+    x["q"][..., 0] = 2.0 ** 50
+    x["k"][..., 0] = -2.0 ** 51
+    got = _run_attention_prefill(x, d ** -0.5)
+    ref = ent.attention_prefill(x["q"], x["k"], x["v"], d ** -0.5)
+    assert np.all(np.isfinite(got))
+    assert max_rel_err(got, ref) <= 2e-2
+
+
 def test_attention_prefill_last_row_equals_attention_decode_and_full_size_sample():
     """B = 2, H = 8, T = 4096 at head size 128: sampled heads against the oracle, and the last query of every head
     against the single-query kernel on the same keys and values."""
