@@ -104,7 +104,7 @@ __device__ __forceinline__ u32x4 buffer_of(const void *p, int bytes)
 template <int D>
 __global__ __launch_bounds__(64 * kWaves, 2) void attention_prefill_kernel(const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
                                                                    const bf16_t *__restrict__ v, bf16_t *__restrict__ o,
-                                                                   int H, int T, int blocks_per_seq, float scale_log2e)
+                                                                   int BH, int H, int T, int blocks_per_seq, float scale_log2e)
 {
     using L = AttnTiles<D>;
     constexpr int NKB = D / 16;    // contraction blocks over the features
@@ -114,14 +114,16 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attention_prefill_kernel(const
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ln = lane & 31, g = lane >> 5;
-    // Heads run fastest, in groups of kHeads: workgroup ids go round-robin over the 8 XCDs, so a head stays on one XCD,
-    // whose L2 serves its keys and values to all query blocks that are in flight, and the heavy blocks (late queries:
-    // more keys) of the whole group come first.  B = 8, H = 32, T = 8192: one head after the other over all XCDs 5.63 ms
-    // (every XCD reads the keys and values of all heads in flight, 32 MB against 4 MB of L2); groups of 8, 16, 32, 64 heads
-    // 4.61, 4.42, 4.44, 4.54 ms.  T = 2048, B = 1: 70, 66, 65, 55, 55 us (with few heads an early end of the light blocks leaves the
-    // chip idle).  At d = 64 a head has half the bytes.
+    // Heads run fastest, in groups of kHeads: workgroup ids go round-robin over the 8 XCDs, so in a group of a multiple of
+    // 8 heads a head stays on one XCD (of 12 or 28 heads on two, of an odd number on all), whose L2 serves its keys and
+    // values to all query blocks that are in flight, and the heavy blocks (late queries: more keys) of the whole group come
+    // first.  B = 8, H = 32, T = 8192: one head after the other over all XCDs 5.63 ms (every XCD reads the keys and values
+    // of all heads in flight, 32 MB against 4 MB of L2); groups of 8, 16, 32, 64 heads 4.61, 4.42, 4.44, 4.54 ms.
+    // T = 2048, B = 1: 70, 66, 65, 55, 55 us (with few heads an early end of the light blocks leaves the chip idle).  At
+    // d = 64 a head has half the bytes.  (A single group does without the division by the size of the groups: an index
+    // division is 0.05 of the 3.4 us of a call of one block of queries.)
     constexpr int kHeads = D == 128 ? 32 : 64;
-    const int BH = gridDim.x / blocks_per_seq, h0 = blockIdx.x / (kHeads * blocks_per_seq) * kHeads;
+    const int h0 = BH > kHeads ? static_cast<int>(blockIdx.x / (kHeads * blocks_per_seq)) * kHeads : 0;
     const int in_group = blockIdx.x - h0 * blocks_per_seq, heads = BH - h0 < kHeads ? BH - h0 : kHeads;
     const int bh = h0 + in_group % heads, qb = blocks_per_seq - 1 - in_group / heads;
     const int b = bh / H, h = bh % H;
@@ -352,11 +354,11 @@ hipError_t launch_attn_prefill(int B, int H, int d, int64_t T, float scale, cons
     ProfileScope ps(DSLA_KERNEL_ATTENTION_PREFILL, stream);
     if (d == 128)
         DSLA_LAUNCH(ps, (attention_prefill_kernel<128>), dim3(grid), dim3(64 * kWaves), 0, stream, static_cast<const bf16_t *>(q),
-                           static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v), static_cast<bf16_t *>(o), H,
+                           static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v), static_cast<bf16_t *>(o), B * H, H,
                            static_cast<int>(T), blocks_per_seq, sl2);
     else
         DSLA_LAUNCH(ps, (attention_prefill_kernel<64>), dim3(grid), dim3(64 * kWaves), 0, stream, static_cast<const bf16_t *>(q),
-                           static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v), static_cast<bf16_t *>(o), H,
+                           static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v), static_cast<bf16_t *>(o), B * H, H,
                            static_cast<int>(T), blocks_per_seq, sl2);
     return hipGetLastError();
 }
