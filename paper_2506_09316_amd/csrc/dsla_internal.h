@@ -92,6 +92,7 @@ struct PrefillPlan {
     int64_t max_items;       // packed sequences with P > 1: capacity of the list of all segments (else 0)
     int64_t max_pre_items;   //   and of the list of segments that have a successor
     size_t ws_lists_bytes;   //   and the bytes of the lists
+    bool longest_first;      // packed sequences, whole: the chunk loop takes them in the order of their lengths
     size_t ws_total_bytes;
 };
 bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan);  // false: unsupported combination

@@ -1278,24 +1278,30 @@ struct Kern {
     // The r-th longest of the B <= NT packed sequences (the earlier one where lengths are equal).  With several rounds of
     // workgroups per compute unit the last to start decide when the call ends: 37 sequences of up to 2782 tokens (32
     // heads, d = 128) take 343 us in a random order and 242 us longest first; 37 of up to 413 tokens 115 and 104 us.
-    // Finding the rank costs a workgroup the two loads of a length and B / 4 LDS reads.
+    // Finding the rank costs every workgroup the loads of the lengths, four barriers and B compares per wavefront that holds a
+    // sequence, before it has loaded anything: 1 to 2 us at up to 64 sequences, 3 at 256, 7 at 512 (d = 128).  order_pays()
+    // has the rule.
     static __device__ int sequence_of_rank(const PrefillArgs &a, uint32_t sm, int r, int B)
     {
         typedef int i32x4 __attribute__((ext_vector_type(4)));
         const int t = threadIdx.x;
-        int len = -1;
+        // The length with the place below it: keys differ, so the ranks of 0 .. B - 1 are those numbers whatever the offsets
+        // hold (lengths past 2^21 count as equal).
+        int key = -1;
         if (t < B) {
             const int sq = a.seq ? a.seq[t] : t;
-            len = a.cu[sq + 1] - a.cu[sq];
-            len = len > 0 ? len : 0;   // above the entries past the last sequence: the ranks are those of 0 .. B - 1 whatever the offsets
+            const int len = a.cu[sq + 1] - a.cu[sq];
+            key = (len < 0 ? 0 : (len < (1 << 21) ? len : 1 << 21)) * NT + (NT - 1 - t);
         }
-        lds_st<int>(sm + 4 * t, len);
+        lds_st<int>(sm + 4 * t, key);
         __syncthreads();
         int rank = 0;
-        for (int u = 0; u < B; u += 4) {   // entries past the last sequence hold -1
-            const i32x4 l = lds_ld<i32x4>(sm + 4 * u);
+        if (t < B) {   // (wavefronts without a sequence go straight on)
+            for (int u = 0; u < B; u += 4) {   // entries past the last sequence hold -1
+                const i32x4 k = lds_ld<i32x4>(sm + 4 * u);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) rank += (l[e] > len || (l[e] == len && u + e < t)) ? 1 : 0;
+                for (int e = 0; e < 4; ++e) rank += k[e] > key ? 1 : 0;
+            }
         }
         __syncthreads();
         if (t < B && rank == r) lds_st<int>(sm, t);
@@ -2120,6 +2126,7 @@ void finish_plan(const dsla_desc &d, int C, int64_t P, int64_t nchunks, bool may
     plan->segment_tokens = cps * C;
     plan->state_elems = static_cast<size_t>(BH) * D * D;
     plan->max_items = plan->max_pre_items = 0;
+    plan->longest_first = false;
     plan->ws_lists_bytes = 0;
     // The pre-pass has one workgroup per (segment but the last, sequence, head).  With two segments that is at most
     // half of the compute units (65 .. 128 heads in all; short sequences): it then works on the two halves of the first
@@ -2182,6 +2189,40 @@ bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan)
     return true;
 }
 
+namespace {
+// Estimates (us): a step of 32 tokens where the chain of one workgroup counts / where every compute unit is busy, a step of
+// the pre-pass, what a workgroup costs besides its steps, a state slot written, scanned and read again.
+struct PrefillCosts {
+    double step, step_full, pre, wg, slot;
+};
+PrefillCosts prefill_costs(const dsla_desc &d)
+{
+    const bool f32 = d.io_dtype == DSLA_F32, small = d.d_k == 64, preact = d.gate_mode == DSLA_GATE_PREACT;
+    PrefillCosts c;
+    c.step = f32 ? (small ? 7.0 : 16.0) : (small ? (preact ? 1.8 : 1.4) : (preact ? 2.35 : 2.0));
+    c.step_full = f32 ? c.step : (small ? 2.5 : (preact ? 3.4 : 2.9));
+    c.pre = f32 ? c.step / 3 : (small ? 1.2 : (preact ? 2.1 : 1.5));
+    c.wg = small ? 5.0 : 8.0;
+    c.slot = small ? 0.0125 : 0.05;
+    return c;
+}
+// Do whole packed sequences go longest first?  Every workgroup pays for its rank (about 2 us and 1 more per 128 sequences),
+// so with R rounds of workgroups the call pays R times, and it gains at most a part of the longest chain, which no longer
+// starts late; max_T may bound the lengths loosely, and then there is nothing to gain: the rank also has to be small
+// against an average workgroup.  Own order / longest first (us, d = 128, 32 heads): 16 sequences of 1 to 600 tokens
+// 57 / 46, 32 of 1 to 2500 151 / 134, 48 of 64 to 1000 216 / 207; 8 heads: 128 of 1 to 2500 211 / 158.  Not taken: 64 of
+// 64 to 1000 467 / 476, 128 of 1 to 2500 602 / 631, 48 (512) of up to 40 and one of 300 86 / 101 (950 / 1390).  Up to 256
+// tokens it never paid.
+bool order_pays(const dsla_desc &d, int64_t total_T, int64_t max_T)
+{
+    const double rounds = static_cast<double>(d.B) * d.H / chip_slots(d), rank = 2.0 + d.B / 128.0;
+    if (d.B < 2 || d.B > 4 * d.d_k || max_T <= 256 || rounds <= 1.0) return false;   // a thread per sequence
+    const PrefillCosts c = prefill_costs(d);
+    const double longest = static_cast<double>(max_T) / 32, mean = static_cast<double>(total_T) / 32 / d.B;
+    return longest * c.step >= 4 * rounds * rank && c.wg + mean * c.step_full >= 6 * rank;
+}
+}  // namespace
+
 // Packed sequences of different lengths share one segment length; a sequence of length T_b has
 // ceil(T_b / segment_tokens) segments.  If they are cut, the segment length is chosen so that all sequences together make
 // about one workgroup per compute unit, the same rule as above on the total instead of a common length (measured on
@@ -2207,26 +2248,21 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
         if (cps < 4) cps = 4;
         P = (nchunks + cps - 1) / cps;
         if (P > 1) {
-            const bool f32 = d.io_dtype == DSLA_F32, small = d.d_k == 64, preact = d.gate_mode == DSLA_GATE_PREACT;
-            // a step of 32 tokens where the chain of one workgroup counts / where every compute unit is busy, a step of the
-            // pre-pass, what a workgroup costs besides its steps, a state slot written, scanned and read again
-            const double step = f32 ? (small ? 7.0 : 16.0) : (small ? (preact ? 1.8 : 1.4) : (preact ? 2.35 : 2.0));
-            const double step_full = f32 ? step : (small ? 2.5 : (preact ? 3.4 : 2.9));
-            const double pre = f32 ? step / 3 : (small ? 1.2 : (preact ? 2.1 : 1.5));
-            const double wg = small ? 5.0 : 8.0, slot = small ? 0.0125 : 0.05;
+            const PrefillCosts c = prefill_costs(d);
             const double chip = chip_slots(d), steps = static_cast<double>(total_T) / 32, L = static_cast<double>(cps * C);
             const double n = L / 32, longest = static_cast<double>(max_T) / 32;
             const double cuts = static_cast<double>(total_T) / L * d.H, items = cuts + static_cast<double>(d.B) * d.H;
             auto loop = [&](double chain, double workgroups) {
-                const double spread = workgroups / chip * wg + steps * d.H / chip * step_full;
-                return spread > wg + chain * step ? spread : wg + chain * step;
+                const double spread = workgroups / chip * c.wg + steps * d.H / chip * c.step_full;
+                return spread > c.wg + chain * c.step ? spread : c.wg + chain * c.step;
             };
             const double whole = loop(longest, static_cast<double>(d.B) * d.H);
-            const double cut = 7 + wg + (cuts > chip ? cuts / chip : 1.0) * n * pre + 4 + slot * items + loop(n, items);
+            const double cut = 7 + c.wg + (cuts > chip ? cuts / chip : 1.0) * n * c.pre + 4 + c.slot * items + loop(n, items);
             if (whole <= cut) P = 1;
         }
     }
     finish_plan(d, C, P, nchunks, false, plan);
+    plan->longest_first = plan->segments == 1 && order_pays(d, total_T, max_T);
     if (plan->segments > 1) {
         const int D = d.d_k;
         auto up = [](size_t n) { return (n + 255) / 256 * 256; };
@@ -2280,8 +2316,7 @@ hipError_t launch_prefill(const dsla_desc &d, const PrefillPlan &plan, int64_t T
         w += up(plan.max_items * 8);
         a.list_pre = reinterpret_cast<int2 *>(w);
     }
-    a.longest_first = cu_seqlens && plan.segments == 1 && d.B > 1 && d.B <= 4 * d.d_k &&
-                      T > 256 && static_cast<int64_t>(d.B) * d.H > chip_slots(d);   // (up to 256 tokens the rank costs what it gains)
+    a.longest_first = plan.longest_first ? 1 : 0;
     a.T = T;
     a.seg_tokens = plan.segment_tokens;
     a.H = d.H;

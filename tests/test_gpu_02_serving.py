@@ -132,6 +132,15 @@ def test_varlen_longest_first(lengths, H, d, io, gate):
     _run_varlen(lengths, H, d, io, gate, 1e-4 if io == "f32" else 2e-2, slots=list(range(B))[::-1], n_slots=B + 1)
 
 
+@pytest.mark.parametrize("B,H,d", [(256, 3, 64), (257, 3, 64), (130, 3, 128)])
+def test_varlen_longest_first_many_long_sequences(B, H, d):
+    """Sequence counts at and past the number of threads of a workgroup (4 d), long enough for the order to pay where it
+    exists; equal lengths, empty sequences, the longest one last."""
+    rng = np.random.default_rng(17)
+    lengths = [int(x) for x in rng.choice([0, 255, 256, 257, 300, 330], size=B - 1)] + [1200]
+    _run_varlen(lengths, H, d, "bf16", "bf16", 2e-2, slots=[int(x) for x in rng.permutation(B)], seed=95)
+
+
 def test_varlen_gate_preactivations():
     import torch
     lengths, H, d, tau = [300, 77, 1, 640], 2, 128, 16.0
