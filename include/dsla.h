@@ -193,6 +193,10 @@ DSLA_API dsla_status dsla_prefill_static_ws(const dsla_desc *desc, int64_t T,
  * Everything else (chunking, gate domain, dtypes, in-place continuation of the states) is as for dsla_prefill.
  * desc->segments > 0 cuts a sequence of max_T tokens into that many segments; shorter sequences use the first
  * few of them.
+ * dsla_prefill_varlen_workspace_bytes with desc->segments = 0: the size of a batch whose sequences are left whole because
+ * that is faster is the size of cutting them (smaller batches are cut), unless even the smallest batch of that max_T
+ * would stay whole; a call that cuts nothing uses no workspace and takes any.  The size is not monotone in total_T and
+ * max_T: a buffer for several batches takes the largest of their sizes.
  */
 DSLA_API size_t dsla_prefill_varlen_workspace_bytes(const dsla_desc *desc, int64_t total_T, int64_t max_T);
 DSLA_API dsla_status dsla_prefill_varlen(const dsla_desc *desc, int64_t total_T, int64_t max_T,

@@ -180,7 +180,7 @@ size_t dsla_prefill_varlen_workspace_bytes(const dsla_desc *desc, int64_t total_
     if (check_varlen(desc, total_T, max_T) != DSLA_OK || max_T == 0) return 0;
     PrefillPlan plan;
     if (!prefill_plan_varlen(*desc, total_T, max_T, &plan)) return 0;
-    return plan.ws_total_bytes;
+    return plan.ws_ask_bytes;
 }
 
 dsla_status dsla_prefill_varlen(const dsla_desc *desc, int64_t total_T, int64_t max_T, const int32_t *cu_seqlens,

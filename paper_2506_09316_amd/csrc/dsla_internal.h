@@ -93,7 +93,8 @@ struct PrefillPlan {
     int64_t max_pre_items;   //   and of the list of segments that have a successor
     size_t ws_lists_bytes;   //   and the bytes of the lists
     bool longest_first;      // packed sequences, whole: the chunk loop takes them in the order of their lengths
-    size_t ws_total_bytes;
+    size_t ws_total_bytes;   // what this plan uses
+    size_t ws_ask_bytes;     // what the size query answers: at least that
 };
 bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan);  // false: unsupported combination
 bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, PrefillPlan *plan);

@@ -2143,7 +2143,7 @@ void finish_plan(const dsla_desc &d, int C, int64_t P, int64_t nchunks, bool may
         plan->ws_state_bytes = 0;
         plan->ws_decay_bytes = 0;
     }
-    plan->ws_total_bytes = plan->ws_state_bytes + plan->ws_decay_bytes;
+    plan->ws_total_bytes = plan->ws_ask_bytes = plan->ws_state_bytes + plan->ws_decay_bytes;
 }
 int plan_chunk(const dsla_desc &d)
 {
@@ -2239,14 +2239,27 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
     const int C = plan_chunk(d);
     if (!C) return false;
     const int64_t nchunks = (max_T + C - 1) / C;
-    int64_t P;
+    auto finish_packed = [&](int64_t segments, PrefillPlan *p) {
+        finish_plan(d, C, segments, nchunks, false, p);
+        if (p->segments == 1) return;
+        const int D = d.d_k;
+        auto up = [](size_t n) { return (n + 255) / 256 * 256; };
+        p->max_pre_items = total_T / p->segment_tokens;
+        p->max_items = p->max_pre_items + d.B;
+        const size_t slots = static_cast<size_t>(p->max_items) * d.H;
+        p->ws_state_bytes = slots * 2 * D * D * sizeof(float);
+        p->ws_decay_bytes = up(slots * 2 * D * sizeof(float));
+        p->ws_lists_bytes = up((static_cast<size_t>(d.B) + 1) * 4) + 256 + up(p->max_items * 8) + up(p->max_pre_items * 8);
+        p->ws_total_bytes = p->ws_ask_bytes = p->ws_state_bytes + p->ws_decay_bytes + p->ws_lists_bytes;
+    };
+    int64_t P, P_cut;   // what is done; what the cut alone would be
     if (d.segments > 0) {
-        P = d.segments;
+        P = P_cut = d.segments;
     } else {
         const int64_t target = (d.d_k == 64) ? 512 : 256;
         int64_t cps = (total_T * d.H / target + C - 1) / C;   // chunks per segment
         if (cps < 4) cps = 4;
-        P = (nchunks + cps - 1) / cps;
+        P = P_cut = (nchunks + cps - 1) / cps;
         if (P > 1) {
             const PrefillCosts c = prefill_costs(d);
             const double chip = chip_slots(d), steps = static_cast<double>(total_T) / 32, L = static_cast<double>(cps * C);
@@ -2261,19 +2274,18 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
             if (whole <= cut) P = 1;
         }
     }
-    finish_plan(d, C, P, nchunks, false, plan);
+    finish_packed(P, plan);
     plan->longest_first = plan->segments == 1 && order_pays(d, total_T, max_T);
-    if (plan->segments > 1) {
-        const int D = d.d_k;
-        auto up = [](size_t n) { return (n + 255) / 256 * 256; };
-        plan->max_pre_items = total_T / plan->segment_tokens;
-        plan->max_items = plan->max_pre_items + d.B;
-        const size_t slots = static_cast<size_t>(plan->max_items) * d.H;
-        plan->ws_state_bytes = slots * 2 * D * D * sizeof(float);
-        plan->ws_decay_bytes = up(slots * 2 * D * sizeof(float));
-        plan->ws_lists_bytes = up((static_cast<size_t>(d.B) + 1) * 4) + 256 + up(plan->max_items * 8) +
-                               up(plan->max_pre_items * 8);
-        plan->ws_total_bytes = plan->ws_state_bytes + plan->ws_decay_bytes + plan->ws_lists_bytes;
+    if (P < P_cut) {
+        // Whole by the estimate: the size query still answers with what cutting takes, if any smaller batch is cut (of one
+        // sequence at least: the least the cut can cost), so that a buffer sized for a large batch serves smaller ones.
+        const PrefillCosts c = prefill_costs(d);
+        const double n = 4.0 * C / 32;
+        if (c.wg + static_cast<double>(max_T) / 32 * c.step > 11 + 2 * c.wg + n * (c.pre + c.step) + c.slot * d.H) {
+            PrefillPlan cut;
+            finish_packed(P_cut, &cut);
+            plan->ws_ask_bytes = cut.ws_total_bytes;
+        }
     }
     return true;
 }

@@ -228,3 +228,19 @@ def test_plans_follow_the_work(lib):
     assert packed(40, 32, 128, 3460, 651) == 0                # many short sequences fill the chip whole
     assert packed(8, 32, 128, 1959, 1900) > 0                 # one long chain is cut
     assert packed(22, 8, 128, 9484, 4015) > 0
+
+
+def test_packed_workspace_of_a_large_batch_serves_smaller_ones(lib):
+    """A batch that stays whole because that is faster answers the size query with what cutting it takes: 20 sequences of up
+    to 8192 tokens, as the batch shrinks from whole ones to cut ones; none where even one sequence of that length stays
+    whole, or where every batch does because nothing is longer than four chunks."""
+    ask = lambda B, H, d, total, longest, preact=1: lib.dsla_prefill_varlen_workspace_bytes(
+        ctypes.byref(dsla.make_desc(B, H, d, d, io_dtype=1, gate_dtype=1, chunk=64, gate_mode=preact)), total, longest)
+    # (within the few per cent that the rounding of the segment length to whole chunks makes between neighbouring totals)
+    sizes = [ask(20, 32, 128, total, 8192) for total in (9000, 16384, 20000, 25000, 30000, 37157)]
+    assert all(s >= 0.9 * max(sizes) for s in sizes)
+    for B, H, d, total, longest in ((64, 32, 128, 41523, 7076), (8, 64, 64, 12913, 4336), (53, 40, 128, 1085, 886)):
+        big = ask(B, H, d, total, longest)
+        for part in (2, 3, 5):
+            assert big >= 0.9 * ask(B, H, d, max(total // part, longest), longest) > 0
+    assert ask(40, 32, 128, 3460, 651) == 0 and ask(300, 32, 128, 30000, 256) == 0
