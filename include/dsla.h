@@ -114,6 +114,9 @@ DSLA_API dsla_status dsla_state_init(const dsla_desc *desc, float *S1, float *S2
  * dsla_prefill_workspace_bytes - size in bytes of the scratch buffer dsla_prefill needs
  * for this descriptor and sequence length (0 when none is needed).  Returns 0 for an
  * invalid descriptor as well; dsla_prefill reports the actual error.
+ * With desc->segments = 0 the size is not monotone in T (the number of segments is not): a buffer for several lengths
+ * takes the largest of their sizes.  A call whose buffer is too small for the cut it would choose takes a coarser one
+ * if the buffer holds that (the result then differs by rounding).
  */
 DSLA_API size_t dsla_prefill_workspace_bytes(const dsla_desc *desc, int64_t T);
 

@@ -92,7 +92,7 @@ size_t dsla_prefill_workspace_bytes(const dsla_desc *desc, int64_t T)
     if (check_desc(desc) != DSLA_OK || T <= 0) return 0;
     PrefillPlan plan;
     if (!prefill_plan(*desc, T, &plan)) return 0;
-    return plan.ws_total_bytes;
+    return plan.ws_ask_bytes;
 }
 
 dsla_status dsla_prefill(const dsla_desc *desc, int64_t T, const void *q, const void *k, const void *v,
@@ -110,7 +110,7 @@ dsla_status dsla_prefill(const dsla_desc *desc, int64_t T, const void *q, const 
         return DSLA_ERR_SHAPE;
     if (T > (int64_t(1) << 40)) return DSLA_ERR_SHAPE;
     PrefillPlan plan;
-    if (!prefill_plan(*desc, T, &plan)) return DSLA_ERR_UNSUPPORTED;
+    if (!prefill_plan(*desc, T, &plan, workspace ? workspace_bytes : 0)) return DSLA_ERR_UNSUPPORTED;
     if (static_cast<int64_t>(desc->B) * desc->H * plan.segments > 0x7fffffffLL) return DSLA_ERR_SHAPE;
     if (plan.ws_total_bytes > 0) {
         if (!workspace || workspace_bytes < plan.ws_total_bytes) return DSLA_ERR_WORKSPACE;
@@ -289,7 +289,7 @@ size_t dsla_prefill_multi_workspace_bytes(const dsla_desc *desc, const dsla_mult
     // an odd state out runs beside an idle partner, whose states live behind the plan's own scratch (reserved whatever
     // the parity of the states that pair up: which of them carry a beta gate is not part of the size query's contract)
     const size_t partner = plan.state_elems * sizeof(float);
-    return (plan.ws_total_bytes + 255) / 256 * 256 + partner;
+    return (plan.ws_ask_bytes + 255) / 256 * 256 + partner;
 }
 
 dsla_status dsla_prefill_multi(const dsla_desc *desc, const dsla_multi *multi, int64_t T, const void *q, const void *k,
@@ -304,13 +304,13 @@ dsla_status dsla_prefill_multi(const dsla_desc *desc, const dsla_multi *multi, i
     if (!q || !k || !v || !o) return DSLA_ERR_NULL;
     if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o)) return DSLA_ERR_SHAPE;
     PrefillPlan plan;
-    if (!prefill_plan(*desc, T, &plan)) return DSLA_ERR_UNSUPPORTED;
+    const size_t partner_bytes = static_cast<size_t>(desc->B) * desc->H * desc->d_k * desc->d_v * sizeof(float);
+    if (!prefill_plan(*desc, T, &plan, workspace && workspace_bytes > partner_bytes ? (workspace_bytes - partner_bytes) / 256 * 256 : 0))
+        return DSLA_ERR_UNSUPPORTED;
     if (static_cast<int64_t>(desc->B) * desc->H * plan.segments > 0x7fffffffLL) return DSLA_ERR_SHAPE;
-    const size_t need = dsla_prefill_multi_workspace_bytes(desc, multi, T);
-    if (need > 0) {
-        if (!workspace || workspace_bytes < need) return DSLA_ERR_WORKSPACE;
-        if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return DSLA_ERR_SHAPE;
-    }
+    const size_t need = (plan.ws_total_bytes + 255) / 256 * 256 + partner_bytes;
+    if (!workspace || workspace_bytes < need) return DSLA_ERR_WORKSPACE;
+    if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return DSLA_ERR_SHAPE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int N = multi->n_states;
     float *partner = reinterpret_cast<float *>(static_cast<char *>(workspace) + (plan.ws_total_bytes + 255) / 256 * 256);

@@ -96,7 +96,8 @@ struct PrefillPlan {
     size_t ws_total_bytes;   // what this plan uses
     size_t ws_ask_bytes;     // what the size query answers: at least that
 };
-bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan);  // false: unsupported combination
+// false: unsupported combination.  available: bytes of workspace there are (the size query: any number)
+bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t available = SIZE_MAX);
 bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, PrefillPlan *plan);
 // cu_seqlens == nullptr: B sequences of T tokens each; else packed sequences and T = upper bound of their lengths.
 // seq_index (with cu_seqlens only): which packed sequences take part; nullptr: all, in order.

@@ -2154,13 +2154,13 @@ int plan_chunk(const dsla_desc &d)
 }
 }  // namespace
 
-bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan)
+bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t available)
 {
     const int C = plan_chunk(d);
     if (!C) return false;
     const int64_t nchunks = (T + C - 1) / C;
     const int64_t BH = static_cast<int64_t>(d.B) * d.H;
-    int64_t P;
+    int64_t P, P_coarse = 0;
     if (d.segments > 0) {
         P = d.segments;
     } else {
@@ -2168,6 +2168,7 @@ bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan)
         const int64_t target = (d.d_k == 64) ? 512 : 256;
         P = target / BH;
         if (P > nchunks / 4) P = nchunks / 4;
+        P_coarse = P < 1 ? 1 : P;
         // ... or fewer where that leaves the chip idle (plans of one or two segments stay as they are in 16 bits: there
         // the pre-pass and the scan cost what the shorter segments gain).  A step of 32 tokens takes 2 us in 16-bit
         // arithmetic however few workgroups run, in fp32 7 us (d = 64) and 16 us (d = 128), a segment's share of the
@@ -2176,16 +2177,27 @@ bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan)
         // 199, 166, 141; fp32, 4 heads, d = 64, 256 tokens whole and with 4, 2, 1 chunks: 60, 60, 49, 33.
         const bool f32 = d.io_dtype == DSLA_F32;
         // 256 heads of 1000, 2000, 8000 tokens, d = 64, whole / in two: 54 / 71, 104 / 156, 382 / 602; 160 heads whole / in three: 52 / 62, 127 / 135, 365 / 394
-        if (!f32 && d.d_k == 64 && BH > 128) P = 1;
+        if (!f32 && d.d_k == 64 && BH > 128) P = P_coarse = 1;
         if (P >= 3 || (f32 && (P < 2 || BH * P > chip_slots(d)))) {
             const int64_t most = chip_slots(d) / BH;
             const int64_t least = f32 ? 1 : (BH * ((nchunks + 1) / 2) <= 128 ? 2 : 3);   // chunks per segment
             int64_t cps = most > 0 ? (nchunks + most - 1) / most : nchunks;
             if (cps < least) cps = least;
             P = (nchunks + cps - 1) / cps;
+            if (most <= 1) P_coarse = 1;
         }
     }
     finish_plan(d, C, P, nchunks, d.segments <= 0, plan);
+    if (P_coarse > 0 && P_coarse != P) {
+        // The first rule's cut needs other numbers of slots at other lengths.  The size query covers both, and a call takes the
+        // first rule's where only that one fits: a buffer sized for a longer sequence may hold fewer slots than
+        // this one would fill, and has to serve it all the same.
+        PrefillPlan coarse;
+        finish_plan(d, C, P_coarse, nchunks, true, &coarse);
+        const size_t ask = coarse.ws_total_bytes > plan->ws_total_bytes ? coarse.ws_total_bytes : plan->ws_total_bytes;
+        if (plan->ws_total_bytes > available && coarse.ws_total_bytes <= available) *plan = coarse;
+        plan->ws_ask_bytes = ask;
+    }
     return true;
 }
 

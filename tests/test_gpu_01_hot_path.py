@@ -537,3 +537,27 @@ def test_random_configurations():
             err = max_rel_err(got, ref)
             assert err <= tol, f"case {case} {name}: {err:.3e} > {tol}"
 
+
+
+@pytest.mark.parametrize("io,B,H,d,T_buffer,T", [("f32", 1, 4, 64, 5000, 4096), ("f32", 1, 8, 128, 3, 250), ("f32", 2, 32, 64, 700, 448),
+                                                 ("bf16", 1, 8, 128, 2152, 1827), ("bf16", 1, 8, 64, 2300, 2000)])
+def test_prefill_buffer_of_a_longer_sequence(io, B, H, d, T_buffer, T):
+    """A workspace sized for T_buffer tokens holds fewer slots than T tokens would fill, and enough for the coarser cut."""
+    import torch
+    desc = dsla.make_desc(B, H, d, d, io_dtype=code(io), gate_dtype=code(io), gamma=0.45, chunk=64)
+    n = dsla.dsla_prefill_workspace_bytes(desc, T_buffer)
+    assert n < dsla.dsla_prefill_workspace_bytes(desc, T)
+    x = wl.layer_inputs(97, B, T, H, d, d, io_dtype=io, gate_dtype=io, qk_scale=d ** -0.5)
+    S10, S20 = wl.initial_states(97, B, H, d, d, amplitude=1.0)
+    S1, S2 = (torch.from_numpy(a.copy()).cuda() for a in (S10, S20))
+    t = {name: to_gpu(x[name], io) for name in x}
+    o = torch.full_like(t["v"], float("nan"))
+    ws = torch.empty(n + 256, dtype=torch.uint8, device="cuda")     # (a guard behind it)
+    ws[n:] = 77
+    dsla.dsla_prefill(desc, T, t["q"], t["k"], t["v"], t["g1"], t["g2"], S1, S2, o, ws[:n] if n else None)
+    torch.cuda.synchronize()
+    assert bool((ws[n:] == 77).all())
+    ro, rS1, rS2 = orc.recurrent(x["q"], x["k"], x["v"], x["g1"], x["g2"], 0.45, S1=S10, S2=S20)
+    check("o", o.float().cpu().numpy(), ro, TOL[io])
+    check("S1", S1.cpu().numpy(), rS1, TOL[io])
+    check("S2", S2.cpu().numpy(), rS2, TOL[io])

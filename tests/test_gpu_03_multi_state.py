@@ -163,6 +163,29 @@ def test_prefill_multi_hard_resets_in_neighbouring_groups(io, d, segments):
     assert int(status.item()) == 0
 
 
+def test_prefill_multi_buffer_of_a_longer_sequence():
+    """A workspace sized for a longer sequence that holds fewer slots than this one would fill: the coarser cut, and the idle
+    partner of the third state behind its slots."""
+    import torch
+    B, T, H, d, io = 1, 1827, 8, 128, "bf16"
+    q, k, v, ga, gb, w, S0 = _inputs(395, 3, B, T, H, H, d, io, io, False)
+    desc = dsla.make_desc(B, H, d, d, io_dtype=code(io), gate_dtype=code(io), chunk=64)
+    S = [torch.from_numpy(S0[n].copy()).cuda() for n in range(3)]
+    multi = dsla.make_multi([to_gpu(ga[n], io) for n in range(3)], S, w)
+    n = dsla.dsla_prefill_multi_workspace_bytes(desc, multi, 2152)
+    assert n < dsla.dsla_prefill_multi_workspace_bytes(desc, multi, T)
+    ws = torch.empty(n + 256, dtype=torch.uint8, device="cuda")
+    ws[n:] = 77
+    o = torch.full((B, T, H, d), float("nan"), device="cuda", dtype=torch.bfloat16)
+    dsla.dsla_prefill_multi(desc, multi, T, to_gpu(q, io), to_gpu(k, io), to_gpu(v, io), o, ws[:n])
+    torch.cuda.synchronize()
+    assert bool((ws[n:] == 77).all())
+    ro, rS = orc.nstate(q, k, v, ga, None, w, 1.0, S=S0)
+    check("o", o.float().cpu().numpy(), ro, TOL[io])
+    for i in range(3):
+        check(f"S[{i}]", S[i].cpu().numpy(), rS[i], TOL[io])
+
+
 def test_multi_state_argument_checks():
     import torch
     B, H, d, T = 1, 2, 64, 64
