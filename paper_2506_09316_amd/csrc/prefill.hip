@@ -1118,7 +1118,7 @@ struct Kern {
         const uint32_t l16k = lo & 15, sgm = ((l16k & 1) << 1) | ((l16k >> 1) & 1);
         const uint32_t ktr_r = setb + O_KS + ((4 * (l16k >> 2) + g) * QP + 16 * ((lo >> 4) & 1) + 4 * sgm) * ESZ;
         const uint32_t dec_r = setb + O_DEC + (8 * g) * 4;
-        const uint32_t moves = lds_ld<uint32_t>(setb + O_FLAG);
+        const uint32_t moves = kLineProd ? lds_ld<uint32_t>(setb + O_FLAG) : 0u;
 
         // transposing reads of the V rows: the 16 lanes of a group address 4 tokens x 4 pieces of 4 columns and each
         // receives 4 tokens of ONE column; lane l ends up with column 32 ct + l % 32 and tokens 16 kb + 4 g + 0..3 (first
@@ -1227,8 +1227,8 @@ struct Kern {
         // ---- the states move to the middle frame of the next step (after the last step: to their own frame), with line
         // producers those whose frame does move ----
         // (a block of its own for the register allocator: merged into the code above it costs four spilled registers)
-        const uint32_t m = __builtin_amdgcn_readfirstlane(moves) & (CT == 4 ? 0xffffffffu : 0xffffu);
-        if constexpr (kLineProd) {   // byte i FHN + f of m: features 64 f .. + 63 of state i
+        if constexpr (kLineProd) {
+            const uint32_t m = __builtin_amdgcn_readfirstlane(moves);   // byte i FHN + f: features 64 f .. + 63 of state i
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -1241,7 +1241,8 @@ struct Kern {
             rescale(acc, dec_r, g, 32 * ct + ln);
             // (all tiles once more, those that need it or not: branches or loops around the tiles of one wavefront cost the
             // extended kernel at d = 128 15 to 38 spilled registers, 4 to 9 % of a call with several states)
-            if (__builtin_expect(m != 0, 0)) rescale(acc, dec_r + (O_DEC2 - O_DEC), g, 32 * ct + ln);
+            if (__builtin_expect((__builtin_amdgcn_readfirstlane(lds_ld<uint32_t>(setb + O_FLAG)) & (CT == 4 ? 0xffffffffu : 0xffffu)) != 0, 0))
+                rescale(acc, dec_r + (O_DEC2 - O_DEC), g, 32 * ct + ln);
         }
     }
 
