@@ -2155,6 +2155,25 @@ int plan_chunk(const dsla_desc &d)
 }
 }  // namespace
 
+namespace {
+// Estimates (us): a step of 32 tokens where the chain of one workgroup counts / where every compute unit is busy, a step of
+// the pre-pass, what a workgroup costs besides its steps, a state slot written, scanned and read again.
+struct PrefillCosts {
+    double step, step_full, pre, wg, slot;
+};
+PrefillCosts prefill_costs(const dsla_desc &d)
+{
+    const bool f32 = d.io_dtype == DSLA_F32, small = d.d_k == 64, preact = d.gate_mode == DSLA_GATE_PREACT;
+    PrefillCosts c;
+    c.step = f32 ? (small ? 7.0 : 16.0) : (small ? (preact ? 1.8 : 1.4) : (preact ? 2.35 : 2.0));
+    c.step_full = f32 ? c.step : (small ? 2.5 : (preact ? 3.4 : 2.9));
+    c.pre = f32 ? c.step / 3 : (small ? 1.2 : (preact ? 2.1 : 1.5));
+    c.wg = small ? 5.0 : 8.0;
+    c.slot = f32 ? (small ? 0.025 : 0.06) : (small ? 0.0125 : 0.05);
+    return c;
+}
+}  // namespace
+
 bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t available)
 {
     const int C = plan_chunk(d);
@@ -2182,8 +2201,24 @@ bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t avail
         if (P >= 3 || (f32 && (P < 2 || BH * P > chip_slots(d)))) {
             const int64_t most = chip_slots(d) / BH;
             const int64_t least = f32 ? 1 : (BH * ((nchunks + 1) / 2) <= 128 ? 2 : 3);   // chunks per segment
-            int64_t cps = most > 0 ? (nchunks + most - 1) / most : nchunks;
-            if (cps < least) cps = least;
+            auto chunks_of = [&](int64_t segments_at_most) {
+                const int64_t cps = segments_at_most > 0 ? (nchunks + segments_at_most - 1) / segments_at_most : nchunks;
+                return cps < least ? least : cps;
+            };
+            int64_t cps = chunks_of(most);
+            // Two workgroups on a compute unit take 1.7 times as long as one: either every segment has a unit to itself, or
+            // they are as short as two to a unit allow.  d = 64, segments of one / two to a unit: 24 heads of 2500 tokens 41 / 46,
+            // 60 of 1000 39 / 42, 8 of 8000 54 / 61; 24 of 4000 59 / 55, 60 of 1500 49 / 47.
+            if (chip_slots(d) == 512 && 10 * chunks_of(256 / BH) <= 17 * cps) cps = chunks_of(256 / BH);
+            // fp32, short: the cut saves steps of the chain and costs the pre-pass, its launches and the slots (133 tokens, 96 heads
+            // whole / in two: d = 64 42 / 54, d = 128 93 / 116; 70 tokens, 4 heads, d = 64 27 / 31)
+            if (f32 && P < 2) {
+                const PrefillCosts c = prefill_costs(d);
+                const int64_t steps = (T + 31) / 32, chain = cps * C / 32 < steps ? cps * C / 32 : steps;
+                const double launches = d.d_k == 64 ? 6.0 : 8.5;
+                if (static_cast<double>(steps - chain) * c.step <= chain * c.pre + launches + c.slot * BH * ((nchunks + cps - 1) / cps))
+                    cps = nchunks;
+            }
             P = (nchunks + cps - 1) / cps;
             if (most <= 1) P_coarse = 1;
         }
@@ -2203,22 +2238,6 @@ bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t avail
 }
 
 namespace {
-// Estimates (us): a step of 32 tokens where the chain of one workgroup counts / where every compute unit is busy, a step of
-// the pre-pass, what a workgroup costs besides its steps, a state slot written, scanned and read again.
-struct PrefillCosts {
-    double step, step_full, pre, wg, slot;
-};
-PrefillCosts prefill_costs(const dsla_desc &d)
-{
-    const bool f32 = d.io_dtype == DSLA_F32, small = d.d_k == 64, preact = d.gate_mode == DSLA_GATE_PREACT;
-    PrefillCosts c;
-    c.step = f32 ? (small ? 7.0 : 16.0) : (small ? (preact ? 1.8 : 1.4) : (preact ? 2.35 : 2.0));
-    c.step_full = f32 ? c.step : (small ? 2.5 : (preact ? 3.4 : 2.9));
-    c.pre = f32 ? c.step / 3 : (small ? 1.2 : (preact ? 2.1 : 1.5));
-    c.wg = small ? 5.0 : 8.0;
-    c.slot = small ? 0.0125 : 0.05;
-    return c;
-}
 // Do whole packed sequences go longest first?  Every workgroup pays for its rank (about 2 us and 1 more per 128 sequences),
 // so with R rounds of workgroups the call pays R times, and it gains at most a part of the longest chain, which no longer
 // starts late; max_T may bound the lengths loosely, and then there is nothing to gain: the rank also has to be small

@@ -223,6 +223,10 @@ def test_plans_follow_the_work(lib):
     assert dense(1, 32, 128, 0, 1000) == want(8, 32, 128)     # and never into more than the chip holds
     assert dense(8, 32, 64, 1, 4000) == 0                     # 256 heads at d = 64: whole
     assert dense(1, 32, 128, 1, 256) == 0
+    assert dense(1, 4, 64, 0, 70) == dense(1, 96, 64, 0, 133) == dense(1, 120, 128, 0, 176) == 0   # fp32: too few steps to save
+    assert dense(1, 96, 128, 0, 256) == want(2, 96, 128)
+    assert dense(1, 24, 64, 1, 2500) == want(10, 24, 64)      # d = 64: one workgroup to a compute unit ...
+    assert dense(1, 24, 64, 1, 4000) == want(21, 24, 64)      # ... or as short as two to a unit make them
     packed = lambda B, H, d, total, longest: lib.dsla_prefill_varlen_workspace_bytes(
         ctypes.byref(dsla.make_desc(B, H, d, d, io_dtype=1, gate_dtype=1, chunk=64)), total, longest)
     assert packed(40, 32, 128, 3460, 651) == 0                # many short sequences fill the chip whole
