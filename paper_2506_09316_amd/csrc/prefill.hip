@@ -2157,9 +2157,10 @@ int plan_chunk(const dsla_desc &d)
 
 namespace {
 // Estimates (us): a step of 32 tokens where the chain of one workgroup counts / where every compute unit is busy, a step of
-// the pre-pass, what a workgroup costs besides its steps, a state slot written, scanned and read again.
+// the pre-pass, what a workgroup costs besides its steps, a state slot written, scanned and read again, the lists of a packed
+// batch and the scan besides its slots.
 struct PrefillCosts {
-    double step, step_full, pre, wg, slot;
+    double step, step_full, pre, wg, slot, lists;
 };
 PrefillCosts prefill_costs(const dsla_desc &d)
 {
@@ -2168,8 +2169,9 @@ PrefillCosts prefill_costs(const dsla_desc &d)
     c.step = f32 ? (small ? 7.0 : 16.0) : (small ? (preact ? 1.8 : 1.4) : (preact ? 2.35 : 2.0));
     c.step_full = f32 ? c.step : (small ? 2.5 : (preact ? 3.4 : 2.9));
     c.pre = f32 ? c.step / 3 : (small ? 1.2 : (preact ? 2.1 : 1.5));
-    c.wg = small ? 5.0 : 8.0;
-    c.slot = f32 ? (small ? 0.025 : 0.06) : (small ? 0.0125 : 0.05);
+    c.wg = f32 ? (small ? 7.0 : 16.0) : (small ? 5.0 : 8.0);
+    c.slot = f32 ? (small ? 0.025 : 0.06) : (small ? 0.04 : 0.05);
+    c.lists = f32 ? (small ? 5.0 : 4.0) : (small ? 9.0 : 6.0);
     return c;
 }
 }  // namespace
@@ -2242,8 +2244,8 @@ namespace {
 // so with R rounds of workgroups the call pays R times, and it gains at most a part of the longest chain, which no longer
 // starts late; max_T may bound the lengths loosely, and then there is nothing to gain: the rank also has to be small
 // against an average workgroup.  Own order / longest first (us, d = 128, 32 heads): 16 sequences of 1 to 600 tokens
-// 57 / 46, 32 of 1 to 2500 151 / 134, 48 of 64 to 1000 216 / 207; 8 heads: 128 of 1 to 2500 211 / 158.  Not taken: 64 of
-// 64 to 1000 467 / 476, 128 of 1 to 2500 602 / 631, 48 (512) of up to 40 and one of 300 86 / 101 (950 / 1390).  Up to 256
+// 57 / 46, 32 of 1 to 2500 151 / 134, 48 of 64 to 1000 216 / 207, 64 of those 467 / 476; 8 heads: 128 of 1 to 2500
+// 211 / 158.  Not taken: 48 of up to 40 and one of 300 86 / 101 (512: 950 / 1390), 256 of 1 to 600 658 / 752.  Up to 256
 // tokens it never paid.
 bool order_pays(const dsla_desc &d, int64_t total_T, int64_t max_T)
 {
@@ -2251,7 +2253,7 @@ bool order_pays(const dsla_desc &d, int64_t total_T, int64_t max_T)
     if (d.B < 2 || d.B > 4 * d.d_k || max_T <= 256 || rounds <= 1.0) return false;   // a thread per sequence
     const PrefillCosts c = prefill_costs(d);
     const double longest = static_cast<double>(max_T) / 32, mean = static_cast<double>(total_T) / 32 / d.B;
-    return longest * c.step >= 4 * rounds * rank && c.wg + mean * c.step_full >= 6 * rank;
+    return longest * c.step >= 2.4 * rounds * rank && c.wg + mean * c.step_full >= 2.5 * rank;
 }
 }  // namespace
 
@@ -2294,7 +2296,8 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
         P = P_cut = (nchunks + cps - 1) / cps;
         if (P > 1) {
             const PrefillCosts c = prefill_costs(d);
-            const double chip = chip_slots(d), steps = static_cast<double>(total_T) / 32, L = static_cast<double>(cps * C);
+            const double chip = chip_slots(d), steps = static_cast<double>(total_T) / 32;
+            const double L = static_cast<double>((nchunks + P - 1) / P * C);   // finish_plan evens the segments out
             const double n = L / 32, longest = static_cast<double>(max_T) / 32;
             const double cuts = static_cast<double>(total_T) / L * d.H, items = cuts + static_cast<double>(d.B) * d.H;
             auto loop = [&](double chain, double workgroups) {
@@ -2302,18 +2305,24 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
                 return spread > c.wg + chain * c.step ? spread : c.wg + chain * c.step;
             };
             const double whole = loop(longest, static_cast<double>(d.B) * d.H);
-            const double cut = 7 + c.wg + (cuts > chip ? cuts / chip : 1.0) * n * c.pre + 4 + c.slot * items + loop(n, items);
+            const double cut = c.lists + c.wg + (cuts > chip ? cuts / chip : 1.0) * n * c.pre + c.slot * cuts + loop(n, items);
             if (whole <= cut) P = 1;
         }
     }
     finish_packed(P, plan);
     plan->longest_first = plan->segments == 1 && order_pays(d, total_T, max_T);
     if (P < P_cut) {
-        // Whole by the estimate: the size query still answers with what cutting takes, if any smaller batch is cut (of one
-        // sequence at least: the least the cut can cost), so that a buffer sized for a large batch serves smaller ones.
+        // Whole by the estimate: the size query still answers with what cutting takes, if any smaller batch is cut, so that a
+        // buffer sized for a large batch serves smaller ones.  The least a cut can cost is that of one sequence of n chunks.
         const PrefillCosts c = prefill_costs(d);
-        const double n = 4.0 * C / 32;
-        if (c.wg + static_cast<double>(max_T) / 32 * c.step > 11 + 2 * c.wg + n * (c.pre + c.step) + c.slot * d.H) {
+        bool some = nchunks > 64;
+        for (int64_t n = 5; n <= nchunks && !some; ++n)
+            for (int64_t most = 4; most < 8 && !some; ++most) {
+                const int64_t tokens = n * C < max_T ? n * C : max_T, parts = (n + most - 1) / most;
+                const double chain = static_cast<double>((n + parts - 1) / parts * C) / 32;
+                some = parts > 1 && c.wg + static_cast<double>(tokens) / 32 * c.step > c.lists + 2 * c.wg + chain * (c.pre + c.step) + c.slot * d.H;
+            }
+        if (some) {
             PrefillPlan cut;
             finish_packed(P_cut, &cut);
             plan->ws_ask_bytes = cut.ws_total_bytes;
