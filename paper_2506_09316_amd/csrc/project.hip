@@ -76,10 +76,11 @@ __device__ __forceinline__ void wait_loads()   // at most N of this wavefront's 
 // XCDs, each XCD has its own L2), and the linear order runs in groups of GM row tiles: inside a group the row tile
 // runs fastest, then the column tile, so the tiles in flight at one time (a few dozen per XCD) share GM panels of x
 // and a handful of panels of W instead of one panel of W and dozens of x.  M = 16384, K = 4096, N = 20480 with GM = 4, 6, 8,
-// 16: 1.98, 1.99, 2.09, 2.24 ms.  False: no tile for this workgroup.
-__device__ __forceinline__ bool tile_of(int tiles_m, int tiles_n, int &tm, int &tn)
+// 16: 1.98, 1.99, 2.09, 2.24 ms.  Each group reads all of W, so a last group of one or two row tiles after a single full
+// one is worth avoiding (group_rows()): M = 1060, K = 11008, N = 20480 in 4 + 1 and 5 row tiles 562 and 509 us.
+// False: no tile for this workgroup.
+__device__ __forceinline__ bool tile_of(int tiles_m, int tiles_n, int GM, int &tm, int &tn)
 {
-    constexpr int GM = 4;
     const long long ntiles = static_cast<long long>(tiles_m) * tiles_n;
     const long long per_xcd = (ntiles + 7) / 8;
     const long long lin = static_cast<long long>(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
@@ -124,7 +125,7 @@ constexpr int ROWB = BK * 2;                     // bytes per LDS row: 64
 template <int Q>
 __global__ __launch_bounds__(256, Q == 4 ? 1 : 2) void project_tile_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w,
                                                                  const float *__restrict__ bias, ProjectOuts outs, long long M,
-                                                                 int K, int N, int width, int tiles_m, int tiles_n)
+                                                                 int K, int N, int width, int tiles_m, int tiles_n, int group)
 {
     constexpr int BM = 64 * Q, BN = BM, QS = 32 * Q;   // workgroup tile, quadrant
     constexpr int OPB = BM * ROWB;                      // bytes per operand tile and stage
@@ -136,7 +137,7 @@ __global__ __launch_bounds__(256, Q == 4 ? 1 : 2) void project_tile_kernel(const
     __shared__ __attribute__((aligned(1024))) char st2[STAGEB];
     __shared__ __attribute__((aligned(1024))) char st3[STAGEB];
     int tm, tn;
-    if (!tile_of(tiles_m, tiles_n, tm, tn)) return;
+    if (!tile_of(tiles_m, tiles_n, group, tm, tn)) return;
     const long long m0 = static_cast<long long>(tm) * BM;
     const int n0 = tn * BN;
 
@@ -276,13 +277,13 @@ __global__ __launch_bounds__(256, Q == 4 ? 1 : 2) void project_tile_kernel(const
 // ---------------------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void project_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w,
                                                       const float *__restrict__ bias, ProjectOuts outs, long long M, int K,
-                                                      int width, int tiles_m, int tiles_n)
+                                                      int width, int tiles_m, int tiles_n, int group)
 {
     __shared__ __attribute__((aligned(16))) bf16_t sA[2][TM * PITCH];
     __shared__ __attribute__((aligned(16))) bf16_t sB[2][TN * PITCH];
 
     int tm, tn;
-    if (!tile_of(tiles_m, tiles_n, tm, tn)) return;
+    if (!tile_of(tiles_m, tiles_n, group, tm, tn)) return;
     const long long m0 = static_cast<long long>(tm) * TM;
     const int n0 = tn * TN;
 
@@ -534,6 +535,9 @@ __global__ __launch_bounds__(256) void project_rows_kernel(const bf16_t *__restr
 }  // namespace
 
 namespace {
+// Row tiles per group of the tile order: four, or all of them up to `whole`.
+int group_rows(int tiles_m, int whole) { return tiles_m <= whole ? tiles_m : 4; }
+
 template <int MT, int NT>
 void launch_rows(ProfileScope &ps, int M, int K, int N, int width, const void *x, const void *w, const float *bias,
                  const ProjectOuts &po, hipStream_t stream)
@@ -563,7 +567,8 @@ void launch_tiles(ProfileScope &ps, int64_t M, int K, int N, int width, const vo
     const long long ntiles = static_cast<long long>(tiles_m) * tiles_n;
     const unsigned grid = static_cast<unsigned>((ntiles + 7) / 8 * 8);
     DSLA_LAUNCH(ps, project_tile_kernel<Q>, dim3(grid), dim3(256), 0, stream, static_cast<const bf16_t *>(x),
-                static_cast<const bf16_t *>(w), bias, po, static_cast<long long>(M), K, N, width, tiles_m, tiles_n);
+                static_cast<const bf16_t *>(w), bias, po, static_cast<long long>(M), K, N, width, tiles_m, tiles_n,
+                group_rows(tiles_m, 5));
 }
 }  // namespace
 
@@ -595,7 +600,8 @@ hipError_t launch_project(int64_t M, int K, int n_out, int width, const void *x,
         const long long ntiles = static_cast<long long>(tiles_m) * tiles_n;
         const unsigned grid = static_cast<unsigned>((ntiles + 7) / 8 * 8);
         DSLA_LAUNCH(ps, project_kernel, dim3(grid), dim3(256), 0, stream, static_cast<const bf16_t *>(x),
-                           static_cast<const bf16_t *>(w), bias, po, static_cast<long long>(M), K, width, tiles_m, tiles_n);
+                           static_cast<const bf16_t *>(w), bias, po, static_cast<long long>(M), K, width, tiles_m, tiles_n,
+                           group_rows(tiles_m, 6));
     }
     return hipGetLastError();
 }
