@@ -588,12 +588,14 @@ hipError_t launch_project(int64_t M, int K, int n_out, int width, const void *x,
         else if (M <= 64) launch_rows_n<4>(ps, m, K, N, width, x, w, bias, po, stream);
         else launch_rows_n<8>(ps, m, K, N, width, x, w, bias, po, stream);
     } else if (K % (4 * BK) == 0) {   // the loop of project_tile_kernel goes four stages at a time
-        // Small tiles while the chip has compute units for them: a large tile does four times the work of a small one in
-        // about 2.5 times its time, so the rounds over the 256 compute units decide (K = 4096: M = 384, N = 20480 95 against
-        // 102 us; M = 1300, N = 3072 59 against 77 us; M = 640, N = 20480 154 against 114 us).
+        // Small tiles while the chip has compute units for them: the rounds over the 256 compute units decide.  A large tile does
+        // four times the work of a small one in 2.2 times its time where K is long; where it is short the epilogue weighs
+        // more, 2.8 times at K = 512.  Small / large (us): K = 4096: M = 384, N = 20480 95 / 102; M = 1300, N = 3072 59 / 77;
+        // M = 640, N = 20480 154 / 114; M = 1480, N = 12288 189 / 174; K = 11008: M = 520, N = 28672 521 / 459; K = 512:
+        // M = 2600, N = 12288 45 / 56, M = 384, N = 28672 26 / 21.
         const int64_t rounds128 = ((M + 127) / 128 * (N / 128) + 255) / 256;
         const int64_t rounds256 = ((M + 255) / 256 * ((N + 255) / 256) + 255) / 256;
-        if (2 * rounds128 <= 5 * rounds256) launch_tiles<2>(ps, M, K, N, width, x, w, bias, po, stream);
+        if (10 * rounds128 * K <= (22 * static_cast<int64_t>(K) + 3200) * rounds256) launch_tiles<2>(ps, M, K, N, width, x, w, bias, po, stream);
         else launch_tiles<4>(ps, M, K, N, width, x, w, bias, po, stream);
     } else {
         const int tiles_m = static_cast<int>((M + TM - 1) / TM), tiles_n = N / TN;
