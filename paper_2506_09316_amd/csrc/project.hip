@@ -547,14 +547,26 @@ void launch_rows(ProfileScope &ps, int M, int K, int N, int width, const void *x
     DSLA_LAUNCH(ps, (project_rows_kernel<MT, NT>), dim3(grid), dim3(256), 0, stream, static_cast<const bf16_t *>(x),
                 static_cast<const bf16_t *>(w), bias, po, M, K, N, width, tiles_m, tiles_n);
 }
+// Column tiles per workgroup of the row kernel: the most that still leave 256 workgroups, one for every compute unit, of the
+// numbers that are built: 1, 2, 3 and 5 (from N = 4096 times that number).  Between 12288 and 20479 columns, where four would be
+// the number, three make up to 426 workgroups: M = 64, K = 4096, N = 16384 43 us against 34 at N = 20480.
+int row_column_tiles(int N)
+{
+    const int nt = N / (16 * 256);
+    return nt >= 5 ? 5 : (nt >= 3 ? 3 : (nt == 2 ? 2 : 1));
+}
+int row_workgroups(int N)
+{
+    const int columns = 16 * row_column_tiles(N);
+    return (N + columns - 1) / columns;
+}
 template <int MT>
 void launch_rows_n(ProfileScope &ps, int M, int K, int N, int width, const void *x, const void *w, const float *bias,
                    const ProjectOuts &po, hipStream_t stream)
 {
-    // as many column tiles per workgroup as leave a workgroup for every compute unit
-    const int nt = N / (16 * 256);
-    if (nt >= 5) launch_rows<MT, 5>(ps, M, K, N, width, x, w, bias, po, stream);
-    else if (nt >= 3) launch_rows<MT, 3>(ps, M, K, N, width, x, w, bias, po, stream);
+    const int nt = row_column_tiles(N);
+    if (nt == 5) launch_rows<MT, 5>(ps, M, K, N, width, x, w, bias, po, stream);
+    else if (nt == 3) launch_rows<MT, 3>(ps, M, K, N, width, x, w, bias, po, stream);
     else if (nt == 2) launch_rows<MT, 2>(ps, M, K, N, width, x, w, bias, po, stream);
     else launch_rows<MT, 1>(ps, M, K, N, width, x, w, bias, po, stream);
 }
@@ -579,9 +591,15 @@ hipError_t launch_project(int64_t M, int K, int n_out, int width, const void *x,
     for (int j = 0; j < DSLA_MAX_PROJECTIONS; ++j) po.p[j] = j < n_out ? outs[j] : nullptr;
     const int N = n_out * width;
     ProfileScope ps(DSLA_KERNEL_PROJECT, stream);
-    // Few rows: the weights are the traffic (65 .. 128 rows: 22 against 34 us at K = 4096, N = 3072, but 17 against 13 us at
-    // K = 1024, N = 20480, where the tile kernel's stages are few).
-    if (M <= 64 || (M <= 128 && (K >= 2048 || K % (4 * BK) != 0))) {
+    // Few rows: the weights are the traffic.  Not where the row kernel's workgroups need a second, nearly empty round over the
+    // compute units and the others pass the weights in one: with 65 .. 128 rows N = 24576, K = 4096 86 / 59 us (row kernel /
+    // 128 x 128 tiles), N = 16384, K = 2048 34 / 30, but N = 20480 47 / 58 and 27 / 31 (K = 1024: 17 / 13, where the tile
+    // kernel's stages are few); where K is no multiple of 128, N = 28672, K = 160 13 / 10, K = 480 20 / 18, K = 1056 31 / 32.
+    // Up to 64 rows a second round is the lesser evil, except for the shortest K: N = 28672, K = 160 10.6 / 9.3, K = 480 16 / 18.
+    // (Past 32768 columns the others' tiles go twice over the chip as well: N = 35840, K = 4096, 97 rows 87 / 99.)
+    const bool second_round = N > 12288 && N <= 32768 && row_workgroups(N) > 256;
+    if (M <= 16 || (M <= 64 && (N <= 20480 || K >= 256)) ||
+        (M > 64 && M <= 128 && (K % (4 * BK) == 0 ? K >= 2048 && !second_round : K >= 1024 || !second_round))) {
         const int m = static_cast<int>(M);
         if (M <= 16) launch_rows_n<1>(ps, m, K, N, width, x, w, bias, po, stream);
         else if (M <= 32) launch_rows_n<2>(ps, m, K, N, width, x, w, bias, po, stream);
