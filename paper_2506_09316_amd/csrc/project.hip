@@ -358,15 +358,17 @@ __global__ __launch_bounds__(256) void project_kernel(const bf16_t *__restrict__
 // ---------------------------------------------------------------------------------------------------------------
 // Few rows: the weights are the traffic
 // ---------------------------------------------------------------------------------------------------------------
-// Bound by HBM: 2 N K bytes of weights.  Workgroup = 4 wavefronts on 16 MT rows of x (all of them up to 128) and 16 NT
-// columns, NT chosen so that there is a workgroup per compute unit.  Stages of 64 KS values of K - KS lines of 128 bytes
+// Bound by HBM: 2 N K bytes of weights.  Workgroup = 4 wavefronts on 16 MT rows of x (all of them: at most 128) and 16 NT
+// columns (row_column_tiles() has the rule).  Stages of 64 KS values of K - KS lines of 128 bytes
 // of each of the 16 (NT + MT) rows; whole lines, because a request costs the L2 the same whatever its size - go through
 // a ring of LDS slots filled by loads that write LDS directly, so three stages are in flight whatever the registers
 // hold.  The fragments of the next stage are read while the MFMAs of the current one run (without that a stage costs
-// its LDS latency on top: M = 64 41.5 us instead of 36.7), and short stages are merged (KS) because the barrier of a
-// stage costs about 0.2 us (M = 20, N = 3072, K = 4096: KS = 1 18.2, 2 12.9, 4 11.0 us).
-// K = 4096, N = 20480 (170 MB): M = 1 29.8 us = 5.7 TB/s, M = 64 36.7 us = 4.7 TB/s, M = 128 51 us; the 256 x 256 tiles
-// take 75, 82 and 98 us.
+// its LDS latency on top: M = 64 41.5 us instead of 34.5), and short stages are merged (KS) because the barrier of a
+// stage costs about 0.2 us (M = 20, N = 3072, K = 4096: KS = 1 18.2, 2 12.9, 4 11.0 us).  One row tile and five column tiles keep
+// stages of one line: with 48 KB three workgroups share a compute unit, with 96 KB one (M = 8, N = 28672, K = 512 8.4 against
+// 10.6 us, K = 4096 48.5 against 50.5; N = 20480, which is one round either way, 6.3 against 6.7 and 31.2 against 31.8).
+// K = 4096, N = 20480 (170 MB): M = 1 32 us = 5.3 TB/s, M = 64 34.5 us = 5.0 TB/s, M = 128 48 us; the 128 x 128 tiles take
+// 56, 56 and 59 us, the 256 x 256 ones 80, 83 and 94.
 template <int MT, int NT>
 struct Rows {
     static constexpr int KS = MT + NT <= 3 ? 4 : (MT + NT > 12 || (MT == 1 && NT == 5) ? 1 : 2);   // lines of 64 values per row and stage
@@ -390,16 +392,12 @@ __device__ __forceinline__ void load_to_lds16(uint32_t lds, uint32_t voff, const
 template <int MT, int NT>
 __global__ __launch_bounds__(256) void project_rows_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w,
                                                            const float *__restrict__ bias, ProjectOuts outs, int M, int K,
-                                                           int N, int width, int tiles_m, int tiles_n)
+                                                           int N, int width)
 {
     using R = Rows<MT, NT>;
     constexpr int DEPTH = R::DEPTH;
     __shared__ __attribute__((aligned(1024))) char ring[DEPTH * R::STAGE];
-    // workgroup ids go round-robin over the 8 XCDs: the row tiles of one column tile follow each other on one XCD, so
-    // that its L2 serves the weights again
-    const int slot = blockIdx.x / 8, tn = slot / tiles_m * 8 + blockIdx.x % 8, tm = slot % tiles_m;
-    if (tn >= tiles_n) return;
-    const int m0 = tm * 16 * MT, n0 = tn * 16 * NT;
+    const int n0 = blockIdx.x * 16 * NT;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const uint32_t ring_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const char *)ring));
 
@@ -422,15 +420,15 @@ __global__ __launch_bounds__(256) void project_rows_kernel(const bf16_t *__restr
             row = n0 + row < N ? row : N - 1 - n0;
         } else {
             row = static_cast<int>(srow) - 16 * NT;
-            row = m0 + row < M ? row : M - 1 - m0;
+            row = row < M ? row : M - 1;
         }
         voff[c] = static_cast<uint32_t>(row) * static_cast<uint32_t>(K) * 2u + 128 * (n / R::LB) + 16 * piece;
         unit[c] = 2 * (n / R::LB) + (piece >> 2);
-        src[c] = reinterpret_cast<const char *>(i < 2 * NT ? w + static_cast<size_t>(n0) * K : x + static_cast<size_t>(m0) * K);
+        src[c] = reinterpret_cast<const char *>(i < 2 * NT ? w + static_cast<size_t>(n0) * K : x);
     }
     // Workgroups start their walk at different stages, so that the lines they ask for at one time spread over the memory
     // channels (rows are a large power of two apart; M = 16: 35.0 us when all start at stage 0, 29.8 us).
-    const int rot = (3 * slot) % ns;
+    const int rot = (3 * (blockIdx.x / 8)) % ns;
     auto issue = [&](int i, int at) {   // stage i of the walk into ring slot `at`
         int s = i + rot;
         s = s < ns ? s : s - ns;
@@ -514,7 +512,7 @@ __global__ __launch_bounds__(256) void project_rows_kernel(const bf16_t *__restr
     }
 #pragma unroll
     for (int a = 0; a < R::TM_; ++a) {
-        const int m = m0 + 16 * (wm + R::WM * a) + r;
+        const int m = 16 * (wm + R::WM * a) + r;
         if (m >= M) continue;
 #pragma unroll
         for (int b = 0; b < R::TN_; ++b) {
@@ -542,10 +540,9 @@ template <int MT, int NT>
 void launch_rows(ProfileScope &ps, int M, int K, int N, int width, const void *x, const void *w, const float *bias,
                  const ProjectOuts &po, hipStream_t stream)
 {
-        const int tiles_m = (M + 16 * MT - 1) / (16 * MT), tiles_n = (N + 16 * NT - 1) / (16 * NT);
-    const unsigned grid = static_cast<unsigned>((tiles_n + 7) / 8 * 8) * tiles_m;
+    const unsigned grid = static_cast<unsigned>((N + 16 * NT - 1) / (16 * NT));   // one workgroup has all rows: M <= 16 MT
     DSLA_LAUNCH(ps, (project_rows_kernel<MT, NT>), dim3(grid), dim3(256), 0, stream, static_cast<const bf16_t *>(x),
-                static_cast<const bf16_t *>(w), bias, po, M, K, N, width, tiles_m, tiles_n);
+                static_cast<const bf16_t *>(w), bias, po, M, K, N, width);
 }
 // Column tiles per workgroup of the row kernel: the most that still leave 256 workgroups, one for every compute unit, of the
 // numbers that are built: 1, 2, 3 and 5 (from N = 4096 times that number).  Between 12288 and 20479 columns, where four would be

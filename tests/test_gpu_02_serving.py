@@ -265,11 +265,16 @@ def test_project_against_library_matmul(M, K, n_out, width, bias):
 
 
 # (rows of x, K, tensors, width): row counts on and off the 16 .. 128 rows a workgroup takes, every number of column tiles
-# (N / 4096 = 0, 2, 3, 5 and a ragged last tile), K of one block of 32, of a partial last stage and of many stages; then
-# outputs that take the 128 x 128 and the 256 x 256 tiles, with ragged edges in both directions.
+# for every number of row tiles (N / 4096 = 0, 2, 3, 5 and a ragged last tile), K of one block of 32, of a partial last stage and
+# of more stages than the ring has slots (three slots: 65 .. 128 rows with 2 and 3 column tiles); then outputs that take the
+# 128 x 128 and the 256 x 256 tiles, with ragged edges in both directions and groups of one to five row tiles.
 @pytest.mark.parametrize("M,K,n_out,width", [(1, 32, 1, 128), (16, 96, 3, 256), (17, 160, 2, 4096), (32, 288, 5, 2560), (33, 352, 7, 2944),
                                              (64, 1024, 5, 512), (5, 224, 7, 2944), (16, 4096, 4, 128), (65, 96, 2, 384), (100, 2048, 1, 256),
-                                             (128, 2080, 7, 2944), (129, 256, 3, 384), (1000, 128, 5, 640), (1991, 256, 7, 896)])
+                                             (128, 2080, 7, 2944), (129, 256, 3, 384), (1000, 128, 5, 640), (1991, 256, 7, 896),
+                                             (9, 1056, 2, 4096), (16, 800, 3, 4096), (20, 800, 5, 512), (30, 800, 5, 4096), (50, 800, 2, 4096),
+                                             (64, 800, 3, 4096), (100, 2080, 3, 4096), (128, 2080, 2, 4096), (120, 1056, 5, 4096),
+                                             (40, 160, 7, 2944), (100, 2048, 6, 4096), (77, 224, 4, 4096),
+                                             (600, 256, 3, 384), (600, 160, 3, 384), (1160, 1024, 7, 2944), (2600, 512, 3, 4096)])
 def test_project_kernels(M, K, n_out, width):
     """Every kernel behind dsla_project against a library matmul in fp64: each element within half a bf16 unit of itself
     plus fp32 accumulation (as test_project_against_library_matmul), rows past the end of the outputs untouched."""
