@@ -15,7 +15,7 @@
 // stages to arrive.  Bound by power: the chip runs it at 1.8 GHz with the matrix pipes 73 % busy, and what an MFMA draws
 // decides - registers only, 16 x 16 x 32 sustains 2.04 PFLOP/s and 32 x 32 x 16 1.77 (fewer accumulators are read and written
 // per product).  M = 16384, K = 4096, N = 20480: 2.29 ms on 32 x 32 x 16, 2.09 on 16 x 16 x 32, 1.98 with the tile order
-// below (1390 TFLOP/s; a plain library product of this shape 1.87 ms); with other inputs each time 2.34 ms before and 2.15 now;
+// below (1390 TFLOP/s; a plain library product of this shape 1.87 ms); with other inputs each time 2.34 ms before and 2.09 to 2.15 now;
 // M = 4096 0.54, 0.49, 0.48 ms.
 // A row of a stage is 64 bytes; its piece c sits at piece position c ^ 2 (row / 8 % 2).  A 16-byte LDS read takes lanes 0-3,
 // 12-15, 20-27 at one time, then 4-11, 16-19, 28-31, and so on (32-63 alike): with this placement each of those
