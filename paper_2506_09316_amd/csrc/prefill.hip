@@ -12,7 +12,8 @@
 // turns these into the true state entering each segment.  (3) chunk_loop: every segment runs the
 // fused step loop from its true initial state and writes o; the last segment writes the final
 // states.  P = 1 runs (3) alone.  (1) and (3) are one kernel template; for 16-bit inputs and gates at d = 128, (1) has a
-// kernel of its own that walks a segment backwards (segment_state_fast_kernel, below the template).
+// kernel of its own that walks a segment backwards (segment_state_fast_kernel, below the template), and for 32-bit inputs both
+// have kernels that are made for the rate of fp32 MFMAs (F32Kern; the template keeps the launches with a beta gate).
 // Packed sequences of different lengths share one segment length; a one-workgroup kernel (segment_list) turns
 // their offsets into the lists of (sequence, segment) pairs that (1) and (3) take their work from, so that no
 // workgroup is launched for a segment that does not exist.  Sequences may be a subset of the packed batch and
@@ -1651,6 +1652,356 @@ __global__ __launch_bounds__(4 * D, (D == 64 && sizeof(TIO) == 4 && kFull) ? 1 :
 }
 
 // ---------------------------------------------------------------------------------------------
+// The kernels of 32-bit inputs (chunk loop, and with kFull = false the segment pre-pass): fp32 arithmetic throughout, bound by
+// the fp32 matrix pipe (32 multiply-adds per clock and SIMD, a sixteenth of the bf16 rate).  The step algebra is the one above;
+// what differs from the template is who does what, so that no matrix pipe idles and nothing is multiplied twice:
+//  * No roles.  D / 16 wavefronts, each of which prepares operands and owns 16 columns of both states, so all four SIMDs
+//    multiply (with D / 32 consumers, half of them at d = 64), and D / 16 x 2 tiles of 16 x 16 leave the registers to
+//    prefetch a whole step.
+//  * The scores of a step are computed once: the three 16 x 16 tiles at and below the diagonal, divided over the wavefronts, meet
+//    in LDS (every consumer of the template multiplies all four: a third of its matrix work).
+//  * K~ and V exist once in LDS, as rows.  v_mfma_f32_16x16x4 takes one value per lane, so the token-contiguous operands of the
+//    update are plain 4-byte reads (row pitches of 4 beyond a multiple of 64 floats: no conflicts); with the features of an MFMA
+//    at 4 g + e the accumulators are fed back as operands and the row operands are 16-byte reads.
+// Two barriers per step: operands ready; scores ready and operands read.  In between the matrix pipes are busy from the scores
+// through the read-out to the update; the preparation (about a sixth of a step) is not overlapped inside a workgroup, at d = 64
+// two workgroups share a compute unit and do it for each other.
+// The frame moves in every step (a frame that stays would put larger exponents, and with them larger rounding errors, into fp32
+// factors): 64 multiplications, taken tile by tile in front of a tile's MFMAs, are 2 % of a step's matrix work.
+// A step takes 11.5 us at d = 128 and 4.6 us at d = 64 where the template took 16.3 and 7.0 (8.1 and 2.3 of them are MFMAs at
+// 2.3 GHz; the preparation is 1.0 and 1.3).  7 prompts of 1089 tokens, 32 heads, d = 128: 708 -> 450 us; 8 of 600, 32 heads, d = 64:
+// 141 -> 100; one of 256, 4 heads, d = 64 (four segments): 33 -> 24.  Left out: the next step prepared in registers by one
+// wavefront of a SIMD while the other multiplies (97 spilled registers at d = 128: 470 instead of 362 us for 1024 tokens; at
+// d = 64, without spills, 156 instead of 147).
+// ---------------------------------------------------------------------------------------------
+template <int D, class TG, bool kFull>
+struct F32Kern {
+    using Base = Kern<D, float, TG, kFull, true, false>;   // constants of the step algebra, the order of packed sequences
+    static constexpr int S = 32;                // tokens per step
+    static constexpr int NW = D / 16, NT = 64 * NW;
+    static constexpr int FG = D / 32;           // wavefronts per state when preparing: wavefront w prepares state w / FG, features 32 (w % FG) ..
+    static constexpr int DT = D / 16;           // 16-row tiles of a state
+    static constexpr int PARTS = NW >= 6 ? 2 : 1;   // summands of a score tile: one per state, or both in one
+    static constexpr int QP = 2 * D + 4, VP = D + 4, SP = S + 4;   // row pitches (floats)
+    static constexpr uint32_t O_QS = 0, O_KS = O_QS + (kFull ? S * QP * 4 : 0), O_V = O_KS + S * QP * 4, O_SC = O_V + S * VP * 4;
+    static constexpr uint32_t O_CS = O_SC + (kFull ? PARTS * S * SP * 4 : 0);   // per wavefront: float [16][32] scan scratch
+    static constexpr uint32_t O_DEC = O_CS + NW * 2048, O_DEC2 = O_DEC + 2 * D * 4;   // float [2D] each: frame change into the step; its second factor
+    static constexpr uint32_t O_END = O_DEC2 + 2 * D * 4;                       // float [2D]: from the middle of the step to its end
+    static constexpr uint32_t O_FLAG = O_END + 2 * D * 4;                       // uint8 [NW]: the second factors of this wavefront's features count
+    static constexpr uint32_t LDS_BYTES = O_FLAG + 16;
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
+
+    struct Raw {   // inputs of one step as loaded: 2 tokens x 8 features of q, k and one state's gates, 1 token x 8 columns of v
+        Raw8<float> q[2], k[2], v;
+        Raw8<TG> g[2];
+    };
+
+    static __device__ __forceinline__ void run(const PrefillArgs &a, uint32_t sm)
+    {
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+
+        // ---- the work item: as Kern::run ----
+        int bidx, h, p;
+        size_t slot0, slot_step;
+        if (a.list_full) {
+            const int it = blockIdx.x / a.H;
+            if (it >= a.seg_count[kFull ? 0 : 1]) return;
+            const int2 e = (kFull ? a.list_full : a.list_pre)[it];
+            bidx = e.x;
+            p = e.y;
+            h = blockIdx.x % a.H;
+            slot0 = static_cast<size_t>(a.seg_first[bidx]) * a.H + h;
+            slot_step = a.H;
+        } else {
+            const int nseg = kFull ? a.P : a.P - 1;
+            const int bh = blockIdx.x / nseg;
+            p = blockIdx.x % nseg;
+            bidx = bh / a.H;
+            h = bh % a.H;
+            slot0 = bh;
+            slot_step = gridDim.x / nseg;
+            if (kFull && a.longest_first) bidx = Base::sequence_of_rank(a, sm, bidx, static_cast<int>(slot_step) / a.H);
+        }
+        const int sq = (a.cu && a.seq) ? a.seq[bidx] : bidx;
+        const int64_t seq0 = a.cu ? static_cast<int64_t>(a.cu[sq]) : static_cast<int64_t>(bidx) * a.T;
+        const int64_t Tb = a.cu ? static_cast<int64_t>(a.cu[sq + 1]) - seq0 : a.T;
+        const size_t sbh = static_cast<size_t>(a.slot ? a.slot[bidx] : bidx) * a.H + h;
+        const int64_t t0 = static_cast<int64_t>(p) * a.seg_tokens;
+        if (kFull ? t0 >= Tb : t0 + a.seg_tokens >= Tb) return;   // (uniform, before any barrier)
+        const int64_t t1 = (t0 + a.seg_tokens < Tb) ? t0 + a.seg_tokens : Tb;
+        const int ntok = static_cast<int>(t1 - t0), nsteps = (ntok + S - 1) / S;
+        const uint32_t rs = static_cast<uint32_t>(a.H) * D, rskv = static_cast<uint32_t>(a.Hkv) * D;   // elements between tokens
+        const size_t seg0 = (static_cast<size_t>(seq0 + t0) * a.H + h) * D;
+        const size_t seg0kv = (static_cast<size_t>(seq0 + t0) * a.Hkv + h / (a.H / a.Hkv)) * D;
+
+        // ---- preparing: lane (sg, dgl) has tokens 2 sg, 2 sg + 1 and features 32 pw + 8 dgl .. of state st; of v token 16 st + sg ----
+        const uint32_t st = static_cast<uint32_t>(wave) / FG, pw = static_cast<uint32_t>(wave) % FG;
+        const uint32_t sg = static_cast<uint32_t>(lane) >> 2, f0 = 32 * pw + 8 * (lane & 3u);
+        const uint32_t fcol = static_cast<uint32_t>(lane) & 31u, hh = static_cast<uint32_t>(lane) >> 5;   // scan: feature, half of the token pairs
+        const uint32_t cs = sm + O_CS + wave * 2048, cs_own = cs + (sg * 32 + 8 * (lane & 3u)) * 4, cs_col = cs + (8 * hh * 32 + fcol) * 4;
+        const uint32_t decl = (st * D + 32 * pw + fcol) * 4;
+        const bool preact = a.gate_inv_tau != 0.f;
+        const float unit = preact ? a.gate_inv_tau : kLog2e;   // gate sums times this = log2 of a decay
+        float gs;
+        if (a.explicit_w) {
+            const float *per_head = st ? a.wb_per_head : a.wa_per_head;
+            gs = (per_head ? per_head[h] : (st ? a.wb : a.wa)) * a.scale;
+        } else {
+            const float gm = a.gamma_per_head ? a.gamma_per_head[h] : a.gamma;
+            gs = (st ? 1.0f - gm : gm) * a.scale;
+        }
+        const float lg = __builtin_amdgcn_logf(fabsf(gs));
+        const uint32_t sgn = gs < 0.f ? 0x80000000u : 0u;
+        const float *q0 = static_cast<const float *>(a.q) + seg0, *k0 = static_cast<const float *>(a.k) + seg0kv,
+                    *v0 = static_cast<const float *>(a.v) + seg0kv;
+        const TG *gate0 = static_cast<const TG *>(st ? a.g2 : a.g1) + seg0;
+        auto valid_of = [&](int n) -> int {
+            const int left = ntok - n * S;
+            return left >= S ? S : left;
+        };
+        auto load = [&](Raw &x, int n) {   // step n < nsteps; a token past the end re-reads the last one
+            const size_t so = static_cast<size_t>(n) * S * rs, sokv = static_cast<size_t>(n) * S * rskv;
+            const uint32_t last = static_cast<uint32_t>(valid_of(n)) - 1;
+            auto row = [&](uint32_t t) { return t < last ? t : last; };
+#pragma unroll
+            for (uint32_t j = 0; j < 2; ++j) x.g[j].load(gate0 + so, row(2 * sg + j) * rs + f0);
+#pragma unroll
+            for (uint32_t j = 0; j < 2; ++j) {
+                x.k[j].load(k0 + sokv, row(2 * sg + j) * rskv + f0);
+                if (kFull) x.q[j].load(q0 + so, row(2 * sg + j) * rs + f0);
+            }
+            x.v.load(v0 + sokv, row(16 * st + sg) * rskv + f0);
+        };
+        float tot = 0.f, seg_decay = 0.f;   // of this lane's scan column: gate sum of the step prepared last, log2 decay of the segment
+        auto prepare = [&](Raw &x, int valid) {
+            float c[2][8];   // gate sums over this thread's tokens
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                x.g[j].unpack(c[j]);
+                if (preact) Base::activate(c[j]);
+                if (static_cast<int>(2 * sg) + j >= valid) {   // past the end: no decay, no key
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) c[j][e] = 0.f;
+                    x.k[j].zero();
+                }
+            }
+            if (static_cast<int>(16 * st + sg) >= valid) x.v.zero();
+#pragma unroll
+            for (int e = 0; e < 8; ++e) c[1][e] += c[0][e];
+            lds_st<f32x4>(cs_own, f32x4{c[1][0], c[1][1], c[1][2], c[1][3]});
+            lds_st<f32x4>(cs_own + 16, f32x4{c[1][4], c[1][5], c[1][6], c[1][7]});
+            const uint32_t va = sm + O_V + ((16 * st + sg) * VP + f0) * 4;
+            lds_st<f32x4>(va, x.v.a);
+            lds_st<f32x4>(va + 16, x.v.b);
+            Base::wave_sync();
+            {   // the scan over the 16 token pairs of a feature, 8 to a lane; centred on the step (see the step algebra)
+                float t[8];
+#pragma unroll
+                for (int s2 = 0; s2 < 8; ++s2) t[s2] = lds_ld<float>(cs_col + s2 * 128);
+                const float mine = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7])), other = __shfl_xor(mine, 32);
+                const float sum = mine + other;
+                float run = -0.5f * sum + (hh ? other : 0.f);
+#pragma unroll
+                for (int s2 = 0; s2 < 8; ++s2) {
+                    lds_st<float>(cs_col + s2 * 128, run);
+                    run += t[s2];
+                }
+                // from the middle of the step before (or the state itself) to the middle of this one; past one factor as two equal ones
+                const float change = 0.5f * unit * (tot + sum);
+                const bool twice = __builtin_amdgcn_ballot_w64(change < -Base::kOneFactor) != 0;
+                const float factor = __builtin_amdgcn_exp2f(twice ? 0.5f * change : change);
+                lds_st<float>(sm + O_DEC + decl, factor);   // (both lanes of a feature write the same)
+                lds_st<float>(sm + O_DEC2 + decl, twice ? factor : 1.f);
+                lds_st<float>(sm + O_END + decl, __builtin_amdgcn_exp2f(0.5f * unit * sum));
+                if (lane == 0) lds_st<uint8_t>(sm + O_FLAG + wave, twice);
+                tot = sum;
+                const float r = sum * unit;
+                seg_decay += r;
+                if (a.status && !(r >= -Base::kMaxStepLog2Decay)) *a.status = DSLA_STATUS_GATE_DOMAIN;
+            }
+            Base::wave_sync();
+            const f32x4 p0 = lds_ld<f32x4>(cs_own), p1 = lds_ld<f32x4>(cs_own + 16);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                float kf[8], qf[8];
+                x.k[j].unpack(kf);
+                if (kFull) x.q[j].unpack(qf);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float y = (e < 4 ? p0[e & 3] : p1[e & 3]) + c[j][e];
+                    kf[e] *= __builtin_amdgcn_exp2f(-unit * y);
+                    if (kFull) qf[e] = __uint_as_float(__float_as_uint(qf[e]) ^ sgn) * __builtin_amdgcn_exp2f(fmaf(y, unit, lg));
+                }
+                const uint32_t at = ((2 * sg + j) * QP + st * D + f0) * 4;
+                lds_st<f32x4>(sm + O_KS + at, f32x4{kf[0], kf[1], kf[2], kf[3]});
+                lds_st<f32x4>(sm + O_KS + at + 16, f32x4{kf[4], kf[5], kf[6], kf[7]});
+                if (kFull) {
+                    lds_st<f32x4>(sm + O_QS + at, f32x4{qf[0], qf[1], qf[2], qf[3]});
+                    lds_st<f32x4>(sm + O_QS + at + 16, f32x4{qf[4], qf[5], qf[6], qf[7]});
+                }
+            }
+        };
+
+        // ---- multiplying: lane (r, g); acc[i][dt][e] = T^i[16 dt + 4 g + e][16 wave + r] ----
+        const uint32_t r = lane & 15, g = static_cast<uint32_t>(lane) >> 4;
+        f32x4 acc[2][DT];
+        const bool cut = Tb > a.seg_tokens;   // (which states a segment starts from: see Kern::run)
+        const uint32_t sbase = 4 * g * D + 16 * wave + r;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (kFull && (!a.zero_init || (cut && p > 0))) {
+                const float *src = cut ? a.ws_state + ((slot0 + static_cast<size_t>(p) * a.slot_mul * slot_step) * 2 + i) * D * D
+                                       : (i ? a.S2 : a.S1) + sbh * D * D;
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[i][dt][e] = src[sbase + (16 * dt + e) * D];
+            } else {
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) acc[i][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+        auto scale = [&](uint32_t factors, int i, int dt) {
+            const f32x4 f = lds_ld<f32x4>(factors + (i * D + 16 * dt + 4 * g) * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i][dt][e] *= f[e];
+        };
+        auto rescale = [&](uint32_t factors) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) scale(factors, i, dt);
+        };
+        auto move = [&](int i, int dt) { scale(sm + O_DEC, i, dt); };   // into the middle frame of the step, tile by tile under the MFMAs
+        auto mma = [](f32x4 &c, float x, float y) { c = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, c, 0, 0, 0); };
+        const uint32_t qrow = sm + O_QS + (r * QP + 4 * g) * 4, krow = sm + O_KS + (r * QP + 4 * g) * 4;   // row r, features 4 g ..
+        const uint32_t kcol = sm + O_KS + (4 * g * QP + r) * 4;                    // K~[4 g][r]
+        const uint32_t vcol = sm + O_V + (4 * g * VP + 16 * wave + r) * 4;         // V[4 g][16 wave + r]
+
+        Raw x;
+        load(x, 0);
+        for (int n = 0; n < nsteps; ++n) {
+            prepare(x, valid_of(n));
+            if (n + 1 < nsteps) load(x, n + 1);
+            lds_barrier();   // the operands of step n are ready
+
+            bool again = false;
+#pragma unroll
+            for (int w = 0; w < NW; w += 4) again |= __builtin_amdgcn_readfirstlane(lds_ld<uint32_t>(sm + O_FLAG + w)) != 0;
+            if (__builtin_expect(again, 0)) rescale(sm + O_DEC2);
+            float vf[2][4];   // V[16 kt + 4 g + e][16 wave + r]: operand of the output and of the update
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) vf[kt][e] = lds_ld<float>(vcol + (16 * kt + e) * VP * 4);
+
+            f32x4 oacc[2];   // o[16 qt + 4 g + e][16 wave + r]
+            if constexpr (kFull) {
+                // a score tile (queries 16 qt .., keys 16 kt ..; (0, 0), (1, 0), (1, 1)) or its share of one state
+                if (wave < 3 * PARTS) {
+                    const int tile = wave % 3, part = wave / 3, qt = tile > 0, kt = tile > 1;
+                    constexpr int NB = 2 * D / PARTS / 16;   // blocks of 16 features
+                    const uint32_t qa = qrow + (16 * qt * QP + part * D) * 4, ka = krow + (16 * kt * QP + part * D) * 4;
+                    f32x4 sc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        const f32x4 qv = lds_ld<f32x4>(qa + b * 64), kv = lds_ld<f32x4>(ka + b * 64);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) mma(sc[e & 1], qv[e], kv[e]);
+                    }
+                    const uint32_t out = sm + O_SC + ((part * S + 16 * qt + 4 * g) * SP + 16 * kt + r) * 4;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        lds_st<float>(out + e * SP * 4, 16 * kt + r <= 16 * qt + 4 * g + e ? sc[0][e] + sc[1][e] : 0.f);
+                }
+#pragma unroll
+                for (int qt = 0; qt < 2; ++qt) oacc[qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int dt = 0; dt < DT; ++dt) {
+                        move(i, dt);
+                        const f32x4 qa = lds_ld<f32x4>(qrow + (i * D + 16 * dt) * 4), qb = lds_ld<f32x4>(qrow + (16 * QP + i * D + 16 * dt) * 4);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            mma(oacc[0], qa[e], acc[i][dt][e]);
+                            mma(oacc[1], qb[e], acc[i][dt][e]);
+                        }
+                    }
+            }
+            // T += K~^T V
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            if (!kFull && kt == 0 && e == 0) move(i, dt);
+                            mma(acc[i][dt], lds_ld<float>(kcol + ((16 * kt + e) * QP + i * D + 16 * dt) * 4), vf[kt][e]);
+                        }
+            if (n + 1 == nsteps) rescale(sm + O_END);
+            lds_barrier();   // the scores are there; everybody has read the operands of step n
+
+            if constexpr (kFull) {
+                const uint32_t sa = sm + O_SC + (r * SP + 4 * g) * 4;
+                auto weights = [&](int qt, int kt) {
+                    f32x4 w = lds_ld<f32x4>(sa + (16 * qt * SP + 16 * kt) * 4);
+                    if (PARTS == 2) {
+                        const f32x4 w2 = lds_ld<f32x4>(sa + ((S + 16 * qt) * SP + 16 * kt) * 4);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) w[e] += w2[e];
+                    }
+                    return w;
+                };
+                const f32x4 w00 = weights(0, 0), w10 = weights(1, 0), w11 = weights(1, 1);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    mma(oacc[0], w00[e], vf[0][e]);
+                    mma(oacc[1], w10[e], vf[0][e]);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) mma(oacc[1], w11[e], vf[1][e]);
+                const int valid = valid_of(n);
+                float *orow = static_cast<float *>(a.o) + seg0 + static_cast<size_t>(n) * S * rs + 16 * wave + r;
+                if (a.accumulate) {
+#pragma unroll
+                    for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (static_cast<int>(16 * qt + 4 * g + e) < valid) oacc[qt][e] += orow[(16 * qt + 4 * g + e) * rs];
+                }
+#pragma unroll
+                for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (static_cast<int>(16 * qt + 4 * g + e) < valid) orow[(16 * qt + 4 * g + e) * rs] = oacc[qt][e];
+            }
+        }
+        // ---- the states: of the segment with the last token to the caller, a segment's contribution to slot p + 1 ----
+        if (!kFull || t1 == Tb) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                float *dst = kFull ? (i ? a.S2 : a.S1) + sbh * D * D : a.ws_state + ((slot0 + (p + 1) * slot_step) * 2 + i) * D * D;
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) dst[sbase + (16 * dt + e) * D] = acc[i][dt][e];
+            }
+        }
+        if (!kFull && lane < 32) a.ws_decay[(slot0 + p * slot_step) * 2 * D + st * D + 32 * pw + fcol] = seg_decay;
+    }
+};
+template <int D, class TG, bool kFull>
+__global__ __launch_bounds__(4 * D, 2) void prefill_f32_kernel(PrefillArgs a)
+{
+    using K = F32Kern<D, TG, kFull>;
+    __shared__ __attribute__((aligned(16))) char smem[K::LDS_BYTES];
+    K::run(a, lds_addr_of(smem));
+}
+
+// ---------------------------------------------------------------------------------------------
 // Segment pre-pass of its own design for the common case: 16-bit io and gates, d = 128, two states.
 //
 // The state contribution of a segment of N tokens is U^i = sum_t diag(prod_{s > t} alpha^i_s) k_t^T v_t (Section 4.1,
@@ -2059,7 +2410,9 @@ hipError_t launch_x(const dsla_desc &d, const PrefillPlan &plan, PrefillArgs &a,
             ProfileScope ps(DSLA_KERNEL_PREFILL_SEGMENT_STATE, stream);
             // the pre-pass of its own design where it is built; its per-lane offsets inside a step are 32-bit
             constexpr bool kFast = D == SegFast::D && std::is_same<TIO, bf16_t>::value && std::is_same<TG, bf16_t>::value && !kBeta;
-            if (kFast && static_cast<int64_t>(d.H) * D * 2 * SegFast::S < (int64_t{1} << 31))
+            if constexpr (std::is_same<TIO, float>::value && !kBeta)
+                DSLA_LAUNCH(ps, (prefill_f32_kernel<D, TG, false>), dim3(grid_pre), dim3(4 * D), 0, stream, af);
+            else if (kFast && static_cast<int64_t>(d.H) * D * 2 * SegFast::S < (int64_t{1} << 31))
                 DSLA_LAUNCH(ps, segment_state_fast_kernel, dim3(grid_pre), dim3(SegFast::NT), 0, stream, af);
             else
                 DSLA_LAUNCH(ps, (prefill_kernel<D, TIO, TG, false, kExt, kBeta>), dim3(grid_pre), dim3(4 * D), 0, stream, af);
@@ -2078,7 +2431,10 @@ hipError_t launch_x(const dsla_desc &d, const PrefillPlan &plan, PrefillArgs &a,
     }
     {
         ProfileScope ps(DSLA_KERNEL_PREFILL_CHUNK_LOOP, stream);
-        DSLA_LAUNCH(ps, (prefill_kernel<D, TIO, TG, true, kExt, kBeta>), dim3(grid_full), dim3(4 * D), 0, stream, a);
+        if constexpr (std::is_same<TIO, float>::value && !kBeta)
+            DSLA_LAUNCH(ps, (prefill_f32_kernel<D, TG, true>), dim3(grid_full), dim3(4 * D), 0, stream, a);
+        else
+            DSLA_LAUNCH(ps, (prefill_kernel<D, TIO, TG, true, kExt, kBeta>), dim3(grid_full), dim3(4 * D), 0, stream, a);
     }
     err = hipGetLastError();
     return err;
@@ -2166,11 +2522,11 @@ PrefillCosts prefill_costs(const dsla_desc &d)
 {
     const bool f32 = d.io_dtype == DSLA_F32, small = d.d_k == 64, preact = d.gate_mode == DSLA_GATE_PREACT;
     PrefillCosts c;
-    c.step = f32 ? (small ? 7.0 : 16.0) : (small ? (preact ? 1.8 : 1.4) : (preact ? 2.35 : 2.0));
+    c.step = f32 ? (small ? 4.5 : 11.1) : (small ? (preact ? 1.8 : 1.4) : (preact ? 2.35 : 2.0));
     c.step_full = f32 ? c.step : (small ? 2.5 : (preact ? 3.4 : 2.9));
-    c.pre = f32 ? c.step / 3 : (small ? 1.2 : (preact ? 2.1 : 1.5));
-    c.wg = f32 ? (small ? 7.0 : 16.0) : (small ? 5.0 : 8.0);
-    c.slot = f32 ? (small ? 0.025 : 0.06) : (small ? 0.04 : 0.05);
+    c.pre = f32 ? (small ? 2.2 : 5.1) : (small ? 1.2 : (preact ? 2.1 : 1.5));
+    c.wg = f32 ? (small ? 3.0 : 5.0) : (small ? 5.0 : 8.0);
+    c.slot = f32 ? (small ? 0.028 : 0.06) : (small ? 0.04 : 0.05);
     c.lists = f32 ? (small ? 5.0 : 4.0) : (small ? 9.0 : 6.0);
     return c;
 }
@@ -2193,10 +2549,10 @@ bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t avail
         P_coarse = P < 1 ? 1 : P;
         // ... or fewer where that leaves the chip idle (plans of one or two segments stay as they are in 16 bits: there
         // the pre-pass and the scan cost what the shorter segments gain).  A step of 32 tokens takes 2 us in 16-bit
-        // arithmetic however few workgroups run, in fp32 7 us (d = 64) and 16 us (d = 128), a segment's share of the
-        // pre-pass half of that, pre-pass and scan about 15 us more.  Measured in us at 1000 tokens with 4, 3, 2 chunks per
+        // arithmetic however few workgroups run, in fp32 4.5 us (d = 64) and 11 us (d = 128), a segment's share of the
+        // pre-pass half of that, pre-pass and scan about 6 to 9 us more.  Measured in us at 1000 tokens with 4, 3, 2 chunks per
         // segment: bf16, 32 heads, d = 128 47, 43, 47; 8 heads 43, 38, 36; 4 heads, d = 64 35, 30, 27; fp32, 32 heads, d = 128
-        // 199, 166, 141; fp32, 4 heads, d = 64, 256 tokens whole and with 4, 2, 1 chunks: 60, 60, 49, 33.
+        // 165, 132, 108; fp32, 4 heads, d = 64, 256 tokens whole and with 2, 1 chunks: 39, 36, 24.
         const bool f32 = d.io_dtype == DSLA_F32;
         // 256 heads of 1000, 2000, 8000 tokens, d = 64, whole / in two: 54 / 71, 104 / 156, 382 / 602; 160 heads whole / in three: 52 / 62, 127 / 135, 365 / 394
         if (!f32 && d.d_k == 64 && BH > 128) P = P_coarse = 1;
@@ -2212,12 +2568,13 @@ bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t avail
             // they are as short as two to a unit allow.  d = 64, segments of one / two to a unit: 24 heads of 2500 tokens 41 / 46,
             // 60 of 1000 39 / 42, 8 of 8000 54 / 61; 24 of 4000 59 / 55, 60 of 1500 49 / 47.
             if (chip_slots(d) == 512 && 10 * chunks_of(256 / BH) <= 17 * cps) cps = chunks_of(256 / BH);
-            // fp32, short: the cut saves steps of the chain and costs the pre-pass, its launches and the slots (133 tokens, 96 heads
-            // whole / in two: d = 64 42 / 54, d = 128 93 / 116; 70 tokens, 4 heads, d = 64 27 / 31)
+            // fp32, short: the cut saves steps of the chain and costs the pre-pass, its launches and the slots (us, whole / in
+            // segments of one chunk: 128 tokens, d = 64, 4 heads 20.9 / 22.5, 64 heads 21.6 / 26.4; 180 tokens, 4 heads 29.6 / 23.5;
+            // 128 tokens, d = 128, 8 heads 50.0 / 47.2, 32 heads 51.1 / 52.3, 96 heads 53.4 / 61.1; 180 tokens, 32 heads 73 / 54)
             if (f32 && P < 2) {
                 const PrefillCosts c = prefill_costs(d);
                 const int64_t steps = (T + 31) / 32, chain = cps * C / 32 < steps ? cps * C / 32 : steps;
-                const double launches = d.d_k == 64 ? 6.0 : 8.5;
+                const double launches = d.d_k == 64 ? 6.1 : 9.1;
                 if (static_cast<double>(steps - chain) * c.step <= chain * c.pre + launches + c.slot * BH * ((nchunks + cps - 1) / cps))
                     cps = nchunks;
             }

@@ -381,6 +381,16 @@ def test_prefill_fp32_d128_chunk64():
                      qk_scale=128 ** -0.5)
 
 
+@pytest.mark.parametrize("d,gd", [(64, "f32"), (64, "bf16"), (128, "f32"), (128, "bf16")])
+@pytest.mark.parametrize("T,segments", [(1, 1), (15, 1), (16, 1), (17, 1), (32, 1), (33, 1), (49, 1), (65, 2), (97, 3)])
+def test_prefill_fp32_tile_edges(d, gd, T, segments):
+    """Ends of a sequence inside and on the 16-token score tiles and the 32-token steps, one and several segments (the last of
+    one token, of half a step), a negative blend coefficient of the second state.  TOL["f32"] = 1e-4; the sums of up to 4 d
+    products of 24-bit values are off by some 1e-6."""
+    run_prefill_case(1, T, 3, d, "f32", gd, chunk=32, segments=segments, gamma=1.4, scale=0.9, seed=7 + T, init=True,
+                     qk_scale=d ** -0.5)
+
+
 @pytest.mark.parametrize("io,gd,d", [("f32", "f32", 64), ("bf16", "f32", 128), ("bf16", "bf16", 128), ("f32", "f32", 128)])
 @pytest.mark.parametrize("chunk", [64, 128])
 @pytest.mark.parametrize("gate_mean", [0.0, -2.0])
