@@ -141,6 +141,25 @@ def test_varlen_longest_first_many_long_sequences(B, H, d):
     _run_varlen(lengths, H, d, "bf16", "bf16", 2e-2, slots=[int(x) for x in rng.permutation(B)], seed=95)
 
 
+@pytest.mark.parametrize("d,segments", [(128, 1), (128, 3), (64, 1)])
+def test_gate_preactivations_past_the_exponential(d, segments):
+    """Pre-activations around and far below -88, where 2^-y overflows fp32, as single features of single tokens of every place in
+    a thread's group of four, beside ordinary ones: log alpha down to -25, less than 159 over any 32 tokens."""
+    B, T, H, tau = 1, 200, 2, 16.0
+    x = wl.layer_inputs(78, B, T, H, d, d, io_dtype="bf16", gate_dtype="bf16", gates="preact", qk_scale=d ** -0.5, tau=tau)
+    for i, (t, z) in enumerate([(0, -400.0), (33, -89.0), (66, -87.0), (99, -130.0), (101, -300.0), (199, -95.0)]):
+        x["g1"][:, t, :, i::7] = z
+        x["g2"][:, t, i % H, 3 * i:3 * i + 9] = z
+    lg = {n: orc.log_gates_from_preactivations(x[n], tau) for n in ("g1", "g2")}
+    layer = GpuLayer(B, H, d, "bf16", "bf16", gamma=0.35, chunk=64, segments=segments, gate_mode=1, tau=tau)
+    o = layer.prefill(x)
+    S1, S2 = layer.states()
+    ro, rS1, rS2 = orc.recurrent(x["q"], x["k"], x["v"], lg["g1"], lg["g2"], 0.35)
+    check("o", o, ro, 2e-2)
+    check("S1", S1, rS1, 2e-2)
+    check("S2", S2, rS2, 2e-2)
+
+
 def test_varlen_gate_preactivations():
     import torch
     lengths, H, d, tau = [300, 77, 1, 640], 2, 128, 16.0
