@@ -2584,7 +2584,36 @@ bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t avail
         const bool f32 = d.io_dtype == DSLA_F32;
         // 256 heads of 1000, 2000, 8000 tokens, d = 64, whole / in two: 54 / 71, 104 / 156, 382 / 602; 160 heads whole / in three: 52 / 62, 127 / 135, 365 / 394
         if (!f32 && d.d_k == 64 && BH > 128) P = P_coarse = 1;
-        if (P >= 3 || (f32 && (P < 2 || BH * P > chip_slots(d)))) {
+        // 16 bits, 257 to 704 tokens: neither of the rules above fits (the first makes one or two segments, at two of which half of the
+        // chip idles through a pre-pass of its own length).  Whole, or one to three chunks per segment, by estimates (us) fitted
+        // to 64 .. 704 tokens; a finer cut has to be 7 % ahead.  Two segments / this: d = 128, 4 heads of 520 and 700 tokens 42.5 / 25.6,
+        // 42.4 / 28.7; 32 heads 45.5 / 36.1 and 46.0 / 38.5; 96 heads, now whole, 54.6 / 41.0 and 60.1 / 50.4; d = 64, 32 heads
+        // 37.3 / 26.8 and 36.6 / 28.0; whole / this: d = 128, 4 heads of 400 tokens 30.7 / 24.0.  (A caller's chunk of 128 keeps its
+        // granularity.)  One chunk per segment only with few workgroups: d = 128, 16 heads of 378 tokens 31.0, whole 29.0.
+        // More than 85 heads fill a third of the chip and more by themselves: a cut saves the less per step the more heads there
+        // are, and costs 13 to 20 us whatever their number.  In two / whole (d = 128): 96 heads of 710, 1100, 1500 tokens 61.5 / 52.5,
+        // 86 / 75, 92 / 95; 128 heads of 710, 1500, 3000 71.5 / 53.8, 119 / 99, 194 / 184; d = 64, in four or five / whole: 96 heads of
+        // 710, 1300 41.4 / 37.1, 59 / 62; 128 heads of 710, 1500, 2200 45.2 / 37.6, 77 / 71, 100 / 101.
+        const double heads = static_cast<double>(BH - 96) / 32, steps_d = static_cast<double>(T) / 32;
+        if (!f32 && C <= 64 && T > 704 && BH > 85 && BH <= 128 &&
+            (d.d_k == 64 ? steps_d * (0.48 - 0.29 * heads) < 13.5 : steps_d * (0.43 - 0.33 * heads) < 20.0)) {
+            P = 1;
+        } else if (!f32 && C <= 64 && T > 256 && T <= 704) {
+            const bool small = d.d_k == 64, preact = d.gate_mode == DSLA_GATE_PREACT;
+            const double step = (small ? 1.37 : 1.81) + (preact ? 0.38 : 0.0), pre = (small ? 1.2 : 1.3) + (preact ? 0.3 : 0.0);
+            const double fixed = small ? 6.8 : 7.0, slot = small ? 0.026 : 0.057, wg = small ? 5.6 : 7.5;
+            double best = wg + static_cast<double>((T + 31) / 32) * step;
+            P = 1;
+            for (int64_t tokens = 192; tokens >= 64; tokens -= 64) {
+                const int64_t parts = (T + tokens - 1) / tokens;
+                if (BH * parts > (tokens > 64 ? 256 : (small ? 160 : 64))) break;
+                const double cut = wg + fixed + static_cast<double>(tokens / 32) * (step + pre) + slot * static_cast<double>(BH * parts);
+                if (cut < 0.93 * best) {
+                    best = cut;
+                    P = parts;
+                }
+            }
+        } else if (P >= 3 || (f32 && (P < 2 || BH * P > chip_slots(d)))) {
             const int64_t most = chip_slots(d) / BH;
             const int64_t least = f32 ? 1 : (BH * ((nchunks + 1) / 2) <= 128 ? 2 : 3);   // chunks per segment
             auto chunks_of = [&](int64_t segments_at_most) {

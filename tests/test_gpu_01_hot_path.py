@@ -66,6 +66,13 @@ def test_prefill_pre_pass_on_half_segments(io, d, B, H, T, chunk, init):
     run_prefill_case(B, T, H, d, io, gd, chunk=chunk, segments=0, gamma=0.35, seed=91, init=init, qk_scale=d ** -0.5)
 
 
+@pytest.mark.parametrize("B,H,d,T,chunk", [(1, 4, 128, 257, 64), (1, 8, 128, 704, 64), (1, 32, 128, 520, 64), (2, 48, 128, 641, 64),
+                                           (1, 5, 64, 513, 32), (3, 32, 64, 1000, 64)])
+def test_prefill_short_prompt_plans(B, H, d, T, chunk):
+    """The library's own plans of 257 to 1023 tokens: segments of one and two chunks, a last one of a single token, whole ones."""
+    run_prefill_case(B, T, H, d, "bf16", "bf16", chunk=chunk, segments=0, gamma=0.35, seed=92, init=True, qk_scale=d ** -0.5)
+
+
 @pytest.mark.parametrize("d,T,segments,gamma,f1,f2", [
     (128, 1000, 1, 0.4, (1, 1), (128, 128)),        # one state's frames never move, the other's in every step
     (128, 777, 1, -0.3, (16, 64), (0, 32)),         # the halves of the features at their own times; gates of exactly one

@@ -111,6 +111,32 @@ def test_prefill_multi(N, Hkv, io, gd, d, T, segments, beta):
         check(f"S[{n}]", S[n].cpu().numpy(), rS[n], tol)
 
 
+@pytest.mark.parametrize("beta", [(), (1,)])
+def test_prefill_multi_half_segments(beta):
+    """A plan of two segments of the library's own in 16 bits, whose pre-pass works on the halves of the first one (chunks of 128
+    tokens: 11 of them, 3 state slots)."""
+    import torch
+    N, B, H, Hkv, d, T = 2, 1, 4, 2, 128, 1400
+    q, k, v, ga, gb, w, S0 = _inputs(345, N, B, T, H, Hkv, d, "bf16", "bf16", bool(beta))
+    if beta:
+        gb[0] = 0.0
+    desc = dsla.make_desc(B, H, d, d, io_dtype=code("bf16"), gate_dtype=code("bf16"), scale=0.9, chunk=128)
+    S = [torch.from_numpy(S0[n].copy()).cuda() for n in range(N)]
+    multi = dsla.make_multi([to_gpu(ga[n], "bf16") for n in range(N)], S, w, H_kv=Hkv,
+                            g_beta=[None, to_gpu(gb[1], "bf16")] if beta else None)
+    nbytes = dsla.dsla_prefill_multi_workspace_bytes(desc, multi, T)
+    assert nbytes >= 3 * B * H * 2 * d * d * 4
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    tq, tk, tv = to_gpu(q, "bf16"), to_gpu(k, "bf16"), to_gpu(v, "bf16")
+    o = torch.full((B, T, H, d), float("nan"), device="cuda", dtype=tq.dtype)
+    dsla.dsla_prefill_multi(desc, multi, T, tq, tk, tv, o, ws)
+    torch.cuda.synchronize()
+    ro, rS = orc.nstate(q, k, v, ga, gb if beta else None, w, 0.9, S=S0)
+    check("o", o.float().cpu().numpy(), ro, 2e-2)
+    for n in range(N):
+        check(f"S[{n}]", S[n].cpu().numpy(), rS[n], 2e-2)
+
+
 def test_prefill_multi_beta_gate_with_strong_column_decay():
     """A beta gate as strong as plain-sigmoid gates with pre-activations around -1 (tau = 1): the decay of a column over a
     32-token step spans tens of binary orders of magnitude, which the centred split between the values and the output

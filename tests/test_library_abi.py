@@ -234,6 +234,21 @@ def test_plans_follow_the_work(lib):
     assert packed(22, 8, 128, 9484, 4015) > 0
 
 
+def test_plans_of_short_prompts(lib):
+    """16 bits, 257 to 1023 tokens: as many segments as pay, and buffers that hold the coarse cut as well."""
+    slots = lambda n, H, d: n * H * 2 * d * d * 4
+    up = lambda n: (n + 255) // 256 * 256
+    dense = lambda BH, d, T, chunk=64: lib.dsla_prefill_workspace_bytes(
+        ctypes.byref(dsla.make_desc(1, BH, d, d, io_dtype=1, gate_dtype=1, chunk=chunk)), T)
+    want = lambda P, BH, d: slots(P, BH, d) + up((P - 1) * BH * 2 * d * 4)
+    assert dense(4, 128, 400) == want(7, 4, 128)              # one chunk per segment
+    assert dense(32, 128, 640) == want(5, 32, 128)            # two
+    assert dense(32, 128, 400) == dense(64, 64, 400) == 0     # whole, and the coarse cut is whole too
+    assert dense(96, 128, 640) == want(2, 96, 128)            # whole, and the buffer holds the coarse cut in two (10 chunks),
+    assert dense(128, 128, 1000) == slots(3, 128, 128) + up(2 * 128 * 2 * 128 * 4)   # or in two with the pre-pass on half segments
+    assert dense(4, 128, 1400, 128) == slots(3, 4, 128) + up(2 * 4 * 2 * 128 * 4)   # a chunk of 128 keeps its granularity
+
+
 def test_packed_workspace_of_a_large_batch_serves_smaller_ones(lib):
     """A batch that stays whole because that is faster answers the size query with what cutting it takes: 20 sequences of up
     to 8192 tokens, as the batch shrinks from whole ones to cut ones; none where even one sequence of that length stays
