@@ -24,8 +24,17 @@
 // 2.31 against 2.13 ms), tiles one after the other on a persistent grid with the next tile's stages loaded under
 // the results' stores (2.17 against 2.08 ms: 512 registers do not hold it without spills).
 //
-// project_tile_kernel<2>: the same on 128 x 128 tiles, two workgroups per compute unit, for outputs that do not fill the
+// project_tile_kernel<2, 1>: the same on 128 x 128 tiles, two workgroups per compute unit, for outputs that do not fill the
 // chip with large tiles.
+//
+// project_tile_kernel<1, 2>: 64 x 64 tiles and stages of 64 values of K, for outputs that do not fill it with those either.  A
+// step of the 128 x 128 tiles takes 0.25 us however few there are (256 cycles of MFMAs behind a barrier and the LDS), so K = 4096
+// took 33 us for 129 as for 1500 rows of 1536 columns; here a stage twice as long in K has a quarter of the MFMAs, and four
+// times as many compute units share the work.  M = 300, K = 4096, N = 1536: 33.4 -> 17.8 us; M = 128, K = 2048, N = 5120 21.5 -> 10.7
+// (row kernel before); M = 200, K = 1024, N = 3072 8.2 -> 5.1; M = 512, K = 4096, N = 1536 34.1 -> 18.8.  Tried: stages of 32 values in
+// eight slots (the same within 5 %), of 128 in four (one workgroup per compute unit, 2 to 40 % slower), the 128 x 128 tiles with
+// eight slots or stages of 64 (31 instead of 33 us), K split over the wavefronts with fragments straight from memory to
+// registers (33 us for one 64 x 64 tile of K = 4096: 16 rows per load instruction run at 33 KB per us and compute unit).
 //
 // project_rows_kernel: up to 128 rows of x (the tokens of a decoding batch), where reading the weights is the work.
 //
@@ -121,15 +130,16 @@ __device__ __forceinline__ void store_tile(const f32x16 &acc, const ProjectOuts 
 constexpr int BK = 32;                            // values of K per stage
 constexpr int ROWB = BK * 2;                     // bytes per LDS row: 64
 
-// Q: 32 x 32 tiles along each side of a wavefront's quadrant (4: 256 x 256 per workgroup, 2: 128 x 128)
-template <int Q>
+// Q: 32 x 32 tiles along each side of a wavefront's quadrant (4: 256 x 256 per workgroup, 2: 128 x 128, 1: 64 x 64); KS: blocks
+// of 32 values of K per stage
+template <int Q, int KS>
 __global__ __launch_bounds__(256, Q == 4 ? 1 : 2) void project_tile_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w,
                                                                  const float *__restrict__ bias, ProjectOuts outs, long long M,
                                                                  int K, int N, int width, int tiles_m, int tiles_n, int group)
 {
     constexpr int BM = 64 * Q, BN = BM, QS = 32 * Q;   // workgroup tile, quadrant
-    constexpr int OPB = BM * ROWB;                      // bytes per operand tile and stage
-    constexpr int STAGEB = 2 * OPB;                     // A tile, then B tile
+    constexpr int OPB = BM * ROWB;                      // bytes per operand tile and block of 32 values of K
+    constexpr int STAGEB = 2 * OPB * KS;                // KS times: A tile, then B tile
     // four stages as four objects: the compiler's wait-count insertion then knows that a load into one stage does not
     // touch what is read from another
     __shared__ __attribute__((aligned(1024))) char st0[STAGEB];
@@ -161,15 +171,17 @@ __global__ __launch_bounds__(256, Q == 4 ? 1 : 2) void project_tile_kernel(const
     for (int i = 0; i < Q; ++i)
         voff[i] = (16 * (uwave + 4 * i) + (static_cast<uint32_t>(lane) >> 2)) * static_cast<uint32_t>(K) * 2u +
                   16 * ((lane & 3u) ^ (((static_cast<uint32_t>(lane) >> 5) & 1u) << 1));
-    const int nk = K / BK;
+    const int nk = K / (BK * KS);
     auto fetch = [&](char *st, int ks) {   // K-step ks (past the end: the last one again, never used) into a stage
-        const int kbyte = (ks < nk ? ks : nk - 1) * BK * 2;
+        const int kbyte = (ks < nk ? ks : nk - 1) * (BK * KS * 2);
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            const uint32_t n = uwave + 4 * i;
-            buffer_load_lds16(res_a, st + n * 1024, voff[i], kbyte);
-            buffer_load_lds16(res_b, st + OPB + n * 1024, voff[i], kbyte);
-        }
+        for (int kk = 0; kk < KS; ++kk)
+#pragma unroll
+            for (int i = 0; i < Q; ++i) {
+                const uint32_t n = uwave + 4 * i;
+                buffer_load_lds16(res_a, st + kk * 2 * OPB + n * 1024, voff[i], kbyte + kk * BK * 2);
+                buffer_load_lds16(res_b, st + kk * 2 * OPB + OPB + n * 1024, voff[i], kbyte + kk * BK * 2);
+            }
     };
 
     // fragment reads: row (quadrant + 16 i + r) of a tile, values 8 g .. 8 g + 7 of the stage: piece g
@@ -178,14 +190,16 @@ __global__ __launch_bounds__(256, Q == 4 ? 1 : 2) void project_tile_kernel(const
     const uint32_t fa_row = static_cast<uint32_t>((QS * wm + r) * ROWB) + fo;
     const uint32_t fb_row = static_cast<uint32_t>(OPB + (QS * wn + r) * ROWB) + fo;
     struct Frags {
-        bf16x8 a[NF], b[NF];
+        bf16x8 a[KS][NF], b[KS][NF];
     };
     auto read_frags = [&](Frags &f, const char *st) {
 #pragma unroll
-        for (int i = 0; i < NF; ++i) {
-            f.a[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(st + fa_row + i * 16 * ROWB));
-            f.b[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(st + fb_row + i * 16 * ROWB));
-        }
+        for (int kk = 0; kk < KS; ++kk)
+#pragma unroll
+            for (int i = 0; i < NF; ++i) {
+                f.a[kk][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(st + kk * 2 * OPB + fa_row + i * 16 * ROWB));
+                f.b[kk][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(st + kk * 2 * OPB + fb_row + i * 16 * ROWB));
+            }
     };
 
     f32x4 acc[NF][NF];
@@ -201,30 +215,32 @@ __global__ __launch_bounds__(256, Q == 4 ? 1 : 2) void project_tile_kernel(const
     // which then takes K-step ks + 3.  So a load has two steps to arrive, and the fragments of `nxt` are read under the
     // MFMAs of the current step.
     auto step = [&](const Frags &cur, Frags &nf, const char *nxt, char *old, int ks) {
-        wait_loads<2 * Q>();
+        wait_loads<2 * Q * KS>();
         asm volatile("s_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         fetch(old, ks + 3);
         read_frags(nf, nxt);
 #pragma unroll
-        for (int i = 0; i < NF; ++i)
+        for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
-            for (int j = 0; j < NF; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.b[j], cur.a[i], acc[i][j], 0, 0, 0);
+            for (int i = 0; i < NF; ++i)
 #pragma unroll
-        for (int t = 0; t < 2 * NF; ++t) {
-            __builtin_amdgcn_sched_group_barrier(0x008, NF / 4, 0);                 // MFMAs
+                for (int j = 0; j < NF; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.b[kk][j], cur.a[kk][i], acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int t = 0; t < 2 * NF * KS; ++t) {
+            __builtin_amdgcn_sched_group_barrier(0x008, NF / 2 - NF / 4, 0);        // MFMAs
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                      // 1 LDS read
-            __builtin_amdgcn_sched_group_barrier(0x008, NF / 4, 0);
+            if (NF >= 4) __builtin_amdgcn_sched_group_barrier(0x008, NF / 4, 0);
             if (t % 2 == 0) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);      // 1 load into LDS
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    // nk is a multiple of 4 (K is a multiple of 128): the loop body has no branch, so the accumulators stay where they are
+    // nk is a multiple of 4 (K is a multiple of 128 KS): the loop body has no branch, so the accumulators stay where they are
     fetch(st0, 0);
     fetch(st1, 1);
     fetch(st2, 2);
-    wait_loads<4 * Q>();
+    wait_loads<4 * Q * KS>();
     asm volatile("s_barrier" ::: "memory");   // stage 0 is complete
     Frags f0, f1;
     read_frags(f0, st0);
@@ -567,7 +583,7 @@ void launch_rows_n(ProfileScope &ps, int M, int K, int N, int width, const void 
     else if (nt == 2) launch_rows<MT, 2>(ps, M, K, N, width, x, w, bias, po, stream);
     else launch_rows<MT, 1>(ps, M, K, N, width, x, w, bias, po, stream);
 }
-template <int Q>
+template <int Q, int KS>
 void launch_tiles(ProfileScope &ps, int64_t M, int K, int N, int width, const void *x, const void *w, const float *bias,
                   const ProjectOuts &po, hipStream_t stream)
 {
@@ -575,7 +591,7 @@ void launch_tiles(ProfileScope &ps, int64_t M, int K, int N, int width, const vo
     const int tiles_m = static_cast<int>((M + B - 1) / B), tiles_n = (N + B - 1) / B;
     const long long ntiles = static_cast<long long>(tiles_m) * tiles_n;
     const unsigned grid = static_cast<unsigned>((ntiles + 7) / 8 * 8);
-    DSLA_LAUNCH(ps, project_tile_kernel<Q>, dim3(grid), dim3(256), 0, stream, static_cast<const bf16_t *>(x),
+    DSLA_LAUNCH(ps, (project_tile_kernel<Q, KS>), dim3(grid), dim3(256), 0, stream, static_cast<const bf16_t *>(x),
                 static_cast<const bf16_t *>(w), bias, po, static_cast<long long>(M), K, N, width, tiles_m, tiles_n,
                 group_rows(tiles_m, 5));
 }
@@ -595,7 +611,14 @@ hipError_t launch_project(int64_t M, int K, int n_out, int width, const void *x,
     // Up to 64 rows a second round is the lesser evil, except for the shortest K: N = 28672, K = 160 10.6 / 9.3, K = 480 16 / 18.
     // (Past 32768 columns the others' tiles go twice over the chip as well: N = 35840, K = 4096, 97 rows 87 / 99.)
     const bool second_round = N > 12288 && N <= 32768 && row_workgroups(N) > 256;
-    if (M <= 16 || (M <= 64 && (N <= 20480 || K >= 256)) ||
+    // 64 x 64 tiles while they find compute units of their own, against the 128 x 128 ones also where a few units get two.  Row
+    // kernel or 128 x 128 / 64 x 64 tiles (us): 160 tiles 21.5 / 10.7 and 33.2 / 17.2, 240 10.5 / 6.4, 264 34.0 / 29.2, 320 34.2 / 32.0
+    // and 18.3 / 13.6, 384 11.3 / 10.7, 400 18.5 / 16.2, but 528 11.5 / 14.7 and 640 34.9 / 46.7; up to 128 rows 384 tiles 16.9 / 14.3
+    // and 17.4 / 18.5, and at K = 512 320 tiles 6.1 / 5.6, 360 6.2 / 6.6.  Up to 64 rows the row kernel reads the weights as fast or faster.
+    const int64_t tiles64 = (M + 63) / 64 * (N / 64);
+    if (M > 64 && K % (8 * BK) == 0 && tiles64 <= (M <= 128 ? 256 : (K >= 1024 ? 400 : 320))) {
+        launch_tiles<1, 2>(ps, M, K, N, width, x, w, bias, po, stream);
+    } else if (M <= 16 || (M <= 64 && (N <= 20480 || K >= 256)) ||
         (M > 64 && M <= 128 && (K % (4 * BK) == 0 ? K >= 2048 && !second_round : K >= 1024 || !second_round))) {
         const int m = static_cast<int>(M);
         if (M <= 16) launch_rows_n<1>(ps, m, K, N, width, x, w, bias, po, stream);
@@ -610,8 +633,8 @@ hipError_t launch_project(int64_t M, int K, int n_out, int width, const void *x,
         // M = 2600, N = 12288 45 / 56, M = 384, N = 28672 26 / 21.
         const int64_t rounds128 = ((M + 127) / 128 * (N / 128) + 255) / 256;
         const int64_t rounds256 = ((M + 255) / 256 * ((N + 255) / 256) + 255) / 256;
-        if (10 * rounds128 * K <= (22 * static_cast<int64_t>(K) + 3200) * rounds256) launch_tiles<2>(ps, M, K, N, width, x, w, bias, po, stream);
-        else launch_tiles<4>(ps, M, K, N, width, x, w, bias, po, stream);
+        if (10 * rounds128 * K <= (22 * static_cast<int64_t>(K) + 3200) * rounds256) launch_tiles<2, 1>(ps, M, K, N, width, x, w, bias, po, stream);
+        else launch_tiles<4, 1>(ps, M, K, N, width, x, w, bias, po, stream);
     } else {
         const int tiles_m = static_cast<int>((M + TM - 1) / TM), tiles_n = N / TN;
         const long long ntiles = static_cast<long long>(tiles_m) * tiles_n;

@@ -316,6 +316,14 @@ def test_project_kernels(M, K, n_out, width):
         assert bool(torch.isnan(bufs[j][M].float()).all()), f"output {j}: wrote past its last row"
 
 
+# 64 x 64 tiles (K a multiple of 256): one and several tiles with ragged last rows, one stage group and several, the most tiles that
+# take them and one more row of tiles
+@pytest.mark.parametrize("M,K,n_out,width", [(65, 256, 1, 128), (127, 512, 3, 384), (128, 1280, 2, 256), (129, 256, 5, 512), (513, 768, 3, 128),
+                                             (640, 512, 5, 512), (641, 512, 5, 512)])
+def test_project_small_tiles(M, K, n_out, width):
+    test_project_kernels(M, K, n_out, width)
+
+
 def test_projections_feed_the_prefill():
     """The layer from its input: x -> one GEMM -> q, k, v and the two gate pre-activations in the prefill's own
     layout -> dsla_prefill with gate_mode = DSLA_GATE_PREACT.  The oracle takes the same bf16 weights and input
