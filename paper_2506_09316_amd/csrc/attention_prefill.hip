@@ -23,7 +23,7 @@
 // their MFMAs and exponentials under the MFMAs of the second product 3.92; loads the compiler does not wait for and a
 // raised priority in the second product 3.79 ms = 1160 TFLOP/s (a plain library product of 8192^3: 1400).  Workgroups of eight
 // wavefronts: 3.74 ms, but 54 against 47 us at B = 1, T = 2048 and 27 against 20 us at 24 heads of 1000 tokens.
-// bf16 operands, fp32 accumulation and softmax statistics.
+// bf16 operands, fp32 accumulation and softmax statistics.  Short prompts of few heads have a kernel of their own (below).
 #include "dsla_internal.h"
 
 namespace dsla {
@@ -33,6 +33,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -74,12 +75,12 @@ struct AttnTiles {
 // address 4 keys x 4 pieces of 4 columns and each receives 4 keys of ONE column.  With `a` as computed in the kernel
 // lane l ends up with column (tile) + l % 32 and keys 4 g + 0..3 (from a) and 8 + 4 g + 0..3 (from a + 8 rows): the
 // order in which the result registers of a score tile hold the keys.
-__device__ __forceinline__ bf16x8 load_vt_frag(const char *a, uint32_t eight_rows)
+__device__ __forceinline__ bf16x8 load_vt_frag(const char *a, uint32_t step)
 {
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef s16x4 __attribute__((address_space(3))) *lds_ptr;
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(a));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(a + eight_rows));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(a + step));
     const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
     return __builtin_bit_cast(bf16x8, u32x4{l2[0], l2[1], h2[0], h2[1]});
 }
@@ -343,15 +344,258 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attention_prefill_kernel(const
     }
 }
 
+
+// ---------------------------------------------------------------------------------------------------------------
+// Short prompts and few heads: the chain of key blocks of a workgroup is the call
+// ---------------------------------------------------------------------------------------------------------------
+// With few workgroups nothing overlaps the latencies of a block of keys (LDS, the dependent MFMAs, the test of the reference),
+// and a workgroup's chain of blocks is the call: 1.1 us a block in the kernel above, of which 0.4 are MFMAs.  Here a
+// workgroup has 64 queries, 16 to a wavefront, on 16 x 16 x 32 MFMAs: half of the work behind each of those latencies, twice as many
+// workgroups, and less than one tile of queries wasted on a short prompt.  Where the chains are long and workgroups few (GROUPS = 2),
+// four more wavefronts take every other block of keys, and the two groups' sums meet in LDS at the end, relative to the higher
+// of their references.  Before / one group / two (us, d = 128): 32 heads of 100 tokens 6.3 / 5.1 / 6.6, of 400 10.7 / 8.8 / 9.7, of 1500
+// 31.6 / 28.8 / 39.8; 8 heads of 1000 18.3 / 15.1 / 14.3, of 2000 31.9 / 26.5 / 23.8; d = 64: 32 heads of 362 7.1 / 5.5 / 6.1; 4 heads of
+// 4000 38.6 / 28.4 / 23.3.  Not here: a ring of three or four blocks (15.0 and 15.6 against 12.4 us at 575 tokens: it is not the
+// loads that are waited for), wavefronts of 48 queries in workgroups of eight for long prompts (LDS traffic falls by a third, 8 x 32
+// heads of 8192 tokens 3.71 against 3.73 ms).
+constexpr int kShortQueries = 64;   // queries per workgroup
+template <int D, int GROUPS>
+__global__ __launch_bounds__(256 * GROUPS, 2) void attention_prefill_short_kernel(
+    const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v, bf16_t *__restrict__ o, int BH, int H, int T,
+    int blocks_per_seq, float scale_log2e)
+{
+    using L = AttnTiles<D>;
+    constexpr int NKB = D / 32;       // contraction blocks over the features
+    constexpr int KT = kKeys / 16;    // score tiles along the keys
+    constexpr int CT = D / 16;        // output column tiles
+    __shared__ __attribute__((aligned(1024))) char ring[2 * GROUPS][L::BUF_BYTES];
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int grp = wave >> 2, w4 = wave & 3, r = lane & 15, g = lane >> 4;
+    const int bh = blockIdx.x % BH, qb = blocks_per_seq - 1 - static_cast<int>(blockIdx.x) / BH;   // late queries, which have more keys, first
+    const int b = bh / H, h = bh % H;
+    const int q0 = qb * kShortQueries, my_q = q0 + 16 * w4 + r;
+    const size_t rs = static_cast<size_t>(H) * D;                                   // elements between tokens
+    const size_t base = (static_cast<size_t>(b) * T * H + h) * D;                   // (b, 0, h, 0)
+
+    // ---- staging, as in the kernel above: the four wavefronts of a group fill its blocks.  Keys as there; values with the
+    // 32-byte piece p of row r at position p ^ swz (a pass of the transposing read takes one piece of 8 consecutive rows) ----
+    auto swz_v = [](uint32_t row) { return D == 128 ? (row & 7u) : ((row >> 1) & 3u); };
+    constexpr int RPI = 1024 / L::RB, NI = kKeys / RPI / 4;
+    const uint32_t rs2 = static_cast<uint32_t>(rs) * 2;
+    const int kv_bytes = static_cast<int>(static_cast<uint32_t>(T - 1) * rs2 + D * 2);   // an unsigned 32-bit count to the hardware
+    const u32x4 res_k = buffer_of(k + base, kv_bytes), res_v = buffer_of(v + base, kv_bytes);
+    const uint32_t uw4 = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(w4));
+    const uint32_t row0 = RPI * uw4 + static_cast<uint32_t>(lane) / L::NC, lp = static_cast<uint32_t>(lane) % L::NC;
+    const uint32_t goff_k = row0 * rs2 + 16 * (lp ^ L::swz_k(row0)), goff_v = row0 * rs2 + 16 * (lp ^ (swz_v(row0) << 1));
+    auto stage_block = [&](char *buf, int key0) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const uint32_t n = uw4 + 4 * i, rowoff = (static_cast<uint32_t>(key0) + RPI * 4 * i) * rs2;   // (the swizzles do not see rows 4 RPI apart)
+            load_to_lds16(buf + n * 1024, rowoff + goff_k, res_k);
+            load_to_lds16(buf + L::K_BYTES + n * 1024, rowoff + goff_v, res_v);
+        }
+    };
+    const int wg_last_q = (q0 + kShortQueries < T ? q0 + kShortQueries : T) - 1;
+    const int nblocks = wg_last_q / kKeys + 1, rounds = (nblocks + GROUPS - 1) / GROUPS;
+    if (grp < nblocks) stage_block(ring[grp], grp * kKeys);
+
+    bf16x8 qf[NKB];   // this lane's query: features 32 kb + 8 g .., scaled by scale * log2 e, as bf16
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb) {
+        u32x4 u = {0, 0, 0, 0};
+        if (my_q < T) u = *reinterpret_cast<const u32x4 *>(q + base + static_cast<size_t>(my_q) * rs + 32 * kb + 8 * g);
+        u32x4 s;
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            s[w] = pack2(__uint_as_float(u[w] << 16) * scale_log2e, __uint_as_float(u[w] & 0xffff0000u) * scale_log2e);
+        qf[kb] = __builtin_bit_cast(bf16x8, s);
+    }
+    const uint32_t sk = L::swz_k(r), kf_off = r * L::RB;                       // keys: row 16 t + r, logical piece 4 kb + g
+    const uint32_t vrow = 4 * g + (r >> 2), sv = swz_v(vrow), vt_off = vrow * L::RB + 8 * (r & 3);   // values: rows 4 g + r / 4 of a tile, piece ct
+
+    f32x4 oacc[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) oacc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 mneg = {0.f, 0.f, 0.f, 0.f};   // minus the reference of this lane's query
+    float l_run = 0.f;
+
+    auto compute = [&](const char *kb_, int key0) {
+        const char *vb_ = kb_ + L::K_BYTES;
+        f32x4 sc[KT];   // lane (r, g): keys 16 t + 4 g + e of query r
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+            for (int t = 0; t < KT; ++t) {
+                const bf16x8 kf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kb_ + 16 * t * L::RB + kf_off + 16 * ((4 * kb + g) ^ sk)));
+                sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[kb], kb ? sc[t] : mneg, 0, 0, 0);
+            }
+        constexpr int NV = 2 * CT, VD = 4;   // value fragments of a block, fragments on their way
+        bf16x8 vf[VD];
+        auto read_v = [&](int s) {   // fragment s: keys 32 (s / CT) .., columns 16 (s % CT) ..
+            vf[s % VD] = load_vt_frag(vb_ + vt_off + 32 * (s / CT) * L::RB + 32 * ((s % CT) ^ sv), 16 * L::RB);
+        };
+#pragma unroll
+        for (int s = 0; s < VD; ++s) read_v(s);
+        __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+#pragma unroll
+        for (int i = 0; i < KT * NKB; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            if (i < KT * NKB - 6) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            else if (i < KT * NKB - 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
+        if (key0 + kKeys - 1 > q0 + 16 * w4) {   // reaches past the first query of the wavefront
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sc[t][e] = key0 + 16 * t + 4 * g + e <= my_q ? sc[t][e] : -1.0e30f;
+        }
+        int top = 0;   // (as signed integers: see above)
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int x = __float_as_int(sc[t][e]);
+                top = top > x ? top : x;
+            }
+        if (__builtin_amdgcn_ballot_w64(top > __float_as_int(kMaxSlack) || l_run == 0.f) != 0) {
+            float bmax = sc[0][0];
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) bmax = fmaxf(bmax, sc[t][e]);
+            bmax = fmaxf(bmax, __shfl_xor(bmax, 16));
+            bmax = fmaxf(bmax, __shfl_xor(bmax, 32));
+            float l_all = l_run + __shfl_xor(l_run, 16);
+            l_all += __shfl_xor(l_all, 32);
+            const bool fresh = l_all == 0.f;   // nothing summed yet: any reference will do
+            const float up = fresh ? (bmax > -1.0e30f ? bmax : 0.f) : fmaxf(bmax, 0.f);   // (-1e30: masked; -inf: no weight yet)
+            const float alpha = fresh ? 1.f : __builtin_amdgcn_exp2f(-up);
+            l_run *= alpha;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mneg[e] -= up;
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sc[t][e] -= up;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) oacc[ct][e] *= alpha;
+        }
+        // 32 keys at a time (two score tiles are an input fragment): the exponentials of the second 32 run under the MFMAs of the
+        // first, and the values are read four fragments ahead
+        bf16x8 pf[2];
+        auto exps = [&](int half) {
+            float x[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = __builtin_amdgcn_exp2f(sc[2 * half + (i >> 2)][i & 3]);
+            l_run += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+            pf[half] = __builtin_bit_cast(bf16x8, u32x4{pack2(x[0], x[1]), pack2(x[2], x[3]), pack2(x[4], x[5]), pack2(x[6], x[7])});
+        };
+        exps(0);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            if (half == 0) exps(1);
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                const int s = half * CT + ct;
+                oacc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[s % VD], pf[half], oacc[ct], 0, 0, 0);
+                if (s + VD < NV) read_v(s + VD);
+            }
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if (half * CT + ct + VD < NV) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                if (half == 0) {
+                    __builtin_amdgcn_sched_group_barrier(0x400, 8 / CT, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 12 / CT, 0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __builtin_amdgcn_s_setprio(0);
+    };
+    // round j: block GROUPS j + grp, loaded one round ahead into the other of the group's two buffers
+    auto round = [&](int j, char *cur, char *nxt) {
+        const int jb = GROUPS * j + grp;
+        loads_landed_barrier();   // this round's blocks are there; everybody is done with the last round's
+        if (jb + GROUPS < nblocks) stage_block(nxt, (jb + GROUPS) * kKeys);
+        if (jb < nblocks && jb * kKeys <= q0 + 16 * w4 + 15) compute(cur, jb * kKeys);
+    };
+    char *const even = GROUPS == 1 ? ring[0] : ring[grp], *const odd = GROUPS == 1 ? ring[1] : ring[2 + grp];
+    for (int j = 0; j < rounds; j += 2) {
+        round(j, even, odd);
+        if (j + 1 < rounds) round(j + 1, odd, even);
+    }
+
+    // ---- the second group's record goes through LDS to the first: its reference, denominator and sums per query ----
+    float l_all = l_run + __shfl_xor(l_run, 16);
+    l_all += __shfl_xor(l_all, 32);
+    float f0 = 1.f, f1 = 0.f, l1 = 0.f;
+    // per wavefront of a group: [CT][64] f32x4, then 64 x (reference, denominator)
+    float *rec = reinterpret_cast<float *>(&ring[0][0]) + w4 * (CT * 256 + 128);
+    if constexpr (GROUPS == 2) {
+        __syncthreads();   // the last blocks have been read
+        if (grp == 1) {
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) *reinterpret_cast<f32x4 *>(rec + ct * 256 + 4 * lane) = oacc[ct];
+            rec[CT * 256 + 2 * lane] = mneg[0];
+            rec[CT * 256 + 2 * lane + 1] = l_all;
+        }
+        __syncthreads();
+        if (grp == 1) return;
+        const float m1 = rec[CT * 256 + 2 * lane];
+        l1 = rec[CT * 256 + 2 * lane + 1];
+        // minus the references: the smaller one is the higher level.  A group without any weight (no key yet) does not count.
+        const float low = l1 == 0.f ? mneg[0] : (l_all == 0.f ? m1 : fminf(mneg[0], m1));
+        f0 = l_all == 0.f ? 0.f : __builtin_amdgcn_exp2f(low - mneg[0]);
+        f1 = l1 == 0.f ? 0.f : __builtin_amdgcn_exp2f(low - m1);
+    }
+    if (my_q < T) {
+        const float inv = 1.0f / (GROUPS == 2 ? f0 * l_all + f1 * l1 : l_all);   // the query's own key is never masked
+        bf16_t *op = o + base + static_cast<size_t>(my_q) * rs;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            f32x4 x = oacc[ct];
+            if constexpr (GROUPS == 2) {   // (a group that does not count may hold 0 times infinity)
+                const f32x4 y = *reinterpret_cast<const f32x4 *>(rec + ct * 256 + 4 * lane);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = f1 == 0.f ? f0 * x[e] : (f0 == 0.f ? f1 * y[e] : f0 * x[e] + f1 * y[e]);
+            }
+            *reinterpret_cast<u32x2 *>(op + 16 * ct + 4 * g) = u32x2{pack2(x[0] * inv, x[1] * inv), pack2(x[2] * inv, x[3] * inv)};
+        }
+    }
+}
+
 }  // namespace
 
 hipError_t launch_attn_prefill(int B, int H, int d, int64_t T, float scale, const void *q, const void *k, const void *v,
                                void *o, hipStream_t stream)
 {
-    const int blocks_per_seq = static_cast<int>((T + kQueriesPerWg - 1) / kQueriesPerWg);
-    const unsigned grid = static_cast<unsigned>(B) * H * blocks_per_seq;
     const float sl2 = scale * 1.4426950408889634f;
     ProfileScope ps(DSLA_KERNEL_ATTENTION_PREFILL, stream);
+    const int64_t short_grid = static_cast<int64_t>(B) * H * ((T + kShortQueries - 1) / kShortQueries);
+    // While the workgroups of 64 queries make at most 3 (d = 64: 5) to a compute unit, where two (four) are resident.  Before / now (us):
+    // d = 128, 768 of them 27.1 / 22.8 and 19.4 / 18.1, 864 37.0 / 34.6 but 16.7 / 17.5, 1024 14.1 / 16.7, 1216 36.1 / 40.3; d = 64, 1024 10.0 / 9.3, 1280 39.3 / 36.5, 1504 50.3 / 51.5.
+    if (short_grid <= (d == 128 ? 768 : 1280)) {
+        // Two groups where the chain has 16 blocks and every workgroup a compute unit to itself, or 32 blocks and two units' worth
+        // of workgroups.  One / two groups: 128 workgroups, 16 blocks 15.1 / 14.3, 384, 16 blocks 18.4 / 18.7, 504, 63 blocks 56.3 / 49.6, 752, 47 30.2 / 29.9.
+        const int64_t key_blocks = (T + kKeys - 1) / kKeys;
+        const bool two = (short_grid <= 256 && key_blocks >= 16) || (short_grid <= 512 && key_blocks >= 32);
+        auto launch = [&](auto kernel, int groups) {
+            DSLA_LAUNCH(ps, kernel, dim3(static_cast<unsigned>(short_grid)), dim3(256 * groups), 0, stream, static_cast<const bf16_t *>(q),
+                        static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v), static_cast<bf16_t *>(o), B * H, H, static_cast<int>(T),
+                        static_cast<int>(short_grid / (static_cast<int64_t>(B) * H)), sl2);
+        };
+        if (two) launch(d == 128 ? attention_prefill_short_kernel<128, 2> : attention_prefill_short_kernel<64, 2>, 2);
+        else launch(d == 128 ? attention_prefill_short_kernel<128, 1> : attention_prefill_short_kernel<64, 1>, 1);
+        return hipGetLastError();
+    }
+    const int blocks_per_seq = static_cast<int>((T + kQueriesPerWg - 1) / kQueriesPerWg);
+    const unsigned grid = static_cast<unsigned>(B) * H * blocks_per_seq;
     if (d == 128)
         DSLA_LAUNCH(ps, (attention_prefill_kernel<128>), dim3(grid), dim3(64 * kWaves), 0, stream, static_cast<const bf16_t *>(q),
                            static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v), static_cast<bf16_t *>(o), B * H, H,

@@ -614,9 +614,9 @@ hipError_t launch_project(int64_t M, int K, int n_out, int width, const void *x,
     // 64 x 64 tiles while they find compute units of their own, against the 128 x 128 ones also where a few units get two.  Row
     // kernel or 128 x 128 / 64 x 64 tiles (us): 160 tiles 21.5 / 10.7 and 33.2 / 17.2, 240 10.5 / 6.4, 264 34.0 / 29.2, 320 34.2 / 32.0
     // and 18.3 / 13.6, 384 11.3 / 10.7, 400 18.5 / 16.2, but 528 11.5 / 14.7 and 640 34.9 / 46.7; up to 128 rows 384 tiles 16.9 / 14.3
-    // and 17.4 / 18.5, and at K = 512 320 tiles 6.1 / 5.6, 360 6.2 / 6.6.  Up to 64 rows the row kernel reads the weights as fast or faster.
+    // and 17.4 / 18.5, and at K = 512 288 tiles 6.0 / 6.7, 320 6.1 / 5.6, 360 6.2 / 6.6.  Up to 64 rows the row kernel reads the weights as fast or faster.
     const int64_t tiles64 = (M + 63) / 64 * (N / 64);
-    if (M > 64 && K % (8 * BK) == 0 && tiles64 <= (M <= 128 ? 256 : (K >= 1024 ? 400 : 320))) {
+    if (M > 64 && K % (8 * BK) == 0 && tiles64 <= (M <= 128 ? 256 : (K >= 1024 ? 400 : 256))) {
         launch_tiles<1, 2>(ps, M, K, N, width, x, w, bias, po, stream);
     } else if (M <= 16 || (M <= 64 && (N <= 20480 || K >= 256)) ||
         (M > 64 && M <= 128 && (K % (4 * BK) == 0 ? K >= 2048 && !second_round : K >= 1024 || !second_round))) {

@@ -235,6 +235,47 @@ def test_attention_prefill_scores_near_the_mask(T, d):
     assert max_rel_err(got, ref) <= 2e-2
 
 
+@pytest.mark.parametrize("d,heads,T,levels", [
+    # 64 queries per workgroup, one group of wavefronts: ends of 16-query tiles, of query and key blocks
+    (128, 3, 15, None), (64, 2, 16, None), (128, 2, 17, None), (64, 3, 63, None), (128, 1, 66, None), (64, 1, 127, (-300.0, 90.0)),
+    (128, 2, 577, (300.0, -90.0)),
+    # two groups, each with every other key block: an odd and an even number of blocks, levels far apart between the groups
+    (128, 1, 961, None), (64, 2, 1025, None), (128, 2, 1100, (-300.0, 90.0)), (64, 1, 1100, (90.0, -300.0)), (128, 3, 1000, (-300.0, -310.0)),
+    # many heads: 128 queries per workgroup
+    (128, 1400, 1, None), (64, 1400, 33, None), (128, 700, 65, None), (64, 700, 128, None), (128, 470, 129, (-300.0, 90.0)),
+    (64, 360, 200, (90.0, -300.0))])
+def test_attention_prefill_kernels(d, heads, T, levels):
+    """Every kernel behind dsla_attention_prefill against the definition; the level (log2 units) of the scores alternates between
+    the blocks of 64 keys.  Many heads are copies of two, so that the oracle has two to do.  Tolerance as above."""
+    base = min(heads, 2)
+    x = wl.layer_inputs(720 + T, 1, T, base, d, d, io_dtype="bf16", gate_dtype="f32", qk_scale=1.0)
+    scale = d ** -0.5
+    if levels:
+        x["q"][..., 0] = 16.0
+        level = np.where(np.arange(T) // 64 % 2 == 0, levels[0], levels[1]).astype(np.float32) / np.float32(16.0 * scale * 1.4426950408889634)
+        x["k"][..., 0] = wl.round_to_bf16(np.broadcast_to(level[None, :, None], x["k"][..., 0].shape).copy())
+    ref = ent.attention_prefill(x["q"], x["k"], x["v"], scale)
+    idx = np.arange(heads) % base
+    got = _run_attention_prefill({n: np.ascontiguousarray(x[n][:, :, idx]) for n in ("q", "k", "v")}, scale)
+    assert np.all(np.isfinite(got))
+    assert max_rel_err(got[:, :, :base], ref) <= 2e-2
+    assert np.array_equal(got, got[:, :, idx])
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_attention_prefill_two_groups_near_the_mask(d):
+    """Equal scores of -3e29 and below in prompts whose key blocks two groups of wavefronts share: the mean of the values so far."""
+    T = 1000
+    x = wl.layer_inputs(810, 1, T, 1, d, d, io_dtype="bf16", gate_dtype="f32", qk_scale=1.0)
+    x["q"][:] = 0.0
+    x["q"][..., 0] = 2.0 ** 50
+    x["k"][..., 0] = -2.0 ** 51
+    got = _run_attention_prefill(x, d ** -0.5)
+    ref = ent.attention_prefill(x["q"], x["k"], x["v"], d ** -0.5)
+    assert np.all(np.isfinite(got))
+    assert max_rel_err(got, ref) <= 2e-2
+
+
 def test_attention_prefill_last_row_equals_attention_decode_and_full_size_sample():
     """B = 2, H = 8, T = 4096 at head size 128: sampled heads against the oracle, and the last query of every head
     against the single-query kernel on the same keys and values."""
