@@ -115,6 +115,8 @@ dsla_status dsla_prefill(const dsla_desc *desc, int64_t T, const void *q, const 
     if (plan.ws_total_bytes > 0) {
         if (!workspace || workspace_bytes < plan.ws_total_bytes) return DSLA_ERR_WORKSPACE;
         if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return DSLA_ERR_SHAPE;
+    } else if (plan.ws_ask_bytes > 0 && (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) {
+        return DSLA_ERR_SHAPE;
     }
     return hip_status(launch_prefill(*desc, plan, T, nullptr, nullptr, nullptr, q, k, v, g1, g2, S1, S2, o, workspace,
                                      static_cast<hipStream_t>(stream)));

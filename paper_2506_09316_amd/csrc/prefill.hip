@@ -2648,6 +2648,9 @@ bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t avail
         finish_plan(d, C, P_coarse, nchunks, true, &coarse);
         const size_t ask = coarse.ws_total_bytes > plan->ws_total_bytes ? coarse.ws_total_bytes : plan->ws_total_bytes;
         if (plan->ws_total_bytes > available && coarse.ws_total_bytes <= available) *plan = coarse;
+        // Whole where the coarse cut needs a buffer: the caller brings that buffer all the same (it is what the size query asks for),
+        // so that whether a call is accepted does not change with the estimates.
+        if (P == 1 && coarse.ws_total_bytes > available) *plan = coarse;
         plan->ws_ask_bytes = ask;
     }
     return true;

@@ -246,6 +246,12 @@ def test_plans_of_short_prompts(lib):
     assert dense(32, 128, 400) == dense(64, 64, 400) == 0     # whole, and the coarse cut is whole too
     assert dense(96, 128, 640) == want(2, 96, 128)            # whole, and the buffer holds the coarse cut in two (10 chunks),
     assert dense(128, 128, 1000) == slots(3, 128, 128) + up(2 * 128 * 2 * 128 * 4)   # or in two with the pre-pass on half segments
+    # a call that runs whole needs the buffer it was asked for, as one that is cut does
+    d = dsla.make_desc(1, 96, 128, 128, io_dtype=1, gate_dtype=1, chunk=64)
+    fake = ctypes.c_void_p(4096)
+    call = lambda ws, n: lib.dsla_prefill(ctypes.byref(d), 640, *([fake] * 8), ws, n, None)
+    assert call(None, 0) == call(fake, want(2, 96, 128) - 1) == 4
+    assert call(ctypes.c_void_p(4096 + 64), want(2, 96, 128)) == 2
     assert dense(4, 128, 1400, 128) == slots(3, 4, 128) + up(2 * 4 * 2 * 128 * 4)   # a chunk of 128 keeps its granularity
 
 
