@@ -180,19 +180,21 @@ struct RawRow<float> {
     }
 };
 
-// Same decomposition as entropy_kernel; a part's record is (m, z, acc[D]).
-template <int D, class TIO>
-__global__ __launch_bounds__(kEntThreads) void attn_decode_kernel(const TIO *__restrict__ q_last, const TIO *__restrict__ k,
+// Same decomposition as entropy_kernel, in workgroups of NT threads; a part's record is (m, z, acc[D]).  The lane groups of a
+// wavefront merge by shuffles, the wavefronts through LDS (all groups through LDS: at d = 64, with 32 of them, 0.5 us more, 9.1
+// against 8.5 us for 32 heads of 1200 positions; none at d = 128).
+template <int D, class TIO, int NT>
+__global__ __launch_bounds__(NT) void attn_decode_kernel(const TIO *__restrict__ q_last, const TIO *__restrict__ k,
                                                                   const TIO *__restrict__ v,
                                                                   const int32_t *__restrict__ seq_lens, float scale,
                                                                   int H, long long T, int P, long long rows_per_part,
                                                                   float *__restrict__ parts, TIO *__restrict__ o)
 {
     constexpr int LPR = D / 8;
-    constexpr int GROUPS = kEntThreads / LPR;
+    constexpr int GROUPS = NT / LPR, NW = NT / 64;
     constexpr int UNR = sizeof(TIO) == 2 ? 8 : 4;   // key/value row pairs in flight per lane group
-    __shared__ float s_m[GROUPS], s_z[GROUPS];
-    __shared__ float s_acc[GROUPS][D];
+    __shared__ float s_m[NW], s_z[NW];
+    __shared__ float s_acc[NW][D];
 
     const int bh = blockIdx.x / P, part = blockIdx.x % P;
     const int b = bh / H, h = bh % H;
@@ -254,22 +256,35 @@ __global__ __launch_bounds__(kEntThreads) void attn_decode_kernel(const TIO *__r
             for (int e = 0; e < 8; ++e) acc[e] = fmaf(w, vf[e], acc[e]);
         }
     }
-    if (c == 0) {
-        s_m[grp] = m;
-        s_z[grp] = z;
-    }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) s_acc[grp][8 * c + e] = acc[e];
+    for (int off = LPR; off < 64; off <<= 1) {
+        const float mo = __shfl_xor(m, off), top = fmaxf(m, mo), c0 = expf(m - top), c1 = expf(mo - top);
+        z = c0 * z + c1 * __shfl_xor(z, off);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] = c0 * acc[e] + c1 * __shfl_xor(acc[e], off);
+        m = top;
+    }
+    const int wave = threadIdx.x / 64;
+    if (threadIdx.x % 64 < LPR) {
+        if (c == 0) {
+            s_m[wave] = m;
+            s_z[wave] = z;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s_acc[wave][8 * c + e] = acc[e];
+    }
     __syncthreads();
-    if (threadIdx.x < D) {   // thread f merges feature f over the lane groups
+    if (threadIdx.x < D) {   // thread f merges feature f over the wavefronts
         const int f = threadIdx.x;
         float M = s_m[0];
-        for (int g = 1; g < GROUPS; ++g) M = fmaxf(M, s_m[g]);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) M = fmaxf(M, s_m[w]);
         float Z = 0.f, A = 0.f;
-        for (int g = 0; g < GROUPS; ++g) {
-            const float c0 = expf(s_m[g] - M);
-            Z = fmaf(c0, s_z[g], Z);
-            A = fmaf(c0, s_acc[g][f], A);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float c0 = expf(s_m[w] - M);
+            Z = fmaf(c0, s_z[w], Z);
+            A = fmaf(c0, s_acc[w][f], A);
         }
         if (P == 1) {
             o[static_cast<size_t>(bh) * D + f] = from_f32<TIO>(A / Z);
@@ -328,13 +343,21 @@ hipError_t launch_attn_decode_t(int B, int H, int64_t T, const EntropyPlan &plan
 {
     const int BH = B * H;
     ProfileScope ps(DSLA_KERNEL_ATTENTION_DECODE, stream);
-    if (plan.parts == 1) ps.e1_first = ps.e1;   // no merge kernel follows: the first launch closes the record too
-    DSLA_LAUNCH_FIRST(ps, (attn_decode_kernel<D, TIO>), dim3(static_cast<unsigned>(BH) * plan.parts), dim3(kEntThreads), 0,
+    // Two parts cost a second launch: one workgroup of 1024 threads takes both where they are short or the pairs fill the chip
+    // without them.  In two / in one (us), 16 bits: d = 128, 256 pairs of 280, 800, 1200, 2000 positions 12.0 / 9.9, 20.4 / 18.3, 26.8 / 26.2,
+    // 38.8 / 39.5, 32 pairs of 280, 500 8.8 / 7.8, 9.6 / 9.5; d = 64, 256 pairs of 500, 2000, 3500 11.3 / 9.6, 26.2 / 23.0, 41.6 / 39.0, 96 pairs of
+    // 500 8.7 / 9.2; fp32, 256 pairs of 500 26.2 / 26.6.
+    const bool one = sizeof(TIO) == 2 && plan.parts == 2 &&
+                     (D == 128 ? (BH >= 256 && T <= 1200) || (BH >= 32 && T <= 400) : BH >= 256 && T <= 3600);
+    const int parts = one ? 1 : plan.parts;
+    auto kernel = one ? attn_decode_kernel<D, TIO, 1024> : attn_decode_kernel<D, TIO, kEntThreads>;
+    if (parts == 1) ps.e1_first = ps.e1;   // no merge kernel follows: the first launch closes the record too
+    DSLA_LAUNCH_FIRST(ps, kernel, dim3(static_cast<unsigned>(BH) * parts), dim3(one ? 1024 : kEntThreads), 0,
                        stream, static_cast<const TIO *>(q_last), static_cast<const TIO *>(k), static_cast<const TIO *>(v),
-                       seq_lens, scale, H, static_cast<long long>(T), plan.parts, static_cast<long long>(plan.rows_per_part),
+                       seq_lens, scale, H, static_cast<long long>(T), parts, static_cast<long long>(one ? T : plan.rows_per_part),
                        static_cast<float *>(workspace), static_cast<TIO *>(o));
     hipError_t err = hipGetLastError();
-    if (err != hipSuccess || plan.parts == 1) return err;
+    if (err != hipSuccess || parts == 1) return err;
     DSLA_LAUNCH_LAST(ps, (attn_decode_merge_kernel<D, TIO>), dim3(BH), dim3(D), 0, stream,
                        static_cast<const float *>(workspace), plan.parts, static_cast<TIO *>(o));
     return hipGetLastError();

@@ -144,6 +144,33 @@ def test_attention_decode_infinite_values(io, B, T, H, d):
         assert max_rel_err(got[b, h][rest], ref) < (1e-4 if io == "f32" else 2e-2), (b, h)
 
 
+@pytest.mark.parametrize("io,B,T,H,d", [("bf16", 8, 257, 32, 128), ("bf16", 1, 400, 32, 128), ("bf16", 8, 1200, 32, 128), ("bf16", 8, 1201, 32, 128),
+                                        ("bf16", 8, 600, 32, 64), ("f32", 8, 300, 32, 64), ("bf16", 1, 513, 3, 64), ("bf16", 1, 50, 3, 64)])
+def test_attention_decode_workgroup_sizes(io, B, T, H, d):
+    """Both workgroup sizes, one part and several, last rows of a lane group missing, requests of 1 position and of all of them;
+    every 37th head against the oracle (tolerance as above), and a context of one position is that position's value."""
+    import torch
+    q, k = inputs(51 + T, B, T, H, d, io, spread=2.0)
+    v = wl.layer_inputs(53, B, T, H, d, d, io_dtype=io, gate_dtype="f32")["v"]
+    lens = np.array([T if b % 2 == 0 else 1 + (b * T) // (2 * B) for b in range(B)], dtype=np.int32)
+    if B > 1:
+        lens[1] = 1
+    qg, kg, vg = to_gpu(q, io), to_gpu(k, io), to_gpu(v, io)
+    o = torch.full_like(qg, float("nan"))
+    n = dsla.dsla_attention_decode_workspace_bytes(B, H, d, T)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda") if n else None
+    dsla.dsla_attention_decode(qg, kg, vg, o, d ** -0.5, ws, seq_lens=torch.from_numpy(lens).cuda())
+    torch.cuda.synchronize()
+    got = o.float().cpu().numpy()
+    assert np.all(np.isfinite(got))
+    for i in range(0, B * H, 37):
+        b, h = divmod(i, H)
+        ref = ent.attention_decode(q[b:b + 1, h:h + 1], k[b:b + 1, :lens[b], h:h + 1], v[b:b + 1, :lens[b], h:h + 1], d ** -0.5)[0, 0]
+        assert max_rel_err(got[b, h], ref) < (1e-4 if io == "f32" else 2e-2), (b, h)
+    if B > 1:
+        np.testing.assert_allclose(got[1], v[1, 0], rtol=2 ** -7, atol=1e-6)
+
+
 def test_attention_decode_mixed_context_lengths():
     """Requests of one batch at different context lengths in a cache of T positions each: only the filled positions
     count (the rest of the cache holds NaN here), also where a whole key range of the split lies past the end."""
