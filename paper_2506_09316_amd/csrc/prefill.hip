@@ -1566,7 +1566,7 @@ struct Kern {
                 }
                 // One or two steps are left and nothing is prepared past the last (a copy of its own, so that the loop above has
                 // no branch around its loads): a segment of one step used to wait for two steps that do not exist.  70 tokens,
-                // 32 heads, d = 128: 17.4 -> 14.9 us; 85 tokens, 16 heads, d = 64: 14.3 -> 10.9; fp32, 32 tokens, 32 heads, d = 128: 27.4 -> 20.4.
+                // 32 heads, d = 128: 17.4 -> 14.9 us; 85 tokens, 16 heads, d = 64: 14.3 -> 10.9.
                 if (n + 1 < nsteps) {
                     const LineSrc io = src_of(n + 2), gs = src_of(n + 4);
                     line_produce(pa, 1, r1, s1, valid_of(n + 1), g0, s0, valid_of(n + 2), lgs, sgns, pos, a.status,
