@@ -1683,7 +1683,7 @@ __global__ __launch_bounds__(4 * D, (D == 64 && sizeof(TIO) == 4 && kFull) ? 1 :
 // The kernels of 32-bit inputs (chunk loop, and with kFull = false the segment pre-pass): fp32 arithmetic throughout, bound by
 // the fp32 matrix pipe (32 multiply-adds per clock and SIMD, a sixteenth of the bf16 rate).  The step algebra is the one above;
 // what differs from the template is who does what, so that no matrix pipe idles and nothing is multiplied twice:
-//  * No roles.  D / 16 wavefronts, each of which prepares operands and owns 16 columns of both states, so all four SIMDs
+//  * D / 16 wavefronts, each of which prepares operands and owns 16 columns of both states (no roles), so all four SIMDs
 //    multiply (with D / 32 consumers, half of them at d = 64), and D / 16 x 2 tiles of 16 x 16 leave the registers to
 //    prefetch a whole step.
 //  * The scores of a step are computed once: the three 16 x 16 tiles at and below the diagonal, divided over the wavefronts, meet
@@ -1691,32 +1691,40 @@ __global__ __launch_bounds__(4 * D, (D == 64 && sizeof(TIO) == 4 && kFull) ? 1 :
 //  * K~ and V exist once in LDS, as rows.  v_mfma_f32_16x16x4 takes one value per lane, so the token-contiguous operands of the
 //    update are plain 4-byte reads (row pitches of 4 beyond a multiple of 64 floats: no conflicts); with the features of an MFMA
 //    at 4 g + e the accumulators are fed back as operands and the row operands are 16-byte reads.
-// Two barriers per step: operands ready; scores ready and operands read.  In between the matrix pipes are busy from the scores
-// through the read-out to the update; the preparation (about a sixth of a step) is not overlapped inside a workgroup, at d = 64
-// two workgroups share a compute unit and do it for each other.
+// Without roles, two barriers per step: operands ready; scores ready and operands read.  In between the matrix pipes are busy from
+// the scores through the read-out to the update; the preparation (about a sixth of a step) is not overlapped inside a workgroup,
+// at d = 64 two workgroups share a compute unit and do it for each other.
 // The frame moves in every step (a frame that stays would put larger exponents, and with them larger rounding errors, into fp32
 // factors): 64 multiplications, taken tile by tile in front of a tile's MFMAs, are 2 % of a step's matrix work.
 // A step takes 11.5 us at d = 128 and 4.6 us at d = 64 where the template took 16.3 and 7.0 (8.1 and 2.3 of them are MFMAs at
 // 2.3 GHz; the preparation is 1.0 and 1.3).  7 prompts of 1089 tokens, 32 heads, d = 128: 708 -> 450 us; 8 of 600, 32 heads, d = 64:
-// 141 -> 100; one of 256, 4 heads, d = 64 (four segments): 33 -> 24.  Left out: the next step prepared in registers by one
-// wavefront of a SIMD while the other multiplies (97 spilled registers at d = 128: 470 instead of 362 us for 1024 tokens; at
-// d = 64, without spills, 156 instead of 147).
+// 141 -> 100; one of 256, 4 heads, d = 64 (four segments): 33 -> 24.
+// With roles (kRoles; d = 64, where a workgroup has its compute unit to itself: launch_f32) as many wavefronts again prepare the
+// operands of step n + 1 under the MFMAs of step n, into the other of two operand sets; the scores of a step get their values after
+// its one barrier, together with the read-out of the next.  A step takes 3.6 us instead of 4.6, the results are the same bits: 256
+// tokens, 4 heads, whole 40.2 -> 34.0 us and in four segments 24.8 -> 24.0; 8 prompts of 600 tokens, 32 heads 109 -> 91; 50 random
+// packed batches at d = 64 and 128 0.96.  At d = 128 the registers hold no second set of wavefronts and LDS no second set of operands.
+// Left out: the next step prepared in registers by one wavefront of a SIMD while the other multiplies (97 spilled registers at
+// d = 128: 470 instead of 362 us for 1024 tokens; at d = 64, without spills, 156 instead of 147).
 // ---------------------------------------------------------------------------------------------
-template <int D, class TG, bool kFull>
+template <int D, class TG, bool kFull, bool kRoles>
 struct F32Kern {
     using Base = Kern<D, float, TG, kFull, true, false>;   // constants of the step algebra, the order of packed sequences
     static constexpr int S = 32;                // tokens per step
-    static constexpr int NW = D / 16, NT = 64 * NW;
+    static constexpr int NW = D / 16;           // wavefronts that multiply, and that prepare: the same ones, or as many more
+    static constexpr int NT = 64 * NW * (kRoles ? 2 : 1);
     static constexpr int FG = D / 32;           // wavefronts per state when preparing: wavefront w prepares state w / FG, features 32 (w % FG) ..
     static constexpr int DT = D / 16;           // 16-row tiles of a state
     static constexpr int PARTS = NW >= 6 ? 2 : 1;   // summands of a score tile: one per state, or both in one
     static constexpr int QP = 2 * D + 4, VP = D + 4, SP = S + 4;   // row pitches (floats)
-    static constexpr uint32_t O_QS = 0, O_KS = O_QS + (kFull ? S * QP * 4 : 0), O_V = O_KS + S * QP * 4, O_SC = O_V + S * VP * 4;
-    static constexpr uint32_t O_CS = O_SC + (kFull ? PARTS * S * SP * 4 : 0);   // per wavefront: float [16][32] scan scratch
-    static constexpr uint32_t O_DEC = O_CS + NW * 2048, O_DEC2 = O_DEC + 2 * D * 4;   // float [2D] each: frame change into the step; its second factor
-    static constexpr uint32_t O_END = O_DEC2 + 2 * D * 4;                       // float [2D]: from the middle of the step to its end
-    static constexpr uint32_t O_FLAG = O_END + 2 * D * 4;                       // uint8 [NW]: the second factors of this wavefront's features count
-    static constexpr uint32_t LDS_BYTES = O_FLAG + 16;
+    // An operand set (two with roles): Q~, K~, V; float [2D] the frame change into the step; its second factor; from the middle of the
+    // step to its end; uint8 [NW] whether the second factors of a wavefront's features count.
+    static constexpr uint32_t O_QS = 0, O_KS = O_QS + (kFull ? S * QP * 4 : 0), O_V = O_KS + S * QP * 4, O_DEC = O_V + S * VP * 4;
+    static constexpr uint32_t O_DEC2 = O_DEC + 2 * D * 4, O_END = O_DEC2 + 2 * D * 4, O_FLAG = O_END + 2 * D * 4;
+    static constexpr uint32_t SET_BYTES = O_FLAG + 16, SC_BYTES = kFull ? PARTS * S * SP * 4 : 0;
+    static constexpr uint32_t O_SC = SET_BYTES * (kRoles ? 2 : 1);                  // scores of a step
+    static constexpr uint32_t O_CS = O_SC + SC_BYTES * (kRoles ? 2 : 1);            // per wavefront: float [16][32] scan scratch
+    static constexpr uint32_t LDS_BYTES = O_CS + NW * 2048;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
 
     struct Raw {   // inputs of one step as loaded: 2 tokens x 8 features of q, k and one state's gates, 1 token x 8 columns of v
@@ -1726,7 +1734,9 @@ struct F32Kern {
 
     static __device__ __forceinline__ void run(const PrefillArgs &a, uint32_t sm)
     {
-        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+        const int lane = threadIdx.x & 63, wave_id = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+        const int wave = wave_id % NW;   // among those of its role
+        const bool prepares = wave_id >= NW;
 
         // ---- the work item: as Kern::run ----
         int bidx, h, p;
@@ -1801,7 +1811,7 @@ struct F32Kern {
             x.v.load(v0 + sokv, row(16 * st + sg) * rskv + f0);
         };
         float tot = 0.f, seg_decay = 0.f;   // of this lane's scan column: gate sum of the step prepared last, log2 decay of the segment
-        auto prepare = [&](Raw &x, int valid) {
+        auto prepare = [&](Raw &x, int valid, uint32_t set) {   // set: of the operands (bytes)
             float c[2][8];   // gate sums over this thread's tokens
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
@@ -1818,7 +1828,7 @@ struct F32Kern {
             for (int e = 0; e < 8; ++e) c[1][e] += c[0][e];
             lds_st<f32x4>(cs_own, f32x4{c[1][0], c[1][1], c[1][2], c[1][3]});
             lds_st<f32x4>(cs_own + 16, f32x4{c[1][4], c[1][5], c[1][6], c[1][7]});
-            const uint32_t va = sm + O_V + ((16 * st + sg) * VP + f0) * 4;
+            const uint32_t va = sm + set + O_V + ((16 * st + sg) * VP + f0) * 4;
             lds_st<f32x4>(va, x.v.a);
             lds_st<f32x4>(va + 16, x.v.b);
             Base::wave_sync();
@@ -1838,10 +1848,10 @@ struct F32Kern {
                 const float change = 0.5f * unit * (tot + sum);
                 const bool twice = __builtin_amdgcn_ballot_w64(change < -Base::kOneFactor) != 0;
                 const float factor = __builtin_amdgcn_exp2f(twice ? 0.5f * change : change);
-                lds_st<float>(sm + O_DEC + decl, factor);   // (both lanes of a feature write the same)
-                lds_st<float>(sm + O_DEC2 + decl, twice ? factor : 1.f);
-                lds_st<float>(sm + O_END + decl, __builtin_amdgcn_exp2f(0.5f * unit * sum));
-                if (lane == 0) lds_st<uint8_t>(sm + O_FLAG + wave, twice);
+                lds_st<float>(sm + set + O_DEC + decl, factor);   // (both lanes of a feature write the same)
+                lds_st<float>(sm + set + O_DEC2 + decl, twice ? factor : 1.f);
+                lds_st<float>(sm + set + O_END + decl, __builtin_amdgcn_exp2f(0.5f * unit * sum));
+                if (lane == 0) lds_st<uint8_t>(sm + set + O_FLAG + wave, twice);
                 tot = sum;
                 const float r = sum * unit;
                 seg_decay += r;
@@ -1860,7 +1870,7 @@ struct F32Kern {
                     kf[e] *= __builtin_amdgcn_exp2f(-unit * y);
                     if (kFull) qf[e] = __uint_as_float(__float_as_uint(qf[e]) ^ sgn) * __builtin_amdgcn_exp2f(fmaf(y, unit, lg));
                 }
-                const uint32_t at = ((2 * sg + j) * QP + st * D + f0) * 4;
+                const uint32_t at = set + ((2 * sg + j) * QP + st * D + f0) * 4;
                 lds_st<f32x4>(sm + O_KS + at, f32x4{kf[0], kf[1], kf[2], kf[3]});
                 lds_st<f32x4>(sm + O_KS + at + 16, f32x4{kf[4], kf[5], kf[6], kf[7]});
                 if (kFull) {
@@ -1869,6 +1879,23 @@ struct F32Kern {
                 }
             }
         };
+
+        if (kRoles && prepares) {
+            Raw x;
+            load(x, 0);
+            prepare(x, valid_of(0), 0);
+            if (nsteps > 1) load(x, 1);
+            lds_barrier();   // the operands of step 0 are ready
+            for (int n = 0; n < nsteps; ++n) {
+                if (n + 1 < nsteps) {
+                    prepare(x, valid_of(n + 1), ((n + 1) & 1) * SET_BYTES);
+                    if (n + 2 < nsteps) load(x, n + 2);
+                }
+                lds_barrier();   // those of step n + 1 are, and step n has been read
+            }
+            if (!kFull && lane < 32) a.ws_decay[(slot0 + p * slot_step) * 2 * D + st * D + 32 * pw + fcol] = seg_decay;
+            return;
+        }
 
         // ---- multiplying: lane (r, g); acc[i][dt][e] = T^i[16 dt + 4 g + e][16 wave + r] ----
         const uint32_t r = lane & 15, g = static_cast<uint32_t>(lane) >> 4;
@@ -1900,30 +1927,26 @@ struct F32Kern {
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) scale(factors, i, dt);
         };
-        auto move = [&](int i, int dt) { scale(sm + O_DEC, i, dt); };   // into the middle frame of the step, tile by tile under the MFMAs
         auto mma = [](f32x4 &c, float x, float y) { c = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, c, 0, 0, 0); };
-        const uint32_t qrow = sm + O_QS + (r * QP + 4 * g) * 4, krow = sm + O_KS + (r * QP + 4 * g) * 4;   // row r, features 4 g ..
-        const uint32_t kcol = sm + O_KS + (4 * g * QP + r) * 4;                    // K~[4 g][r]
-        const uint32_t vcol = sm + O_V + (4 * g * VP + 16 * wave + r) * 4;         // V[4 g][16 wave + r]
 
-        Raw x;
-        load(x, 0);
-        for (int n = 0; n < nsteps; ++n) {
-            prepare(x, valid_of(n));
-            if (n + 1 < nsteps) load(x, n + 1);
-            lds_barrier();   // the operands of step n are ready
-
+        float vf[2][4];   // V[16 kt + 4 g + e][16 wave + r]: operand of the output and of the update
+        f32x4 oacc[2];    // o[16 qt + 4 g + e][16 wave + r]
+        // scores, read-out and update of step n from its operand set; the scores go to LDS at sm + O_SC + sc_at
+        auto product = [&](int n, uint32_t set, uint32_t sc_at) {
+            const uint32_t sb = sm + set;
+            const uint32_t qrow = sb + O_QS + (r * QP + 4 * g) * 4, krow = sb + O_KS + (r * QP + 4 * g) * 4;   // row r, features 4 g ..
+            const uint32_t kcol = sb + O_KS + (4 * g * QP + r) * 4;                    // K~[4 g][r]
+            const uint32_t vcol = sb + O_V + (4 * g * VP + 16 * wave + r) * 4;         // V[4 g][16 wave + r]
+            auto move = [&](int i, int dt) { scale(sb + O_DEC, i, dt); };   // into the middle frame of the step, tile by tile under the MFMAs
             bool again = false;
 #pragma unroll
-            for (int w = 0; w < NW; w += 4) again |= __builtin_amdgcn_readfirstlane(lds_ld<uint32_t>(sm + O_FLAG + w)) != 0;
-            if (__builtin_expect(again, 0)) rescale(sm + O_DEC2);
-            float vf[2][4];   // V[16 kt + 4 g + e][16 wave + r]: operand of the output and of the update
+            for (int w = 0; w < NW; w += 4) again |= __builtin_amdgcn_readfirstlane(lds_ld<uint32_t>(sb + O_FLAG + w)) != 0;
+            if (__builtin_expect(again, 0)) rescale(sb + O_DEC2);
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) vf[kt][e] = lds_ld<float>(vcol + (16 * kt + e) * VP * 4);
 
-            f32x4 oacc[2];   // o[16 qt + 4 g + e][16 wave + r]
             if constexpr (kFull) {
                 // a score tile (queries 16 qt .., keys 16 kt ..; (0, 0), (1, 0), (1, 1)) or its share of one state
                 if (wave < 3 * PARTS) {
@@ -1937,7 +1960,7 @@ struct F32Kern {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) mma(sc[e & 1], qv[e], kv[e]);
                     }
-                    const uint32_t out = sm + O_SC + ((part * S + 16 * qt + 4 * g) * SP + 16 * kt + r) * 4;
+                    const uint32_t out = sm + O_SC + sc_at + ((part * S + 16 * qt + 4 * g) * SP + 16 * kt + r) * 4;
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         lds_st<float>(out + e * SP * 4, 16 * kt + r <= 16 * qt + 4 * g + e ? sc[0][e] + sc[1][e] : 0.f);
@@ -1969,11 +1992,12 @@ struct F32Kern {
                             if (!kFull && kt == 0 && e == 0) move(i, dt);
                             mma(acc[i][dt], lds_ld<float>(kcol + ((16 * kt + e) * QP + i * D + 16 * dt) * 4), vf[kt][e]);
                         }
-            if (n + 1 == nsteps) rescale(sm + O_END);
-            lds_barrier();   // the scores are there; everybody has read the operands of step n
-
+            if (n + 1 == nsteps) rescale(sb + O_END);
+        };
+        // the scores' share of the output of step n, and its rows
+        auto output = [&](int n, uint32_t sc_at) {
             if constexpr (kFull) {
-                const uint32_t sa = sm + O_SC + (r * SP + 4 * g) * 4;
+                const uint32_t sa = sm + O_SC + sc_at + (r * SP + 4 * g) * 4;
                 auto weights = [&](int qt, int kt) {
                     f32x4 w = lds_ld<f32x4>(sa + (16 * qt * SP + 16 * kt) * 4);
                     if (PARTS == 2) {
@@ -2006,6 +2030,26 @@ struct F32Kern {
                     for (int e = 0; e < 4; ++e)
                         if (static_cast<int>(16 * qt + 4 * g + e) < valid) orow[(16 * qt + 4 * g + e) * rs] = oacc[qt][e];
             }
+        };
+        if constexpr (kRoles) {
+            lds_barrier();   // the operands of step 0 are ready
+            for (int n = 0; n < nsteps; ++n) {
+                if (n > 0) output(n - 1, ((n - 1) & 1) * SC_BYTES);
+                product(n, (n & 1) * SET_BYTES, (n & 1) * SC_BYTES);
+                lds_barrier();   // the scores of step n and the operands of step n + 1 are there
+            }
+            output(nsteps - 1, ((nsteps - 1) & 1) * SC_BYTES);
+        } else {
+            Raw x;
+            load(x, 0);
+            for (int n = 0; n < nsteps; ++n) {
+                prepare(x, valid_of(n), 0);
+                if (n + 1 < nsteps) load(x, n + 1);
+                lds_barrier();   // the operands of step n are ready
+                product(n, 0, 0);
+                lds_barrier();   // the scores are there; everybody has read the operands of step n
+                output(n, 0);
+            }
         }
         // ---- the states: of the segment with the last token to the caller, a segment's contribution to slot p + 1 ----
         if (!kFull || t1 == Tb) {
@@ -2018,13 +2062,13 @@ struct F32Kern {
                     for (int e = 0; e < 4; ++e) dst[sbase + (16 * dt + e) * D] = acc[i][dt][e];
             }
         }
-        if (!kFull && lane < 32) a.ws_decay[(slot0 + p * slot_step) * 2 * D + st * D + 32 * pw + fcol] = seg_decay;
+        if (!kFull && !kRoles && lane < 32) a.ws_decay[(slot0 + p * slot_step) * 2 * D + st * D + 32 * pw + fcol] = seg_decay;
     }
 };
-template <int D, class TG, bool kFull>
-__global__ __launch_bounds__(4 * D, 2) void prefill_f32_kernel(PrefillArgs a)
+template <int D, class TG, bool kFull, bool kRoles>
+__global__ __launch_bounds__((F32Kern<D, TG, kFull, kRoles>::NT), 2) void prefill_f32_kernel(PrefillArgs a)
 {
-    using K = F32Kern<D, TG, kFull>;
+    using K = F32Kern<D, TG, kFull, kRoles>;
     __shared__ __attribute__((aligned(16))) char smem[K::LDS_BYTES];
     K::run(a, lds_addr_of(smem));
 }
@@ -2406,6 +2450,22 @@ __global__ __launch_bounds__(256) void segment_scan_kernel(const float *__restri
 }
 
 
+// F32Kern with or without roles.  With them (d = 64) a compute unit holds one workgroup, so they are taken where every workgroup has
+// a unit to itself.  Without / with, us, 600 tokens in one segment: 256 heads 109 / 91; past one
+// to a unit 288 heads 157 / 164, 512 heads 165 / 173, 2048 heads of 512 tokens 535 / 573.
+template <int D, class TG, bool kFull>
+hipError_t launch_f32(unsigned grid, const PrefillArgs &a, ProfileScope &ps, hipStream_t stream)
+{
+    if constexpr (D == 64) {
+        if (grid <= 256) {
+            DSLA_LAUNCH(ps, (prefill_f32_kernel<D, TG, kFull, true>), dim3(grid), dim3(F32Kern<D, TG, kFull, true>::NT), 0, stream, a);
+            return hipGetLastError();
+        }
+    }
+    DSLA_LAUNCH(ps, (prefill_f32_kernel<D, TG, kFull, false>), dim3(grid), dim3(F32Kern<D, TG, kFull, false>::NT), 0, stream, a);
+    return hipGetLastError();
+}
+
 template <int D, class TIO, class TG, bool kExt, bool kBeta = false>
 hipError_t launch_x(const dsla_desc &d, const PrefillPlan &plan, PrefillArgs &a, hipStream_t stream)
 {
@@ -2439,7 +2499,7 @@ hipError_t launch_x(const dsla_desc &d, const PrefillPlan &plan, PrefillArgs &a,
             // the pre-pass of its own design where it is built; its per-lane offsets inside a step are 32-bit
             constexpr bool kFast = D == SegFast::D && std::is_same<TIO, bf16_t>::value && std::is_same<TG, bf16_t>::value && !kBeta;
             if constexpr (std::is_same<TIO, float>::value && !kBeta)
-                DSLA_LAUNCH(ps, (prefill_f32_kernel<D, TG, false>), dim3(grid_pre), dim3(4 * D), 0, stream, af);
+                err = launch_f32<D, TG, false>(grid_pre, af, ps, stream);
             else if (kFast && static_cast<int64_t>(d.H) * D * 2 * SegFast::S < (int64_t{1} << 31))
                 DSLA_LAUNCH(ps, segment_state_fast_kernel, dim3(grid_pre), dim3(SegFast::NT), 0, stream, af);
             else
@@ -2460,7 +2520,7 @@ hipError_t launch_x(const dsla_desc &d, const PrefillPlan &plan, PrefillArgs &a,
     {
         ProfileScope ps(DSLA_KERNEL_PREFILL_CHUNK_LOOP, stream);
         if constexpr (std::is_same<TIO, float>::value && !kBeta)
-            DSLA_LAUNCH(ps, (prefill_f32_kernel<D, TG, true>), dim3(grid_full), dim3(4 * D), 0, stream, a);
+            err = launch_f32<D, TG, true>(grid_full, a, ps, stream);
         else
             DSLA_LAUNCH(ps, (prefill_kernel<D, TIO, TG, true, kExt, kBeta>), dim3(grid_full), dim3(4 * D), 0, stream, a);
     }

@@ -398,6 +398,14 @@ def test_prefill_fp32_tile_edges(d, gd, T, segments):
                      qk_scale=d ** -0.5)
 
 
+@pytest.mark.parametrize("B,H,T,segments", [(1, 256, 33, 1), (1, 257, 33, 1), (1, 128, 97, 2), (1, 129, 97, 2), (2, 129, 80, 3)])
+def test_prefill_fp32_d64_heads_per_compute_unit(B, H, T, segments):
+    """Workgroups on both sides of one to a compute unit (256), in the chunk loop and in the pre-pass of two and three segments:
+    up to there further wavefronts prepare the operands, past it the multiplying ones.  TOL["f32"] = 1e-4, sums as above."""
+    run_prefill_case(B, T, H, 64, "f32", "f32", chunk=32, segments=segments, gamma=0.4, scale=0.9, seed=5 + H, init=True,
+                     qk_scale=64 ** -0.5)
+
+
 @pytest.mark.parametrize("io,gd,d", [("f32", "f32", 64), ("bf16", "f32", 128), ("bf16", "bf16", 128), ("f32", "f32", 128)])
 @pytest.mark.parametrize("chunk", [64, 128])
 @pytest.mark.parametrize("gate_mean", [0.0, -2.0])
