@@ -943,41 +943,13 @@ struct Kern {
                     else r.g[j].zero();
                 }
         }
-        // Pre-activations: one logarithm and no case distinction, tau log2 alpha = -log2(1 + 2^-y), instead of activate(): four of
-        // its six instructions per element, which is what bounds the producers in this mode (a step of one chain 2.28 -> 2.20 us at
-        // d = 128, 1.87 -> 1.75 at d = 64; 8 x 8192 tokens, 32 heads 788 -> 771 us).  It holds while 2^-y is finite; where it
-        // overflows (z below -88) the sum is -inf, and all of the thread's gates are mapped again by activate().  (In the segment
-        // pre-pass, which waits for memory, the same change is worth nothing: 327.8 and 328.0 us for 16384 tokens.)
         float g[8];
-        if (!pa.preact) {
 #pragma unroll
-            for (int j = 0; j < TPT; ++j) {
-                r.g[j].unpack(g);
+        for (int j = 0; j < TPT; ++j) {
+            r.g[j].unpack(g);
+            if (pa.preact) activate(g);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) o.c[j][e] = j ? o.c[j - 1][e] + g[e] : g[e];
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < TPT; ++j) {
-                r.g[j].unpack(g);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float l = __builtin_amdgcn_logf(1.0f + __builtin_amdgcn_exp2f(-kLog2e * g[e]));
-                    o.c[j][e] = j ? o.c[j - 1][e] - l : -l;
-                }
-            }
-            float low = o.c[TPT - 1][0];
-#pragma unroll
-            for (int e = 1; e < 8; ++e) low = fminf(low, o.c[TPT - 1][e]);
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(low < -1e30f) != 0, 0)) {
-#pragma unroll
-                for (int j = 0; j < TPT; ++j) {
-                    r.g[j].unpack(g);
-                    activate(g);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) o.c[j][e] = j ? o.c[j - 1][e] + g[e] : g[e];
-                }
-            }
+            for (int e = 0; e < 8; ++e) o.c[j][e] = j ? o.c[j - 1][e] + g[e] : g[e];
         }
         lds_st<f32x4>(pa.tot, f32x4{o.c[TPT - 1][0], o.c[TPT - 1][1], o.c[TPT - 1][2], o.c[TPT - 1][3]});
         lds_st<f32x4>(pa.tot + 16, f32x4{o.c[TPT - 1][4], o.c[TPT - 1][5], o.c[TPT - 1][6], o.c[TPT - 1][7]});

@@ -160,6 +160,31 @@ def test_gate_preactivations_past_the_exponential(d, segments):
     check("S2", S2, rS2, 2e-2)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lo,hi,bound", [(-87.0, -45.0, 4.5e-6), (-8.0, 8.0, 1.4e-6)])
+def test_gate_preactivations_keep_their_precision(d, lo, hi, bound):
+    """In the step loop: one gate per feature, all others exactly one, no keys, states of one, so sigmoid(z) is left.  With y = z log2 e in
+    fp32 the exponent is y - log2(1 + 2^y): off by half a unit of y's last place (3.8e-6 up to 128), by the constant's 1.3e-8 y
+    and by a last subtraction that is exact here (2^y vanishes), so ln 2 (3.8 + 1.7) 1e-6 = 3.8e-6 for y in [-126, -64], and
+    4 units of 1.2e-7 for the exponentials.  For |y| < 12 half a unit is 4.8e-7, the subtraction rounds as well and the logarithm
+    is off by 1.8e-7: 1.4e-6 in all.  (A map by one logarithm of 1 + 2^-y is off by 8.7e-6 on the first range.)"""
+    import torch
+    H, T, tau = 16, 64, 1.0
+    z = np.linspace(lo, hi, H * d, dtype=np.float32).reshape(H, d)
+    g = torch.full((1, T, H, d), 200.0, device="cuda", dtype=torch.bfloat16)
+    g[0, 5] = torch.from_numpy(z).cuda().bfloat16()
+    ref = 1.0 / (1.0 + np.exp(-g[0, 5].double().cpu().numpy()))
+    zero, one = torch.zeros_like(g), torch.ones_like(g)
+    S1 = torch.ones((1, H, d, d), device="cuda", dtype=torch.float32)
+    S2 = S1.clone()
+    desc = dsla.make_desc(1, H, d, d, io_dtype=code("bf16"), gate_dtype=code("bf16"), chunk=64, segments=1, gate_mode=1, tau=tau)
+    dsla.dsla_prefill(desc, T, one, zero, zero, g, g, S1, S2, torch.empty_like(g), None)
+    torch.cuda.synchronize()
+    for S in (S1, S2):
+        err = np.abs(S[0].double().cpu().numpy() / ref[:, :, None] - 1.0)
+        assert np.max(err) <= bound, np.max(err)
+
+
 def test_varlen_gate_preactivations():
     import torch
     lengths, H, d, tau = [300, 77, 1, 640], 2, 128, 16.0
