@@ -144,6 +144,22 @@ def test_attention_decode_infinite_values(io, B, T, H, d):
         assert max_rel_err(got[b, h][rest], ref) < (1e-4 if io == "f32" else 2e-2), (b, h)
 
 
+@pytest.mark.parametrize("io,B,T,H,d", [("bf16", 8, 768, 32, 128), ("bf16", 8, 769, 32, 128), ("bf16", 8, 1536, 32, 64), ("bf16", 1, 50, 3, 64),
+                                        ("f32", 2, 700, 3, 64), ("bf16", 1, 1000, 2, 128)])
+def test_attention_decode_infinite_value_in_the_last_position(io, B, T, H, d):
+    """The last position is also what the lanes past the end read: its infinite value counts once, in its feature, whatever the
+    number of rows in a workgroup's last round."""
+    q, k = inputs(47, B, T, H, d, io)
+    v = wl.layer_inputs(49, B, T, H, d, d, io_dtype=io, gate_dtype="f32")["v"]
+    v[:, T - 1, :, 3] = np.inf
+    got, _ = run_decode(q, k, v, d ** -0.5, io)
+    assert np.all(got[..., 3] == np.inf)
+    rest = [f for f in range(d) if f != 3]
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        ref = ent.attention_decode(q[b:b + 1, h:h + 1], k[b:b + 1, :, h:h + 1], v[b:b + 1, :, h:h + 1][..., rest], d ** -0.5)[0, 0]
+        assert max_rel_err(got[b, h][rest], ref) < (1e-4 if io == "f32" else 2e-2), (b, h)
+
+
 @pytest.mark.parametrize("io,B,T,H,d", [("bf16", 8, 257, 32, 128), ("bf16", 1, 400, 32, 128), ("bf16", 8, 1200, 32, 128), ("bf16", 8, 1201, 32, 128),
                                         ("bf16", 8, 600, 32, 64), ("f32", 8, 300, 32, 64), ("bf16", 1, 513, 3, 64), ("bf16", 1, 50, 3, 64)])
 def test_attention_decode_workgroup_sizes(io, B, T, H, d):
