@@ -2425,17 +2425,17 @@ __global__ __launch_bounds__(256) void segment_scan_kernel(const float *__restri
 // F32Kern with or without roles.  With them (d = 64) a compute unit holds one workgroup, so they are taken where every workgroup has
 // a unit to itself.  Without / with, us, 600 tokens in one segment: 256 heads 109 / 91; past one
 // to a unit 288 heads 157 / 164, 512 heads 165 / 173, 2048 heads of 512 tokens 535 / 573.
+// (The caller takes the launch's error: hipGetLastError() answers only once.)
 template <int D, class TG, bool kFull>
-hipError_t launch_f32(unsigned grid, const PrefillArgs &a, ProfileScope &ps, hipStream_t stream)
+void launch_f32(unsigned grid, const PrefillArgs &a, ProfileScope &ps, hipStream_t stream)
 {
     if constexpr (D == 64) {
         if (grid <= 256) {
             DSLA_LAUNCH(ps, (prefill_f32_kernel<D, TG, kFull, true>), dim3(grid), dim3(F32Kern<D, TG, kFull, true>::NT), 0, stream, a);
-            return hipGetLastError();
+            return;
         }
     }
     DSLA_LAUNCH(ps, (prefill_f32_kernel<D, TG, kFull, false>), dim3(grid), dim3(F32Kern<D, TG, kFull, false>::NT), 0, stream, a);
-    return hipGetLastError();
 }
 
 template <int D, class TIO, class TG, bool kExt, bool kBeta = false>
@@ -2471,7 +2471,7 @@ hipError_t launch_x(const dsla_desc &d, const PrefillPlan &plan, PrefillArgs &a,
             // the pre-pass of its own design where it is built; its per-lane offsets inside a step are 32-bit
             constexpr bool kFast = D == SegFast::D && std::is_same<TIO, bf16_t>::value && std::is_same<TG, bf16_t>::value && !kBeta;
             if constexpr (std::is_same<TIO, float>::value && !kBeta)
-                err = launch_f32<D, TG, false>(grid_pre, af, ps, stream);
+                launch_f32<D, TG, false>(grid_pre, af, ps, stream);
             else if (kFast && static_cast<int64_t>(d.H) * D * 2 * SegFast::S < (int64_t{1} << 31))
                 DSLA_LAUNCH(ps, segment_state_fast_kernel, dim3(grid_pre), dim3(SegFast::NT), 0, stream, af);
             else
@@ -2492,7 +2492,7 @@ hipError_t launch_x(const dsla_desc &d, const PrefillPlan &plan, PrefillArgs &a,
     {
         ProfileScope ps(DSLA_KERNEL_PREFILL_CHUNK_LOOP, stream);
         if constexpr (std::is_same<TIO, float>::value && !kBeta)
-            err = launch_f32<D, TG, true>(grid_full, a, ps, stream);
+            launch_f32<D, TG, true>(grid_full, a, ps, stream);
         else
             DSLA_LAUNCH(ps, (prefill_kernel<D, TIO, TG, true, kExt, kBeta>), dim3(grid_full), dim3(4 * D), 0, stream, a);
     }

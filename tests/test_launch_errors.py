@@ -1,0 +1,73 @@
+"""Launch errors reach the caller: every entry point with the kernel launches stubbed out (no GPU; a process of its own, in which
+the stub comes before the runtime), each launch of a call failing in turn."""
+import os
+import subprocess
+import sys
+
+import paper_2506_09316_amd as dsla
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+CHILD = r"""
+import ctypes, sys
+stub = ctypes.CDLL(None)
+stub.launch_stub_reset(-1)   # (missing where the stub is not loaded: then nothing is called)
+from paper_2506_09316_amd import binding
+lib = ctypes.CDLL(binding.library_path())
+for n in ("dsla_prefill_workspace_bytes", "dsla_prefill_varlen_workspace_bytes", "dsla_prefill_multi_workspace_bytes",
+          "dsla_attention_decode_workspace_bytes"):
+    getattr(lib, n).restype = ctypes.c_size_t
+i64, size, f32, fake = ctypes.c_int64, ctypes.c_size_t, ctypes.c_float, ctypes.c_void_p(4096)
+OK, ERR_HIP = 0, 5
+
+def each_launch(name, launches, call):
+    stub.launch_stub_reset(-1)
+    assert call() == OK and stub.launch_stub_count() == launches, (name, stub.launch_stub_count())
+    for n in range(launches):
+        stub.launch_stub_reset(n)
+        assert call() == ERR_HIP, (name, n)
+        assert stub.launch_stub_count() == n + 1, (name, n)   # nothing runs on what a failed launch left unwritten
+
+for io in (0, 1):
+    for gate in (0, 1):
+        for d in (64, 128):
+            desc = lambda B, H, segments: ctypes.byref(binding.make_desc(B, H, d, d, io_dtype=io, gate_dtype=gate, chunk=64, segments=segments))
+            for H in (4, 300):                     # at most one workgroup to a compute unit and more
+                for segments, launches in ((1, 1), (3, 3)):
+                    q = desc(1, H, segments)
+                    n = lib.dsla_prefill_workspace_bytes(q, i64(192))
+                    each_launch(("prefill", io, gate, d, H, segments), launches,
+                                lambda: lib.dsla_prefill(q, i64(192), *[fake] * 8, fake, size(n), None))
+                    n = lib.dsla_prefill_varlen_workspace_bytes(q, i64(500), i64(192))
+                    each_launch(("packed", io, gate, d, H, segments), launches + (segments > 1),
+                                lambda: lib.dsla_prefill_varlen(q, i64(500), i64(192), fake, None, None, *[fake] * 8, fake, size(n), None))
+                    vp = ctypes.c_void_p * 2
+                    for beta in (None, vp(None, 4096)):
+                        multi = binding.DslaMulti(2, 0, vp(4096, 4096), beta, vp(4096, 8192), (ctypes.c_float * 2)(.5, .5), None)
+                        n = lib.dsla_prefill_multi_workspace_bytes(q, ctypes.byref(multi), i64(192))
+                        # with a beta gate on the second state, the first has an idle partner, whose state is cleared by a launch
+                        each_launch(("states", io, gate, d, H, segments, bool(beta)), 2 * launches + 1 if beta else launches,
+                                    lambda: lib.dsla_prefill_multi(q, ctypes.byref(multi), i64(192), *[fake] * 5, size(n), None))
+            each_launch(("decode", io, gate, d), 1, lambda: lib.dsla_decode(desc(2, 4, 0), *[fake] * 9))
+for d in (64, 128):
+    for T in (100, 5000):
+        each_launch(("attention prefill", d, T), 1, lambda: lib.dsla_attention_prefill(1, 4, d, i64(T), 1, f32(1), *[fake] * 4, None))
+    for io, T, launches in ((0, 5000, 2), (1, 5000, 2), (1, 100, 1)):
+        n = lib.dsla_attention_decode_workspace_bytes(1, 4, d, i64(T))
+        each_launch(("attention decode", d, io, T), launches,
+                    lambda: lib.dsla_attention_decode(1, 4, d, i64(T), io, f32(1), *[fake] * 3, None, fake, fake, size(n), None))
+for M, K in ((1, 256), (100, 256), (100, 128), (300, 96), (300, 128), (5000, 4096)):
+    each_launch(("project", M, K), 1, lambda: lib.dsla_project(i64(M), K, 1, 4096, fake, fake, None, (ctypes.c_void_p * 1)(4096), None))
+print("done")
+"""
+
+
+def test_launch_errors_reach_the_caller(tmp_path):
+    if not os.path.exists(dsla.library_path()):
+        from paper_2506_09316_amd import build
+        build.build()
+    stub = str(tmp_path / "launch_stub.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-o", stub, os.path.join(HERE, "launch_stub.c")], check=True)
+    env = dict(os.environ, LD_PRELOAD=":".join(p for p in (stub, os.environ.get("LD_PRELOAD")) if p))
+    run = subprocess.run([sys.executable, "-c", CHILD], env=env, cwd=os.path.dirname(HERE), capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0 and run.stdout.strip().endswith("done"), run.stderr
