@@ -111,12 +111,12 @@ dsla_status dsla_prefill(const dsla_desc *desc, int64_t T, const void *q, const 
     if (T > (int64_t(1) << 40)) return DSLA_ERR_SHAPE;
     PrefillPlan plan;
     if (!prefill_plan(*desc, T, &plan, workspace ? workspace_bytes : 0)) return DSLA_ERR_UNSUPPORTED;
+    const bool misaligned = (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0;
+    if (misaligned && plan.ws_need_bytes == 0) prefill_plan(*desc, T, &plan, 0);   // no buffer that it could use
     if (static_cast<int64_t>(desc->B) * desc->H * plan.segments > 0x7fffffffLL) return DSLA_ERR_SHAPE;
-    if (plan.ws_total_bytes > 0) {
-        if (!workspace || workspace_bytes < plan.ws_total_bytes) return DSLA_ERR_WORKSPACE;
-        if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return DSLA_ERR_SHAPE;
-    } else if (plan.ws_ask_bytes > 0 && (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) {
-        return DSLA_ERR_SHAPE;
+    if (plan.ws_need_bytes > 0) {
+        if (!workspace || workspace_bytes < plan.ws_need_bytes) return DSLA_ERR_WORKSPACE;
+        if (misaligned) return DSLA_ERR_SHAPE;
     }
     return hip_status(launch_prefill(*desc, plan, T, nullptr, nullptr, nullptr, q, k, v, g1, g2, S1, S2, o, workspace,
                                      static_cast<hipStream_t>(stream)));

@@ -2560,7 +2560,7 @@ void finish_plan(const dsla_desc &d, int C, int64_t P, int64_t nchunks, bool may
         plan->ws_state_bytes = 0;
         plan->ws_decay_bytes = 0;
     }
-    plan->ws_total_bytes = plan->ws_ask_bytes = plan->ws_state_bytes + plan->ws_decay_bytes;
+    plan->ws_total_bytes = plan->ws_ask_bytes = plan->ws_need_bytes = plan->ws_state_bytes + plan->ws_decay_bytes;
 }
 int plan_chunk(const dsla_desc &d)
 {
@@ -2680,9 +2680,11 @@ bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t avail
         finish_plan(d, C, P_coarse, nchunks, true, &coarse);
         const size_t ask = coarse.ws_total_bytes > plan->ws_total_bytes ? coarse.ws_total_bytes : plan->ws_total_bytes;
         if (plan->ws_total_bytes > available && coarse.ws_total_bytes <= available) *plan = coarse;
-        // Whole where the coarse cut needs a buffer: the caller brings that buffer all the same (it is what the size query asks for),
-        // so that whether a call is accepted does not change with the estimates.
+        // Whole where the coarse cut needs a buffer: the caller brings that buffer all the same (it is what the size query asks for).
+        // In 16 bits a cut where the coarse plan is whole is an offer: a call without a buffer that it can use runs whole.
         if (P == 1 && coarse.ws_total_bytes > available) *plan = coarse;
+        if (P == 1) plan->ws_need_bytes = coarse.ws_total_bytes;
+        else if (P_coarse == 1 && d.io_dtype == DSLA_BF16) plan->ws_need_bytes = 0;
         plan->ws_ask_bytes = ask;
     }
     return true;
@@ -2733,7 +2735,7 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
         p->ws_state_bytes = slots * 2 * D * D * sizeof(float);
         p->ws_decay_bytes = up(slots * 2 * D * sizeof(float));
         p->ws_lists_bytes = up((static_cast<size_t>(d.B) + 1) * 4) + 256 + up(p->max_items * 8) + up(p->max_pre_items * 8);
-        p->ws_total_bytes = p->ws_ask_bytes = p->ws_state_bytes + p->ws_decay_bytes + p->ws_lists_bytes;
+        p->ws_total_bytes = p->ws_ask_bytes = p->ws_need_bytes = p->ws_state_bytes + p->ws_decay_bytes + p->ws_lists_bytes;
     };
     int64_t P, P_cut;   // what is done; what the cut alone would be
     if (d.segments > 0) {

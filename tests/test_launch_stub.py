@@ -1,5 +1,5 @@
-"""Launch errors reach the caller: every entry point with the kernel launches stubbed out (no GPU; a process of its own, in which
-the stub comes before the runtime), each launch of a call failing in turn."""
+"""What the library does around its launches, with these stubbed out (no GPU; a process of its own, in which the stub comes before
+the runtime): launch errors reach the caller, and which calls are accepted with which buffer."""
 import os
 import subprocess
 import sys
@@ -18,8 +18,10 @@ for n in ("dsla_prefill_workspace_bytes", "dsla_prefill_varlen_workspace_bytes",
           "dsla_attention_decode_workspace_bytes"):
     getattr(lib, n).restype = ctypes.c_size_t
 i64, size, f32, fake = ctypes.c_int64, ctypes.c_size_t, ctypes.c_float, ctypes.c_void_p(4096)
-OK, ERR_HIP = 0, 5
+OK, ERR_SHAPE, ERR_WORKSPACE, ERR_HIP = 0, 2, 4, 5
+"""
 
+LAUNCH_ERRORS = r"""
 def each_launch(name, launches, call):
     stub.launch_stub_reset(-1)
     assert call() == OK and stub.launch_stub_count() == launches, (name, stub.launch_stub_count())
@@ -58,16 +60,46 @@ for d in (64, 128):
                     lambda: lib.dsla_attention_decode(1, 4, d, i64(T), io, f32(1), *[fake] * 3, None, fake, fake, size(n), None))
 for M, K in ((1, 256), (100, 256), (100, 128), (300, 96), (300, 128), (5000, 4096)):
     each_launch(("project", M, K), 1, lambda: lib.dsla_project(i64(M), K, 1, 4096, fake, fake, None, (ctypes.c_void_p * 1)(4096), None))
-print("done")
+"""
+
+BUFFERS = r"""
+odd = ctypes.c_void_p(4096 + 64)   # not on a multiple of 256
+
+def dense(H, d, T, io, ws, n, B=1):
+    stub.launch_stub_reset(-1)
+    status = lib.dsla_prefill(ctypes.byref(binding.make_desc(B, H, d, d, io_dtype=io, gate_dtype=io, chunk=64)), i64(T), *[fake] * 8, ws, size(n), None)
+    return status, stub.launch_stub_count()
+
+big = 1 << 40
+# nothing is asked for where the first rule cuts nothing and the buffer is too small to use: its alignment does not matter
+for H, d, T in ((4, 64, 255), (32, 128, 300)):
+    assert dense(H, d, T, 0, odd, 1024) == dense(H, d, T, 0, None, 0) == (OK, 1)
+    assert dense(H, d, T, 0, fake, big) == (OK, 3) and dense(H, d, T, 0, odd, big) == (ERR_SHAPE, 0)
+# 16 bits, 257 tokens and more: cut with a buffer, whole with none that can be used
+for H, d, T in ((8, 128, 372), (4, 128, 400), (4, 64, 400)):
+    assert dense(H, d, T, 1, fake, big) == (OK, 3)
+    assert dense(H, d, T, 1, odd, big) == dense(H, d, T, 1, odd, 1024) == dense(H, d, T, 1, fake, 1024) == dense(H, d, T, 1, None, 0) == (OK, 1)
+# the first rule cuts: a buffer is asked for, whatever the estimates make of the call
+for H, d, T, launches in ((96, 128, 640, 1), (8, 128, 1000, 3)):
+    assert dense(H, d, T, 1, fake, big) == (OK, launches)
+    assert dense(H, d, T, 1, odd, big) == (ERR_SHAPE, 0) and dense(H, d, T, 1, None, 0) == dense(H, d, T, 1, odd, 1024) == (ERR_WORKSPACE, 0)
 """
 
 
-def test_launch_errors_reach_the_caller(tmp_path):
+def run_stubbed(tmp_path, body):
     if not os.path.exists(dsla.library_path()):
         from paper_2506_09316_amd import build
         build.build()
     stub = str(tmp_path / "launch_stub.so")
     subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-o", stub, os.path.join(HERE, "launch_stub.c")], check=True)
     env = dict(os.environ, LD_PRELOAD=":".join(p for p in (stub, os.environ.get("LD_PRELOAD")) if p))
-    run = subprocess.run([sys.executable, "-c", CHILD], env=env, cwd=os.path.dirname(HERE), capture_output=True, text=True, timeout=300)
+    run = subprocess.run([sys.executable, "-c", CHILD + body + "print('done')"], env=env, cwd=os.path.dirname(HERE), capture_output=True, text=True, timeout=300)
     assert run.returncode == 0 and run.stdout.strip().endswith("done"), run.stderr
+
+
+def test_launch_errors_reach_the_caller(tmp_path):
+    run_stubbed(tmp_path, LAUNCH_ERRORS)
+
+
+def test_which_buffers_a_call_is_refused_for(tmp_path):
+    run_stubbed(tmp_path, BUFFERS)
