@@ -200,11 +200,12 @@ dsla_status dsla_prefill_varlen(const dsla_desc *desc, int64_t total_T, int64_t 
         (reinterpret_cast<uintptr_t>(seq_index) & 3u) || (reinterpret_cast<uintptr_t>(state_slot) & 3u))
         return DSLA_ERR_SHAPE;
     PrefillPlan plan;
-    if (!prefill_plan_varlen(*desc, total_T, max_T, &plan)) return DSLA_ERR_UNSUPPORTED;
+    const bool misaligned = (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0;
+    if (!prefill_plan_varlen(*desc, total_T, max_T, &plan, workspace && !misaligned ? workspace_bytes : 0)) return DSLA_ERR_UNSUPPORTED;
     if (plan.max_items * desc->H > 0x7fffffffLL) return DSLA_ERR_SHAPE;   // one workgroup per (segment, head)
     if (plan.ws_total_bytes > 0) {
         if (!workspace || workspace_bytes < plan.ws_total_bytes) return DSLA_ERR_WORKSPACE;
-        if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return DSLA_ERR_SHAPE;
+        if (misaligned) return DSLA_ERR_SHAPE;
     }
     return hip_status(launch_prefill(*desc, plan, max_T, cu_seqlens, seq_index, state_slot, q, k, v, g1, g2, S1, S2, o,
                                      workspace, static_cast<hipStream_t>(stream)));

@@ -99,7 +99,7 @@ struct PrefillPlan {
 };
 // false: unsupported combination.  available: bytes of workspace there are (the size query: any number)
 bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t available = SIZE_MAX);
-bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, PrefillPlan *plan);
+bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, PrefillPlan *plan, size_t available = SIZE_MAX);
 // cu_seqlens == nullptr: B sequences of T tokens each; else packed sequences and T = upper bound of their lengths.
 // seq_index (with cu_seqlens only): which packed sequences take part; nullptr: all, in order.
 // state_slot == nullptr: sequence b owns entry b of S1, S2.

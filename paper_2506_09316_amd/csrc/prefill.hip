@@ -2590,6 +2590,20 @@ PrefillCosts prefill_costs(const dsla_desc &d)
     c.lists = f32 ? (small ? 5.0 : 4.0) : (small ? 9.0 : 6.0);
     return c;
 }
+// The figures by which a packed call without its buffer is refused or runs whole.  They are part of what callers rely on: they stay
+// when kernels get faster and the estimates follow.
+PrefillCosts refusal_costs(const dsla_desc &d)
+{
+    const bool f32 = d.io_dtype == DSLA_F32, small = d.d_k == 64, preact = d.gate_mode == DSLA_GATE_PREACT;
+    PrefillCosts c;
+    c.step = f32 ? (small ? 7.0 : 16.0) : (small ? (preact ? 1.8 : 1.4) : (preact ? 2.35 : 2.0));
+    c.step_full = f32 ? c.step : (small ? 2.5 : (preact ? 3.4 : 2.9));
+    c.pre = f32 ? c.step / 3 : (small ? 1.2 : (preact ? 2.1 : 1.5));
+    c.wg = f32 ? (small ? 7.0 : 16.0) : (small ? 5.0 : 8.0);
+    c.slot = f32 ? (small ? 0.025 : 0.06) : (small ? 0.04 : 0.05);
+    c.lists = f32 ? (small ? 5.0 : 4.0) : (small ? 9.0 : 6.0);
+    return c;
+}
 }  // namespace
 
 bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t available)
@@ -2719,7 +2733,7 @@ bool order_pays(const dsla_desc &d, int64_t total_T, int64_t max_T)
 // The kernels find their work in lists built on the device (the lengths are not known here); list and workspace
 // sizes are worst cases: sum_b ceil(T_b / L) <= total_T / L + B segments, of which at most total_T / L have a
 // successor.
-bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, PrefillPlan *plan)
+bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, PrefillPlan *plan, size_t available)
 {
     const int C = plan_chunk(d);
     if (!C) return false;
@@ -2738,6 +2752,7 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
         p->ws_total_bytes = p->ws_ask_bytes = p->ws_need_bytes = p->ws_state_bytes + p->ws_decay_bytes + p->ws_lists_bytes;
     };
     int64_t P, P_cut;   // what is done; what the cut alone would be
+    bool must_cut = true;
     if (d.segments > 0) {
         P = P_cut = d.segments;
     } else {
@@ -2746,21 +2761,24 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
         if (cps < 4) cps = 4;
         P = P_cut = (nchunks + cps - 1) / cps;
         if (P > 1) {
-            const PrefillCosts c = prefill_costs(d);
             const double chip = chip_slots(d), steps = static_cast<double>(total_T) / 32;
             const double L = static_cast<double>((nchunks + P - 1) / P * C);   // finish_plan evens the segments out
             const double n = L / 32, longest = static_cast<double>(max_T) / 32;
             const double cuts = static_cast<double>(total_T) / L * d.H, items = cuts + static_cast<double>(d.B) * d.H;
-            auto loop = [&](double chain, double workgroups) {
-                const double spread = workgroups / chip * c.wg + steps * d.H / chip * c.step_full;
-                return spread > c.wg + chain * c.step ? spread : c.wg + chain * c.step;
+            auto cut_pays = [&](const PrefillCosts &c) {
+                auto loop = [&](double chain, double workgroups) {
+                    const double spread = workgroups / chip * c.wg + steps * d.H / chip * c.step_full;
+                    return spread > c.wg + chain * c.step ? spread : c.wg + chain * c.step;
+                };
+                const double whole = loop(longest, static_cast<double>(d.B) * d.H);
+                return whole > c.lists + c.wg + (cuts > chip ? cuts / chip : 1.0) * n * c.pre + c.slot * cuts + loop(n, items);
             };
-            const double whole = loop(longest, static_cast<double>(d.B) * d.H);
-            const double cut = c.lists + c.wg + (cuts > chip ? cuts / chip : 1.0) * n * c.pre + c.slot * cuts + loop(n, items);
-            if (whole <= cut) P = 1;
+            must_cut = cut_pays(refusal_costs(d));
+            if (!cut_pays(prefill_costs(d))) P = 1;
         }
     }
     finish_packed(P, plan);
+    if (!must_cut && plan->ws_total_bytes > available) finish_packed(P = 1, plan);
     plan->longest_first = plan->segments == 1 && order_pays(d, total_T, max_T);
     if (P < P_cut) {
         // Whole by the estimate: the size query still answers with what cutting takes, if any smaller batch is cut, so that a

@@ -83,6 +83,21 @@ for H, d, T in ((8, 128, 372), (4, 128, 400), (4, 64, 400)):
 for H, d, T, launches in ((96, 128, 640, 1), (8, 128, 1000, 3)):
     assert dense(H, d, T, 1, fake, big) == (OK, launches)
     assert dense(H, d, T, 1, odd, big) == (ERR_SHAPE, 0) and dense(H, d, T, 1, None, 0) == dense(H, d, T, 1, odd, 1024) == (ERR_WORKSPACE, 0)
+
+def packed(B, H, d, total, longest, io, ws, n):
+    stub.launch_stub_reset(-1)
+    status = lib.dsla_prefill_varlen(ctypes.byref(binding.make_desc(B, H, d, d, io_dtype=io, gate_dtype=io, chunk=64)), i64(total), i64(longest), fake, None,
+                                     None, *[fake] * 8, ws, size(n), None)
+    return status, stub.launch_stub_count()
+
+# packed, fp32: a cut that faster kernels made worth it, which no buffer used to be asked for, and one that always needed its buffer
+for B, H, d, total, longest in ((22, 32, 128, 1217, 346), (18, 64, 128, 1323, 641)):
+    assert packed(B, H, d, total, longest, 0, fake, big) == (OK, 4)
+    assert packed(B, H, d, total, longest, 0, odd, big) == packed(B, H, d, total, longest, 0, fake, 1024) == packed(B, H, d, total, longest, 0, None, 0) == (OK, 1)
+for io in (0, 1):
+    assert packed(8, 32, 128, 1959, 1900, io, fake, big) == (OK, 4)
+    assert packed(8, 32, 128, 1959, 1900, io, odd, big) == (ERR_SHAPE, 0)
+    assert packed(8, 32, 128, 1959, 1900, io, fake, 1024) == packed(8, 32, 128, 1959, 1900, io, None, 0) == (ERR_WORKSPACE, 0)
 """
 
 
