@@ -187,6 +187,12 @@ def test_attention_decode_workgroup_sizes(io, B, T, H, d):
         np.testing.assert_allclose(got[1], v[1, 0], rtol=2 ** -7, atol=1e-6)
 
 
+@pytest.mark.parametrize("H,T,d", [(192, 450, 64), (193, 450, 64), (193, 500, 128), (257, 300, 64), (257, 300, 128)])
+def test_attention_decode_pairs_per_compute_unit(H, T, d):
+    """Both sides of the numbers of pairs between which one workgroup takes a whole context."""
+    test_attention_decode_workgroup_sizes("bf16", 1, T, H, d)
+
+
 def test_attention_decode_mixed_context_lengths():
     """Requests of one batch at different context lengths in a cache of T positions each: only the filled positions
     count (the rest of the cache holds NaN here), also where a whole key range of the split lies past the end."""
