@@ -371,7 +371,7 @@ hipError_t launch_attn_decode_t(int B, int H, int64_t T, const EntropyPlan &plan
     // 256 pairs of 280, 800, 1200, 2000 positions 12.0 / 9.9, 20.4 / 18.3, 26.8 / 26.2, 38.8 / 39.5, 216 of 435, 1183 13.1 / 11.0, 26.1 / 26.1,
     // 32 pairs of 280, 500 8.8 / 7.8, 9.6 / 9.5; d = 64, 256 pairs of 500, 2000, 3500 11.3 / 9.6, 26.2 / 23.0, 41.6 / 39.0, 200 of 391,
     // 3351 10.0 / 8.6, 34.9 / 34.6, 96 pairs of 500 8.7 / 9.2; fp32, 256 pairs of 500 26.2 / 26.6.  More pairs than units: d = 64, 260
-    // pairs of 331, 1327 10.2 / 14.2, 22.3 / 28.5; d = 128, 260 of 692 22.6 / 28.7, 384 of 643 20.8 / 24.9.
+    // pairs of 331, 1327 10.2 / 14.2, 22.3 / 28.5; d = 128, 260 of 692 22.6 / 28.7, 384 of 643 25.1 / 30.0.
     const bool one = sizeof(TIO) == 2 && plan.parts == 2 && BH <= 256 &&
                      (D == 128 ? (BH >= 32 && T <= 400) || (BH > 192 && T <= 1200) : BH > 192 && T <= 3600);
     const int parts = one ? 1 : plan.parts;
