@@ -570,6 +570,28 @@ __global__ __launch_bounds__(256 * GROUPS, 2) void attention_prefill_short_kerne
     }
 }
 
+// How many workgroups of 64 queries the kernel for short prompts still pays with; two (d = 64: four) are resident on a compute unit.
+// Past that a second round of them costs what their shorter chains save, unless the chains are long (they even out) or a single
+// block.  Before that the heads decide: those of a multiple of 8 stay on one XCD each, of 4 on two; of other numbers every XCD's L2 reads
+// the keys of all heads, twice as often as with workgroups of 128 queries.  Before / now (us or, alone, now in parts of before),
+// d = 128: 596 workgroups of 2 blocks 7.9 / 10.8, 756 of 4 (189 heads) 12.2 / 17.2, 512 (128 heads) 0.91, 376 of 8 (47 heads) 1.08, 544 (68 heads) 0.76, 640
+// (80 heads) 0.90, 689 of 13 (53 heads) 1.16, 684 of 9 (76 heads) 0.89, 720 of 18 (40 heads) 0.75, 650 of 50 0.89; d = 64: 1014 of 2 1.03, 906 of
+// 3 0.90, 756 of 4 (189 heads) 0.94, 836 (209 heads) 1.13, 1146 of 6 (191 heads) 11.7 / 15.8, 1176 of 7 (168 heads) 0.89, 1177 of 11 (107
+// heads) 1.20, 1274 of 98 0.92.
+int64_t most_short_workgroups(int d, int64_t heads, int64_t key_blocks)
+{
+    const bool wide = d == 128;
+    if (key_blocks == 1 || key_blocks >= 20) return wide ? 768 : 1280;
+    if (key_blocks <= 3) return wide ? 512 : (key_blocks == 2 ? 768 : 1024);
+    if (heads % 4 == 0) {
+        if (!wide) return 1088;
+        if (heads % 8 == 0) return key_blocks == 4 ? 608 : 768;
+        return key_blocks <= 6 ? 416 : (key_blocks <= 8 ? 560 : 768);
+    }
+    if (wide) return key_blocks <= 8 ? 288 : (key_blocks <= 12 ? 320 : 512);
+    return key_blocks <= 5 ? 720 : (key_blocks <= 12 ? 640 : 768);
+}
+
 }  // namespace
 
 hipError_t launch_attn_prefill(int B, int H, int d, int64_t T, float scale, const void *q, const void *k, const void *v,
@@ -578,12 +600,10 @@ hipError_t launch_attn_prefill(int B, int H, int d, int64_t T, float scale, cons
     const float sl2 = scale * 1.4426950408889634f;
     ProfileScope ps(DSLA_KERNEL_ATTENTION_PREFILL, stream);
     const int64_t short_grid = static_cast<int64_t>(B) * H * ((T + kShortQueries - 1) / kShortQueries);
-    // While the workgroups of 64 queries make at most 3 (d = 64: 5) to a compute unit, where two (four) are resident.  Before / now (us):
-    // d = 128, 768 of them 27.1 / 22.8 and 19.4 / 18.1, 864 37.0 / 34.6 but 16.7 / 17.5, 1024 14.1 / 16.7, 1216 36.1 / 40.3; d = 64, 1024 10.0 / 9.3, 1280 39.3 / 36.5, 1504 50.3 / 51.5.
-    if (short_grid <= (d == 128 ? 768 : 1280)) {
+    const int64_t key_blocks = (T + kKeys - 1) / kKeys;
+    if (short_grid <= most_short_workgroups(d, static_cast<int64_t>(B) * H, key_blocks)) {
         // Two groups where the chain has 16 blocks and every workgroup a compute unit to itself, or 32 blocks and two units' worth
         // of workgroups.  One / two groups: 128 workgroups, 16 blocks 15.1 / 14.3, 384, 16 blocks 18.4 / 18.7, 504, 63 blocks 56.3 / 49.6, 752, 47 30.2 / 29.9.
-        const int64_t key_blocks = (T + kKeys - 1) / kKeys;
         const bool two = (short_grid <= 256 && key_blocks >= 16) || (short_grid <= 512 && key_blocks >= 32);
         auto launch = [&](auto kernel, int groups) {
             DSLA_LAUNCH(ps, kernel, dim3(static_cast<unsigned>(short_grid)), dim3(256 * groups), 0, stream, static_cast<const bf16_t *>(q),

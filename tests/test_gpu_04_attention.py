@@ -311,6 +311,13 @@ def test_attention_prefill_kernels(d, heads, T, levels):
     assert np.array_equal(got, got[:, :, idx])
 
 
+@pytest.mark.parametrize("d,heads,T", [(128, 256, 66), (128, 257, 66), (128, 76, 300), (128, 84, 300), (128, 58, 300), (128, 57, 300), (128, 72, 600),
+                                       (64, 180, 200), (64, 182, 200), (64, 109, 580), (64, 65, 580), (64, 63, 580)])
+def test_attention_prefill_workgroups_per_compute_unit(d, heads, T):
+    """Numbers of heads on both sides of where prompts of 2, 4, 5 and 10 blocks of keys change the kernel."""
+    test_attention_prefill_kernels(d, heads, T, None)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_attention_prefill_two_groups_near_the_mask(d):
     """Equal scores of -3e29 and below in prompts whose key blocks two groups of wavefronts share: the mean of the values so far."""
