@@ -27,6 +27,7 @@
 // read-out without passing through LDS; the partner operand is stored in LDS with the matching order of
 // the contraction index (bits 2 and 3 of the feature index swapped).
 #include <cstdio>
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -2640,20 +2641,33 @@ bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t avail
         // are, and costs 13 to 20 us whatever their number.  In two / whole (d = 128): 96 heads of 710, 1100, 1500 tokens 61.5 / 52.5,
         // 86 / 75, 92 / 95; 128 heads of 710, 1500, 3000 71.5 / 53.8, 119 / 99, 194 / 184; d = 64, in four or five / whole: 96 heads of
         // 710, 1300 41.4 / 37.1, 59 / 62; 128 heads of 710, 1500, 2200 45.2 / 37.6, 77 / 71, 100 / 101.
+        // Per step a whole prompt loses 0.48 (d = 128: 0.43) us at 96 heads and less by 0.29 (0.33) for 32 more, but not less than a
+        // floor: past 110 heads their number hardly counts.  At d = 128, where the cut is in two, it costs least where the pre-pass works on
+        // the halves of the first segment (an even number of chunks), and less from zero states.  Cut / whole: d = 128, 128 heads of 3267 tokens 193 / 233, of 1959
+        // (halves) 127 / 138, of 2572 (none) 1.00, 120 of 2709 as pre-activations (halves) 170 / 205, 104 of 1491 (halves) 87 / 97, of 1589
+        // (none) as pre-activations 0.91; d = 64, 128 heads of 1651 69 / 77, 112 of 1232 1.07.
         const double heads = static_cast<double>(BH - 96) / 32, steps_d = static_cast<double>(T) / 32;
-        if (!f32 && C <= 64 && T > 704 && BH > 85 && BH <= 128 &&
-            (d.d_k == 64 ? steps_d * (0.48 - 0.29 * heads) < 13.5 : steps_d * (0.43 - 0.33 * heads) < 20.0)) {
+        const bool gates32 = d.gate_dtype != DSLA_BF16, preacts = d.gate_mode == DSLA_GATE_PREACT;
+        const int64_t half = (nchunks + 1) / 2;   // chunks per segment of a cut in two
+        const double loss = d.d_k == 64 ? std::max(0.48 - 0.29 * heads, preacts ? 0.33 : (gates32 ? 0.24 : 0.36))
+                                        : std::max(0.43 - 0.33 * heads, gates32 ? 0.28 : (preacts ? 0.30 : 0.25));
+        double costs;   // (us; 32-bit gates go through the general pre-pass)
+        if (d.d_k == 64) costs = preacts ? (gates32 ? 12.3 : 11.2) : (gates32 ? 15.5 : 13.2);
+        else if (half % 2 != 0) costs = gates32 ? (d.zero_init ? 24.0 : 28.0) : 20.0;
+        else if (gates32) costs = preacts ? (d.zero_init ? 15.5 : 20.0) : (d.zero_init ? 16.5 : 25.0);
+        else costs = d.zero_init ? 12.0 : 13.2;
+        if (!f32 && C <= 64 && T > 704 && BH > 85 && BH <= 128 && steps_d * loss < costs) {
             P = 1;
         } else if (!f32 && C <= 64 && T > 256 && T <= 704) {
             const bool small = d.d_k == 64, preact = d.gate_mode == DSLA_GATE_PREACT;
-            const double step = (small ? 1.37 : 1.81) + (preact ? 0.38 : 0.0), pre = (small ? 1.2 : 1.3) + (preact ? 0.3 : 0.0);
+            const double step = (small ? 1.37 : 1.81) + (preact ? 0.48 : 0.0), pre = (small ? 1.2 : 1.3) + (preact ? 0.3 : 0.0);
             const double fixed = small ? 6.8 : 7.0, slot = small ? 0.026 : 0.057, wg = small ? 5.6 : 7.5;
             double best = wg + static_cast<double>((T + 31) / 32) * step;
             P = 1;
-            for (int64_t tokens = 192; tokens >= 64; tokens -= 64) {
-                const int64_t parts = (T + tokens - 1) / tokens;
+            for (int64_t tokens = 192; tokens >= 64; tokens -= C) {   // (chunks of 32: also the lengths between)
+                const int64_t parts = (T + tokens - 1) / tokens, longest = (nchunks + parts - 1) / parts * C;   // as finish_plan evens them out
                 if (BH * parts > (tokens > 64 ? 256 : (small ? 160 : 64))) break;
-                const double cut = wg + fixed + static_cast<double>(tokens / 32) * (step + pre) + slot * static_cast<double>(BH * parts);
+                const double cut = wg + fixed + static_cast<double>(longest / 32) * (step + pre) + slot * static_cast<double>(BH * parts);
                 if (cut < 0.93 * best) {
                     best = cut;
                     P = parts;
