@@ -2578,12 +2578,14 @@ namespace {
 // batch and the scan besides its slots.
 struct PrefillCosts {
     double step, step_full, pre, wg, slot, lists;
+    double step_alone;   // a step where no compute unit has two workgroups
 };
 PrefillCosts prefill_costs(const dsla_desc &d)
 {
     const bool f32 = d.io_dtype == DSLA_F32, small = d.d_k == 64, preact = d.gate_mode == DSLA_GATE_PREACT;
     PrefillCosts c;
     c.step = f32 ? (small ? 4.5 : 11.1) : (small ? (preact ? 1.8 : 1.4) : (preact ? 2.35 : 2.0));
+    c.step_alone = f32 && small ? 3.6 : c.step;   // (launch_f32)
     c.step_full = f32 ? c.step : (small ? 2.5 : (preact ? 3.4 : 2.9));
     c.pre = f32 ? (small ? 2.2 : 5.1) : (small ? 1.2 : (preact ? 2.1 : 1.5));
     c.wg = f32 ? (small ? 3.0 : 5.0) : (small ? 5.0 : 8.0);
@@ -2598,6 +2600,7 @@ PrefillCosts refusal_costs(const dsla_desc &d)
     const bool f32 = d.io_dtype == DSLA_F32, small = d.d_k == 64, preact = d.gate_mode == DSLA_GATE_PREACT;
     PrefillCosts c;
     c.step = f32 ? (small ? 7.0 : 16.0) : (small ? (preact ? 1.8 : 1.4) : (preact ? 2.35 : 2.0));
+    c.step_alone = c.step;
     c.step_full = f32 ? c.step : (small ? 2.5 : (preact ? 3.4 : 2.9));
     c.pre = f32 ? c.step / 3 : (small ? 1.2 : (preact ? 2.1 : 1.5));
     c.wg = f32 ? (small ? 7.0 : 16.0) : (small ? 5.0 : 8.0);
@@ -2624,7 +2627,7 @@ bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t avail
         P_coarse = P < 1 ? 1 : P;
         // ... or fewer where that leaves the chip idle (plans of one or two segments stay as they are in 16 bits: there
         // the pre-pass and the scan cost what the shorter segments gain).  A step of 32 tokens takes 2 us in 16-bit
-        // arithmetic however few workgroups run, in fp32 4.5 us (d = 64) and 11 us (d = 128), a segment's share of the
+        // arithmetic however few workgroups run, in fp32 3.6 us (d = 64) and 11 us (d = 128), a segment's share of the
         // pre-pass half of that, pre-pass and scan about 6 to 9 us more.  Measured in us at 1000 tokens with 4, 3, 2 chunks per
         // segment: bf16, 32 heads, d = 128 47, 43, 47; 8 heads 43, 38, 36; 4 heads, d = 64 35, 30, 27; fp32, 32 heads, d = 128
         // 165, 132, 108; fp32, 4 heads, d = 64, 256 tokens whole and with 2, 1 chunks: 39, 36, 24.
@@ -2686,13 +2689,14 @@ bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t avail
             // 60 of 1000 39 / 42, 8 of 8000 54 / 61; 24 of 4000 59 / 55, 60 of 1500 49 / 47.
             if (chip_slots(d) == 512 && 10 * chunks_of(256 / BH) <= 17 * cps) cps = chunks_of(256 / BH);
             // fp32, short: the cut saves steps of the chain and costs the pre-pass, its launches and the slots (us, whole / in
-            // segments of one chunk: 128 tokens, d = 64, 4 heads 20.9 / 22.5, 64 heads 21.6 / 26.4; 180 tokens, 4 heads 29.6 / 23.5;
-            // 128 tokens, d = 128, 8 heads 50.0 / 47.2, 32 heads 51.1 / 52.3, 96 heads 53.4 / 61.1; 180 tokens, 32 heads 73 / 54)
+            // segments of one chunk: 128 tokens, d = 64, 4 heads 18.7 / 21.8, 64 heads 19.4 / 25.0; 160 tokens, 4 heads 22.2 / 22.4, 32
+            // heads 22.7 / 24.3; 180 tokens, 4 heads 25.8 / 22.6, 64 heads 26.4 / 27.5; 128 tokens, d = 128, 8 heads 49.4 / 46.0, 32 heads
+            // 50.3 / 51.2, 96 heads 53.6 / 60.8; 180 tokens, 32 heads 72.2 / 53.7)
             if (f32 && P < 2) {
                 const PrefillCosts c = prefill_costs(d);
                 const int64_t steps = (T + 31) / 32, chain = cps * C / 32 < steps ? cps * C / 32 : steps;
                 const double launches = d.d_k == 64 ? 6.1 : 9.1;
-                if (static_cast<double>(steps - chain) * c.step <= chain * c.pre + launches + c.slot * BH * ((nchunks + cps - 1) / cps))
+                if (static_cast<double>(steps - chain) * c.step_alone <= chain * c.pre + launches + c.slot * BH * ((nchunks + cps - 1) / cps))
                     cps = nchunks;
             }
             P = (nchunks + cps - 1) / cps;
@@ -2781,8 +2785,9 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
             const double cuts = static_cast<double>(total_T) / L * d.H, items = cuts + static_cast<double>(d.B) * d.H;
             auto cut_pays = [&](const PrefillCosts &c) {
                 auto loop = [&](double chain, double workgroups) {
+                    const double step = workgroups <= 256 ? c.step_alone : c.step;
                     const double spread = workgroups / chip * c.wg + steps * d.H / chip * c.step_full;
-                    return spread > c.wg + chain * c.step ? spread : c.wg + chain * c.step;
+                    return spread > c.wg + chain * step ? spread : c.wg + chain * step;
                 };
                 const double whole = loop(longest, static_cast<double>(d.B) * d.H);
                 return whole > c.lists + c.wg + (cuts > chip ? cuts / chip : 1.0) * n * c.pre + c.slot * cuts + loop(n, items);
