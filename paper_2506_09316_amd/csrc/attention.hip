@@ -375,7 +375,9 @@ hipError_t launch_attn_decode_t(int B, int H, int64_t T, const EntropyPlan &plan
     const bool one = sizeof(TIO) == 2 && plan.parts == 2 && BH <= 256 &&
                      (D == 128 ? (BH >= 32 && T <= 400) || (BH > 192 && T <= 1200) : BH > 192 && T <= 3600);
     const int parts = one ? 1 : plan.parts;
-    auto kernel = one ? attn_decode_kernel<D, TIO, 1024> : attn_decode_kernel<D, TIO, kEntThreads>;
+    auto kernel = attn_decode_kernel<D, TIO, kEntThreads>;
+    if constexpr (sizeof(TIO) == 2)   // (built for 16 bits only)
+        if (one) kernel = attn_decode_kernel<D, TIO, 1024>;
     if (parts == 1) ps.e1_first = ps.e1;   // no merge kernel follows: the first launch closes the record too
     DSLA_LAUNCH_FIRST(ps, kernel, dim3(static_cast<unsigned>(BH) * parts), dim3(one ? 1024 : kEntThreads), 0,
                        stream, static_cast<const TIO *>(q_last), static_cast<const TIO *>(k), static_cast<const TIO *>(v),

@@ -2507,8 +2507,9 @@ template <int D, class TIO, class TG>
 hipError_t launch_t(const dsla_desc &d, const PrefillPlan &plan, PrefillArgs &a, hipStream_t stream)
 {
     if (a.beta) return launch_x<D, TIO, TG, true, true>(d, plan, a, stream);
-    if (a.explicit_w || a.accumulate || a.Hkv != a.H) return launch_x<D, TIO, TG, true>(d, plan, a, stream);
-    return launch_x<D, TIO, TG, false>(d, plan, a, stream);
+    if constexpr (std::is_same<TIO, float>::value) return launch_x<D, TIO, TG, true>(d, plan, a, stream);   // (F32Kern is one for all of them)
+    else if (a.explicit_w || a.accumulate || a.Hkv != a.H) return launch_x<D, TIO, TG, true>(d, plan, a, stream);
+    else return launch_x<D, TIO, TG, false>(d, plan, a, stream);
 }
 
 template <int D, class TIO>
