@@ -50,20 +50,26 @@ def test_carried_states_short_last_segment(io, d, chunk):
         check(f"packed S1[seq {b}]", S1[sl:sl + 1].cpu().numpy(), rS1, TOL[io])
         check(f"packed S2[seq {b}]", S2[sl:sl + 1].cpu().numpy(), rS2, TOL[io])
 
-@pytest.mark.parametrize("io,d,B,H,T,chunk,init", [("bf16", 128, 4, 32, 1024, 0, False), ("bf16", 128, 3, 32, 1500, 64, True),
+@pytest.mark.parametrize("io,d,B,H,T,chunk,init", [("bf16", 128, 4, 32, 1792, 0, False), ("bf16", 128, 3, 32, 1500, 64, True),
                                                    ("f32", 64, 2, 4, 512, 64, True), ("f32", 128, 1, 2, 700, 64, True),
                                                    ("bf16", 128, 2, 2, 1400, 128, False)])
 def test_prefill_pre_pass_on_half_segments(io, d, B, H, T, chunk, init):
     """Plans of two segments that the library makes itself (no segment count given): the pre-pass, which would have a
     workgroup for at most half of the compute units, works on the two halves of the first segment, the scan combines
-    them and the second segment of the chunk loop starts from slot 2.  The workspace size shows that the case is one
-    of those (3 state slots and 2 decay vectors per (sequence, head)); the results are held to the oracle like any
-    other."""
+    them and the second segment of the chunk loop starts from slot 2.  The workspace size (3 state slots and 2 decay vectors
+    per (sequence, head)) and the launches of the call show that the case is one of those (a call that runs whole may ask
+    for the same size); the results are held to the oracle like any other."""
     gd = "bf16" if io == "bf16" else "f32"
     desc = dsla.make_desc(B, H, d, d, io_dtype=code(io), gate_dtype=code(gd), chunk=chunk)
     decay = 2 * B * H * 2 * d * 4
     assert dsla.dsla_prefill_workspace_bytes(desc, T) == 3 * B * H * 2 * d * d * 4 + (decay + 255) // 256 * 256
-    run_prefill_case(B, T, H, d, io, gd, chunk=chunk, segments=0, gamma=0.35, seed=91, init=init, qk_scale=d ** -0.5)
+    dsla.profile_enable(True, 16)
+    try:
+        run_prefill_case(B, T, H, d, io, gd, chunk=chunk, segments=0, gamma=0.35, seed=91, init=init, qk_scale=d ** -0.5)
+        launches = {n: count for n, (_, count) in dsla.profile_collect().items()}
+    finally:
+        dsla.profile_enable(False)
+    assert [launches[n] for n in ("prefill_segment_state", "prefill_segment_scan", "prefill_chunk_loop")] == [1, 1, 1]
 
 
 @pytest.mark.parametrize("B,H,d,T,chunk", [(1, 4, 128, 257, 64), (1, 8, 128, 704, 64), (1, 32, 128, 520, 64), (2, 48, 128, 641, 64),
@@ -404,6 +410,26 @@ def test_prefill_fp32_d64_heads_per_compute_unit(B, H, T, segments):
     up to there further wavefronts prepare the operands, past it the multiplying ones.  TOL["f32"] = 1e-4, sums as above."""
     run_prefill_case(B, T, H, 64, "f32", "f32", chunk=32, segments=segments, gamma=0.4, scale=0.9, seed=5 + H, init=True,
                      qk_scale=64 ** -0.5)
+
+
+@pytest.mark.parametrize("H,segments", [(256, 1), (257, 1), (129, 3)])
+@pytest.mark.parametrize("preact", [False, True])
+def test_prefill_fp32_d64_16_bit_gates_per_compute_unit(H, segments, preact):
+    """The same switch under gates of 16 bits, as log-gates and as pre-activations."""
+    T, tau = 80, 16.0
+    if not preact:
+        run_prefill_case(1, T, H, 64, "f32", "bf16", chunk=32, segments=segments, gamma=0.4, scale=0.9, seed=6 + H, init=True,
+                         qk_scale=64 ** -0.5)
+        return
+    x = wl.layer_inputs(6 + H, 1, T, H, 64, 64, io_dtype="f32", gate_dtype="bf16", gates="preact", qk_scale=64 ** -0.5, tau=tau)
+    lg = {n: orc.log_gates_from_preactivations(x[n], tau) for n in ("g1", "g2")}
+    layer = GpuLayer(1, H, 64, "f32", "bf16", gamma=0.4, chunk=32, segments=segments, gate_mode=1, tau=tau)
+    o = layer.prefill(x)
+    S1, S2 = layer.states()
+    ro, rS1, rS2 = orc.recurrent(x["q"], x["k"], x["v"], lg["g1"], lg["g2"], 0.4)
+    check("o", o, ro, TOL["f32"])
+    check("S1", S1, rS1, TOL["f32"])
+    check("S2", S2, rS2, TOL["f32"])
 
 
 @pytest.mark.parametrize("io,gd,d", [("f32", "f32", 64), ("bf16", "f32", 128), ("bf16", "bf16", 128), ("f32", "f32", 128)])

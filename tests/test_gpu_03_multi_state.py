@@ -74,7 +74,7 @@ def test_decode_multi_equals_decode_for_two_states():
     (4, 2, "bf16", "bf16", 128, 1100, 0, ()), (4, 4, "f32", "bf16", 128, 150, 2, ()), (8, 2, "bf16", "f32", 64, 450, 2, ()),
     (1, 4, "f32", "f32", 64, 300, 2, (0,)), (1, 4, "bf16", "bf16", 128, 500, 3, (0,)), (2, 2, "f32", "f32", 128, 170, 1, (0, 1)),
     (3, 1, "bf16", "bf16", 128, 900, 2, (1,)), (4, 4, "bf16", "f32", 64, 257, 2, (0, 3)), (2, 4, "f32", "f32", 64, 31, 1, (1,)),
-    # plans of the library's own with two segments: the pre-pass works on the halves of the first one
+    # plans of the library's own: short segments in 16 bits; two in 32 bits, the pre-pass on the halves of the first one
     (3, 2, "bf16", "bf16", 128, 700, 0, (1,)), (2, 4, "f32", "f32", 64, 700, 0, (0,))])
 def test_prefill_multi(N, Hkv, io, gd, d, T, segments, beta):
     """N states through the prefill kernels (two at a time without a beta gate, one at a time with one), grouped
@@ -109,6 +109,28 @@ def test_prefill_multi(N, Hkv, io, gd, d, T, segments, beta):
     check("o decode", do.float().cpu().numpy()[:, None], ro[:, T:], tol)
     for n in range(N):
         check(f"S[{n}]", S[n].cpu().numpy(), rS[n], tol)
+
+
+@pytest.mark.parametrize("gd", ["f32", "bf16"])
+@pytest.mark.parametrize("H,segments", [(128, 1), (130, 1), (130, 2)])
+def test_prefill_multi_fp32_heads_per_compute_unit(H, segments, gd):
+    """fp32, d = 64, workgroups on both sides of one to a compute unit (256): explicit blend coefficients, a second pair of states
+    that adds to the output, grouped key/value heads, in the step loop and in the pre-pass."""
+    import torch
+    N, B, Hkv, d, T = 3, 2, H // 2, 64, 75
+    q, k, v, ga, gb, w, S0 = _inputs(360 + H, N, B, T, H, Hkv, d, "f32", gd, False)
+    desc = dsla.make_desc(B, H, d, d, io_dtype=code("f32"), gate_dtype=code(gd), scale=0.9, chunk=32, segments=segments)
+    S = [torch.from_numpy(S0[n].copy()).cuda() for n in range(N)]
+    multi = dsla.make_multi([to_gpu(ga[n], gd) for n in range(N)], S, w, H_kv=Hkv)
+    tq, tk, tv = to_gpu(q, "f32"), to_gpu(k, "f32"), to_gpu(v, "f32")
+    o = torch.full((B, T, H, d), float("nan"), device="cuda", dtype=tq.dtype)
+    ws = torch.empty(dsla.dsla_prefill_multi_workspace_bytes(desc, multi, T), dtype=torch.uint8, device="cuda")
+    dsla.dsla_prefill_multi(desc, multi, T, tq, tk, tv, o, ws)
+    torch.cuda.synchronize()
+    ro, rS = orc.nstate(q, k, v, ga, None, w, 0.9, S=S0)
+    check("o", o.cpu().numpy(), ro, TOL["f32"])
+    for n in range(N):
+        check(f"S[{n}]", S[n].cpu().numpy(), rS[n], TOL["f32"])
 
 
 @pytest.mark.parametrize("beta", [(), (1,)])
