@@ -87,12 +87,10 @@ __device__ __forceinline__ void wait_loads()   // at most N of this wavefront's 
 // and a handful of panels of W instead of one panel of W and dozens of x.  M = 16384, K = 4096, N = 20480 with GM = 4, 6, 8,
 // 16: 1.98, 1.99, 2.09, 2.24 ms.  Each group reads all of W, so a last group of one or two row tiles after a single full
 // one is worth avoiding (group_rows()): M = 1060, K = 11008, N = 20480 in 4 + 1 and 5 row tiles 562 and 509 us.
-// Runs are multiples of `unit` tiles (tile_order()).  False: no tile for this workgroup.
-__host__ __device__ __forceinline__ long long tiles_per_xcd(long long ntiles, int unit) { return ((ntiles + 7) / 8 + unit - 1) / unit * unit; }
-__device__ __forceinline__ bool tile_of(int tiles_m, int tiles_n, int GM, int unit, int &tm, int &tn)
+// False: no tile for this workgroup.
+__device__ __forceinline__ bool tile_of(int tiles_m, int tiles_n, int GM, long long per_xcd, int &tm, int &tn)
 {
     const long long ntiles = static_cast<long long>(tiles_m) * tiles_n;
-    const long long per_xcd = tiles_per_xcd(ntiles, unit);
     const long long lin = static_cast<long long>(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
     if (lin >= ntiles) return false;
     const long long per_group = static_cast<long long>(GM) * tiles_n;
@@ -136,7 +134,8 @@ constexpr int ROWB = BK * 2;                     // bytes per LDS row: 64
 template <int Q, int KS>
 __global__ __launch_bounds__(256, Q == 4 ? 1 : 2) void project_tile_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ w,
                                                                  const float *__restrict__ bias, ProjectOuts outs, long long M,
-                                                                 int K, int N, int width, int tiles_m, int tiles_n, int group, int unit)
+                                                                 int K, int N, int width, int tiles_m, int tiles_n, int group,
+                                                                 long long per_xcd)
 {
     constexpr int BM = 64 * Q, BN = BM, QS = 32 * Q;   // workgroup tile, quadrant
     constexpr int OPB = BM * ROWB;                      // bytes per operand tile and block of 32 values of K
@@ -148,7 +147,11 @@ __global__ __launch_bounds__(256, Q == 4 ? 1 : 2) void project_tile_kernel(const
     __shared__ __attribute__((aligned(1024))) char st2[STAGEB];
     __shared__ __attribute__((aligned(1024))) char st3[STAGEB];
     int tm, tn;
-    if (!tile_of(tiles_m, tiles_n, group, unit, tm, tn)) return;
+    if (Q > 1 || group > 0) {
+        if (!tile_of(tiles_m, tiles_n, group, per_xcd, tm, tn)) return;
+    } else if (!tile_of(tiles_n, tiles_m, -group, per_xcd, tn, tm)) {
+        return;
+    }
     const long long m0 = static_cast<long long>(tm) * BM;
     const int n0 = tn * BN;
 
@@ -300,7 +303,7 @@ __global__ __launch_bounds__(256) void project_kernel(const bf16_t *__restrict__
     __shared__ __attribute__((aligned(16))) bf16_t sB[2][TN * PITCH];
 
     int tm, tn;
-    if (!tile_of(tiles_m, tiles_n, group, 1, tm, tn)) return;
+    if (!tile_of(tiles_m, tiles_n, group, (static_cast<long long>(tiles_m) * tiles_n + 7) / 8, tm, tn)) return;
     const long long m0 = static_cast<long long>(tm) * TM;
     const int n0 = tn * TN;
 
@@ -556,15 +559,22 @@ int group_rows(int tiles_m, int whole) { return tiles_m <= whole ? tiles_m : 4; 
 // step, and with one tile to a compute unit the slowest is the call.  Two row tiles: runs of whole pairs (M = 96, K = 7936,
 // N = 2816 37.4 us with pairs split between two XCDs, 35.4 in the row kernel, 30.5 so).  More tiles than units, up to 15 row tiles: all of
 // them are one group, in runs of whole columns (M = 371, K = 1536, N = 3456 in 4 + 2 and 6 row tiles 14.3 and 10.7 us, 128 x 128
-// tiles 10.9; M = 960, K = 2048, N = 1152 in 4 + 4 + 4 + 3 and 15 16.7 and 13.5, 12.9).  400 random products of 257 to 400 tiles: slower
-// than 128 x 128 tiles by more than 3 % in 5 (all of 16 row tiles and more, or K = 8192), in groups of four in about 65.  Not for K >= 4096, where the tiles of a column
-// drift apart (K = 8192 2.5 % slower on average), nor for up to 256 tiles of three and more row tiles, where a whole column may be
-// one tile too many for an XCD's 32 units (up to 26 %).
+// tiles 10.9; M = 960, K = 2048, N = 1152 in 4 + 4 + 4 + 3 and 15 16.7 and 13.5, 12.9); up to 15 column tiles: the same the other way
+// round, runs of whole rows, which share those of x (a negative group; M = 1959, K = 2048, N = 640 17.5 and 13.0, 13.7).  800 random products
+// of 257 to 400 tiles: slower than 128 x 128 tiles by more than 3 % in about 1 of 100 (16 and more tiles both ways, or K = 8192), in
+// groups of four in 16 of 100.  Not for K >= 4096, where the tiles of a column drift apart (K = 8192 2.5 % slower on average), nor for
+// up to 256 tiles of three and more row tiles, where a whole column may be one tile too many for an XCD's 32 units (up to 26 %).
 void tile_order(int tiles_m, int tiles_n, int K, int &group, int &unit)
 {
-    const bool columns = K < 4096 && tiles_m <= 15 && static_cast<long long>(tiles_m) * tiles_n > 256;
-    group = columns ? tiles_m : group_rows(tiles_m, 5);
-    unit = columns || tiles_m == 2 ? group : 1;
+    const bool many = K < 4096 && static_cast<long long>(tiles_m) * tiles_n > 256;
+    group = group_rows(tiles_m, 5);
+    unit = tiles_m == 2 ? group : 1;
+    if (many && tiles_m <= 15) {
+        group = unit = tiles_m;
+    } else if (many && tiles_n <= 15) {
+        group = -tiles_n;
+        unit = tiles_n;
+    }
 }
 
 template <int MT, int NT>
@@ -607,10 +617,11 @@ void launch_tiles(ProfileScope &ps, int64_t M, int K, int N, int width, const vo
     const long long ntiles = static_cast<long long>(tiles_m) * tiles_n;
     int group = group_rows(tiles_m, 5), unit = 1;
     if (Q == 1) tile_order(tiles_m, tiles_n, K, group, unit);
-    const unsigned grid = static_cast<unsigned>(8 * tiles_per_xcd(ntiles, unit));
+    const long long per_xcd = ((ntiles + 7) / 8 + unit - 1) / unit * unit;
+    const unsigned grid = static_cast<unsigned>(8 * per_xcd);
     DSLA_LAUNCH(ps, (project_tile_kernel<Q, KS>), dim3(grid), dim3(256), 0, stream, static_cast<const bf16_t *>(x),
                 static_cast<const bf16_t *>(w), bias, po, static_cast<long long>(M), K, N, width, tiles_m, tiles_n,
-                group, unit);
+                group, per_xcd);
 }
 }  // namespace
 

@@ -343,11 +343,12 @@ def test_project_kernels(M, K, n_out, width):
 
 # 64 x 64 tiles (K a multiple of 256): one and several tiles with ragged last rows, one stage group and several; past them the 128 x 128
 # tiles; on both sides of the limits of 256 tiles for up to 128 rows and for short K, and of 400 for K >= 1024 (more workgroups than
-# compute units); two row tiles in runs of pairs, 6 and 15 row tiles in runs of whole columns, 16 in groups of four
+# compute units); two row tiles in runs of pairs, 6 and 15 row tiles in runs of whole columns, 15 column tiles in runs of whole rows, 16
+# by 18 in groups of four
 @pytest.mark.parametrize("M,K,n_out,width", [(65, 256, 1, 128), (127, 512, 3, 384), (128, 1280, 2, 256), (129, 256, 5, 512), (513, 768, 3, 128),
                                              (640, 512, 5, 512), (641, 512, 5, 512), (640, 1024, 5, 512), (641, 1024, 5, 512),
                                              (512, 512, 4, 512), (513, 512, 4, 512), (128, 256, 1, 8192), (128, 256, 1, 8320),
-                                             (331, 1280, 2, 1408), (957, 1024, 3, 384), (961, 1024, 3, 384)])
+                                             (331, 1280, 2, 1408), (957, 1024, 3, 384), (961, 1024, 3, 384), (1281, 1024, 7, 128), (2017, 1280, 2, 128)])
 def test_project_small_tiles(M, K, n_out, width):
     test_project_kernels(M, K, n_out, width)
 
