@@ -31,7 +31,7 @@
 #include <type_traits>
 #include <utility>
 
-#include "dsla_internal.h"
+#include "prefill_common.h"
 
 namespace dsla {
 namespace {
@@ -40,51 +40,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-
-constexpr float kLog2e = 1.4426950408889634f;
-
-// Workgroup barrier that orders LDS traffic only.  __syncthreads() would also wait for the global
-// loads of the next chunk that are deliberately left in flight across the contraction phases.
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_sched_barrier(0);   // phases are not interleaved by the instruction scheduler
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
-
-// ---------------------------------------------------------------------------------------------
-// LDS access by byte address.  Every LDS address below is "per-lane base register + compile-time
-// constant"; the bases are computed once and passed through opaque() so that the compiler keeps them
-// as they are instead of materialising one register per (base, constant) pair.
-// ---------------------------------------------------------------------------------------------
-#define DSLA_LDS __attribute__((address_space(3)))
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint32_t lds_addr_of(const void *p)
-{
-    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((DSLA_LDS const char *)p));
-}
-__device__ __forceinline__ uint32_t opaque(uint32_t x)
-{
-    asm volatile("" : "+v"(x));
-    return x;
-}
-template <class T>
-struct LdsPtr {
-    typedef T DSLA_LDS *type;   // pointer into LDS (32-bit)
-};
-template <class T>
-__device__ __forceinline__ T lds_ld(uint32_t a)
-{
-    return *reinterpret_cast<typename LdsPtr<const T>::type>(static_cast<uintptr_t>(a));
-}
-template <class T>
-__device__ __forceinline__ void lds_st(uint32_t a, T v)
-{
-    *reinterpret_cast<typename LdsPtr<T>::type>(static_cast<uintptr_t>(a)) = v;
-}
 
 // ---------------------------------------------------------------------------------------------
 // Arithmetic-type policies: how a contraction operand is stored in LDS and fed to MFMA.
@@ -381,45 +336,6 @@ __device__ __forceinline__ void pipelined_steps(AddrF addr, StepF step, uint32_t
 }
 
 // ---------------------------------------------------------------------------------------------
-struct PrefillArgs {
-    const void *q, *k, *v, *g1, *g2;
-    void *o;
-    float *S1, *S2;          // caller's states
-    // One workspace slot per (segment, sequence, head): slot = (p B + b) H + h, or with work lists
-    // (seg_first[b] + p) H + h.  The last segment of a sequence has no decay entry that anyone reads.
-    float *ws_state;         // [slot][2][D][D] fp32 (P > 1): state at the start of the segment
-    float *ws_decay;         // [slot][2][D] fp32 (P > 1): log2 of the decay over the segment
-    const float *gamma_per_head;
-    const int32_t *cu;       // packed sequences: [B + 1] token offsets (sequence b = tokens cu[b] .. cu[b+1]-1); or null
-    const int32_t *seq;      // with cu: [B] which of the packed sequences take part (entry b names sequence seq[b]); or null (all, in order)
-    const int32_t *slot;     // [B] index of each sequence's states in S1, S2; or null (sequence b uses entry b)
-    // Packed sequences cut into segments: the work lists written by segment_list_kernel.  A workgroup is
-    // (list entry, head); entries past the count exit.  Null when every sequence is one segment or cu is null.
-    const int32_t *seg_first;   // [B + 1] index of the first segment of each sequence among all segments
-    const int32_t *seg_count;   // [2] entries in list_full, list_pre
-    const int2 *list_full;      // (sequence, segment) of every segment
-    const int2 *list_pre;       // (sequence, segment) of every segment that is followed by another one
-    int64_t T;               // tokens per sequence (cu == null); with cu: upper bound of the sequence lengths
-    int64_t seg_tokens;
-    int H;
-    int P;
-    int zero_init;           // nonzero: the states are zero on entry (the caller's S1, S2 are only written)
-    int32_t *status;         // optional device word: set to DSLA_STATUS_GATE_DOMAIN by a step whose gates leave the domain
-    float gamma, scale;
-    // Extended launches (Kern<.., kExt = true>): explicit blend coefficients of the two states instead of
-    // (gamma, 1 - gamma), key/value heads shared by groups of query heads, and output added to what o holds.
-    int Hkv;                 // key/value heads (k, v are [..][Hkv][D]); == H in ordinary launches
-    int explicit_w;          // nonzero: the blend coefficients are wa, wb (or the per-head arrays)
-    int accumulate;          // nonzero: o += result instead of o = result
-    int beta;                // nonzero (Kern<.., kBeta = true>): one state with the outer-product gate, see "Beta mode"
-    float wa, wb;
-    const float *wa_per_head, *wb_per_head;   // optional [H]
-    float gate_inv_tau;      // 0: g1, g2 are log-gates; else they are pre-activations and this is 1 / tau
-    int longest_first;       // chunk loop on whole packed sequences: workgroups take them in the order of their lengths
-    int slot_mul;            // chunk loop: segment p starts from workspace slot p * slot_mul (the pre-pass and the scan may
-                             // work on pieces of a segment: see PrefillPlan::pre_split)
-};
-
 // Workgroup layout: producer / consumer wavefronts.  4 D threads = D/8 wavefronts.  The first D/32
 // wavefronts are CONSUMERS: wavefront ct owns columns [32 ct, 32 ct + 32) of BOTH states for all d_k rows as fp32
 // MFMA accumulators and runs every contraction of a step.  The other D/32 wavefronts are PRODUCERS: they load
@@ -650,11 +566,7 @@ struct Kern {
     static __device__ __forceinline__ void activate(float (&g)[8])
     {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float y = g[e] * kLog2e;
-            const float l = __builtin_amdgcn_logf(1.0f + __builtin_amdgcn_exp2f(-__builtin_fabsf(y)));
-            g[e] = fminf(y, 0.f) - l;
-        }
+        for (int e = 0; e < 8; ++e) g[e] = log2_sigmoid(g[e]);
     }
     // stage A: sums over this thread's tokens; totals of the token pair -> scan scratch.
     // `valid` = tokens of the step that exist; tokens past the end act as "no decay".
@@ -713,8 +625,6 @@ struct Kern {
         }
         total = tot;
     }
-    // The largest exponent a step may produce: Q~ and K~ carry 2^{+-R/2}, and bf16 / fp32 hold 2^{+-126}.
-    static constexpr float kMaxStepLog2Decay = 230.f;
     // bookkeeping after stage B of a step: the segment's log2 decay, and the domain check
     static __device__ __forceinline__ void note_step(const ProdAddr &pa, float total, float &seg_log2_decay, int32_t *status)
     {
@@ -1828,7 +1738,7 @@ struct F32Kern {
                 tot = sum;
                 const float r = sum * unit;
                 seg_decay += r;
-                if (a.status && !(r >= -Base::kMaxStepLog2Decay)) *a.status = DSLA_STATUS_GATE_DOMAIN;
+                if (a.status && !(r >= -kMaxStepLog2Decay)) *a.status = DSLA_STATUS_GATE_DOMAIN;
             }
             Base::wave_sync();
             const f32x4 p0 = lds_ld<f32x4>(cs_own), p1 = lds_ld<f32x4>(cs_own + 16);
@@ -2611,6 +2521,19 @@ PrefillCosts refusal_costs(const dsla_desc &d)
 }
 }  // namespace
 
+namespace {
+// Estimate (us) of a dense fp32 call by its plan.  Estimated / measured: 256 tokens in four segments, d = 64, 4 and 32 heads 21.1 / 22.6 and
+// 24.3 / 24.8, d = 128, 8 and 32 heads 48 / 47 and 54 / 53; 512 tokens in two 47 / 47 and 123 / 124; whole, d = 64, 64 and 128 tokens 10.2 / 11.2 and 17.4 / 18.4, d = 128, 64 tokens 27.2 / 27.3.
+double plan_cost(const dsla_desc &d, const PrefillPlan &plan, int64_t T)
+{
+    const PrefillCosts c = prefill_costs(d);
+    const double groups = static_cast<double>(d.B) * d.H * plan.segments, rounds = groups > 256 ? groups / 256 : 1.0;
+    const double steps = static_cast<double>(((T < plan.segment_tokens ? T : plan.segment_tokens) + 31) / 32);
+    if (plan.segments == 1) return c.wg + rounds * steps * (groups > 256 ? c.step / 1.3 : c.step_alone);
+    return c.wg + (d.d_k == 64 ? 6.1 : 9.1) + rounds * steps * (c.pre / plan.pre_split + c.step_alone) + c.slot * groups;
+}
+}  // namespace
+
 bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t available)
 {
     const int C = plan_chunk(d);
@@ -2868,6 +2791,8 @@ hipError_t launch_prefill(const dsla_desc &d, const PrefillPlan &plan, int64_t T
     a.gamma = d.gamma;
     a.scale = d.scale;
     a.gate_inv_tau = d.gate_mode == DSLA_GATE_PREACT ? 1.0f / d.tau : 0.f;
+    if (!ext && !cu_seqlens && !state_slot && prefill_short_built(d) && prefill_short_cost(d, T) < plan_cost(d, plan, T))
+        return launch_prefill_short(d, a, stream);
     const int D = d.d_k;
     if (d.io_dtype == DSLA_BF16) {
         if (D == 128) return launch_g<128, bf16_t>(d, plan, a, stream);

@@ -173,6 +173,51 @@ def test_prefill_zero_init_does_not_read_the_states(io, d, segments, T):
     check("S2", S2, rS2, TOL[io])
 
 
+@pytest.mark.parametrize("d,gate,gates,B,H,T", [
+    (64, "f32", "log", 1, 4, 1), (64, "f32", "preact", 3, 2, 16), (64, "bf16", "log", 1, 4, 17), (64, "f32", "log", 1, 4, 255),
+    (64, "f32", "preact", 1, 4, 257), (64, "bf16", "preact", 1, 4, 272), (64, "f32", "log", 1, 2, 513), (128, "f32", "log", 1, 3, 2),
+    (128, "f32", "preact", 2, 3, 33), (128, "bf16", "log", 1, 4, 127), (128, "f32", "log", 1, 4, 128), (128, "f32", "log", 1, 4, 130),
+    (128, "bf16", "preact", 1, 4, 144), (128, "f32", "log", 1, 4, 300)])
+@pytest.mark.parametrize("resets", [False, True])
+def test_prefill_short_prompts_from_zero_states(d, gate, gates, B, H, T, resets):
+    """fp32 prompts whose tokens are tiles of 16 in one launch: one tile, a last one of a single token, one round of wavefronts
+    and one tile more (d = 64: 16 tiles, d = 128: 8), pairs of tiles that begin and end a step.  With tau = 1 gates; with single
+    tokens of log alpha = -150 at the edges of a tile, between which every exponent is centred.  The states hold NaN on entry."""
+    import torch
+    x = wl.layer_inputs(95, B, T, H, d, d, io_dtype="f32", gate_dtype=gate, gates=gates, qk_scale=d ** -0.5, tau=1.0)
+    if resets:
+        for n in ("g1", "g2"):
+            x[n][:] = -0.05 if gates == "log" else 2.97
+            for t in (15, 32, 95, 127, 128, 255, 256, 300):   # the last or first token of a tile, or inside one; each in a step of its own
+                if t < T:
+                    x[n][:, t, :, ::2] = -150.0
+            x[n] = wl.round_to_bf16(x[n]) if gate == "bf16" else x[n]
+    lg = {n: x[n] if gates == "log" else orc.log_gates_from_preactivations(x[n], 1.0) for n in ("g1", "g2")}
+    assert step_gate_sums(lg) < GATE_DOMAIN
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    layer = GpuLayer(B, H, d, "f32", gate, gamma=0.3, chunk=64, gate_mode=int(gates == "preact"), tau=1.0, status=status,
+                     zero_init=True, init=False)
+    o = layer.prefill(x)
+    S1, S2 = layer.states()
+    ro, rS1, rS2 = orc.recurrent(x["q"], x["k"], x["v"], lg["g1"], lg["g2"], 0.3)
+    check("o", o, ro, TOL["f32"])
+    check("S1", S1, rS1, TOL["f32"])
+    check("S2", S2, rS2, TOL["f32"])
+    assert int(status.item()) == 0
+
+
+def test_prefill_short_prompts_report_gates_outside_the_domain():
+    """log alpha = -90 in both tiles of a step: each is inside, their sum is not; the same in two steps is."""
+    import torch
+    for tokens, outside in (((40, 50), True), ((31, 32), False)):
+        x = wl.layer_inputs(96, 1, 70, 2, 64, 64, io_dtype="f32", gate_dtype="f32")
+        for t in tokens:
+            x["g2"][0, t, 1, 5] = -90.0
+        status = torch.zeros(1, dtype=torch.int32, device="cuda")
+        GpuLayer(1, 2, 64, "f32", "f32", status=status, zero_init=True, init=False).prefill(x)
+        assert (int(status.item()) != 0) == outside, tokens
+
+
 # ---------------------------------------------------------------- prefill, bf16
 
 
