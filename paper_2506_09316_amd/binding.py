@@ -2,6 +2,9 @@
 marshalling only.  Tensors are torch tensors on the GPU; their data pointers and the
 current torch HIP stream are handed to the library.  No computation happens here, and
 there is no fallback: if the library is missing, loading raises.
+
+The calls of a serving loop go through _marshal.so, the same in native code; arguments that
+it does not take (it then returns None) go the way written out here.
 """
 from __future__ import annotations
 
@@ -12,6 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(HERE, "libdsla.so")
 _lib = None
 _torch = None   # torch._C once the library is loaded
+_native = None  # _marshal once the library is loaded
 
 DSLA_F32, DSLA_BF16 = 0, 1
 KERNEL_NAMES = ("state_init", "prefill_segment_state", "prefill_segment_scan", "prefill_chunk_loop", "decode",
@@ -53,7 +57,7 @@ def library_path() -> str:
 
 def load_library():
     """Loads libdsla.so (built by paper_2506_09316_amd/build.py).  Raises if it is absent."""
-    global _lib, _torch
+    global _lib, _torch, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -122,6 +126,14 @@ def load_library():
     lib.dsla_profile_enable.restype = ctypes.c_int
     lib.dsla_profile_collect.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int64)]
     lib.dsla_profile_collect.restype = ctypes.c_int
+    if _torch is not None:
+        import torch
+        from . import _marshal
+        entries = (lib.dsla_decode, lib.dsla_decode_slots, lib.dsla_prefill, lib.dsla_prefill_varlen, lib.dsla_attention_decode,
+                   lib.dsla_attention_prefill, lib.dsla_project)
+        _marshal.bind(_torch._cuda_getDevice, _torch._cuda_getCurrentRawStream, torch.nn.Parameter,
+                      *[ctypes.cast(f, vp).value for f in entries])
+        _native = _marshal
     _lib = lib
     return lib
 
@@ -153,7 +165,7 @@ def _ptr(t):
 
 def _stream():
     """Handle of torch's current stream on its current device.  torch.cuda.current_stream() builds a Stream object: 3.0 us
-    against 0.2, in a decode call of one sequence that took 8.8 us on the host for 4 us on the GPU (now 5.4)."""
+    against 0.2, in a decode call of one sequence that took 8.8 us on the host for 4 us on the GPU (5.4 this way, 3.5 through _marshal)."""
     return _torch._cuda_getCurrentRawStream(_torch._cuda_getDevice())
 
 
@@ -178,8 +190,12 @@ def dsla_prefill_workspace_bytes(desc: DslaDesc, T: int) -> int:
 def dsla_prefill(desc: DslaDesc, T, q, k, v, g1, g2, S1, S2, o, workspace=None):
     """Chunked prefill over T tokens (include/dsla.h: dsla_prefill).  `workspace` is a uint8 GPU
     tensor of at least dsla_prefill_workspace_bytes(desc, T) bytes, or None when that is zero."""
+    lib = _lib or load_library()
+    status = _native.prefill(desc, T, q, k, v, g1, g2, S1, S2, o, workspace)
+    if status is not None:
+        return _check(status)
     wbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load_library().dsla_prefill(ctypes.byref(desc), int(T), _ptr(q), _ptr(k), _ptr(v), _ptr(g1), _ptr(g2),
+    _check(lib.dsla_prefill(ctypes.byref(desc), int(T), _ptr(q), _ptr(k), _ptr(v), _ptr(g1), _ptr(g2),
                                        _ptr(S1), _ptr(S2), _ptr(o), _ptr(workspace), wbytes, _stream()))
 
 
@@ -191,7 +207,11 @@ def dsla_prefill_static_ws(desc: DslaDesc, T, q, k, v, g1, g2, S1, S2, o):
 
 def dsla_decode(desc: DslaDesc, q, k, v, g1, g2, S1, S2, o):
     """One fused decode step (include/dsla.h: dsla_decode)."""
-    _check(load_library().dsla_decode(ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(g1), _ptr(g2),
+    lib = _lib or load_library()
+    status = _native.decode(desc, q, k, v, g1, g2, S1, S2, o)
+    if status is not None:
+        return _check(status)
+    _check(lib.dsla_decode(ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(g1), _ptr(g2),
                                       _ptr(S1), _ptr(S2), _ptr(o), _stream()))
 
 
@@ -203,15 +223,23 @@ def dsla_prefill_varlen(desc: DslaDesc, total_T, max_T, cu_seqlens, state_slot, 
                         workspace=None, seq_index=None):
     """Prefill of packed sequences (include/dsla.h: dsla_prefill_varlen).  cu_seqlens: int32 GPU tensor;
     state_slot, seq_index: int32 GPU tensors [B] or None."""
+    lib = _lib or load_library()
+    status = _native.prefill_varlen(desc, total_T, max_T, cu_seqlens, seq_index, state_slot, q, k, v, g1, g2, S1, S2, o, workspace)
+    if status is not None:
+        return _check(status)
     wbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load_library().dsla_prefill_varlen(ctypes.byref(desc), int(total_T), int(max_T), _ptr(cu_seqlens),
+    _check(lib.dsla_prefill_varlen(ctypes.byref(desc), int(total_T), int(max_T), _ptr(cu_seqlens),
                                               _ptr(seq_index), _ptr(state_slot), _ptr(q), _ptr(k), _ptr(v), _ptr(g1), _ptr(g2),
                                               _ptr(S1), _ptr(S2), _ptr(o), _ptr(workspace), wbytes, _stream()))
 
 
 def dsla_decode_slots(desc: DslaDesc, q, k, v, g1, g2, state_slot, S1, S2, o, row_index=None):
     """One decode step on states picked from a pool (include/dsla.h: dsla_decode_slots)."""
-    _check(load_library().dsla_decode_slots(ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(g1), _ptr(g2),
+    lib = _lib or load_library()
+    status = _native.decode_slots(desc, q, k, v, g1, g2, row_index, state_slot, S1, S2, o)
+    if status is not None:
+        return _check(status)
+    _check(lib.dsla_decode_slots(ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(g1), _ptr(g2),
                                             _ptr(row_index), _ptr(state_slot), _ptr(S1), _ptr(S2), _ptr(o), _stream()))
 
 
@@ -272,9 +300,13 @@ def dsla_attention_decode_workspace_bytes(B: int, H: int, d: int, T: int) -> int
 def dsla_attention_decode(q, k, v, o, scale: float, workspace=None, seq_lens=None):
     """Single-query softmax attention over cached keys and values (include/dsla.h: dsla_attention_decode).
     q, o [B,H,d]; k, v [B,T,H,d] (all bf16 or all fp32 GPU tensors); seq_lens: int32 GPU tensor [B] or None."""
+    lib = _lib or load_library()
+    status = _native.attention_decode(q, k, v, o, scale, workspace, seq_lens)
+    if status is not None:
+        return _check(status)
     B, T, H, d = k.shape
     wbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load_library().dsla_attention_decode(int(B), int(H), int(d), int(T), _dtype_code(k), float(scale),
+    _check(lib.dsla_attention_decode(int(B), int(H), int(d), int(T), _dtype_code(k), float(scale),
                                                 _ptr(q), _ptr(k), _ptr(v), _ptr(seq_lens), _ptr(o), _ptr(workspace), wbytes,
                                                 _stream()))
 
@@ -282,6 +314,10 @@ def dsla_attention_decode(q, k, v, o, scale: float, workspace=None, seq_lens=Non
 def dsla_project(x, W, outs, bias=None):
     """The projections in front of a layer as one GEMM (include/dsla.h: dsla_project).  x [M,K] bf16; W [n_out*width,K]
     bf16; outs: list of n_out bf16 GPU tensors of M*width elements each; bias: fp32 GPU tensor [n_out*width] or None."""
+    lib = _lib or load_library()
+    status = _native.project(x, W, outs, bias)
+    if status is not None:
+        return _check(status)
     M, K = x.shape
     n_out = len(outs)
     width = W.shape[0] // n_out
@@ -289,13 +325,17 @@ def dsla_project(x, W, outs, bias=None):
     po = (ctypes.c_void_p * n_out)(*[t.data_ptr() for t in outs])
     for t in outs:
         assert t.is_cuda and t.is_contiguous()
-    _check(load_library().dsla_project(int(M), int(K), n_out, int(width), _ptr(x), _ptr(W), _ptr(bias), po, _stream()))
+    _check(lib.dsla_project(int(M), int(K), n_out, int(width), _ptr(x), _ptr(W), _ptr(bias), po, _stream()))
 
 
 def dsla_attention_prefill(q, k, v, o, scale: float):
     """Causal softmax attention over a prompt (include/dsla.h: dsla_attention_prefill).  q, k, v, o: [B,T,H,d] bf16."""
+    lib = _lib or load_library()
+    status = _native.attention_prefill(q, k, v, o, scale)
+    if status is not None:
+        return _check(status)
     B, T, H, d = q.shape
-    _check(load_library().dsla_attention_prefill(int(B), int(H), int(d), int(T), _dtype_code(q), float(scale), _ptr(q),
+    _check(lib.dsla_attention_prefill(int(B), int(H), int(d), int(T), _dtype_code(q), float(scale), _ptr(q),
                                                  _ptr(k), _ptr(v), _ptr(o), _stream()))
 
 

@@ -1,4 +1,5 @@
-"""Builds libdsla.so (the C-ABI library) from csrc/ with hipcc for gfx950, in-tree.
+"""Builds libdsla.so (the C-ABI library) from csrc/ with hipcc for gfx950, and _marshal.so (its hot calls for
+binding.py, against PyTorch's headers) with g++, in-tree.
 
 The translation units are compiled in parallel and linked into
 paper_2506_09316_amd/libdsla.so.  hipcc cross-compiles without a GPU.
@@ -6,11 +7,13 @@ paper_2506_09316_amd/libdsla.so.  hipcc cross-compiles without a GPU.
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdsla.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 SOURCES = ["api.hip", "decode.hip", "attention.hip", "attention_prefill.hip", "controller.hip", "project.hip", "prefill_short.hip", "prefill.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -23,6 +26,16 @@ FLAGS = [
 ]
 
 
+def _marshal_command():
+    import torch
+    root = os.path.dirname(torch.__file__)
+    include = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+               sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
+    return ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-w",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *[x for i in include for x in ("-isystem", i)],
+            os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL, "-L" + os.path.join(root, "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"]
+
+
 def build(verbose: bool = False, extra_flags=()) -> str:
     objs, procs = [], []
     for src in SOURCES:
@@ -30,6 +43,7 @@ def build(verbose: bool = False, extra_flags=()) -> str:
         cmd = [HIPCC, *FLAGS, *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    procs.append(("marshal.cpp", subprocess.Popen(_marshal_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     failed = False
     for src, p in procs:
         out, _ = p.communicate()
@@ -40,7 +54,7 @@ def build(verbose: bool = False, extra_flags=()) -> str:
         elif verbose and out.strip():
             sys.stderr.write(f"--- {src} ---\n{out}\n")
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("compilation failed")
     link = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(link, check=True)
     return LIB

@@ -269,3 +269,30 @@ def test_packed_workspace_of_a_large_batch_serves_smaller_ones(lib):
         for part in (2, 3, 5):
             assert big >= 0.9 * ask(B, H, d, max(total // part, longest), longest) > 0
     assert ask(40, 32, 128, 3460, 600) == 0 and ask(300, 32, 128, 30000, 256) == 0
+
+
+def test_native_calls_leave_unusual_arguments_to_the_general_way():
+    """The native calls answer None, with no exception pending, for anything but contiguous GPU tensors and plain numbers; the
+    general way then refuses or takes it as it always has."""
+    import torch
+    dsla.load_library()
+    native = dsla.binding._native
+    desc = dsla.make_desc(1, 4, 64, 64, io_dtype=0, gate_dtype=0, chunk=64)
+    x, S = torch.zeros(1, 4, 64), torch.zeros(1, 4, 64, 64)
+    for odd in (x, x.transpose(1, 2), torch.nn.Parameter(x), None, 1, "x", x.numpy()):
+        assert native.decode(desc, odd, x, x, x, x, S, S, x) is None
+        assert native.prefill(desc, 1, x, x, x, x, x, S, S, x, odd) is None
+    assert native.decode() is None and native.decode(desc, x) is None and native.decode(3, *[x] * 8) is None
+    assert native.decode_slots(desc, *[x] * 5, None, x, S, S, x) is None
+    assert native.prefill(desc, 2.0, *[x] * 8, None) is None and native.prefill(desc, 1 << 70, *[x] * 8, None) is None
+    assert native.prefill_varlen(desc, 1, 1, x, None, None, *[x] * 8, None) is None
+    assert native.attention_decode(x, x, x, x, 1.0, None, None) is None and native.attention_prefill(x, x, x, x, 1) is None
+    assert native.project(x, x, [x], None) is None and native.project(x, x, (x,), None) is None
+    with pytest.raises(AssertionError):
+        dsla.dsla_decode(desc, x, x, x, x, x, S, S, x)
+    with pytest.raises(AssertionError):
+        dsla.dsla_project(x[0], x[0], [x])
+    with pytest.raises(AttributeError):
+        dsla.dsla_prefill(desc, 1, 3, x, x, x, x, S, S, x)
+    with pytest.raises(ValueError):
+        dsla.dsla_attention_prefill(x, x, x, x, 1.0)
