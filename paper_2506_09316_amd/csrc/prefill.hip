@@ -317,6 +317,12 @@ __device__ __forceinline__ void store4_global(float *p, float a, float b, float 
     *reinterpret_cast<f32x4 *>(p) = f32x4{a, b, c, d};
 }
 
+// Keeps the computation of x where it stands.  Without it the compiler gathers the MFMAs of one accumulator and lets each wait for
+// an LDS read that it issues right before (scheduling barriers alone come too late: the order is gone before they count, and the
+// fragments kept for later spill 112 registers).  A step of a consumer alone 2.1 -> 1.2 us, registers 255 -> 235; the producers, 1.9 us,
+// bound a step then as before: 8 x 8192 tokens 711 -> 701 us, 16384 tokens 273.7 -> 270.7, 1000 on carried states 49.9 -> 49.4.
+__device__ __forceinline__ void stay(f32x16 &x) { asm volatile("" : "+v"(x) : : "memory"); }
+
 // Software-pipelined sequence of N steps: the LDS fragment of step s + DEPTH is requested before the
 // MFMA of step s is issued, so that LDS latency overlaps DEPTH matrix instructions.  Fully unrolled.
 // kTr: the fragments come from rows by two transposing reads, the second TR_STEP bytes (two row slots) further.
@@ -332,6 +338,7 @@ __device__ __forceinline__ void pipelined_steps(AddrF addr, StepF step, uint32_t
         const typename ARITH::Frag cur = buf[s % DEPTH];
         if (s + DEPTH < N) buf[s % DEPTH] = load(s + DEPTH);
         step(s, cur);
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -1066,6 +1073,8 @@ struct Kern {
                             const int kb = s2 >> 1, i = kb / (2 * DT), dt = (kb / 2) % DT, half = kb & 1;
                             A::mma(sc, held, f);
                             A::mma(oacc, A::from_acc(acc[i][dt], half), f);
+                            stay(sc);
+                            stay(oacc);
                         }
                     });
             }
@@ -1078,12 +1087,12 @@ struct Kern {
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) A::mma(oacc, vf[kb], A::from_acc(sc, kb));
         }
-        __builtin_amdgcn_sched_barrier(0);   // the instruction groups requested below start here
+        __builtin_amdgcn_sched_barrier(0);
 
         // ---- add K~^T V (the output tile finishes in the matrix pipeline meanwhile) ----
         {
             constexpr int NS = KB * NST * DT;   // (token block, state, tile)
-            pipelined_steps<NS, 4, A, kTrK>(
+            pipelined_steps<NS, 6, A, kTrK>(
                 [&](int s2) -> uint32_t {
                     const int kb = s2 / (NST * DT), i = (s2 / DT) % NST, dt = s2 % DT;
                     if constexpr (kTrK) return ktr_r + (16 * kb * QP + i * D + 32 * dt) * ESZ;
@@ -1092,16 +1101,9 @@ struct Kern {
                 [&](int s2, const Frag &f) {
                     const int kb = s2 / (NST * DT), i = (s2 / DT) % NST, dt = s2 % DT;
                     A::mma(acc[i][dt], f, vf[kb]);
+                    stay(acc[i][dt]);
                 },
                 2 * QP * ESZ);
-            constexpr int RD = ESZ == 2 ? 1 : 2, MM = ESZ == 2 ? 1 : 8;
-            __builtin_amdgcn_sched_group_barrier(0x100, 4 * RD, 0);
-#pragma unroll
-            for (int s2 = 0; s2 < NS - 4; ++s2) {
-                __builtin_amdgcn_sched_group_barrier(0x008, MM, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, RD, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, 4 * MM, 0);
         }
 
         // ---- store: lane (ln, g) holds query ln, columns 32 ct + 8 jb + 4 g .. + 3 ----
