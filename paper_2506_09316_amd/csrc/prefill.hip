@@ -28,6 +28,7 @@
 // the contraction index (bits 2 and 3 of the feature index swapped).
 #include <cstdio>
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -320,13 +321,15 @@ __device__ __forceinline__ void store4_global(float *p, float a, float b, float 
 // Keeps the computation of x where it stands.  Without it the compiler gathers the MFMAs of one accumulator and lets each wait for
 // an LDS read that it issues right before (scheduling barriers alone come too late: the order is gone before they count, and the
 // fragments kept for later spill 112 registers).  A step of a consumer alone 2.1 -> 1.2 us, registers 255 -> 235; the producers, 1.9 us,
-// bound a step then as before: 8 x 8192 tokens 711 -> 701 us, 16384 tokens 273.7 -> 270.7, 1000 on carried states 49.9 -> 49.4.
+// bound a step then as before: 8 x 8192 tokens 711 -> 701 us, 16384 tokens 273.7 -> 270.7, 1000 on carried states 49.9 -> 49.4.  At d = 64 two
+// workgroups share a compute unit and the compiler's order is the better one (32 heads of 2000 tokens 39.2, this 40.4).
 __device__ __forceinline__ void stay(f32x16 &x) { asm volatile("" : "+v"(x) : : "memory"); }
 
 // Software-pipelined sequence of N steps: the LDS fragment of step s + DEPTH is requested before the
 // MFMA of step s is issued, so that LDS latency overlaps DEPTH matrix instructions.  Fully unrolled.
 // kTr: the fragments come from rows by two transposing reads, the second TR_STEP bytes (two row slots) further.
-template <int N, int DEPTH, class ARITH, bool kTr = false, class AddrF, class StepF>
+// kStay: the steps stay in this order (with stay() in each of them).
+template <int N, int DEPTH, class ARITH, bool kTr = false, bool kStay = false, class AddrF, class StepF>
 __device__ __forceinline__ void pipelined_steps(AddrF addr, StepF step, uint32_t tr_step = 0)
 {
     auto load = [&](int i) { return kTr ? ARITH::load_frag_tr(addr(i), tr_step) : ARITH::load_frag(addr(i)); };
@@ -338,7 +341,7 @@ __device__ __forceinline__ void pipelined_steps(AddrF addr, StepF step, uint32_t
         const typename ARITH::Frag cur = buf[s % DEPTH];
         if (s + DEPTH < N) buf[s % DEPTH] = load(s + DEPTH);
         step(s, cur);
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (kStay) __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -1019,6 +1022,7 @@ struct Kern {
         }
     }
 
+    static constexpr bool kStay = ESZ == 2 && D == 128;   // the order of the MFMAs is kept: see stay()
     static __device__ __forceinline__ void consume(uint32_t sm, uint32_t set, f32x16 (&acc)[2][DT], int ct, int lane,
                                                    TIO *orow, uint32_t rs, int valid, uint32_t set_parity, bool accumulate)
     {
@@ -1064,7 +1068,7 @@ struct Kern {
             for (int j = 0; j < 16; ++j) sc[j] = oacc[j] = 0.f;
             {
                 Frag held;   // the Ks fragment of a block waits here for its Qs partner
-                pipelined_steps<NST * NK, 8, A>(
+                pipelined_steps<NST * NK, 8, A, false, kStay>(
                     [&](int s2) -> uint32_t { return ((s2 & 1) ? qs_r : ks_r) + 16 * (s2 >> 1) * ESZ; },
                     [&](int s2, const Frag &f) {
                         if ((s2 & 1) == 0) {
@@ -1073,8 +1077,10 @@ struct Kern {
                             const int kb = s2 >> 1, i = kb / (2 * DT), dt = (kb / 2) % DT, half = kb & 1;
                             A::mma(sc, held, f);
                             A::mma(oacc, A::from_acc(acc[i][dt], half), f);
-                            stay(sc);
-                            stay(oacc);
+                            if constexpr (kStay) {
+                                stay(sc);
+                                stay(oacc);
+                            }
                         }
                     });
             }
@@ -1092,7 +1098,7 @@ struct Kern {
         // ---- add K~^T V (the output tile finishes in the matrix pipeline meanwhile) ----
         {
             constexpr int NS = KB * NST * DT;   // (token block, state, tile)
-            pipelined_steps<NS, 6, A, kTrK>(
+            pipelined_steps<NS, kStay ? 6 : 4, A, kTrK, kStay>(
                 [&](int s2) -> uint32_t {
                     const int kb = s2 / (NST * DT), i = (s2 / DT) % NST, dt = s2 % DT;
                     if constexpr (kTrK) return ktr_r + (16 * kb * QP + i * D + 32 * dt) * ESZ;
@@ -1101,9 +1107,19 @@ struct Kern {
                 [&](int s2, const Frag &f) {
                     const int kb = s2 / (NST * DT), i = (s2 / DT) % NST, dt = s2 % DT;
                     A::mma(acc[i][dt], f, vf[kb]);
-                    stay(acc[i][dt]);
+                    if constexpr (kStay) stay(acc[i][dt]);
                 },
                 2 * QP * ESZ);
+            if constexpr (!kStay) {
+                constexpr int RD = ESZ == 2 ? 1 : 2, MM = ESZ == 2 ? 1 : 8;
+                __builtin_amdgcn_sched_group_barrier(0x100, 4 * RD, 0);
+#pragma unroll
+                for (int s2 = 0; s2 < NS - 4; ++s2) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, MM, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, RD, 0);
+                }
+                __builtin_amdgcn_sched_group_barrier(0x008, 4 * MM, 0);
+            }
         }
 
         // ---- store: lane (ln, g) holds query ln, columns 32 ct + 8 jb + 4 g .. + 3 ----
@@ -1232,26 +1248,26 @@ struct Kern {
         const int lane = tid & 63;
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront-uniform, kept in scalar registers
 
-        int bidx, h, p;
-        size_t slot0;   // workspace slot of (segment 0, this sequence, this head); segment p' is p' * slot_step further
-        size_t slot_step;
+        int bidx, h, p = 0;
+        int4 entry = {};
+        size_t slot;        // workspace slot of this segment
+        size_t slot_step;   // and from it to the next one's
         if (a.list_full) {
             const int it = blockIdx.x / a.H;
             if (it >= a.seg_count[kFull ? 0 : 1]) return;   // the lists are sized for the worst case
-            const int2 e = (kFull ? a.list_full : a.list_pre)[it];
-            bidx = e.x;
-            p = e.y;
+            entry = (kFull ? a.list_full : a.list_pre)[it];
+            bidx = entry.x;
             h = blockIdx.x % a.H;
-            slot0 = static_cast<size_t>(a.seg_first[bidx]) * a.H + h;
             slot_step = a.H;
+            slot = static_cast<size_t>(entry.w) * slot_step + h;
         } else {
             const int nseg = kFull ? a.P : a.P - 1;
             const int bh = blockIdx.x / nseg;
             p = blockIdx.x % nseg;
             bidx = bh / a.H;
             h = bh % a.H;
-            slot0 = bh;
             slot_step = gridDim.x / nseg;   // B H
+            slot = bh + static_cast<size_t>(p) * (kFull ? a.slot_mul : 1) * slot_step;
             if (kFull && !kExt && a.longest_first) bidx = sequence_of_rank(a, sm, bidx, static_cast<int>(slot_step) / a.H);
         }
 
@@ -1260,11 +1276,11 @@ struct Kern {
         const int64_t seq0 = a.cu ? static_cast<int64_t>(a.cu[sq]) : static_cast<int64_t>(bidx) * a.T;
         const int64_t Tb = a.cu ? static_cast<int64_t>(a.cu[sq + 1]) - seq0 : a.T;
         const size_t sbh = static_cast<size_t>(a.slot ? a.slot[bidx] : bidx) * a.H + h;
-        const int64_t t0 = static_cast<int64_t>(p) * a.seg_tokens;
+        const int64_t t0 = a.list_full ? entry.y : static_cast<int64_t>(p) * a.seg_tokens;
         // A shorter sequence has fewer segments: the chunk loop has nothing to do past its end, and the state
         // of a segment is only needed if another segment follows.  (Uniform exit, before any barrier.)
-        if (kFull ? t0 >= Tb : t0 + a.seg_tokens >= Tb) return;
-        const int64_t t1 = (t0 + a.seg_tokens < Tb) ? t0 + a.seg_tokens : Tb;
+        if (!a.list_full && (kFull ? t0 >= Tb : t0 + a.seg_tokens >= Tb)) return;
+        const int64_t t1 = a.list_full ? entry.z : (t0 + a.seg_tokens < Tb) ? t0 + a.seg_tokens : Tb;
         const int ntok = static_cast<int>(t1 - t0);               // tokens of this segment (>= 1)
         const int nsteps = (ntok + S - 1) / S;
         const uint32_t rs = static_cast<uint32_t>(a.H) * D;       // elements between consecutive tokens
@@ -1288,13 +1304,12 @@ struct Kern {
             // segment scan filled: the workgroup of the last segment overwrites the caller's states in this same
             // launch, so no workgroup of such a sequence may read them here.  A sequence of one segment reads the
             // caller's states itself (it is also the only one that writes them), unless they are zero by contract.
-            const bool cut = Tb > a.seg_tokens;
+            const bool cut = a.list_full ? entry.w >= 0 : Tb > a.seg_tokens;
             // (with states that are zero by contract the first segment has nothing to read: the scan leaves its slot unwritten)
-            if (kFull && (!a.zero_init || (cut && p > 0))) {
+            if (kFull && (!a.zero_init || (cut && t0 > 0))) {
 #pragma unroll
                 for (int i = 0; i < NST; ++i) {
-                    const float *src = cut ? a.ws_state + ((slot0 + static_cast<size_t>(p) * a.slot_mul * slot_step) * 2 + i) * D * D
-                                           : (i ? a.S2 : a.S1) + sbh * D * D;
+                    const float *src = cut ? a.ws_state + (slot * 2 + i) * D * D : (i ? a.S2 : a.S1) + sbh * D * D;
 #pragma unroll
                     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -1335,8 +1350,8 @@ struct Kern {
                 if (kFull) {
                     if (t1 == Tb) dst = (i ? a.S2 : a.S1) + sbh * D * D;   // the segment with the last token
                 } else {
-                    // contribution of segment p goes to state slot p+1
-                    dst = a.ws_state + ((slot0 + (p + 1) * slot_step) * 2 + i) * D * D;
+                    // its contribution goes to the slot of the next one
+                    dst = a.ws_state + ((slot + slot_step) * 2 + i) * D * D;
                 }
                 if (dst) {
                     const uint32_t sb = opaque(static_cast<uint32_t>(8 * g) * D + 32 * ct + ln);
@@ -1547,8 +1562,7 @@ struct Kern {
             if (SETS == 1) lds_barrier();
             lds_barrier();
             if (!kFull) {
-                // log2 decay of segment p goes to decay slot p
-                a.ws_decay[(slot0 + p * slot_step) * 2 * D + (lane >> 5) * D + 32 * pw + (lane & 31)] = seg_decay;
+                a.ws_decay[slot * 2 * D + (lane >> 5) * D + 32 * pw + (lane & 31)] = seg_decay;
             }
         }
     }
@@ -1624,34 +1638,34 @@ struct F32Kern {
         const bool prepares = wave_id >= NW;
 
         // ---- the work item: as Kern::run ----
-        int bidx, h, p;
-        size_t slot0, slot_step;
+        int bidx, h, p = 0;
+        int4 entry = {};
+        size_t slot, slot_step;
         if (a.list_full) {
             const int it = blockIdx.x / a.H;
             if (it >= a.seg_count[kFull ? 0 : 1]) return;
-            const int2 e = (kFull ? a.list_full : a.list_pre)[it];
-            bidx = e.x;
-            p = e.y;
+            entry = (kFull ? a.list_full : a.list_pre)[it];
+            bidx = entry.x;
             h = blockIdx.x % a.H;
-            slot0 = static_cast<size_t>(a.seg_first[bidx]) * a.H + h;
             slot_step = a.H;
+            slot = static_cast<size_t>(entry.w) * slot_step + h;
         } else {
             const int nseg = kFull ? a.P : a.P - 1;
             const int bh = blockIdx.x / nseg;
             p = blockIdx.x % nseg;
             bidx = bh / a.H;
             h = bh % a.H;
-            slot0 = bh;
             slot_step = gridDim.x / nseg;
+            slot = bh + static_cast<size_t>(p) * (kFull ? a.slot_mul : 1) * slot_step;
             if (kFull && a.longest_first) bidx = Base::sequence_of_rank(a, sm, bidx, static_cast<int>(slot_step) / a.H);
         }
         const int sq = (a.cu && a.seq) ? a.seq[bidx] : bidx;
         const int64_t seq0 = a.cu ? static_cast<int64_t>(a.cu[sq]) : static_cast<int64_t>(bidx) * a.T;
         const int64_t Tb = a.cu ? static_cast<int64_t>(a.cu[sq + 1]) - seq0 : a.T;
         const size_t sbh = static_cast<size_t>(a.slot ? a.slot[bidx] : bidx) * a.H + h;
-        const int64_t t0 = static_cast<int64_t>(p) * a.seg_tokens;
-        if (kFull ? t0 >= Tb : t0 + a.seg_tokens >= Tb) return;   // (uniform, before any barrier)
-        const int64_t t1 = (t0 + a.seg_tokens < Tb) ? t0 + a.seg_tokens : Tb;
+        const int64_t t0 = a.list_full ? entry.y : static_cast<int64_t>(p) * a.seg_tokens;
+        if (!a.list_full && (kFull ? t0 >= Tb : t0 + a.seg_tokens >= Tb)) return;   // (uniform, before any barrier)
+        const int64_t t1 = a.list_full ? entry.z : (t0 + a.seg_tokens < Tb) ? t0 + a.seg_tokens : Tb;
         const int ntok = static_cast<int>(t1 - t0), nsteps = (ntok + S - 1) / S;
         const uint32_t rs = static_cast<uint32_t>(a.H) * D, rskv = static_cast<uint32_t>(a.Hkv) * D;   // elements between tokens
         const size_t seg0 = (static_cast<size_t>(seq0 + t0) * a.H + h) * D;
@@ -1778,20 +1792,19 @@ struct F32Kern {
                 }
                 lds_barrier();   // those of step n + 1 are, and step n has been read
             }
-            if (!kFull && lane < 32) a.ws_decay[(slot0 + p * slot_step) * 2 * D + st * D + 32 * pw + fcol] = seg_decay;
+            if (!kFull && lane < 32) a.ws_decay[slot * 2 * D + st * D + 32 * pw + fcol] = seg_decay;
             return;
         }
 
         // ---- multiplying: lane (r, g); acc[i][dt][e] = T^i[16 dt + 4 g + e][16 wave + r] ----
         const uint32_t r = lane & 15, g = static_cast<uint32_t>(lane) >> 4;
         f32x4 acc[2][DT];
-        const bool cut = Tb > a.seg_tokens;   // (which states a segment starts from: see Kern::run)
+        const bool cut = a.list_full ? entry.w >= 0 : Tb > a.seg_tokens;   // (which states a segment starts from: see Kern::run)
         const uint32_t sbase = 4 * g * D + 16 * wave + r;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            if (kFull && (!a.zero_init || (cut && p > 0))) {
-                const float *src = cut ? a.ws_state + ((slot0 + static_cast<size_t>(p) * a.slot_mul * slot_step) * 2 + i) * D * D
-                                       : (i ? a.S2 : a.S1) + sbh * D * D;
+            if (kFull && (!a.zero_init || (cut && t0 > 0))) {
+                const float *src = cut ? a.ws_state + (slot * 2 + i) * D * D : (i ? a.S2 : a.S1) + sbh * D * D;
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -1940,14 +1953,14 @@ struct F32Kern {
         if (!kFull || t1 == Tb) {
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                float *dst = kFull ? (i ? a.S2 : a.S1) + sbh * D * D : a.ws_state + ((slot0 + (p + 1) * slot_step) * 2 + i) * D * D;
+                float *dst = kFull ? (i ? a.S2 : a.S1) + sbh * D * D : a.ws_state + ((slot + slot_step) * 2 + i) * D * D;
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) dst[sbase + (16 * dt + e) * D] = acc[i][dt][e];
             }
         }
-        if (!kFull && !kRoles && lane < 32) a.ws_decay[(slot0 + p * slot_step) * 2 * D + st * D + 32 * pw + fcol] = seg_decay;
+        if (!kFull && !kRoles && lane < 32) a.ws_decay[slot * 2 * D + st * D + 32 * pw + fcol] = seg_decay;
     }
 };
 template <int D, class TG, bool kFull, bool kRoles>
@@ -2031,32 +2044,33 @@ __global__ __launch_bounds__(SegFast::NT, 2) void segment_state_fast_kernel(Pref
     const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
 
     // the work item: as Kern::run with kFull = false
-    int bidx, h, p;
-    size_t slot0, slot_step;
+    int bidx, h, p = 0;
+    int4 entry = {};
+    size_t slot, slot_step;
     if (a.list_full) {
         const int it = blockIdx.x / a.H;
         if (it >= a.seg_count[1]) return;
-        const int2 e = a.list_pre[it];
-        bidx = e.x;
-        p = e.y;
+        entry = a.list_pre[it];
+        bidx = entry.x;
         h = blockIdx.x % a.H;
-        slot0 = static_cast<size_t>(a.seg_first[bidx]) * a.H + h;
         slot_step = a.H;
+        slot = static_cast<size_t>(entry.w) * slot_step + h;
     } else {
         const int nseg = a.P - 1;
         const int bh = blockIdx.x / nseg;
         p = blockIdx.x % nseg;
         bidx = bh / a.H;
         h = bh % a.H;
-        slot0 = bh;
         slot_step = gridDim.x / nseg;
+        slot = bh + p * slot_step;
     }
     const int sq = (a.cu && a.seq) ? a.seq[bidx] : bidx;
     const int64_t seq0 = a.cu ? static_cast<int64_t>(a.cu[sq]) : static_cast<int64_t>(bidx) * a.T;
     const int64_t Tb = a.cu ? static_cast<int64_t>(a.cu[sq + 1]) - seq0 : a.T;
-    const int64_t t0 = static_cast<int64_t>(p) * a.seg_tokens;
-    if (t0 + a.seg_tokens >= Tb) return;   // no segment follows: nobody needs this one's contribution (uniform exit)
-    const int nsteps = static_cast<int>(a.seg_tokens / S);   // a segment with a successor is whole: a multiple of the chunk
+    const int64_t t0 = a.list_full ? entry.y : static_cast<int64_t>(p) * a.seg_tokens;
+    if (!a.list_full && t0 + a.seg_tokens >= Tb) return;   // no segment follows: nobody needs this one's contribution (uniform exit)
+    // what is followed by another segment is whole: a multiple of a step
+    const int nsteps = static_cast<int>((a.list_full ? entry.z - entry.y : a.seg_tokens) / S);
     const uint32_t rs2 = static_cast<uint32_t>(a.H) * D * 2;   // bytes between consecutive tokens
     const size_t seg0 = (static_cast<size_t>(seq0 + t0) * a.H + h) * D * 2;
     const size_t step_bytes = static_cast<size_t>(S) * rs2;
@@ -2207,69 +2221,172 @@ __global__ __launch_bounds__(SegFast::NT, 2) void segment_state_fast_kernel(Pref
         v_i = v_i + 1 == F::V_SLOTS ? 0 : v_i + 1;
     }
 
-    // ---- contribution of segment p -> state slot p + 1; its log2 decay -> decay slot p ----
+    // ---- its contribution -> the slot of the next segment; its log2 decay -> its own decay slot ----
     {
-        float *dst = a.ws_state + ((slot0 + (p + 1) * slot_step) * 2 + st) * D * D + (4 * g) * D + 32 * ct + ln;
+        float *dst = a.ws_state + ((slot + slot_step) * 2 + st) * D * D + (4 * g) * D + 32 * ct + ln;
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
             for (int j = 0; j < 16; ++j) dst[(32 * dt + 8 * (j >> 2) + (j & 3)) * D] = acc[dt][j];
-        if (g == 0) a.ws_decay[(slot0 + p * slot_step) * 2 * D + st * D + 32 * ct + ln] = carry * unit;
+        if (g == 0) a.ws_decay[slot * 2 * D + st * D + 32 * ct + ln] = carry * unit;
     }
 }
 
-// Work lists for packed sequences (one workgroup): sequence b has ceil(T_b / seg_tokens) segments;
-// seg_first = exclusive prefix sum of that over the sequences, list_full = every (sequence, segment),
-// list_pre = those with a successor.  Thread t takes a contiguous run of sequences.
-__global__ __launch_bounds__(256) void segment_list_kernel(const int32_t *__restrict__ cu, const int32_t *__restrict__ seq,
-                                                           int B, int64_t seg_tokens,
-                                                           int32_t *__restrict__ seg_first,
-                                                           int32_t *__restrict__ seg_count, int2 *__restrict__ list_full,
-                                                           int2 *__restrict__ list_pre, int cap_full, int cap_pre)
+// What the lists are made from.
+struct SegmentListArgs {
+    const int32_t *cu, *seq;
+    int B, H;
+    int64_t piece;               // tokens
+    int32_t *seg_first, *seg_count;
+    int4 *list_full, *list_pre;
+    int cap_full, cap_pre;       // entries
+    int run_min, run_max;        // only the long sequences are cut: pieces per segment to choose from (0: every piece is a segment)
+    int chip;                    // workgroups at a time
+    float step, step_full, pre, wg, slot, fixed;   // us: see PrefillCosts
+    float margin;                // a cut has to be estimated at less than this part of none
+};
+
+// Work lists for packed sequences (one workgroup).  Every sequence in pieces of the same length, from its start: list_full =
+// every (sequence, piece), list_pre = those with a successor.  Thread t takes a contiguous run of sequences.
+__global__ __launch_bounds__(256) void segment_list_kernel(SegmentListArgs a)
 {
     __shared__ int s_sum[256];
     const int t = threadIdx.x;
-    const int per = (B + 255) / 256;
-    const int b0 = t * per, b1 = (b0 + per < B) ? b0 + per : B;
-    auto segments_of = [&](int b) -> int {
-        const int sq = seq ? seq[b] : b;
-        const int64_t Tb = static_cast<int64_t>(cu[sq + 1]) - cu[sq];
-        return Tb > 0 ? static_cast<int>((Tb + seg_tokens - 1) / seg_tokens) : 0;
+    const int per = (a.B + 255) / 256;
+    const int b0 = t * per, b1 = (b0 + per < a.B) ? b0 + per : a.B;
+    auto length_of = [&](int b) -> int64_t {
+        const int sq = a.seq ? a.seq[b] : b;
+        return static_cast<int64_t>(a.cu[sq + 1]) - a.cu[sq];
     };
-    int mine = 0, mine_seq = 0;   // segments, and sequences with at least one, in this thread's run
+    auto segments_of = [&](int64_t Tb) -> int { return Tb > 0 ? static_cast<int>((Tb + a.piece - 1) / a.piece) : 0; };
+    int mine = 0, mine_pre = 0, mine_slots = 0;   // segments, those with a successor, and slots in this thread's run
     for (int b = b0; b < b1; ++b) {
-        const int n = segments_of(b);
+        const int n = segments_of(length_of(b));
         mine += n;
-        mine_seq += n > 0;
+        mine_pre += n > 1 ? n - 1 : 0;
+        mine_slots += n > 1 ? n : 0;
     }
-    // exclusive scans over the 256 threads of (segments) and (segments - non-empty sequences) = entries of list_pre
-    s_sum[t] = mine;
-    __syncthreads();
-    int before = 0, before_seq = 0;
-    for (int u = 0; u < t; ++u) before += s_sum[u];
-    __syncthreads();
-    s_sum[t] = mine_seq;
-    __syncthreads();
-    for (int u = 0; u < t; ++u) before_seq += s_sum[u];
-    int at = before, at_pre = before - before_seq;
+    // exclusive sums over the 256 threads
+    auto before = [&](int x) -> int {
+        __syncthreads();
+        s_sum[t] = x;
+        __syncthreads();
+        int sum = 0;
+        for (int u = 0; u < t; ++u) sum += s_sum[u];
+        return sum;
+    };
+    int at = before(mine), at_pre = before(mine_pre), at_slot = before(mine_slots);
     for (int b = b0; b < b1; ++b) {
-        const int n = segments_of(b);
-        seg_first[b] = at;
+        const int64_t Tb = length_of(b);
+        const int n = segments_of(Tb);
+        a.seg_first[b] = at_slot;
         // the capacities hold whenever the offsets add up to the total the caller gave; offsets that do not
         // must not write past the lists (the segments that do not fit are dropped)
         for (int p = 0; p < n; ++p) {
-            if (at + p < cap_full) list_full[at + p] = make_int2(b, p);
+            const int64_t t0 = p * a.piece, t1 = t0 + a.piece < Tb ? t0 + a.piece : Tb;
+            const int4 e = make_int4(b, static_cast<int>(t0), static_cast<int>(t1), n > 1 ? at_slot + p : -1);
+            if (at + p < a.cap_full) a.list_full[at + p] = e;
             if (p + 1 < n) {
-                if (at_pre < cap_pre) list_pre[at_pre] = make_int2(b, p);
+                if (at_pre < a.cap_pre) a.list_pre[at_pre] = e;
                 ++at_pre;
             }
         }
         at += n;
+        at_slot += n > 1 ? n : 0;
     }
     if (t == 255) {
-        seg_first[B] = at;
-        seg_count[0] = at < cap_full ? at : cap_full;
-        seg_count[1] = at_pre < cap_pre ? at_pre : cap_pre;
+        a.seg_first[a.B] = at_slot;
+        a.seg_count[0] = at < a.cap_full ? at : a.cap_full;
+        a.seg_count[1] = at_pre < a.cap_pre ? at_pre : a.cap_pre;
+    }
+}
+
+// The lists where only the sequences are cut whose chain of steps would outlast all the work spread over the chip (at most 128
+// sequences and 256 segments).  A segment is R pieces, counted from the END of the sequence: what precedes the last full segment - the part that
+// the pre-pass has to walk, in pieces so that many workgroups do - is as short as it can be.  Pieces begin at multiples of a step; the first one
+// may be shorter.  The lengths are known here and not on the host, so R is chosen here, by the same estimates, with R = 0 (nothing is cut)
+// among the choices; the longest segments come first.
+__global__ __launch_bounds__(256) void long_segment_list_kernel(SegmentListArgs a)
+{
+    constexpr int kMost = 256;
+    __shared__ int2 s_len[kMost];   // pieces, steps of 32 tokens
+    __shared__ int s_key[kMost], s_n[3][kMost];
+    __shared__ float s_cost[kMost];
+    __shared__ int4 s_entry[kMost];
+    const int t = threadIdx.x, piece = static_cast<int>(a.piece);
+    int Tb = 0;
+    if (t < a.B) {
+        const int sq = a.seq ? a.seq[t] : t;
+        Tb = a.cu[sq + 1] - a.cu[sq];
+        if (Tb < 0) Tb = 0;
+    }
+    s_len[t] = make_int2((Tb + piece - 1) / piece, (Tb + 31) / 32);
+    __syncthreads();
+    const int choices = a.run_max - a.run_min + 2;
+    if (t < choices) {   // thread 0: the cost of nothing cut, thread t: of R = run_min + t - 1
+        const int R = t == 0 ? 0 : a.run_min + t - 1;
+        int chain = 0, pre = 0, more = 0, steps = 0, sequences = 0;
+        for (int b = 0; b < a.B; ++b) {
+            const int2 len = s_len[b];
+            const bool cut = R > 0 && len.x > R;
+            if (cut) {
+                more += (len.x - 1) / R;
+                pre += len.x - R;
+                ++sequences;
+            }
+            steps += len.y;
+            const int longest = cut ? R * (piece / 32) : len.y;
+            chain = longest > chain ? longest : chain;
+        }
+        // The longest chain and all work spread over the chip: the nearer they are, the more the one delays the other (their 4-norm:
+        // 20 sequences of up to 8192 tokens, 610 and 474, take 625 us whole)
+        const float H = static_cast<float>(a.H) / static_cast<float>(a.chip);
+        const float spread = ((a.B + more) * a.wg + steps * a.step_full) * H, alone = a.wg + chain * a.step;
+        const float walks = pre * H, s2 = spread * spread, a2 = alone * alone;
+        float cost = __builtin_sqrtf(__builtin_sqrtf(s2 * s2 + a2 * a2));
+        if (pre > 0) cost += a.fixed + (walks > 1.f ? walks : 1.f) * (piece / 32) * a.pre + a.slot * pre * a.H;
+        if (more > a.cap_full - a.B || pre + sequences > a.cap_pre) cost = 3.0e38f;   // more than there are slots
+        s_cost[t] = cost;
+    }
+    __syncthreads();
+    int R = 0;
+    float least = a.margin * s_cost[0];
+    for (int u = 1; u < choices; ++u)
+        if (s_cost[u] < least) {
+            least = s_cost[u];
+            R = a.run_min + u - 1;
+        }
+    const int n = (Tb + piece - 1) / piece, ahead = (n * piece - Tb) / 32 * 32;   // pieces, and what the first one is short of
+    const bool cut = R > 0 && n > R;
+    const int nseg = cut ? (n + R - 1) / R : (Tb > 0 ? 1 : 0), npre = cut ? n - R : 0, nslot = cut ? npre + 1 : 0;
+    s_n[0][t] = nseg;
+    s_n[1][t] = npre;
+    s_n[2][t] = nslot;
+    s_key[t] = -1;
+    __syncthreads();
+    int at = 0, at_pre = 0, at_slot = 0;
+    for (int u = 0; u < t; ++u) {
+        at += s_n[0][u];
+        at_pre += s_n[1][u];
+        at_slot += s_n[2][u];
+    }
+    auto begin = [&](int i) { return i > 0 ? i * piece - ahead : 0; };   // of piece i
+    if (t <= a.B) a.seg_first[t] = at_slot;                             // (t == B: all slots)
+    for (int i = 0; i < npre; ++i) a.list_pre[at_pre + i] = make_int4(t, begin(i), begin(i + 1), at_slot + i);
+    for (int k = 0; k < nseg; ++k) {
+        const int f = k > 0 ? n - R * (nseg - k) : 0, t0 = begin(f), t1 = k + 1 < nseg ? begin(n - R * (nseg - k - 1)) : Tb;
+        s_entry[at + k] = make_int4(t, t0, t1, cut ? at_slot + f : -1);
+        s_key[at + k] = (t1 - t0 < (1 << 22) ? t1 - t0 : (1 << 22)) * kMost + (kMost - 1 - at - k);
+    }
+    if (t == kMost - 1) {
+        a.seg_count[0] = at + nseg;
+        a.seg_count[1] = at_pre + npre;
+    }
+    __syncthreads();
+    if (s_key[t] >= 0) {
+        int rank = 0;
+        for (int u = 0; u < kMost; ++u) rank += s_key[u] > s_key[t] ? 1 : 0;
+        a.list_full[rank] = s_entry[t];
     }
 }
 
@@ -2280,11 +2397,8 @@ template <int D>
 __global__ __launch_bounds__(256) void segment_scan_kernel(const float *__restrict__ S1, const float *__restrict__ S2,
                                                            float *__restrict__ ws_state,
                                                            const float *__restrict__ ws_decay, int BH, int P,
-                                                           const int32_t *__restrict__ cu,
-                                                           const int32_t *__restrict__ seq,
                                                            const int32_t *__restrict__ slot,
-                                                           const int32_t *__restrict__ seg_first, int H,
-                                                           int64_t seg_tokens, int zero_init, int beta)
+                                                           const int32_t *__restrict__ seg_first, int H, int zero_init, int beta)
 {
     // one thread per 4 adjacent columns of one (bh, state, row)
     const size_t n4 = static_cast<size_t>(BH) * 2 * D * (D / 4);
@@ -2299,20 +2413,16 @@ __global__ __launch_bounds__(256) void segment_scan_kernel(const float *__restri
     const size_t bh = bi >> 1;
     const size_t b = bh / H, h = bh % H;
     size_t slot0 = bh, slot_step = BH;
-    if (cu) {   // a shorter sequence has fewer segments, an empty one none
-        const size_t sq = seq ? static_cast<size_t>(seq[b]) : b;
-        const int64_t Tb = static_cast<int64_t>(cu[sq + 1]) - cu[sq];
-        const int64_t Pb = Tb > 0 ? (Tb + seg_tokens - 1) / seg_tokens : 0;
-        if (Pb < P) P = static_cast<int>(Pb);
-        if (P <= 1) return;
+    if (seg_first) {   // work lists
+        P = seg_first[b + 1] - seg_first[b];
         slot0 = static_cast<size_t>(seg_first[b]) * H + h;
         slot_step = H;
     }
+    if (P <= 1) return;
     const size_t sbh = static_cast<size_t>(slot ? slot[b] : b) * H + h;
     const float *src = (i ? S2 : S1) + (sbh * D + row) * D + c4 * 4;
     float4 s = zero_init ? make_float4(0.f, 0.f, 0.f, 0.f) : *reinterpret_cast<const float4 *>(src);
     const size_t in_slot = (static_cast<size_t>(i) * D + row) * D + c4 * 4;   // this thread's place inside a slot
-    if (P <= 1) return;
     if (!zero_init) *reinterpret_cast<float4 *>(ws_state + slot0 * 2 * D * D + in_slot) = s;   // zero states: segment 0 starts from registers set to zero
     for (int p = 0; p + 1 < P; ++p) {
         const float *dslot = ws_decay + (slot0 + p * slot_step) * 2 * D;
@@ -2334,6 +2444,32 @@ __global__ __launch_bounds__(256) void segment_scan_kernel(const float *__restri
     }
 }
 
+
+// Workgroups of the chunk loop that the chip holds at one time: two per compute unit at d = 64 with 16-bit io, else one (LDS).
+int chip_slots(const dsla_desc &d) { return d.d_k == 64 && d.io_dtype == DSLA_BF16 ? 512 : 256; }
+
+// Estimates (us): a step of 32 tokens where the chain of one workgroup counts / where every compute unit is busy, a step of
+// the pre-pass, what a workgroup costs besides its steps, a state slot written, scanned and read again, the lists of a packed
+// batch and the scan besides its slots.
+struct PrefillCosts {
+    double step, step_full, pre, wg, slot, lists;
+    double step_alone;   // a step where no compute unit has two workgroups
+};
+PrefillCosts prefill_costs(const dsla_desc &d)
+{
+    const bool f32 = d.io_dtype == DSLA_F32, small = d.d_k == 64, preact = d.gate_mode == DSLA_GATE_PREACT;
+    PrefillCosts c;
+    c.step = f32 ? (small ? 4.5 : 11.1) : (small ? (preact ? 1.8 : 1.4) : (preact ? 2.35 : 2.0));
+    c.step_alone = f32 && small ? 3.6 : c.step;   // (launch_f32)
+    c.step_full = f32 ? c.step : (small ? 2.5 : (preact ? 3.4 : 2.9));
+    c.pre = f32 ? (small ? 2.2 : 5.1) : (small ? 1.2 : (preact ? 2.1 : 1.5));
+    c.wg = f32 ? (small ? 3.0 : 5.0) : (small ? 5.0 : 8.0);
+    c.slot = f32 ? (small ? 0.028 : 0.06) : (small ? 0.04 : 0.05);
+    c.lists = f32 ? (small ? 5.0 : 4.0) : (small ? 9.0 : 6.0);
+    return c;
+}
+// All work spread over the chip takes this part of what step_full says (which stays, for the rules that were measured with it).
+constexpr double kSpread = 0.92;
 
 // F32Kern with or without roles.  With them (d = 64) a compute unit holds one workgroup, so they are taken where every workgroup has
 // a unit to itself.  Without / with, us, 600 tokens in one segment: 256 heads 109 / 91; past one
@@ -2372,10 +2508,31 @@ hipError_t launch_x(const dsla_desc &d, const PrefillPlan &plan, PrefillArgs &a,
     if (plan.segments > 1) {
         if (a.list_full) {
             ProfileScope ps(DSLA_KERNEL_PREFILL_SEGMENT_LIST, stream);
-            DSLA_LAUNCH(ps, segment_list_kernel, dim3(1), dim3(256), 0, stream, a.cu, a.seq, d.B, a.seg_tokens,
-                               const_cast<int32_t *>(a.seg_first), const_cast<int32_t *>(a.seg_count),
-                               const_cast<int2 *>(a.list_full), const_cast<int2 *>(a.list_pre),
-                               static_cast<int>(plan.max_items), static_cast<int>(plan.max_pre_items));
+            const PrefillCosts c = prefill_costs(d);
+            SegmentListArgs l;
+            l.cu = a.cu;
+            l.seq = a.seq;
+            l.B = d.B;
+            l.H = d.H;
+            l.piece = a.seg_tokens;
+            l.seg_first = const_cast<int32_t *>(a.seg_first);
+            l.seg_count = const_cast<int32_t *>(a.seg_count);
+            l.list_full = const_cast<int4 *>(a.list_full);
+            l.list_pre = const_cast<int4 *>(a.list_pre);
+            l.cap_full = static_cast<int>(plan.max_items);
+            l.cap_pre = static_cast<int>(plan.max_pre_items);
+            l.run_min = plan.run_min;
+            l.run_max = plan.run_max;
+            l.chip = chip_slots(d);
+            l.step = static_cast<float>(c.step);
+            l.step_full = static_cast<float>(kSpread * c.step_full);
+            l.pre = static_cast<float>(c.pre);
+            l.wg = static_cast<float>(c.wg);
+            l.slot = static_cast<float>(c.slot);
+            l.fixed = static_cast<float>(2 * c.wg + c.lists);
+            l.margin = d.d_k == 64 ? 0.92f : 0.98f;   // (two workgroups to a compute unit are harder to estimate)
+            if (plan.run_max > 0) DSLA_LAUNCH(ps, long_segment_list_kernel, dim3(1), dim3(256), 0, stream, l);
+            else DSLA_LAUNCH(ps, segment_list_kernel, dim3(1), dim3(256), 0, stream, l);
             err = hipGetLastError();
             if (err != hipSuccess) return err;
         }
@@ -2396,8 +2553,8 @@ hipError_t launch_x(const dsla_desc &d, const PrefillPlan &plan, PrefillArgs &a,
             ProfileScope ps(DSLA_KERNEL_PREFILL_SEGMENT_SCAN, stream);
             const size_t n4 = static_cast<size_t>(BH) * 2 * D * (D / 4);
             DSLA_LAUNCH(ps, (segment_scan_kernel<D>), dim3(static_cast<unsigned>((n4 + 255) / 256)), dim3(256), 0,
-                               stream, a.S1, a.S2, a.ws_state, a.ws_decay, BH, af.P, a.cu, a.seq, a.slot,
-                               a.seg_first, a.H, af.seg_tokens, a.zero_init, kBeta ? 1 : 0);
+                               stream, a.S1, a.S2, a.ws_state, a.ws_decay, BH, af.P, a.slot, a.seg_first, a.H, a.zero_init,
+                               kBeta ? 1 : 0);
             err = hipGetLastError();
         }
         if (err != hipSuccess) return err;
@@ -2440,9 +2597,6 @@ bool combo_built(int D, int C, int io)
 }  // namespace
 
 namespace {
-// Workgroups of the chunk loop that the chip holds at one time: two per compute unit at d = 64 with 16-bit io, else one (LDS).
-int chip_slots(const dsla_desc &d) { return d.d_k == 64 && d.io_dtype == DSLA_BF16 ? 512 : 256; }
-
 // Fills the plan from the chunk length, the number of segments P the longest sequence is cut into, and its length.
 void finish_plan(const dsla_desc &d, int C, int64_t P, int64_t nchunks, bool may_split, PrefillPlan *plan)
 {
@@ -2458,6 +2612,7 @@ void finish_plan(const dsla_desc &d, int C, int64_t P, int64_t nchunks, bool may
     plan->state_elems = static_cast<size_t>(BH) * D * D;
     plan->max_items = plan->max_pre_items = 0;
     plan->longest_first = false;
+    plan->run_min = plan->run_max = 0;
     plan->ws_lists_bytes = 0;
     // The pre-pass has one workgroup per (segment but the last, sequence, head).  With two segments that is at most
     // half of the compute units (65 .. 128 heads in all; short sequences): it then works on the two halves of the first
@@ -2486,26 +2641,6 @@ int plan_chunk(const dsla_desc &d)
 }  // namespace
 
 namespace {
-// Estimates (us): a step of 32 tokens where the chain of one workgroup counts / where every compute unit is busy, a step of
-// the pre-pass, what a workgroup costs besides its steps, a state slot written, scanned and read again, the lists of a packed
-// batch and the scan besides its slots.
-struct PrefillCosts {
-    double step, step_full, pre, wg, slot, lists;
-    double step_alone;   // a step where no compute unit has two workgroups
-};
-PrefillCosts prefill_costs(const dsla_desc &d)
-{
-    const bool f32 = d.io_dtype == DSLA_F32, small = d.d_k == 64, preact = d.gate_mode == DSLA_GATE_PREACT;
-    PrefillCosts c;
-    c.step = f32 ? (small ? 4.5 : 11.1) : (small ? (preact ? 1.8 : 1.4) : (preact ? 2.35 : 2.0));
-    c.step_alone = f32 && small ? 3.6 : c.step;   // (launch_f32)
-    c.step_full = f32 ? c.step : (small ? 2.5 : (preact ? 3.4 : 2.9));
-    c.pre = f32 ? (small ? 2.2 : 5.1) : (small ? 1.2 : (preact ? 2.1 : 1.5));
-    c.wg = f32 ? (small ? 3.0 : 5.0) : (small ? 5.0 : 8.0);
-    c.slot = f32 ? (small ? 0.028 : 0.06) : (small ? 0.04 : 0.05);
-    c.lists = f32 ? (small ? 5.0 : 4.0) : (small ? 9.0 : 6.0);
-    return c;
-}
 // The figures by which a packed call without its buffer is refused or runs whole.  They are part of what callers rely on: they stay
 // when kernels get faster and the estimates follow.
 PrefillCosts refusal_costs(const dsla_desc &d)
@@ -2666,6 +2801,69 @@ bool order_pays(const dsla_desc &d, int64_t total_T, int64_t max_T)
 }
 }  // namespace
 
+namespace {
+size_t lists_bytes(const dsla_desc &d, const PrefillPlan &p)
+{
+    auto up = [](size_t n) { return (n + 255) / 256 * 256; };
+    return up((static_cast<size_t>(d.B) + 1) * 4) + 256 + up(p.max_items * 16) + up(p.max_pre_items * 16);
+}
+
+// A batch that stays whole because cutting everything costs more than it saves, but whose longest sequences outlast all its work
+// spread over the chip: these alone are cut (long_segment_list_kernel decides where, and whether).  It takes the lists, a pre-pass over the
+// beginnings of the long sequences and a scan.  Whole / cut, 32 heads, d = 128: 20 sequences of up to 8192 tokens as pre-activations 635 / 532 us, with
+// log-gates 578 / 473; 19 of up to 5605 439 / 345; 17 of up to 4850 338 / 270; d = 64, 32 of up to 6768 430 / 350.
+// Its slots are as many as `bytes` hold (what the size query answers, or less that a caller brings): the device keeps to them.
+void cut_long(const dsla_desc &d, int64_t total_T, int64_t max_T, size_t bytes, PrefillPlan *plan)
+{
+    if (d.io_dtype == DSLA_F32 || d.B < 2 || d.B > 128) return;
+    const PrefillCosts c = prefill_costs(d);
+    const double H = static_cast<double>(d.H) / chip_slots(d);
+    const double spread = (static_cast<double>(d.B) * c.wg + static_cast<double>(total_T) / 32 * kSpread * c.step_full) * H;
+    auto both = [&](int64_t steps) { return std::sqrt(std::hypot(spread * spread, (c.wg + steps * c.step) * (c.wg + steps * c.step))); };
+    PrefillPlan p = *plan;
+    const int64_t piece = max_T >= 4096 ? 512 : 256;   // (a multiple of every chunk)
+    p.run_min = static_cast<int>(0.8 * (spread - c.wg) / c.step * 32 / static_cast<double>(piece));
+    if (p.run_min < 2) p.run_min = 2;
+    const int64_t most = (max_T + piece - 1) / piece - 1;   // pieces per segment that still cut the longest
+    if (most < p.run_min) return;
+    p.run_max = static_cast<int>(most < p.run_min + 200 ? most : p.run_min + 200);
+    // the device's estimate as if two sequences were the longest: has to be below that of the whole batch, because the lists, an empty pre-pass
+    // and an empty scan cost 15 us where the device then cuts nothing
+    double least = 1e30;
+    for (int64_t R = p.run_min; R <= p.run_max; ++R) {
+        const double pieces = 2.0 * static_cast<double>(most + 1 - R), walks = pieces * H;
+        const double cost = both(R * piece / 32) + 2 * c.wg + c.lists + (walks > 1 ? walks : 1) * (piece / 32) * c.pre + c.slot * pieces * d.H;
+        if (cost < least) least = cost;
+    }
+    if (least > (d.d_k == 64 ? 0.92 : 0.95) * both((max_T + 31) / 32)) return;
+    p.segments = 2;
+    p.segment_tokens = piece;
+    p.pre_split = 1;
+    // n sequences of more than run_min pieces hold at most so many pieces past their last segments; all make `cuts` further segments at most
+    const int64_t run = p.run_min * piece, cuts = total_T / run;
+    int64_t slots = 0;   // a sequence has one more slot than pieces past its last segment
+    for (int64_t n = 1; n <= cuts; ++n) {
+        const int64_t tokens = (n * max_T < total_T ? n * max_T : total_T) - n * run;
+        if (tokens > 0 && tokens / piece + 2 * n > slots) slots = tokens / piece + 2 * n;
+    }
+    p.max_items = d.B + cuts;
+    const size_t slot_bytes = static_cast<size_t>(d.H) * 2 * d.d_k * (d.d_k + 1) * sizeof(float);
+    p.max_pre_items = slots;
+    const size_t fixed = lists_bytes(d, p) + 256;
+    if (p.max_items > 256 || bytes < fixed + 2 * slot_bytes) return;
+    const int64_t fit = static_cast<int64_t>((bytes - fixed) / slot_bytes);
+    if (fit < slots) slots = fit;
+    p.max_pre_items = slots;
+    p.ws_state_bytes = static_cast<size_t>(slots) * d.H * 2 * d.d_k * d.d_k * sizeof(float);
+    p.ws_decay_bytes = (static_cast<size_t>(slots) * d.H * 2 * d.d_k * sizeof(float) + 255) / 256 * 256;
+    p.ws_lists_bytes = lists_bytes(d, p);
+    p.ws_total_bytes = p.ws_state_bytes + p.ws_decay_bytes + p.ws_lists_bytes;
+    p.longest_first = false;
+    p.ws_need_bytes = 0;
+    *plan = p;
+}
+}  // namespace
+
 // Packed sequences of different lengths share one segment length; a sequence of length T_b has
 // ceil(T_b / segment_tokens) segments.  If they are cut, the segment length is chosen so that all sequences together make
 // about one workgroup per compute unit, the same rule as above on the total instead of a common length (measured on
@@ -2692,7 +2890,7 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
         const size_t slots = static_cast<size_t>(p->max_items) * d.H;
         p->ws_state_bytes = slots * 2 * D * D * sizeof(float);
         p->ws_decay_bytes = up(slots * 2 * D * sizeof(float));
-        p->ws_lists_bytes = up((static_cast<size_t>(d.B) + 1) * 4) + 256 + up(p->max_items * 8) + up(p->max_pre_items * 8);
+        p->ws_lists_bytes = lists_bytes(d, *p);
         p->ws_total_bytes = p->ws_ask_bytes = p->ws_need_bytes = p->ws_state_bytes + p->ws_decay_bytes + p->ws_lists_bytes;
     };
     int64_t P, P_cut;   // what is done; what the cut alone would be
@@ -2739,6 +2937,7 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
         if (some) {
             PrefillPlan cut;
             finish_packed(P_cut, &cut);
+            if (P == 1) cut_long(d, total_T, max_T, available < cut.ws_total_bytes ? available : cut.ws_total_bytes, plan);
             plan->ws_ask_bytes = cut.ws_total_bytes;
         }
     }
@@ -2779,9 +2978,9 @@ hipError_t launch_prefill(const dsla_desc &d, const PrefillPlan &plan, int64_t T
         w += up((static_cast<size_t>(d.B) + 1) * 4);
         a.seg_count = reinterpret_cast<int32_t *>(w);
         w += 256;
-        a.list_full = reinterpret_cast<int2 *>(w);
-        w += up(plan.max_items * 8);
-        a.list_pre = reinterpret_cast<int2 *>(w);
+        a.list_full = reinterpret_cast<int4 *>(w);
+        w += up(plan.max_items * 16);
+        a.list_pre = reinterpret_cast<int4 *>(w);
     }
     a.longest_first = plan.longest_first ? 1 : 0;
     a.T = T;

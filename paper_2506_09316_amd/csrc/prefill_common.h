@@ -8,20 +8,21 @@ struct PrefillArgs {
     const void *q, *k, *v, *g1, *g2;
     void *o;
     float *S1, *S2;          // caller's states
-    // One workspace slot per (segment, sequence, head): slot = (p B + b) H + h, or with work lists
-    // (seg_first[b] + p) H + h.  The last segment of a sequence has no decay entry that anyone reads.
+    // One workspace slot per (segment, sequence, head): slot = (p B + b) H + h, or with work lists as the entry says, times H, + h.
+    // The last segment of a sequence has no decay entry that anyone reads.
     float *ws_state;         // [slot][2][D][D] fp32 (P > 1): state at the start of the segment
     float *ws_decay;         // [slot][2][D] fp32 (P > 1): log2 of the decay over the segment
     const float *gamma_per_head;
     const int32_t *cu;       // packed sequences: [B + 1] token offsets (sequence b = tokens cu[b] .. cu[b+1]-1); or null
     const int32_t *seq;      // with cu: [B] which of the packed sequences take part (entry b names sequence seq[b]); or null (all, in order)
     const int32_t *slot;     // [B] index of each sequence's states in S1, S2; or null (sequence b uses entry b)
-    // Packed sequences cut into segments: the work lists written by segment_list_kernel.  A workgroup is
-    // (list entry, head); entries past the count exit.  Null when every sequence is one segment or cu is null.
-    const int32_t *seg_first;   // [B + 1] index of the first segment of each sequence among all segments
+    // Packed sequences of which any are cut: the work lists written by segment_list_kernel.  A workgroup is (list entry, head);
+    // entries past the count exit.  An entry: sequence, first token, token past the last, slot of the state on entry
+    // (-1: the sequence is whole).  Null when every sequence is one segment or cu is null.
+    const int32_t *seg_first;   // [B + 1] first slot of each sequence (a sequence that is cut into n pieces by the pre-pass has n + 1)
     const int32_t *seg_count;   // [2] entries in list_full, list_pre
-    const int2 *list_full;      // (sequence, segment) of every segment
-    const int2 *list_pre;       // (sequence, segment) of every segment that is followed by another one
+    const int4 *list_full;      // the chunk loop's segments
+    const int4 *list_pre;       // the pre-pass's pieces: the segment, or a part of it, of every segment that is followed by another one
     int64_t T;               // tokens per sequence (cu == null); with cu: upper bound of the sequence lengths
     int64_t seg_tokens;
     int H;

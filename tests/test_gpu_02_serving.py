@@ -132,6 +132,21 @@ def test_varlen_longest_first(lengths, H, d, io, gate):
     _run_varlen(lengths, H, d, io, gate, 1e-4 if io == "f32" else 2e-2, slots=list(range(B))[::-1], n_slots=B + 1)
 
 
+@pytest.mark.parametrize("lengths,H,d,gate", [
+    ([1335, 0, 4850, 4608, 33, 4609, 1104, 1, 884, 504, 995, 471, 1124], 32, 128, "bf16"),   # on, one past and between the pieces of 512
+    ([335, 3454, 477, 223, 1648], 32, 128, "bf16"),                                          # pieces of 256
+    ([761, 5605, 1548, 64, 4485, 1363, 714, 808], 32, 128, "f32"),                           # the general pre-pass
+    ([1209, 583, 6768, 35, 2229, 1680, 1296, 567, 633, 1003, 2020, 2153, 1709], 32, 64, "bf16")])
+def test_varlen_only_the_long_ones_cut(lengths, H, d, gate):
+    """Batches whose longest sequences outlast the rest: these alone are cut, in pieces counted from their ends, and the longest
+    segments come first.  The launches show that the lists, the pre-pass and the scan are part of the call."""
+    dsla.profile_enable(True)
+    _run_varlen(lengths, H, d, "bf16", gate, 2e-2, slots=list(range(len(lengths)))[::-1], n_slots=len(lengths) + 1)
+    launches = {n: c for n, (_, c) in dsla.profile_collect().items() if c}
+    dsla.profile_enable(False)
+    assert launches == {"prefill_segment_list": 1, "prefill_segment_state": 1, "prefill_segment_scan": 1, "prefill_chunk_loop": 1}
+
+
 @pytest.mark.parametrize("B,H,d", [(256, 3, 64), (257, 3, 64), (130, 3, 128)])
 def test_varlen_longest_first_many_long_sequences(B, H, d):
     """Sequence counts at and past the number of threads of a workgroup (4 d), long enough for the order to pay where it

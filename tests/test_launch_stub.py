@@ -98,6 +98,9 @@ for io in (0, 1):
     assert packed(8, 32, 128, 1959, 1900, io, fake, big) == (OK, 4)
     assert packed(8, 32, 128, 1959, 1900, io, odd, big) == (ERR_SHAPE, 0)
     assert packed(8, 32, 128, 1959, 1900, io, fake, 1024) == packed(8, 32, 128, 1959, 1900, io, None, 0) == (ERR_WORKSPACE, 0)
+# only the long ones cut: with a buffer; whole without one that holds at least the lists and two slots
+assert packed(20, 32, 128, 37157, 8192, 1, fake, big) == (OK, 4)
+assert packed(20, 32, 128, 37157, 8192, 1, None, 0) == packed(20, 32, 128, 37157, 8192, 1, fake, 1 << 22) == packed(20, 32, 128, 37157, 8192, 1, odd, big) == (OK, 1)
 """
 
 
