@@ -132,19 +132,46 @@ def test_varlen_longest_first(lengths, H, d, io, gate):
     _run_varlen(lengths, H, d, io, gate, 1e-4 if io == "f32" else 2e-2, slots=list(range(B))[::-1], n_slots=B + 1)
 
 
-@pytest.mark.parametrize("lengths,H,d,gate", [
-    ([1335, 0, 4850, 4608, 33, 4609, 1104, 1, 884, 504, 995, 471, 1124], 32, 128, "bf16"),   # on, one past and between the pieces of 512
-    ([335, 3454, 477, 223, 1648], 32, 128, "bf16"),                                          # pieces of 256
-    ([761, 5605, 1548, 64, 4485, 1363, 714, 808], 32, 128, "f32"),                           # the general pre-pass
-    ([1209, 583, 6768, 35, 2229, 1680, 1296, 567, 633, 1003, 2020, 2153, 1709], 32, 64, "bf16")])
-def test_varlen_only_the_long_ones_cut(lengths, H, d, gate):
-    """Batches whose longest sequences outlast the rest: these alone are cut, in pieces counted from their ends, and the longest
-    segments come first.  The launches show that the lists, the pre-pass and the scan are part of the call."""
-    dsla.profile_enable(True)
-    _run_varlen(lengths, H, d, "bf16", gate, 2e-2, slots=list(range(len(lengths)))[::-1], n_slots=len(lengths) + 1)
-    launches = {n: c for n, (_, c) in dsla.profile_collect().items() if c}
-    dsla.profile_enable(False)
-    assert launches == {"prefill_segment_list": 1, "prefill_segment_state": 1, "prefill_segment_scan": 1, "prefill_chunk_loop": 1}
+@pytest.mark.parametrize("lengths,long,H,d,gate", [
+    ([1362, 710, 335, 761, 0, 1104, 884, 504, 995, 471, 492, 4850, 347, 1379, 1, 1035, 551, 1124, 116, 33], [11], 32, 128, "bf16"),
+    ([1335] * 9 + [4609], [9], 32, 128, "bf16"),               # one past a multiple of the pieces of 512
+    ([4864] + [1104] * 10, [0], 32, 128, "f32"),               # no remainder; the general pre-pass
+    ([700] * 6 + [3900] + [700] * 6 + [31], [6], 32, 128, "bf16"),   # pieces of 256
+    ([1500] * 10 + [6768] + [1500] * 9, [10], 32, 64, "bf16")])
+def test_varlen_only_the_long_ones_cut(lengths, long, H, d, gate):
+    """Batches whose longest sequences outlast the rest: these alone are cut, in pieces counted from their ends.  Against the same call
+    without a buffer, which runs whole (and is held to the oracle elsewhere): the short sequences come out bit for bit, the long ones do not,
+    and are right."""
+    import torch
+    B, total = len(lengths), sum(lengths)
+    rng = torch.Generator(device="cuda").manual_seed(98)
+    normal = lambda *shape, std=1.0: torch.empty(*shape, device="cuda").normal_(0, std, generator=rng)
+    q, k, v = (normal(total, H, d, std=d ** -0.5).bfloat16() for _ in range(3))
+    g1, g2 = ((torch.nn.functional.softplus(-normal(total, H, d) - 2) / -16).to(torch.bfloat16 if gate == "bf16" else torch.float32) for _ in range(2))
+    S0 = [normal(B + 1, H, d, d, std=0.3) for _ in range(2)]
+    cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    slots = list(range(B))[::-1]
+    desc = dsla.make_desc(B, H, d, d, io_dtype=code("bf16"), gate_dtype=code(gate), gamma=0.6, chunk=64)
+    ws = torch.empty(dsla.dsla_prefill_varlen_workspace_bytes(desc, total, max(lengths)), dtype=torch.uint8, device="cuda")
+    results = []
+    for buffer in (ws, None):
+        S1, S2 = (x.clone() for x in S0)
+        o = torch.full_like(v, float("nan"))
+        dsla.dsla_prefill_varlen(desc, total, max(lengths), torch.from_numpy(cu).cuda(), torch.tensor(slots, dtype=torch.int32, device="cuda"),
+                                 q, k, v, g1, g2, S1, S2, o, buffer)
+        torch.cuda.synchronize()
+        results.append([x.float().cpu().numpy() for x in (o, S1, S2)])
+    (o, S1, S2), (ow, S1w, S2w) = results
+    for b in range(B):
+        rows, sl = slice(cu[b], cu[b + 1]), slots[b]
+        if b not in long:
+            assert np.array_equal(o[rows], ow[rows]) and np.array_equal(S1[sl], S1w[sl]) and np.array_equal(S2[sl], S2w[sl]), b
+            continue
+        assert not np.array_equal(o[rows], ow[rows])
+        check(f"o[{b}]", o[rows], ow[rows], 2e-2)
+        check(f"S1[{b}]", S1[sl], S1w[sl], 2e-2)
+        check(f"S2[{b}]", S2[sl], S2w[sl], 2e-2)
+    assert np.array_equal(S1[B], S1w[B]) and np.array_equal(S2[B], S2w[B])
 
 
 @pytest.mark.parametrize("B,H,d", [(256, 3, 64), (257, 3, 64), (130, 3, 128)])
