@@ -2250,7 +2250,7 @@ struct SegmentListArgs {
 // every (sequence, piece), list_pre = those with a successor.  Thread t takes a contiguous run of sequences.
 __global__ __launch_bounds__(256) void segment_list_kernel(SegmentListArgs a)
 {
-    __shared__ int s_sum[256];
+    __shared__ int4 s_sum[256];
     const int t = threadIdx.x;
     const int per = (a.B + 255) / 256;
     const int b0 = t * per, b1 = (b0 + per < a.B) ? b0 + per : a.B;
@@ -2266,16 +2266,17 @@ __global__ __launch_bounds__(256) void segment_list_kernel(SegmentListArgs a)
         mine_pre += n > 1 ? n - 1 : 0;
         mine_slots += n > 1 ? n : 0;
     }
-    // exclusive sums over the 256 threads
-    auto before = [&](int x) -> int {
-        __syncthreads();
-        s_sum[t] = x;
-        __syncthreads();
-        int sum = 0;
-        for (int u = 0; u < t; ++u) sum += s_sum[u];
-        return sum;
-    };
-    int at = before(mine), at_pre = before(mine_pre), at_slot = before(mine_slots);
+    // exclusive sums over the threads (those past the last sequence have nothing)
+    s_sum[t] = make_int4(mine, mine_pre, mine_slots, 0);
+    __syncthreads();
+    int at = 0, at_pre = 0, at_slot = 0;
+    const int busy = (a.B + per - 1) / per;
+    for (int u = 0; u < (t < busy ? t : busy); ++u) {
+        const int4 n = s_sum[u];
+        at += n.x;
+        at_pre += n.y;
+        at_slot += n.z;
+    }
     for (int b = b0; b < b1; ++b) {
         const int64_t Tb = length_of(b);
         const int n = segments_of(Tb);
@@ -2365,7 +2366,7 @@ __global__ __launch_bounds__(256) void long_segment_list_kernel(SegmentListArgs 
     s_key[t] = -1;
     __syncthreads();
     int at = 0, at_pre = 0, at_slot = 0;
-    for (int u = 0; u < t; ++u) {
+    for (int u = 0; u < (t < a.B ? t : a.B); ++u) {
         at += s_n[0][u];
         at_pre += s_n[1][u];
         at_slot += s_n[2][u];
@@ -2385,7 +2386,7 @@ __global__ __launch_bounds__(256) void long_segment_list_kernel(SegmentListArgs 
     __syncthreads();
     if (s_key[t] >= 0) {
         int rank = 0;
-        for (int u = 0; u < kMost; ++u) rank += s_key[u] > s_key[t] ? 1 : 0;
+        for (int u = 0; u < a.cap_full; ++u) rank += s_key[u] > s_key[t] ? 1 : 0;   // (at most kMost)
         a.list_full[rank] = s_entry[t];
     }
 }
@@ -2813,7 +2814,7 @@ size_t lists_bytes(const dsla_desc &d, const PrefillPlan &p)
 // beginnings of the long sequences and a scan.  Whole / cut, 32 heads, d = 128: 20 sequences of up to 8192 tokens as pre-activations 635 / 532 us, with
 // log-gates 578 / 473; 19 of up to 5605 439 / 345; 17 of up to 4850 338 / 270; d = 64, 32 of up to 6768 430 / 350.
 // Its slots are as many as `bytes` hold (what the size query answers, or less that a caller brings): the device keeps to them.
-void cut_long(const dsla_desc &d, int64_t total_T, int64_t max_T, size_t bytes, PrefillPlan *plan)
+void cut_long(const dsla_desc &d, int64_t total_T, int64_t max_T, size_t bytes, double below, PrefillPlan *plan)
 {
     if (d.io_dtype == DSLA_F32 || d.B < 2 || d.B > 128) return;
     const PrefillCosts c = prefill_costs(d);
@@ -2835,7 +2836,7 @@ void cut_long(const dsla_desc &d, int64_t total_T, int64_t max_T, size_t bytes, 
         const double cost = both(R * piece / 32) + 2 * c.wg + c.lists + (walks > 1 ? walks : 1) * (piece / 32) * c.pre + c.slot * pieces * d.H;
         if (cost < least) least = cost;
     }
-    if (least > (d.d_k == 64 ? 0.92 : 0.95) * both((max_T + 31) / 32)) return;
+    if (least > (below > 0 ? below : (d.d_k == 64 ? 0.92 : 0.95) * both((max_T + 31) / 32))) return;
     p.segments = 2;
     p.segment_tokens = piece;
     p.pre_split = 1;
@@ -2895,6 +2896,7 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
     };
     int64_t P, P_cut;   // what is done; what the cut alone would be
     bool must_cut = true;
+    double cut_cost = 0;   // of cutting every sequence, where that pays
     if (d.segments > 0) {
         P = P_cut = d.segments;
     } else {
@@ -2907,22 +2909,30 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
             const double L = static_cast<double>((nchunks + P - 1) / P * C);   // finish_plan evens the segments out
             const double n = L / 32, longest = static_cast<double>(max_T) / 32;
             const double cuts = static_cast<double>(total_T) / L * d.H, items = cuts + static_cast<double>(d.B) * d.H;
-            auto cut_pays = [&](const PrefillCosts &c) {
+            auto costs = [&](const PrefillCosts &c) {   // whole, cut
                 auto loop = [&](double chain, double workgroups) {
                     const double step = workgroups <= 256 ? c.step_alone : c.step;
                     const double spread = workgroups / chip * c.wg + steps * d.H / chip * c.step_full;
                     return spread > c.wg + chain * step ? spread : c.wg + chain * step;
                 };
                 const double whole = loop(longest, static_cast<double>(d.B) * d.H);
-                return whole > c.lists + c.wg + (cuts > chip ? cuts / chip : 1.0) * n * c.pre + c.slot * cuts + loop(n, items);
+                return std::make_pair(whole, c.lists + c.wg + (cuts > chip ? cuts / chip : 1.0) * n * c.pre + c.slot * cuts + loop(n, items));
             };
-            must_cut = cut_pays(refusal_costs(d));
-            if (!cut_pays(prefill_costs(d))) P = 1;
+            const auto before = costs(refusal_costs(d)), now = costs(prefill_costs(d));
+            must_cut = before.first > before.second;
+            if (now.first > now.second) cut_cost = now.second;
+            else P = 1;
         }
     }
     finish_packed(P, plan);
     if (!must_cut && plan->ws_total_bytes > available) finish_packed(P = 1, plan);
     plan->longest_first = plan->segments == 1 && order_pays(d, total_T, max_T);
+    if (P > 1 && cut_cost > 0 && plan->ws_total_bytes <= available) {   // (its bytes are there: the long ones alone, if that is better still)
+        const PrefillPlan all = *plan;
+        // (32 heads, d = 128: 10 sequences of up to 3379 tokens all cut 260 us, these 223; 8 of up to 1724 122 and 106)
+        cut_long(d, total_T, max_T, all.ws_total_bytes, 0.78 * cut_cost, plan);
+        plan->ws_ask_bytes = plan->ws_need_bytes = all.ws_total_bytes;
+    }
     if (P < P_cut) {
         // Whole by the estimate: the size query still answers with what cutting takes, if any smaller batch is cut, so that a
         // buffer sized for a large batch serves smaller ones.  The least a cut can cost is that of one sequence of n chunks.
@@ -2937,7 +2947,7 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
         if (some) {
             PrefillPlan cut;
             finish_packed(P_cut, &cut);
-            if (P == 1) cut_long(d, total_T, max_T, available < cut.ws_total_bytes ? available : cut.ws_total_bytes, plan);
+            if (P == 1) cut_long(d, total_T, max_T, available < cut.ws_total_bytes ? available : cut.ws_total_bytes, 0, plan);
             plan->ws_ask_bytes = cut.ws_total_bytes;
         }
     }
