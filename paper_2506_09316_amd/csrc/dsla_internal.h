@@ -92,6 +92,7 @@ struct PrefillPlan {
     int64_t max_items;       // packed sequences with P > 1: capacity of the list of all segments (else 0)
     int64_t max_pre_items;   //   and of the list of segments that have a successor
     size_t ws_lists_bytes;   //   and the bytes of the lists
+    int64_t max_cut;         //   and of the list of sequences that are cut
     int run_min, run_max;    // packed sequences, only the long ones cut: pieces of segment_tokens per segment, the device chooses (else 0)
     bool longest_first;      // packed sequences, whole: the chunk loop takes them in the order of their lengths
     size_t ws_total_bytes;   // what this plan uses

@@ -2237,9 +2237,9 @@ struct SegmentListArgs {
     const int32_t *cu, *seq;
     int B, H;
     int64_t piece;               // tokens
-    int32_t *seg_first, *seg_count;
+    int32_t *seg_first, *seg_count, *cut_seq;
     int4 *list_full, *list_pre;
-    int cap_full, cap_pre;       // entries
+    int cap_full, cap_pre, cap_cut;   // entries
     int run_min, run_max;        // only the long sequences are cut: pieces per segment to choose from (0: every piece is a segment)
     int chip;                    // workgroups at a time
     float step, step_full, pre, wg, slot, fixed;   // us: see PrefillCosts
@@ -2259,28 +2259,31 @@ __global__ __launch_bounds__(256) void segment_list_kernel(SegmentListArgs a)
         return static_cast<int64_t>(a.cu[sq + 1]) - a.cu[sq];
     };
     auto segments_of = [&](int64_t Tb) -> int { return Tb > 0 ? static_cast<int>((Tb + a.piece - 1) / a.piece) : 0; };
-    int mine = 0, mine_pre = 0, mine_slots = 0;   // segments, those with a successor, and slots in this thread's run
+    int mine = 0, mine_pre = 0, mine_cut = 0;   // segments, those with a successor, and sequences that have such in this thread's run
     for (int b = b0; b < b1; ++b) {
         const int n = segments_of(length_of(b));
         mine += n;
         mine_pre += n > 1 ? n - 1 : 0;
-        mine_slots += n > 1 ? n : 0;
+        mine_cut += n > 1;
     }
     // exclusive sums over the threads (those past the last sequence have nothing)
-    s_sum[t] = make_int4(mine, mine_pre, mine_slots, 0);
+    s_sum[t] = make_int4(mine, mine_pre, mine_cut, 0);
     __syncthreads();
-    int at = 0, at_pre = 0, at_slot = 0;
+    int at = 0, at_pre = 0, at_cut = 0;
     const int busy = (a.B + per - 1) / per;
     for (int u = 0; u < (t < busy ? t : busy); ++u) {
         const int4 n = s_sum[u];
         at += n.x;
         at_pre += n.y;
-        at_slot += n.z;
+        at_cut += n.z;
     }
+    int at_slot = at_pre + at_cut;   // (a sequence in n segments has n slots, a whole one none)
     for (int b = b0; b < b1; ++b) {
         const int64_t Tb = length_of(b);
         const int n = segments_of(Tb);
         a.seg_first[b] = at_slot;
+        if (n > 1 && at_cut < a.cap_cut) a.cut_seq[at_cut] = b;
+        at_cut += n > 1;
         // the capacities hold whenever the offsets add up to the total the caller gave; offsets that do not
         // must not write past the lists (the segments that do not fit are dropped)
         for (int p = 0; p < n; ++p) {
@@ -2299,6 +2302,7 @@ __global__ __launch_bounds__(256) void segment_list_kernel(SegmentListArgs a)
         a.seg_first[a.B] = at_slot;
         a.seg_count[0] = at < a.cap_full ? at : a.cap_full;
         a.seg_count[1] = at_pre < a.cap_pre ? at_pre : a.cap_pre;
+        a.seg_count[2] = at_cut < a.cap_cut ? at_cut : a.cap_cut;
     }
 }
 
@@ -2371,6 +2375,8 @@ __global__ __launch_bounds__(256) void long_segment_list_kernel(SegmentListArgs 
         at_pre += s_n[1][u];
         at_slot += s_n[2][u];
     }
+    const int at_cut = at_slot - at_pre;   // (one slot more than pieces each)
+    if (cut && at_cut < a.cap_cut) a.cut_seq[at_cut] = t;
     auto begin = [&](int i) { return i > 0 ? i * piece - ahead : 0; };   // of piece i
     if (t <= a.B) a.seg_first[t] = at_slot;                             // (t == B: all slots)
     for (int i = 0; i < npre; ++i) a.list_pre[at_pre + i] = make_int4(t, begin(i), begin(i + 1), at_slot + i);
@@ -2382,6 +2388,7 @@ __global__ __launch_bounds__(256) void long_segment_list_kernel(SegmentListArgs 
     if (t == kMost - 1) {
         a.seg_count[0] = at + nseg;
         a.seg_count[1] = at_pre + npre;
+        a.seg_count[2] = at_cut;
     }
     __syncthreads();
     if (s_key[t] >= 0) {
@@ -2399,7 +2406,8 @@ __global__ __launch_bounds__(256) void segment_scan_kernel(const float *__restri
                                                            float *__restrict__ ws_state,
                                                            const float *__restrict__ ws_decay, int BH, int P,
                                                            const int32_t *__restrict__ slot,
-                                                           const int32_t *__restrict__ seg_first, int H, int zero_init, int beta)
+                                                           const int32_t *__restrict__ seg_first, const int32_t *__restrict__ seg_count,
+                                                           const int32_t *__restrict__ cut_seq, int H, int zero_init, int beta)
 {
     // one thread per 4 adjacent columns of one (bh, state, row)
     const size_t n4 = static_cast<size_t>(BH) * 2 * D * (D / 4);
@@ -2412,9 +2420,11 @@ __global__ __launch_bounds__(256) void segment_scan_kernel(const float *__restri
     const int i = static_cast<int>(bi & 1);
     if (beta && i) return;   // beta mode: one state; the second slot of decays holds the log2 decays of its columns
     const size_t bh = bi >> 1;
-    const size_t b = bh / H, h = bh % H;
-    size_t slot0 = bh, slot_step = BH;
-    if (seg_first) {   // work lists
+    const size_t h = bh % H;
+    size_t b = bh / H, slot0 = bh, slot_step = BH;
+    if (seg_first) {   // work lists: b of the sequences that are cut
+        if (b >= static_cast<size_t>(seg_count[2])) return;
+        b = static_cast<size_t>(cut_seq[b]);
         P = seg_first[b + 1] - seg_first[b];
         slot0 = static_cast<size_t>(seg_first[b]) * H + h;
         slot_step = H;
@@ -2518,6 +2528,8 @@ hipError_t launch_x(const dsla_desc &d, const PrefillPlan &plan, PrefillArgs &a,
             l.piece = a.seg_tokens;
             l.seg_first = const_cast<int32_t *>(a.seg_first);
             l.seg_count = const_cast<int32_t *>(a.seg_count);
+            l.cut_seq = const_cast<int32_t *>(a.cut_seq);
+            l.cap_cut = static_cast<int>(plan.max_cut);
             l.list_full = const_cast<int4 *>(a.list_full);
             l.list_pre = const_cast<int4 *>(a.list_pre);
             l.cap_full = static_cast<int>(plan.max_items);
@@ -2552,10 +2564,11 @@ hipError_t launch_x(const dsla_desc &d, const PrefillPlan &plan, PrefillArgs &a,
         if (err != hipSuccess) return err;
         {
             ProfileScope ps(DSLA_KERNEL_PREFILL_SEGMENT_SCAN, stream);
-            const size_t n4 = static_cast<size_t>(BH) * 2 * D * (D / 4);
+            const int n_scan = a.list_full ? static_cast<int>(plan.max_cut) * d.H : BH;   // (sequence, head)
+            const size_t n4 = static_cast<size_t>(n_scan) * 2 * D * (D / 4);
             DSLA_LAUNCH(ps, (segment_scan_kernel<D>), dim3(static_cast<unsigned>((n4 + 255) / 256)), dim3(256), 0,
-                               stream, a.S1, a.S2, a.ws_state, a.ws_decay, BH, af.P, a.slot, a.seg_first, a.H, a.zero_init,
-                               kBeta ? 1 : 0);
+                               stream, a.S1, a.S2, a.ws_state, a.ws_decay, n_scan, af.P, a.slot, a.seg_first, a.seg_count, a.cut_seq, a.H,
+                               a.zero_init, kBeta ? 1 : 0);
             err = hipGetLastError();
         }
         if (err != hipSuccess) return err;
@@ -2614,6 +2627,7 @@ void finish_plan(const dsla_desc &d, int C, int64_t P, int64_t nchunks, bool may
     plan->max_items = plan->max_pre_items = 0;
     plan->longest_first = false;
     plan->run_min = plan->run_max = 0;
+    plan->max_cut = 0;
     plan->ws_lists_bytes = 0;
     // The pre-pass has one workgroup per (segment but the last, sequence, head).  With two segments that is at most
     // half of the compute units (65 .. 128 heads in all; short sequences): it then works on the two halves of the first
@@ -2806,7 +2820,7 @@ namespace {
 size_t lists_bytes(const dsla_desc &d, const PrefillPlan &p)
 {
     auto up = [](size_t n) { return (n + 255) / 256 * 256; };
-    return up((static_cast<size_t>(d.B) + 1) * 4) + 256 + up(p.max_items * 16) + up(p.max_pre_items * 16);
+    return up((static_cast<size_t>(d.B) + 1) * 4) + up((static_cast<size_t>(d.B) + 4) * 4) + up(p.max_items * 16) + up(p.max_pre_items * 16);
 }
 
 // A batch that stays whole because cutting everything costs more than it saves, but whose longest sequences outlast all its work
@@ -2848,6 +2862,7 @@ void cut_long(const dsla_desc &d, int64_t total_T, int64_t max_T, size_t bytes, 
         if (tokens > 0 && tokens / piece + 2 * n > slots) slots = tokens / piece + 2 * n;
     }
     p.max_items = d.B + cuts;
+    p.max_cut = cuts < d.B ? cuts : d.B;
     const size_t slot_bytes = static_cast<size_t>(d.H) * 2 * d.d_k * (d.d_k + 1) * sizeof(float);
     p.max_pre_items = slots;
     const size_t fixed = lists_bytes(d, p) + 256;
@@ -2888,6 +2903,7 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
         auto up = [](size_t n) { return (n + 255) / 256 * 256; };
         p->max_pre_items = total_T / p->segment_tokens;
         p->max_items = p->max_pre_items + d.B;
+        p->max_cut = p->max_pre_items < d.B ? p->max_pre_items : d.B;
         const size_t slots = static_cast<size_t>(p->max_items) * d.H;
         p->ws_state_bytes = slots * 2 * D * D * sizeof(float);
         p->ws_decay_bytes = up(slots * 2 * D * sizeof(float));
@@ -2979,7 +2995,7 @@ hipError_t launch_prefill(const dsla_desc &d, const PrefillPlan &plan, int64_t T
     a.cu = cu_seqlens;
     a.seq = seq_index;
     a.slot = state_slot;
-    a.seg_first = a.seg_count = nullptr;
+    a.seg_first = a.seg_count = a.cut_seq = nullptr;
     a.list_full = a.list_pre = nullptr;
     if (plan.max_items > 0) {   // packed sequences, more than one segment: carve the work lists
         auto up = [](size_t n) { return (n + 255) / 256 * 256; };
@@ -2987,7 +3003,8 @@ hipError_t launch_prefill(const dsla_desc &d, const PrefillPlan &plan, int64_t T
         a.seg_first = reinterpret_cast<int32_t *>(w);
         w += up((static_cast<size_t>(d.B) + 1) * 4);
         a.seg_count = reinterpret_cast<int32_t *>(w);
-        w += 256;
+        a.cut_seq = a.seg_count + 4;
+        w += up((static_cast<size_t>(d.B) + 4) * 4);
         a.list_full = reinterpret_cast<int4 *>(w);
         w += up(plan.max_items * 16);
         a.list_pre = reinterpret_cast<int4 *>(w);

@@ -20,7 +20,8 @@ struct PrefillArgs {
     // entries past the count exit.  An entry: sequence, first token, token past the last, slot of the state on entry
     // (-1: the sequence is whole).  Null when every sequence is one segment or cu is null.
     const int32_t *seg_first;   // [B + 1] first slot of each sequence (a sequence that is cut into n pieces by the pre-pass has n + 1)
-    const int32_t *seg_count;   // [2] entries in list_full, list_pre
+    const int32_t *seg_count;   // [3] entries in list_full, list_pre, cut_seq
+    const int32_t *cut_seq;     // the sequences that are cut
     const int4 *list_full;      // the chunk loop's segments
     const int4 *list_pre;       // the pre-pass's pieces: the segment, or a part of it, of every segment that is followed by another one
     int64_t T;               // tokens per sequence (cu == null); with cu: upper bound of the sequence lengths
