@@ -1248,24 +1248,28 @@ struct Kern {
         const int lane = tid & 63;
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront-uniform, kept in scalar registers
 
-        int bidx, h, p = 0;
-        int4 entry = {};
+        int bidx, h;
+        int64_t t0, t1;     // first token of the segment, past its last one
         size_t slot;        // workspace slot of this segment
         size_t slot_step;   // and from it to the next one's
         if (a.list_full) {
             const int it = blockIdx.x / a.H;
             if (it >= a.seg_count[kFull ? 0 : 1]) return;   // the lists are sized for the worst case
-            entry = (kFull ? a.list_full : a.list_pre)[it];
-            bidx = entry.x;
+            const int4 e = (kFull ? a.list_full : a.list_pre)[it];
+            bidx = e.x;
+            t0 = e.y;
+            t1 = e.z;
             h = blockIdx.x % a.H;
             slot_step = a.H;
-            slot = static_cast<size_t>(entry.w) * slot_step + h;
+            slot = static_cast<size_t>(e.w) * slot_step + h;
         } else {
             const int nseg = kFull ? a.P : a.P - 1;
             const int bh = blockIdx.x / nseg;
-            p = blockIdx.x % nseg;
+            const int p = blockIdx.x % nseg;
             bidx = bh / a.H;
             h = bh % a.H;
+            t0 = static_cast<int64_t>(p) * a.seg_tokens;
+            t1 = t0 + a.seg_tokens;
             slot_step = gridDim.x / nseg;   // B H
             slot = bh + static_cast<size_t>(p) * (kFull ? a.slot_mul : 1) * slot_step;
             if (kFull && !kExt && a.longest_first) bidx = sequence_of_rank(a, sm, bidx, static_cast<int>(slot_step) / a.H);
@@ -1276,11 +1280,10 @@ struct Kern {
         const int64_t seq0 = a.cu ? static_cast<int64_t>(a.cu[sq]) : static_cast<int64_t>(bidx) * a.T;
         const int64_t Tb = a.cu ? static_cast<int64_t>(a.cu[sq + 1]) - seq0 : a.T;
         const size_t sbh = static_cast<size_t>(a.slot ? a.slot[bidx] : bidx) * a.H + h;
-        const int64_t t0 = a.list_full ? entry.y : static_cast<int64_t>(p) * a.seg_tokens;
         // A shorter sequence has fewer segments: the chunk loop has nothing to do past its end, and the state
         // of a segment is only needed if another segment follows.  (Uniform exit, before any barrier.)
-        if (!a.list_full && (kFull ? t0 >= Tb : t0 + a.seg_tokens >= Tb)) return;
-        const int64_t t1 = a.list_full ? entry.z : (t0 + a.seg_tokens < Tb) ? t0 + a.seg_tokens : Tb;
+        if (kFull ? t0 >= Tb : t1 >= Tb) return;
+        t1 = t1 < Tb ? t1 : Tb;
         const int ntok = static_cast<int>(t1 - t0);               // tokens of this segment (>= 1)
         const int nsteps = (ntok + S - 1) / S;
         const uint32_t rs = static_cast<uint32_t>(a.H) * D;       // elements between consecutive tokens
@@ -1304,7 +1307,7 @@ struct Kern {
             // segment scan filled: the workgroup of the last segment overwrites the caller's states in this same
             // launch, so no workgroup of such a sequence may read them here.  A sequence of one segment reads the
             // caller's states itself (it is also the only one that writes them), unless they are zero by contract.
-            const bool cut = a.list_full ? entry.w >= 0 : Tb > a.seg_tokens;
+            const bool cut = t1 - t0 < Tb;
             // (with states that are zero by contract the first segment has nothing to read: the scan leaves its slot unwritten)
             if (kFull && (!a.zero_init || (cut && t0 > 0))) {
 #pragma unroll
@@ -1638,23 +1641,27 @@ struct F32Kern {
         const bool prepares = wave_id >= NW;
 
         // ---- the work item: as Kern::run ----
-        int bidx, h, p = 0;
-        int4 entry = {};
+        int bidx, h;
+        int64_t t0, t1;
         size_t slot, slot_step;
         if (a.list_full) {
             const int it = blockIdx.x / a.H;
             if (it >= a.seg_count[kFull ? 0 : 1]) return;
-            entry = (kFull ? a.list_full : a.list_pre)[it];
-            bidx = entry.x;
+            const int4 e = (kFull ? a.list_full : a.list_pre)[it];
+            bidx = e.x;
+            t0 = e.y;
+            t1 = e.z;
             h = blockIdx.x % a.H;
             slot_step = a.H;
-            slot = static_cast<size_t>(entry.w) * slot_step + h;
+            slot = static_cast<size_t>(e.w) * slot_step + h;
         } else {
             const int nseg = kFull ? a.P : a.P - 1;
             const int bh = blockIdx.x / nseg;
-            p = blockIdx.x % nseg;
+            const int p = blockIdx.x % nseg;
             bidx = bh / a.H;
             h = bh % a.H;
+            t0 = static_cast<int64_t>(p) * a.seg_tokens;
+            t1 = t0 + a.seg_tokens;
             slot_step = gridDim.x / nseg;
             slot = bh + static_cast<size_t>(p) * (kFull ? a.slot_mul : 1) * slot_step;
             if (kFull && a.longest_first) bidx = Base::sequence_of_rank(a, sm, bidx, static_cast<int>(slot_step) / a.H);
@@ -1663,9 +1670,8 @@ struct F32Kern {
         const int64_t seq0 = a.cu ? static_cast<int64_t>(a.cu[sq]) : static_cast<int64_t>(bidx) * a.T;
         const int64_t Tb = a.cu ? static_cast<int64_t>(a.cu[sq + 1]) - seq0 : a.T;
         const size_t sbh = static_cast<size_t>(a.slot ? a.slot[bidx] : bidx) * a.H + h;
-        const int64_t t0 = a.list_full ? entry.y : static_cast<int64_t>(p) * a.seg_tokens;
-        if (!a.list_full && (kFull ? t0 >= Tb : t0 + a.seg_tokens >= Tb)) return;   // (uniform, before any barrier)
-        const int64_t t1 = a.list_full ? entry.z : (t0 + a.seg_tokens < Tb) ? t0 + a.seg_tokens : Tb;
+        if (kFull ? t0 >= Tb : t1 >= Tb) return;   // (uniform, before any barrier)
+        t1 = t1 < Tb ? t1 : Tb;
         const int ntok = static_cast<int>(t1 - t0), nsteps = (ntok + S - 1) / S;
         const uint32_t rs = static_cast<uint32_t>(a.H) * D, rskv = static_cast<uint32_t>(a.Hkv) * D;   // elements between tokens
         const size_t seg0 = (static_cast<size_t>(seq0 + t0) * a.H + h) * D;
@@ -1799,7 +1805,7 @@ struct F32Kern {
         // ---- multiplying: lane (r, g); acc[i][dt][e] = T^i[16 dt + 4 g + e][16 wave + r] ----
         const uint32_t r = lane & 15, g = static_cast<uint32_t>(lane) >> 4;
         f32x4 acc[2][DT];
-        const bool cut = a.list_full ? entry.w >= 0 : Tb > a.seg_tokens;   // (which states a segment starts from: see Kern::run)
+        const bool cut = t1 - t0 < Tb;   // (which states a segment starts from: see Kern::run)
         const uint32_t sbase = 4 * g * D + 16 * wave + r;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -2044,33 +2050,36 @@ __global__ __launch_bounds__(SegFast::NT, 2) void segment_state_fast_kernel(Pref
     const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
 
     // the work item: as Kern::run with kFull = false
-    int bidx, h, p = 0;
-    int4 entry = {};
+    int bidx, h;
+    int64_t t0, t1;
     size_t slot, slot_step;
     if (a.list_full) {
         const int it = blockIdx.x / a.H;
         if (it >= a.seg_count[1]) return;
-        entry = a.list_pre[it];
-        bidx = entry.x;
+        const int4 e = a.list_pre[it];
+        bidx = e.x;
+        t0 = e.y;
+        t1 = e.z;
         h = blockIdx.x % a.H;
         slot_step = a.H;
-        slot = static_cast<size_t>(entry.w) * slot_step + h;
+        slot = static_cast<size_t>(e.w) * slot_step + h;
     } else {
         const int nseg = a.P - 1;
         const int bh = blockIdx.x / nseg;
-        p = blockIdx.x % nseg;
+        const int p = blockIdx.x % nseg;
         bidx = bh / a.H;
         h = bh % a.H;
+        t0 = static_cast<int64_t>(p) * a.seg_tokens;
+        t1 = t0 + a.seg_tokens;
         slot_step = gridDim.x / nseg;
         slot = bh + p * slot_step;
     }
     const int sq = (a.cu && a.seq) ? a.seq[bidx] : bidx;
     const int64_t seq0 = a.cu ? static_cast<int64_t>(a.cu[sq]) : static_cast<int64_t>(bidx) * a.T;
     const int64_t Tb = a.cu ? static_cast<int64_t>(a.cu[sq + 1]) - seq0 : a.T;
-    const int64_t t0 = a.list_full ? entry.y : static_cast<int64_t>(p) * a.seg_tokens;
-    if (!a.list_full && t0 + a.seg_tokens >= Tb) return;   // no segment follows: nobody needs this one's contribution (uniform exit)
+    if (t1 >= Tb) return;   // no segment follows: nobody needs this one's contribution (uniform exit)
     // what is followed by another segment is whole: a multiple of a step
-    const int nsteps = static_cast<int>((a.list_full ? entry.z - entry.y : a.seg_tokens) / S);
+    const int nsteps = static_cast<int>(t1 - t0) / S;
     const uint32_t rs2 = static_cast<uint32_t>(a.H) * D * 2;   // bytes between consecutive tokens
     const size_t seg0 = (static_cast<size_t>(seq0 + t0) * a.H + h) * D * 2;
     const size_t step_bytes = static_cast<size_t>(S) * rs2;
