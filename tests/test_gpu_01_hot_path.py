@@ -79,6 +79,26 @@ def test_prefill_short_prompt_plans(B, H, d, T, chunk):
     run_prefill_case(B, T, H, d, "bf16", "bf16", chunk=chunk, segments=0, gamma=0.35, seed=92, init=True, qk_scale=d ** -0.5)
 
 
+@pytest.mark.parametrize("io,d", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("segments", [4, 5, 6, 8, 9, 10])
+@pytest.mark.parametrize("zero_init", [False, True])
+def test_prefill_scan_over_segments_four_at_a_time(io, d, segments, zero_init):
+    """The scan loads four segments at a time: one short of a group, whole groups, one and two past them, from states carried in
+    and from states that are zero by contract."""
+    B, T, H = 2, 32 * segments - 5, 3
+    x = wl.layer_inputs(132, B, T, H, d, d, io_dtype=io, gate_dtype=io, qk_scale=d ** -0.5)
+    S10, S20 = wl.initial_states(132, B, H, d, d, amplitude=2.0)
+    layer = GpuLayer(B, H, d, io, io, gamma=0.4, chunk=32, segments=segments, zero_init=zero_init)
+    layer.set_states(S10, S20)
+    o = layer.prefill(x)
+    S1, S2 = layer.states()
+    if zero_init:
+        S10 = S20 = None
+    ro, rS1, rS2 = orc.recurrent(x["q"], x["k"], x["v"], x["g1"], x["g2"], 0.4, 1.0, S1=S10, S2=S20)
+    for name, got, want in (("o", o, ro), ("S1", S1, rS1), ("S2", S2, rS2)):
+        check(name, got, want, TOL[io])
+
+
 @pytest.mark.parametrize("d,T,segments,gamma,f1,f2", [
     (128, 1000, 1, 0.4, (1, 1), (128, 128)),        # one state's frames never move, the other's in every step
     (128, 777, 1, -0.3, (16, 64), (0, 32)),         # the halves of the features at their own times; gates of exactly one
