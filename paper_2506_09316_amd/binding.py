@@ -131,7 +131,7 @@ def load_library():
         from . import _marshal
         entries = (lib.dsla_decode, lib.dsla_decode_slots, lib.dsla_prefill, lib.dsla_prefill_varlen, lib.dsla_attention_decode,
                    lib.dsla_attention_prefill, lib.dsla_project)
-        _marshal.bind(_torch._cuda_getDevice, _torch._cuda_getCurrentRawStream, torch.nn.Parameter,
+        _marshal.bind(_torch._cuda_getDevice, _torch._cuda_getCurrentRawStream, torch.nn.Parameter, DslaDesc,
                       *[ctypes.cast(f, vp).value for f in entries])
         _native = _marshal
     _lib = lib

@@ -13,7 +13,7 @@
 
 namespace {
 
-PyObject *g_device, *g_raw_stream, *g_parameter;   // torch._C._cuda_getDevice, _cuda_getCurrentRawStream; torch.nn.Parameter
+PyObject *g_device, *g_raw_stream, *g_parameter, *g_desc;   // torch._C._cuda_getDevice, _cuda_getCurrentRawStream; torch.nn.Parameter, binding.DslaDesc
 struct Entries {
     decltype(&dsla_decode) decode;
     decltype(&dsla_decode_slots) decode_slots;
@@ -60,6 +60,10 @@ struct Args {
         dsla_desc d;
         std::memset(&d, 0, sizeof(d));
         Py_buffer view;
+        if (reinterpret_cast<PyObject *>(Py_TYPE(o[i])) != g_desc) {   // (bytes of that size have a buffer too)
+            ok = false;
+            return d;
+        }
         if (PyObject_GetBuffer(o[i], &view, PyBUF_SIMPLE) != 0) {
             ok = false;
             return d;
@@ -259,22 +263,23 @@ PyObject *project(PyObject *, PyObject *const *args, Py_ssize_t n)   // x, W, ou
     });
 }
 
-// device, raw_stream, parameter type, addresses of the entry points in the order of Entries
+// device, raw_stream, parameter type, descriptor type, addresses of the entry points in the order of Entries
 PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     constexpr int kEntries = sizeof(Entries) / sizeof(void *);
-    if (n != 3 + kEntries) {
+    constexpr int kObjects = 4;
+    if (n != kObjects + kEntries) {
         PyErr_SetString(PyExc_TypeError, "bind: number of arguments");
         return nullptr;
     }
     void *p[kEntries];
     for (int i = 0; i < kEntries; ++i) {
-        p[i] = PyLong_AsVoidPtr(args[3 + i]);
+        p[i] = PyLong_AsVoidPtr(args[kObjects + i]);
         if (PyErr_Occurred()) return nullptr;
     }
     std::memcpy(&g_entry, p, sizeof(p));
-    PyObject **to[3] = {&g_device, &g_raw_stream, &g_parameter};
-    for (int i = 0; i < 3; ++i) {
+    PyObject **to[kObjects] = {&g_device, &g_raw_stream, &g_parameter, &g_desc};
+    for (int i = 0; i < kObjects; ++i) {
         Py_INCREF(args[i]);
         Py_XDECREF(*to[i]);
         *to[i] = args[i];
