@@ -4,7 +4,8 @@ current torch HIP stream are handed to the library.  No computation happens here
 there is no fallback: if the library is missing, loading raises.
 
 The calls of a serving loop go through _marshal.so, the same in native code; arguments that
-it does not take (it then returns None) go the way written out here.
+it does not take (it then returns None) go the way written out here, and so do all where it is
+not built, or not for this interpreter, PyTorch and header.
 """
 from __future__ import annotations
 
@@ -15,7 +16,14 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(HERE, "libdsla.so")
 _lib = None
 _torch = None   # torch._C once the library is loaded
-_native = None  # _marshal once the library is loaded
+
+
+class _General:
+    """In the place of _marshal: leaves every call to the general way."""
+    decode = decode_slots = prefill = prefill_varlen = attention_decode = attention_prefill = project = staticmethod(lambda *a: None)
+
+
+_native = _General   # _marshal once the library is loaded, where it can be used
 
 DSLA_F32, DSLA_BF16 = 0, 1
 KERNEL_NAMES = ("state_init", "prefill_segment_state", "prefill_segment_scan", "prefill_chunk_loop", "decode",
@@ -127,15 +135,29 @@ def load_library():
     lib.dsla_profile_collect.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int64)]
     lib.dsla_profile_collect.restype = ctypes.c_int
     if _torch is not None:
-        import torch
-        from . import _marshal
-        entries = (lib.dsla_decode, lib.dsla_decode_slots, lib.dsla_prefill, lib.dsla_prefill_varlen, lib.dsla_attention_decode,
-                   lib.dsla_attention_prefill, lib.dsla_project)
-        _marshal.bind(_torch._cuda_getDevice, _torch._cuda_getCurrentRawStream, torch.nn.Parameter, DslaDesc,
-                      *[ctypes.cast(f, vp).value for f in entries])
-        _native = _marshal
+        _native = _load_native(lib)
     _lib = lib
     return lib
+
+
+def _load_native(lib):
+    import torch
+    try:
+        from . import _marshal
+        from .build import marshal_stamp
+        built_for, here = getattr(_marshal, "built_for", "another version"), marshal_stamp()
+        if built_for != here:
+            raise ImportError(f"_marshal.so was built for {built_for}, this is {here}")
+        torch_calls = _torch._cuda_getDevice, _torch._cuda_getCurrentRawStream   # (a PyTorch without GPUs has none)
+    except (ImportError, AttributeError, OSError) as e:
+        import warnings
+        warnings.warn(f"the calls go through ctypes, at 2 us more each on the host ({e}); `python -m paper_2506_09316_amd.build` builds the native ones",
+                      RuntimeWarning, stacklevel=3)
+        return _General
+    entries = (lib.dsla_decode, lib.dsla_decode_slots, lib.dsla_prefill, lib.dsla_prefill_varlen, lib.dsla_attention_decode,
+               lib.dsla_attention_prefill, lib.dsla_project)
+    _marshal.bind(*torch_calls, torch.nn.Parameter, DslaDesc, *[ctypes.cast(f, ctypes.c_void_p).value for f in entries])
+    return _marshal
 
 
 def _check(status: int):

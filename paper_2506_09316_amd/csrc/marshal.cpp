@@ -294,4 +294,9 @@ PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, g_method
 
 }  // namespace
 
-extern "C" __attribute__((visibility("default"))) PyObject *PyInit__marshal(void) { return PyModule_Create(&g_module); }
+extern "C" __attribute__((visibility("default"))) PyObject *PyInit__marshal(void)
+{
+    PyObject *m = PyModule_Create(&g_module);
+    if (m && PyModule_AddStringConstant(m, "built_for", DSLA_BUILT_FOR) != 0) Py_CLEAR(m);   // (build.py: marshal_stamp)
+    return m;
+}

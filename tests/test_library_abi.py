@@ -3,6 +3,9 @@ declares, and its host-side argument checks return the documented codes without 
 import ctypes
 import os
 import re
+import shutil
+import subprocess
+import sys
 
 import pytest
 
@@ -296,3 +299,40 @@ def test_native_calls_leave_unusual_arguments_to_the_general_way():
         dsla.dsla_prefill(desc, 1, 3, x, x, x, x, S, S, x)
     with pytest.raises(ValueError):
         dsla.dsla_attention_prefill(x, x, x, x, 1.0)
+
+
+@pytest.mark.parametrize("found", ["nothing", "no library", "another version", "this one"])
+def test_the_library_loads_without_its_native_calls(lib, tmp_path, found):
+    """_marshal.so missing, unreadable, or built for another header: a warning, and every call goes through ctypes."""
+    package = tmp_path / "paper_2506_09316_amd"
+    here = os.path.dirname(dsla.library_path())
+    shutil.copytree(here, package, ignore=shutil.ignore_patterns("csrc", "__pycache__", *([] if found in ("another version", "this one") else ["_marshal.so"])))
+    shutil.copytree(os.path.join(ROOT, "include"), tmp_path / "include")
+    if found == "no library":
+        (package / "_marshal.so").write_bytes(b"text")
+    if found == "another version":
+        with open(tmp_path / "include" / "dsla.h", "a") as f:
+            f.write("/* changed */\n")
+    child = """
+import ctypes, sys, warnings
+import torch
+import paper_2506_09316_amd as dsla
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    dsla.load_library()
+native = dsla.binding._native is not dsla.binding._General
+x, S = torch.zeros(1, 4, 64), torch.zeros(1, 4, 64, 64)
+desc = dsla.make_desc(1, 4, 64, 64, io_dtype=0, gate_dtype=0)
+for call in (lambda: dsla.dsla_decode(desc, *[x] * 5, S, S, x), lambda: dsla.dsla_prefill(desc, 1, *[x] * 5, S, S, x),
+             lambda: dsla.dsla_prefill_varlen(desc, 1, 1, x, None, *[x] * 5, S, S, x), lambda: dsla.dsla_decode_slots(desc, *[x] * 5, x, S, S, x),
+             lambda: dsla.dsla_attention_decode(x, S, S, x, 1.0), lambda: dsla.dsla_attention_prefill(S, S, S, S, 1.0), lambda: dsla.dsla_project(x[0], x[0], [x])):
+    try:
+        call()
+    except AssertionError:   # (not on the GPU)
+        continue
+    raise SystemExit("taken")
+print("native" if native else "general", sum(w.category is RuntimeWarning for w in seen))
+"""
+    run = subprocess.run([sys.executable, "-c", child], cwd=tmp_path, capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0, run.stderr
+    assert run.stdout.split() == (["native", "0"] if found == "this one" else ["general", "1"])
