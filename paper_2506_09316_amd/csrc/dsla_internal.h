@@ -93,7 +93,9 @@ struct PrefillPlan {
     int64_t max_pre_items;   //   and of the list of segments that have a successor
     size_t ws_lists_bytes;   //   and the bytes of the lists
     int64_t max_cut;         //   and of the list of sequences that are cut
-    int run_min, run_max;    // packed sequences, only the long ones cut: pieces of segment_tokens per segment, the device chooses (else 0)
+    int run_min, run_max;    // packed sequences, only the long ones cut: pieces of long_piece tokens per segment, the device chooses (else 0)
+    int long_piece;
+    float all_cost;          //   estimate (us) of every sequence cut, by this plan, where the device may choose that instead (else 0)
     bool longest_first;      // packed sequences, whole: the chunk loop takes them in the order of their lengths
     size_t ws_total_bytes;   // what this plan uses
     size_t ws_ask_bytes;     // what the size query answers: at least that

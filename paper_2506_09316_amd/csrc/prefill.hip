@@ -2245,19 +2245,21 @@ __global__ __launch_bounds__(SegFast::NT, 2) void segment_state_fast_kernel(Pref
 struct SegmentListArgs {
     const int32_t *cu, *seq;
     int B, H;
-    int64_t piece;               // tokens
+    int64_t segment;             // tokens, where every sequence is cut
+    int piece;                   // tokens, where only the long ones are
     int32_t *seg_first, *seg_count, *cut_seq;
     int4 *list_full, *list_pre;
-    int cap_full, cap_pre, cap_cut;   // entries
-    int run_min, run_max;        // only the long sequences are cut: pieces per segment to choose from (0: every piece is a segment)
+    int cap_full, cap_pre, cap_cut, cap_slot;   // entries; state slots (times H)
+    int run_min, run_max;        // only the long sequences are cut: pieces per segment to choose from
+    float all_cost;              // us: every sequence cut, where that can be chosen too (0: it cannot)
     int chip;                    // workgroups at a time
     float step, step_full, pre, wg, slot, fixed;   // us: see PrefillCosts
     float margin;                // a cut has to be estimated at less than this part of none
 };
 
-// Work lists for packed sequences (one workgroup).  Every sequence in pieces of the same length, from its start: list_full =
-// every (sequence, piece), list_pre = those with a successor.  Thread t takes a contiguous run of sequences.
-__global__ __launch_bounds__(256) void segment_list_kernel(SegmentListArgs a)
+// Work lists for packed sequences (one workgroup).  Every sequence in segments of the same length, from its start: list_full =
+// every (sequence, segment), list_pre = those with a successor.  Thread t takes a contiguous run of sequences.
+__device__ __forceinline__ void list_segments(const SegmentListArgs &a)
 {
     __shared__ int4 s_sum[256];
     const int t = threadIdx.x;
@@ -2267,7 +2269,7 @@ __global__ __launch_bounds__(256) void segment_list_kernel(SegmentListArgs a)
         const int sq = a.seq ? a.seq[b] : b;
         return static_cast<int64_t>(a.cu[sq + 1]) - a.cu[sq];
     };
-    auto segments_of = [&](int64_t Tb) -> int { return Tb > 0 ? static_cast<int>((Tb + a.piece - 1) / a.piece) : 0; };
+    auto segments_of = [&](int64_t Tb) -> int { return Tb > 0 ? static_cast<int>((Tb + a.segment - 1) / a.segment) : 0; };
     int mine = 0, mine_pre = 0, mine_cut = 0;   // segments, those with a successor, and sequences that have such in this thread's run
     for (int b = b0; b < b1; ++b) {
         const int n = segments_of(length_of(b));
@@ -2296,7 +2298,7 @@ __global__ __launch_bounds__(256) void segment_list_kernel(SegmentListArgs a)
         // the capacities hold whenever the offsets add up to the total the caller gave; offsets that do not
         // must not write past the lists (the segments that do not fit are dropped)
         for (int p = 0; p < n; ++p) {
-            const int64_t t0 = p * a.piece, t1 = t0 + a.piece < Tb ? t0 + a.piece : Tb;
+            const int64_t t0 = p * a.segment, t1 = t0 + a.segment < Tb ? t0 + a.segment : Tb;
             const int4 e = make_int4(b, static_cast<int>(t0), static_cast<int>(t1), n > 1 ? at_slot + p : -1);
             if (at + p < a.cap_full) a.list_full[at + p] = e;
             if (p + 1 < n) {
@@ -2315,11 +2317,13 @@ __global__ __launch_bounds__(256) void segment_list_kernel(SegmentListArgs a)
     }
 }
 
+__global__ __launch_bounds__(256) void segment_list_kernel(SegmentListArgs a) { list_segments(a); }
+
 // The lists where only the sequences are cut whose chain of steps would outlast all the work spread over the chip (at most 128
 // sequences and 256 segments).  A segment is R pieces, counted from the END of the sequence: what precedes the last full segment - the part that
 // the pre-pass has to walk, in pieces so that many workgroups do - is as short as it can be.  Pieces begin at multiples of a step; the first one
 // may be shorter.  The lengths are known here and not on the host, so R is chosen here, by the same estimates, with R = 0 (nothing is cut)
-// among the choices; the longest segments come first.
+// among the choices, and every sequence cut where the host's plan has the room for it; the longest segments come first.
 __global__ __launch_bounds__(256) void long_segment_list_kernel(SegmentListArgs a)
 {
     constexpr int kMost = 256;
@@ -2327,7 +2331,7 @@ __global__ __launch_bounds__(256) void long_segment_list_kernel(SegmentListArgs 
     __shared__ int s_key[kMost], s_n[3][kMost];
     __shared__ float s_cost[kMost];
     __shared__ int4 s_entry[kMost];
-    const int t = threadIdx.x, piece = static_cast<int>(a.piece);
+    const int t = threadIdx.x, piece = a.piece;
     int Tb = 0;
     if (t < a.B) {
         const int sq = a.seq ? a.seq[t] : t;
@@ -2359,7 +2363,7 @@ __global__ __launch_bounds__(256) void long_segment_list_kernel(SegmentListArgs 
         const float walks = pre * H, s2 = spread * spread, a2 = alone * alone;
         float cost = __builtin_sqrtf(__builtin_sqrtf(s2 * s2 + a2 * a2));
         if (pre > 0) cost += a.fixed + (walks > 1.f ? walks : 1.f) * (piece / 32) * a.pre + a.slot * pre * a.H;
-        if (more > a.cap_full - a.B || pre + sequences > a.cap_pre) cost = 3.0e38f;   // more than there are slots
+        if (more > (a.cap_full < kMost ? a.cap_full : kMost) - a.B || pre > a.cap_pre || pre + sequences > a.cap_slot) cost = 3.0e38f;   // more than there is room for
         s_cost[t] = cost;
     }
     __syncthreads();
@@ -2370,6 +2374,10 @@ __global__ __launch_bounds__(256) void long_segment_list_kernel(SegmentListArgs 
             least = s_cost[u];
             R = a.run_min + u - 1;
         }
+    if (a.all_cost > 0.f && !((R > 0 ? least : s_cost[0]) < a.all_cost)) {   // (the same for all threads)
+        list_segments(a);
+        return;
+    }
     const int n = (Tb + piece - 1) / piece, ahead = (n * piece - Tb) / 32 * 32;   // pieces, and what the first one is short of
     const bool cut = R > 0 && n > R;
     const int nseg = cut ? (n + R - 1) / R : (Tb > 0 ? 1 : 0), npre = cut ? n - R : 0, nslot = cut ? npre + 1 : 0;
@@ -2402,7 +2410,7 @@ __global__ __launch_bounds__(256) void long_segment_list_kernel(SegmentListArgs 
     __syncthreads();
     if (s_key[t] >= 0) {
         int rank = 0;
-        for (int u = 0; u < a.cap_full; ++u) rank += s_key[u] > s_key[t] ? 1 : 0;   // (at most kMost)
+        for (int u = 0; u < kMost && u < a.cap_full; ++u) rank += s_key[u] > s_key[t] ? 1 : 0;
         a.list_full[rank] = s_entry[t];
     }
 }
@@ -2545,7 +2553,9 @@ hipError_t launch_x(const dsla_desc &d, const PrefillPlan &plan, PrefillArgs &a,
             l.seq = a.seq;
             l.B = d.B;
             l.H = d.H;
-            l.piece = a.seg_tokens;
+            l.segment = a.seg_tokens;
+            l.piece = plan.long_piece;
+            l.all_cost = plan.all_cost;
             l.seg_first = const_cast<int32_t *>(a.seg_first);
             l.seg_count = const_cast<int32_t *>(a.seg_count);
             l.cut_seq = const_cast<int32_t *>(a.cut_seq);
@@ -2554,6 +2564,7 @@ hipError_t launch_x(const dsla_desc &d, const PrefillPlan &plan, PrefillArgs &a,
             l.list_pre = const_cast<int4 *>(a.list_pre);
             l.cap_full = static_cast<int>(plan.max_items);
             l.cap_pre = static_cast<int>(plan.max_pre_items);
+            l.cap_slot = static_cast<int>(plan.all_cost > 0.f ? plan.max_items : plan.max_pre_items);
             l.run_min = plan.run_min;
             l.run_max = plan.run_max;
             l.chip = chip_slots(d);
@@ -2645,7 +2656,8 @@ void finish_plan(const dsla_desc &d, int C, int64_t P, int64_t nchunks, bool may
     plan->state_elems = static_cast<size_t>(BH) * D * D;
     plan->max_items = plan->max_pre_items = 0;
     plan->longest_first = false;
-    plan->run_min = plan->run_max = 0;
+    plan->run_min = plan->run_max = plan->long_piece = 0;
+    plan->all_cost = 0.f;
     plan->max_cut = 0;
     plan->ws_lists_bytes = 0;
     // The pre-pass has one workgroup per (segment but the last, sequence, head).  With two segments that is at most
@@ -2847,7 +2859,13 @@ size_t lists_bytes(const dsla_desc &d, const PrefillPlan &p)
 // beginnings of the long sequences and a scan.  Whole / cut, 32 heads, d = 128: 20 sequences of up to 8192 tokens as pre-activations 635 / 532 us, with
 // log-gates 578 / 473; 19 of up to 5605 439 / 345; 17 of up to 4850 338 / 270; d = 64, 32 of up to 6768 430 / 350.
 // Its slots are as many as `bytes` hold (what the size query answers, or less that a caller brings): the device keeps to them.
-void cut_long(const dsla_desc &d, int64_t total_T, int64_t max_T, size_t bytes, double below, PrefillPlan *plan)
+// Where cutting every sequence pays (all_cost: its estimate), the long ones alone are one more choice, inside the buffer and the launches of
+// cutting all.  How many are long is not known here, and few slots for many long ones make long segments, so the device may also choose to
+// cut all: chosen here as if two sequences were the longest, 7 of up to 6913 tokens (8 heads) took 348 us and not 289, 9 of up to 7898 351 and 320,
+// d = 64, 4 heads, 22 of up to 4078 131 and 105.  All cut / this: 16 of up to 5451 (8 heads) 361 / 277, 28 of up to 1769 with max_T 7076 (none is cut) 281 / 160.
+// The list kernel that chooses takes 3 us more where all are cut in the end, so it has to be worth it for sequences of the same length too; at
+// d = 64, where two workgroups share a compute unit and chains take longer than estimated, by far.
+void cut_long(const dsla_desc &d, int64_t total_T, int64_t max_T, size_t bytes, double all_cost, PrefillPlan *plan)
 {
     if (d.io_dtype == DSLA_F32 || d.B < 2 || d.B > 128) return;
     const PrefillCosts c = prefill_costs(d);
@@ -2869,7 +2887,14 @@ void cut_long(const dsla_desc &d, int64_t total_T, int64_t max_T, size_t bytes, 
         const double cost = both(R * piece / 32) + 2 * c.wg + c.lists + (walks > 1 ? walks : 1) * (piece / 32) * c.pre + c.slot * pieces * d.H;
         if (cost < least) least = cost;
     }
-    if (least > (below > 0 ? below : (d.d_k == 64 ? 0.92 : 0.95) * both((max_T + 31) / 32))) return;
+    if (least > (all_cost > 0 ? 0.78 * all_cost : (d.d_k == 64 ? 0.92 : 0.95) * both((max_T + 31) / 32))) return;
+    p.long_piece = static_cast<int>(piece);
+    if (all_cost > 0) {
+        if (both((total_T / d.B + 31) / 32) > (d.d_k == 64 ? 0.65 : 0.92) * all_cost) return;
+        p.all_cost = static_cast<float>(all_cost);
+        *plan = p;
+        return;
+    }
     p.segments = 2;
     p.segment_tokens = piece;
     p.pre_split = 1;
@@ -2963,10 +2988,8 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
     if (!must_cut && plan->ws_total_bytes > available) finish_packed(P = 1, plan);
     plan->longest_first = plan->segments == 1 && order_pays(d, total_T, max_T);
     if (P > 1 && cut_cost > 0 && plan->ws_total_bytes <= available) {   // (its bytes are there: the long ones alone, if that is better still)
-        const PrefillPlan all = *plan;
         // (32 heads, d = 128: 10 sequences of up to 3379 tokens all cut 260 us, these 223; 8 of up to 1724 122 and 106)
-        cut_long(d, total_T, max_T, all.ws_total_bytes, 0.78 * cut_cost, plan);
-        plan->ws_ask_bytes = plan->ws_need_bytes = all.ws_total_bytes;
+        cut_long(d, total_T, max_T, plan->ws_total_bytes, cut_cost, plan);
     }
     if (P < P_cut) {
         // Whole by the estimate: the size query still answers with what cutting takes, if any smaller batch is cut, so that a
