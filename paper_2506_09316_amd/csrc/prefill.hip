@@ -2857,7 +2857,8 @@ size_t lists_bytes(const dsla_desc &d, const PrefillPlan &p)
 // A batch that stays whole because cutting everything costs more than it saves, but whose longest sequences outlast all its work
 // spread over the chip: these alone are cut (long_segment_list_kernel decides where, and whether).  It takes the lists, a pre-pass over the
 // beginnings of the long sequences and a scan.  Whole / cut, 32 heads, d = 128: 20 sequences of up to 8192 tokens as pre-activations 635 / 532 us, with
-// log-gates 578 / 473; 19 of up to 5605 439 / 345; 17 of up to 4850 338 / 270; d = 64, 32 of up to 6768 430 / 350.
+// log-gates 578 / 473.  Not at d = 64, where a compute unit's second workgroup slows the first one's chain, which no estimate here knows: 32 of up to
+// 6768 tokens 430 / 350, but 8 of up to 7301 338 / 413.
 // Its slots are as many as `bytes` hold (what the size query answers, or less that a caller brings): the device keeps to them.
 // Where cutting every sequence pays (all_cost: its estimate), the long ones alone are one more choice, inside the buffer and the launches of
 // cutting all.  How many are long is not known here, and few slots for many long ones make long segments, so the device may also choose to
@@ -2867,7 +2868,7 @@ size_t lists_bytes(const dsla_desc &d, const PrefillPlan &p)
 // d = 64, where two workgroups share a compute unit and chains take longer than estimated, by far.
 void cut_long(const dsla_desc &d, int64_t total_T, int64_t max_T, size_t bytes, double all_cost, PrefillPlan *plan)
 {
-    if (d.io_dtype == DSLA_F32 || d.B < 2 || d.B > 128) return;
+    if (d.io_dtype == DSLA_F32 || d.B < 2 || d.B > 128 || (d.d_k == 64 && !(all_cost > 0))) return;
     const PrefillCosts c = prefill_costs(d);
     const double H = static_cast<double>(d.H) / chip_slots(d);
     const double spread = (static_cast<double>(d.B) * c.wg + static_cast<double>(total_T) / 32 * kSpread * c.step_full) * H;
@@ -2887,7 +2888,7 @@ void cut_long(const dsla_desc &d, int64_t total_T, int64_t max_T, size_t bytes, 
         const double cost = both(R * piece / 32) + 2 * c.wg + c.lists + (walks > 1 ? walks : 1) * (piece / 32) * c.pre + c.slot * pieces * d.H;
         if (cost < least) least = cost;
     }
-    if (least > (all_cost > 0 ? 0.78 * all_cost : (d.d_k == 64 ? 0.92 : 0.95) * both((max_T + 31) / 32))) return;
+    if (least > (all_cost > 0 ? 0.78 * all_cost : 0.95 * both((max_T + 31) / 32))) return;
     p.long_piece = static_cast<int>(piece);
     if (all_cost > 0) {
         if (both((total_T / d.B + 31) / 32) > (d.d_k == 64 ? 0.65 : 0.92) * all_cost) return;

@@ -137,7 +137,7 @@ def test_varlen_longest_first(lengths, H, d, io, gate):
     ([1335] * 9 + [4609], [9], 32, 128, "bf16"),               # one past a multiple of the pieces of 512
     ([4864] + [1104] * 10, [0], 32, 128, "f32"),               # no remainder; the general pre-pass
     ([700] * 6 + [3900] + [700] * 6 + [31], [6], 32, 128, "bf16"),   # pieces of 256
-    ([1500] * 10 + [6768] + [1500] * 9, [10], 32, 64, "bf16")])
+    ([1500] * 10 + [6768] + [1500] * 9, [], 32, 64, "bf16")])         # d = 64: none is
 def test_varlen_only_the_long_ones_cut(lengths, long, H, d, gate):
     """Batches whose longest sequences outlast the rest: these alone are cut, in pieces counted from their ends.  Against the same call
     without a buffer, which runs whole (and is held to the oracle elsewhere): the short sequences come out bit for bit, the long ones do not,

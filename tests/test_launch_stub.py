@@ -101,6 +101,9 @@ for io in (0, 1):
 # only the long ones cut: with a buffer; whole without one that holds at least the lists and two slots
 assert packed(20, 32, 128, 37157, 8192, 1, fake, big) == (OK, 4)
 assert packed(20, 32, 128, 37157, 8192, 1, None, 0) == packed(20, 32, 128, 37157, 8192, 1, fake, 1 << 22) == packed(20, 32, 128, 37157, 8192, 1, odd, big) == (OK, 1)
+# d = 64: none of them
+for B, H, total, longest in ((8, 32, 41097, 7301), (32, 32, 39561, 7524), (22, 32, 6610, 1924)):
+    assert packed(B, H, 64, total, longest, 1, fake, big) == (OK, 1)
 """
 
 
