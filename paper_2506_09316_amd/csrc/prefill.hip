@@ -2859,6 +2859,10 @@ size_t lists_bytes(const dsla_desc &d, const PrefillPlan &p)
 // beginnings of the long sequences and a scan.  Whole / cut, 32 heads, d = 128: 20 sequences of up to 8192 tokens as pre-activations 635 / 532 us, with
 // log-gates 578 / 473.  Not at d = 64, where a compute unit's second workgroup slows the first one's chain, which no estimate here knows: 32 of up to
 // 6768 tokens 430 / 350, but 8 of up to 7301 338 / 413.
+// max_T may bound the lengths loosely and then nothing is cut: the lists, an empty pre-pass and an empty scan take 10 us (5 to 16, less what the ranks
+// of whole sequences would take).  So only where all work spread over the chip, which the call takes at least, is kOfferLong: nothing cut / whole,
+// 32 heads, d = 128: 22 sequences of up to a quarter of max_T 434 / 430 us, 39 of up to a half 427 / 420, 10 of those 498 / 487; below, 1.03 at 300 us, 1.05 at 200, 1.2 at 50.
+// (What that gives up: 23 of up to 5826 tokens 390 us and not 287.)
 // Its slots are as many as `bytes` hold (what the size query answers, or less that a caller brings): the device keeps to them.
 // Where cutting every sequence pays (all_cost: its estimate), the long ones alone are one more choice, inside the buffer and the launches of
 // cutting all.  How many are long is not known here, and few slots for many long ones make long segments, so the device may also choose to
@@ -2866,6 +2870,7 @@ size_t lists_bytes(const dsla_desc &d, const PrefillPlan &p)
 // d = 64, 4 heads, 22 of up to 4078 131 and 105.  All cut / this: 16 of up to 5451 (8 heads) 361 / 277, 28 of up to 1769 with max_T 7076 (none is cut) 281 / 160.
 // The list kernel that chooses takes 3 us more where all are cut in the end, so it has to be worth it for sequences of the same length too; at
 // d = 64, where two workgroups share a compute unit and chains take longer than estimated, by far.
+constexpr double kOfferLong = 400;   // us
 void cut_long(const dsla_desc &d, int64_t total_T, int64_t max_T, size_t bytes, double all_cost, PrefillPlan *plan)
 {
     if (d.io_dtype == DSLA_F32 || d.B < 2 || d.B > 128 || (d.d_k == 64 && !(all_cost > 0))) return;
@@ -2873,6 +2878,7 @@ void cut_long(const dsla_desc &d, int64_t total_T, int64_t max_T, size_t bytes, 
     const double H = static_cast<double>(d.H) / chip_slots(d);
     const double spread = (static_cast<double>(d.B) * c.wg + static_cast<double>(total_T) / 32 * kSpread * c.step_full) * H;
     auto both = [&](int64_t steps) { return std::sqrt(std::hypot(spread * spread, (c.wg + steps * c.step) * (c.wg + steps * c.step))); };
+    if (!(all_cost > 0) && spread < kOfferLong) return;
     PrefillPlan p = *plan;
     const int64_t piece = max_T >= 4096 ? 512 : 256;   // (a multiple of every chunk)
     p.run_min = static_cast<int>(0.8 * (spread - c.wg) / c.step * 32 / static_cast<double>(piece));
@@ -2880,8 +2886,7 @@ void cut_long(const dsla_desc &d, int64_t total_T, int64_t max_T, size_t bytes, 
     const int64_t most = (max_T + piece - 1) / piece - 1;   // pieces per segment that still cut the longest
     if (most < p.run_min) return;
     p.run_max = static_cast<int>(most < p.run_min + 200 ? most : p.run_min + 200);
-    // the device's estimate as if two sequences were the longest: has to be below that of the whole batch, because the lists, an empty pre-pass
-    // and an empty scan cost 15 us where the device then cuts nothing
+    // the device's estimate as if two sequences were the longest: has to be below that of the whole batch
     double least = 1e30;
     for (int64_t R = p.run_min; R <= p.run_max; ++R) {
         const double pieces = 2.0 * static_cast<double>(most + 1 - R), walks = pieces * H;

@@ -133,10 +133,13 @@ def test_varlen_longest_first(lengths, H, d, io, gate):
 
 
 @pytest.mark.parametrize("lengths,long,H,d,gate", [
-    ([1362, 710, 335, 761, 0, 1104, 884, 504, 995, 471, 492, 4850, 347, 1379, 1, 1035, 551, 1124, 116, 33], [11], 32, 128, "bf16"),
-    ([1335] * 9 + [4609], [9], 32, 128, "bf16"),               # one past a multiple of the pieces of 512
-    ([4864] + [1104] * 10, [0], 32, 128, "f32"),               # no remainder; the general pre-pass
-    ([700] * 6 + [3900] + [700] * 6 + [31], [6], 32, 128, "bf16"),   # pieces of 256
+    ([6000, 710, 335, 2761, 0, 1104, 3884, 504, 2995, 2471, 492, 8192, 2347, 3379, 1, 1035, 551, 1124, 116, 33], [0, 11], 32, 128, "bf16"),
+    ([9217, 5] + [1500] * 8 + [8704] + [600] * 6 + [0, 31, 7000], [0, 10, 19], 32, 128, "bf16"),   # one past a multiple of the pieces of 512, a multiple
+    ([9728] + [1104] * 26, [0], 32, 128, "f32"),               # no remainder; the general pre-pass
+    # too little work for that to be worth trying: whole
+    ([1362, 710, 335, 761, 0, 1104, 884, 504, 995, 471, 492, 4850, 347, 1379, 1, 1035, 551, 1124, 116, 33], [], 32, 128, "bf16"),
+    ([1335] * 9 + [4609], [], 32, 128, "bf16"),
+    ([700] * 6 + [3900] + [700] * 6 + [31], [], 32, 128, "bf16"),
     ([1500] * 10 + [6768] + [1500] * 9, [], 32, 64, "bf16")])         # d = 64: none is
 def test_varlen_only_the_long_ones_cut(lengths, long, H, d, gate):
     """Batches whose longest sequences outlast the rest: these alone are cut, in pieces counted from their ends.  Against the same call

@@ -104,6 +104,9 @@ assert packed(20, 32, 128, 37157, 8192, 1, None, 0) == packed(20, 32, 128, 37157
 # d = 64: none of them
 for B, H, total, longest in ((8, 32, 41097, 7301), (32, 32, 39561, 7524), (22, 32, 6610, 1924)):
     assert packed(B, H, 64, total, longest, 1, fake, big) == (OK, 1)
+# nor at d = 128 where the lists, an empty pre-pass and an empty scan would be much of a call whose bound turns out loose
+for B, H, total, longest in ((31, 8, 19014, 1616), (18, 32, 22985, 6652), (3, 32, 5683, 1926), (24, 32, 18417, 5826)):
+    assert packed(B, H, 128, total, longest, 1, fake, big) == (OK, 1)
 """
 
 
