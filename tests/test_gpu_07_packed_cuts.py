@@ -100,3 +100,41 @@ def test_every_sequence_the_long_ones_or_none(lengths, H, d, preact, max_T, chos
         p.compare(got, all_cut(p, max_T), [])
     else:
         p.compare(got, p.call(max_T, segments=1), [] if chosen == NONE else chosen)
+
+
+LONG = [9217, 5] + [1500] * 8 + [8704] + [600] * 6 + [0, 31, 7000]   # one past a multiple of the pieces of 512, a multiple; empty and short ones between
+SLOT = 32 * 2 * 128 * 129 * 4                                         # bytes of a state slot and its decays, 32 heads of 128
+LISTS = 2048                                                          # of the batch LONG
+
+
+@pytest.mark.parametrize("gate,preact", [("bf16", True), ("f32", False), ("bf16", False)])
+def test_long_ones_from_zero_states(gate, preact):
+    """States that are zero by contract hold NaN on entry: a cut sequence's first segment starts from registers, the others from slots."""
+    p = Packed(LONG, 32, 128, gate, preact)
+    got, whole = (p.call(zero_init=True, segments=n) for n in (0, 1))
+    empty = LONG.index(0)
+    assert all(bool(s[p.slots[empty]].isnan().all()) for s in (*got[1:], *whole[1:]))   # no token: left as it is
+    for s in (*got[1:], *whole[1:]):
+        s[p.slots[empty]] = 0
+    p.compare(got, whole, [0, 10, 19])
+
+
+@pytest.mark.parametrize("take,cut", [([10, 19, 2, 3, 4, 0, 5, 6, 7, 8, 9, 17, 18, 1, 11, 12, 13, 14], [0, 1, 5]),
+                                      ([21, 10, 2, 3, 4, 0, 5, 6, 7, 17, 18, 1, 11, 12], [1, 5])])
+def test_long_ones_among_the_sequences_that_take_part(take, cut):
+    p = Packed(LONG + [300, 200], 32, 128, preact=True, take=take)
+    p.compare(p.call(), p.call(segments=1), cut)
+
+
+@pytest.mark.parametrize("slots,cut", [(2, []), (6, []), (9, [0, 10]), (12, [0, 10]), (14, [0, 10, 19]), (27, [0, 10, 19])])
+def test_long_ones_in_a_buffer_of_few_slots(slots, cut):
+    """The device keeps to the slots there are: longer segments, fewer sequences, or none cut; nothing is written past the buffer."""
+    p = Packed(LONG, 32, 128, preact=True)
+    assert p.ask() > LISTS + 27 * SLOT
+    p.compare(p.call(buffer=LISTS + slots * SLOT + 192), p.call(segments=1), cut)   # (192: not the buffer's whole)
+
+
+def test_long_ones_with_a_loose_bound():
+    """None is long: the lists say so, the pre-pass and the scan do nothing."""
+    p = Packed([1858] * 20, 32, 128, preact=True)
+    p.compare(p.call(max_T=8192), p.call(segments=1), [])
