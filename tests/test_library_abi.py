@@ -275,8 +275,8 @@ def test_packed_workspace_of_a_large_batch_serves_smaller_ones(lib):
 
 
 def test_native_calls_leave_unusual_arguments_to_the_general_way():
-    """The native calls answer None, with no exception pending, for anything but contiguous GPU tensors and plain numbers; the
-    general way then refuses or takes it as it always has."""
+    """Without a GPU: the native calls answer None, with no exception pending, to tensors on the CPU, to what is no tensor and to wrong
+    numbers of arguments; the general way then refuses it as it always has.  (One odd argument among right ones takes GPU tensors: test_gpu_06.)"""
     import torch
     dsla.load_library()
     native = dsla.binding._native
