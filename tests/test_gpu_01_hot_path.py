@@ -238,6 +238,38 @@ def test_prefill_short_prompts_report_gates_outside_the_domain():
         assert (int(status.item()) != 0) == outside, tokens
 
 
+@pytest.mark.parametrize("d,gates,T,state,feature,tokens,outside", [
+    (64, "log", 600, 0, 63, (40, 50), True), (64, "log", 600, 1, 0, (300, 318), True), (64, "preact", 600, 1, 17, (33, 62), True),
+    (64, "log", 600, 1, 17, (319, 320), False), (128, "log", 300, 0, 100, (5, 20), True), (128, "preact", 300, 1, 127, (160, 191), True),
+    (128, "preact", 300, 1, 64, (256, 290), False), (128, "log", 300, 1, 64, (288, 299), True)])
+def test_prefill_short_prompts_report_every_step(d, gates, T, state, feature, tokens, outside):
+    """Steps in the second and third rounds of tiles, the step that ends the prompt, features past the first 64, pre-activations."""
+    import torch
+    B, H = 1, 2
+    x = wl.layer_inputs(97, B, T, H, d, d, io_dtype="f32", gate_dtype="f32", gates=gates, tau=1.0)
+    for n in ("g1", "g2"):
+        x[n][:] = -0.01 if gates == "log" else 4.0
+    for t in tokens:
+        x["g2" if state else "g1"][0, t, 1, feature] = -90.0
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    GpuLayer(B, H, d, "f32", "f32", gate_mode=int(gates == "preact"), tau=1.0, status=status, zero_init=True, init=False).prefill(x)
+    assert (int(status.item()) != 0) == outside
+
+
+@pytest.mark.parametrize("d,B,H,T,gates", [(64, 2, 3, 270, "log"), (128, 2, 3, 140, "preact")])
+def test_prefill_short_prompts_blend_per_head_and_scale(d, B, H, T, gates):
+    x = wl.layer_inputs(99, B, T, H, d, d, io_dtype="f32", gate_dtype="f32", gates=gates)
+    lg = {n: x[n] if gates == "log" else orc.log_gates_from_preactivations(x[n], 16.0) for n in ("g1", "g2")}
+    gph = np.array([-0.3, 0.2, 1.4])
+    layer = GpuLayer(B, H, d, "f32", "f32", scale=0.25, gamma_per_head=gph, gate_mode=int(gates == "preact"), zero_init=True, init=False)
+    o = layer.prefill(x)
+    S1, S2 = layer.states()
+    ro, rS1, rS2 = orc.recurrent(x["q"], x["k"], x["v"], lg["g1"], lg["g2"], gph, 0.25)
+    check("o", o, ro, TOL["f32"])
+    check("S1", S1, rS1, TOL["f32"])
+    check("S2", S2, rS2, TOL["f32"])
+
+
 # ---------------------------------------------------------------- prefill, bf16
 
 

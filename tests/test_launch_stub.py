@@ -107,6 +107,22 @@ for B, H, total, longest in ((8, 32, 41097, 7301), (32, 32, 39561, 7524), (22, 3
 # nor at d = 128 where the lists, an empty pre-pass and an empty scan would be much of a call whose bound turns out loose
 for B, H, total, longest in ((31, 8, 19014, 1616), (18, 32, 22985, 6652), (3, 32, 5683, 1926), (24, 32, 18417, 5826)):
     assert packed(B, H, 128, total, longest, 1, fake, big) == (OK, 1)
+
+# fp32 prompts of a few hundred tokens from zero states: one launch in the attention form (gates as pre-activations too), whatever the batch is
+# cut into otherwise; states carried in, a number of segments that is named, long prompts and many heads take the plan
+def short(B, H, d, T, zero_init, segments=0, gate_mode=0, io=0):
+    stub.launch_stub_reset(-1)
+    desc = ctypes.byref(binding.make_desc(B, H, d, d, io_dtype=io, gate_dtype=io, chunk=64, segments=segments, zero_init=zero_init, gate_mode=gate_mode))
+    status = lib.dsla_prefill(desc, i64(T), *[fake] * 8, fake, size(big), None)
+    return status, stub.launch_stub_count()
+
+for gate_mode in (0, 1):
+    for B, H, d, T in ((1, 4, 64, 256), (2, 3, 64, 270), (1, 2, 64, 600), (2, 3, 128, 140), (1, 2, 128, 300)):
+        assert short(B, H, d, T, 1, 0, gate_mode) == (OK, 1) and short(B, H, d, T, 0, 0, gate_mode) == (OK, 3), (B, H, d, T)
+        assert short(B, H, d, T, 1, 2, gate_mode) == (OK, 3)
+    for B, H, d, T in ((1, 4, 64, 6000), (1, 2, 128, 4000), (8, 8, 64, 2000)):
+        assert short(B, H, d, T, 1, 0, gate_mode) == (OK, 3), (B, H, d, T)
+assert short(1, 2, 64, 600, 1, io=1) == (OK, 3)
 """
 
 
