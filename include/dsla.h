@@ -198,8 +198,10 @@ DSLA_API dsla_status dsla_prefill_static_ws(const dsla_desc *desc, int64_t T,
  * few of them.
  * dsla_prefill_varlen_workspace_bytes with desc->segments = 0: the size of a batch whose sequences are left whole because
  * that is faster is the size of cutting them (smaller batches are cut), unless even the smallest batch of that max_T
- * would stay whole; a call that cuts nothing uses no workspace and takes any.  The size is not monotone in total_T and
- * max_T: a buffer for several batches takes the largest of their sizes.
+ * would stay whole; such a call takes any buffer or none.  What it does with the buffer is up to it: it may write to all of the
+ * bytes it is given, also where nothing is cut in the end, and cut some of the sequences.  Which ones are cut, and so the rounding
+ * of those, depends on the lengths, max_T and the size of the buffer; the same call with the same buffer size repeats bit for bit.
+ * The size is not monotone in total_T and max_T: a buffer for several batches takes the largest of their sizes.
  */
 DSLA_API size_t dsla_prefill_varlen_workspace_bytes(const dsla_desc *desc, int64_t total_T, int64_t max_T);
 DSLA_API dsla_status dsla_prefill_varlen(const dsla_desc *desc, int64_t total_T, int64_t max_T,

@@ -99,7 +99,7 @@ struct PrefillPlan {
     bool longest_first;      // packed sequences, whole: the chunk loop takes them in the order of their lengths
     size_t ws_total_bytes;   // what this plan uses
     size_t ws_ask_bytes;     // what the size query answers: at least that
-    size_t ws_need_bytes;    // what a call has to bring, used or not: which calls are refused does not follow the estimates
+    size_t ws_need_bytes;    // what a dense call has to bring, used or not: which calls are refused does not follow the estimates (a packed one: ws_total_bytes)
 };
 // false: unsupported combination.  available: bytes of workspace there are (the size query: any number)
 bool prefill_plan(const dsla_desc &d, int64_t T, PrefillPlan *plan, size_t available = SIZE_MAX);

@@ -14,9 +14,9 @@
 // states.  P = 1 runs (3) alone.  (1) and (3) are one kernel template; for 16-bit inputs and gates at d = 128, (1) has a
 // kernel of its own that walks a segment backwards (segment_state_fast_kernel, below the template), and for 32-bit inputs both
 // have kernels that are made for the rate of fp32 MFMAs (F32Kern; the template keeps the launches with a beta gate).
-// Packed sequences of different lengths share one segment length; a one-workgroup kernel (segment_list) turns
-// their offsets into the lists of (sequence, segment) pairs that (1) and (3) take their work from, so that no
-// workgroup is launched for a segment that does not exist.  Sequences may be a subset of the packed batch and
+// Packed sequences of different lengths, if any of them is cut: a one-workgroup kernel turns their offsets into the lists of
+// segments that (1) and (3) take their work from, so that no workgroup has a segment that does not exist.  Either every sequence is
+// cut, into segments of one length (segment_list), or only the long ones are, from their ends (long_segment_list).  Sequences may be a subset of the packed batch and
 // their states entries of a pool (both through index arrays).  Gates arrive as log-gates or as the
 // pre-activations of a temperature-sigmoid, which the producers then apply themselves.
 //
@@ -2854,13 +2854,15 @@ size_t lists_bytes(const dsla_desc &d, const PrefillPlan &p)
     return up((static_cast<size_t>(d.B) + 1) * 4) + up((static_cast<size_t>(d.B) + 4) * 4) + up(p.max_items * 16) + up(p.max_pre_items * 16);
 }
 
+constexpr double kOfferLong = 400;   // us: see below
+
 // A batch that stays whole because cutting everything costs more than it saves, but whose longest sequences outlast all its work
 // spread over the chip: these alone are cut (long_segment_list_kernel decides where, and whether).  It takes the lists, a pre-pass over the
 // beginnings of the long sequences and a scan.  Whole / cut, 32 heads, d = 128: 20 sequences of up to 8192 tokens as pre-activations 635 / 532 us, with
 // log-gates 578 / 473.  Not at d = 64, where a compute unit's second workgroup slows the first one's chain, which no estimate here knows: 32 of up to
 // 6768 tokens 430 / 350, but 8 of up to 7301 338 / 413.
 // max_T may bound the lengths loosely and then nothing is cut: the lists, an empty pre-pass and an empty scan take 10 us (5 to 16, less what the ranks
-// of whole sequences would take).  So only where all work spread over the chip, which the call takes at least, is kOfferLong: nothing cut / whole,
+// of whole sequences would take).  So only where all work spread over the chip, which the call takes at least, is kOfferLong or more: nothing cut / whole,
 // 32 heads, d = 128: 22 sequences of up to a quarter of max_T 434 / 430 us, 39 of up to a half 427 / 420, 10 of those 498 / 487; below, 1.03 at 300 us, 1.05 at 200, 1.2 at 50.
 // (What that gives up: 23 of up to 5826 tokens 390 us and not 287.)
 // Its slots are as many as `bytes` hold (what the size query answers, or less that a caller brings): the device keeps to them.
@@ -2870,7 +2872,6 @@ size_t lists_bytes(const dsla_desc &d, const PrefillPlan &p)
 // d = 64, 4 heads, 22 of up to 4078 131 and 105.  All cut / this: 16 of up to 5451 (8 heads) 361 / 277, 28 of up to 1769 with max_T 7076 (none is cut) 281 / 160.
 // The list kernel that chooses takes 3 us more where all are cut in the end, so it has to be worth it for sequences of the same length too; at
 // d = 64, where two workgroups share a compute unit and chains take longer than estimated, by far.
-constexpr double kOfferLong = 400;   // us
 void cut_long(const dsla_desc &d, int64_t total_T, int64_t max_T, size_t bytes, double all_cost, PrefillPlan *plan)
 {
     if (d.io_dtype == DSLA_F32 || d.B < 2 || d.B > 128 || (d.d_k == 64 && !(all_cost > 0))) return;
@@ -2925,13 +2926,12 @@ void cut_long(const dsla_desc &d, int64_t total_T, int64_t max_T, size_t bytes, 
     p.ws_lists_bytes = lists_bytes(d, p);
     p.ws_total_bytes = p.ws_state_bytes + p.ws_decay_bytes + p.ws_lists_bytes;
     p.longest_first = false;
-    p.ws_need_bytes = 0;
     *plan = p;
 }
 }  // namespace
 
-// Packed sequences of different lengths share one segment length; a sequence of length T_b has
-// ceil(T_b / segment_tokens) segments.  If they are cut, the segment length is chosen so that all sequences together make
+// Where every sequence is cut, packed sequences of different lengths share one segment length; a sequence of length T_b has
+// ceil(T_b / segment_tokens) segments (only the long ones cut: cut_long).  The segment length is chosen so that all sequences together make
 // about one workgroup per compute unit, the same rule as above on the total instead of a common length (measured on
 // mixed batches: twice as many segments gain on some mixes and lose on others, within 10 %).  Whether they are cut is a
 // matter of estimates (us): whole sequences take as long as the longest one or as all of them spread over the chip; cut
