@@ -2993,10 +2993,8 @@ bool prefill_plan_varlen(const dsla_desc &d, int64_t total_T, int64_t max_T, Pre
     finish_packed(P, plan);
     if (!must_cut && plan->ws_total_bytes > available) finish_packed(P = 1, plan);
     plan->longest_first = plan->segments == 1 && order_pays(d, total_T, max_T);
-    if (P > 1 && cut_cost > 0 && plan->ws_total_bytes <= available) {   // (its bytes are there: the long ones alone, if that is better still)
-        // (32 heads, d = 128: 10 sequences of up to 3379 tokens all cut 260 us, these 223; 8 of up to 1724 122 and 106)
+    if (P > 1 && cut_cost > 0 && plan->ws_total_bytes <= available)   // (its bytes are there: the long ones alone, if that is better still)
         cut_long(d, total_T, max_T, plan->ws_total_bytes, cut_cost, plan);
-    }
     if (P < P_cut) {
         // Whole by the estimate: the size query still answers with what cutting takes, if any smaller batch is cut, so that a
         // buffer sized for a large batch serves smaller ones.  The least a cut can cost is that of one sequence of n chunks.
